@@ -114,6 +114,9 @@ qlora_status check_view(const qlora_nf4_view* v) {
 // through dequantise + GEMM whatever the token count.
 inline bool streams_few(const qlora_nf4_view* v) { return v->dq_blocksize != 0 && v->dtype != qlora::kTypeInt8; }
 
+// The kernels for tens to hundreds of tokens decode 4-bit indices, with or without Double Quantization.
+inline bool streams_mid(const qlora_nf4_view* v) { return v->dtype != qlora::kTypeInt8; }
+
 inline qlora::NF4Dev to_dev(const qlora_nf4_view* v) {
   return qlora::NF4Dev{v->packed, v->c2_code, v->c1, v->c2_mean, v->rows, v->cols, v->dtype, v->dq_blocksize != 0};
 }
@@ -140,6 +143,30 @@ struct Carver {
   }
 };
 
+// Tens to hundreds of tokens (midtok.hip): its buffers lie where the dequantised weight would.  Small layers need more
+// than that for enough splits: the size queries then report more, and a caller that brings only the dequantise + GEMM
+// plan's bytes is still served, with fewer splits or by that plan.
+constexpr size_t kMidRoom = (size_t)32 << 20;
+struct MidWs { qlora::MidPlan plan; float* part; float* lpart; uint16_t* xpack; };
+size_t mid_bytes(const qlora::MidPlan& p) {
+  return align_up(p.part_floats * sizeof(float), 256) + align_up(p.lpart_floats * sizeof(float), 256) + align_up(p.pack_elems * 2, 256);
+}
+// bytes of the region that holds either the dequantised weight (`base` bytes) or the buffers of this path
+size_t mid_region(size_t base, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r) {
+  const qlora::MidPlan p = qlora::mid_plan(bwd, M, h, o, r, std::max(base, kMidRoom));
+  return p.ok ? std::max(base, mid_bytes(p)) : base;
+}
+MidWs plan_mid(void* buf, size_t room, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r) {
+  MidWs m{};
+  m.plan = qlora::mid_plan(bwd, M, h, o, r, room);
+  if (!m.plan.ok) return m;
+  char* p = (char*)buf;
+  m.part = (float*)p; p += align_up(m.plan.part_floats * sizeof(float), 256);
+  m.lpart = (float*)p; p += align_up(m.plan.lpart_floats * sizeof(float), 256);
+  m.xpack = (uint16_t*)p;
+  return m;
+}
+
 struct FwdPlan {
   uint16_t* Wt;      // o x (h + rp)   dequantised weight, transposed (K-contiguous for the forward), and behind it in
                      //                every row L2^T with the rank zero-padded to a multiple of 64: both K segments
@@ -149,7 +176,8 @@ struct FwdPlan {
   float* lpart;      // few-token path: partials of X L1
   int rp, splits, fsplits, n_lparts;
   bool few;
-  size_t bytes;
+  size_t bytes;      // what the size queries report
+  size_t min_bytes;  // what a call accepts
 };
 FwdPlan plan_fwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allow_few = true) {
   FwdPlan p{};
@@ -161,7 +189,7 @@ FwdPlan plan_fwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allo
     p.fpart = c.take<float>((size_t)p.fsplits * M * o);
     p.n_lparts = qlora::fewtok_fwd_lparts((int)h, r);
     p.lpart = c.take<float>((size_t)p.n_lparts * M * r + 4);
-    p.bytes = c.off;
+    p.bytes = p.min_bytes = c.off;
     return p;
   }
   p.Wt = c.take<uint16_t>((size_t)(h + (r > 0 ? p.rp : 0)) * o);
@@ -170,7 +198,8 @@ FwdPlan plan_fwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allo
     p.Ts = c.take<uint16_t>((size_t)M * p.rp);
     p.part = c.take<float>((size_t)p.splits * M * r);
   }
-  p.bytes = c.off;
+  p.min_bytes = c.off;
+  p.bytes = qlora::kWorkspaceHeaderBytes + mid_region(c.off - qlora::kWorkspaceHeaderBytes, false, M, h, o, r);
   return p;
 }
 
@@ -185,9 +214,11 @@ struct BwdPlan {
   float* lpart;      // few-token path: partials of dY L2^T
   int rp, sU, sT, sL1, sL2, fsplits, n_lparts;
   bool few;
+  size_t wd_bytes;   // of the region at Wd
   size_t bytes;
 };
-BwdPlan plan_bwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allow_few = true) {
+// roomy: the region at Wd also holds the buffers of the path for tens to hundreds of tokens (what the size queries report)
+BwdPlan plan_bwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allow_few = true, bool roomy = true) {
   BwdPlan p{};
   Carver c(ws);
   p.rp = (r + 63) / 64 * 64;
@@ -198,7 +229,9 @@ BwdPlan plan_bwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allo
     p.n_lparts = qlora::fewtok_bwd_lparts((int)o, r);
     p.lpart = c.take<float>((size_t)p.n_lparts * M * r + 4);
   } else {
-    p.Wd = c.take<uint16_t>((size_t)h * o);
+    p.wd_bytes = (size_t)h * o * sizeof(uint16_t);
+    if (roomy) p.wd_bytes = mid_region(p.wd_bytes, true, M, h, o, r);
+    p.Wd = (uint16_t*)c.take<char>(p.wd_bytes);
   }
   if (r > 0) {
     p.sU = qlora::small_gemm_splits((int)M, r, (int)o);
@@ -227,7 +260,7 @@ struct MultiPlan {
   float* lpart[qlora::kFewMaxLayers];
   int splits;
   bool few;
-  size_t bytes;
+  size_t bytes, min_bytes;                   // reported / accepted, see FwdPlan
 };
 MultiPlan plan_fwd_multi(void* ws, int64_t M, int32_t n, int64_t h, const int64_t* o, const int32_t* r) {
   MultiPlan p{};
@@ -245,11 +278,12 @@ MultiPlan plan_fwd_multi(void* ws, int64_t M, int32_t n, int64_t h, const int64_
       p.fpart[l] = c.take<float>((size_t)p.splits * M * o[l]);
       p.lpart[l] = c.take<float>((size_t)qlora::fewtok_fwd_lparts((int)h, r[l]) * M * r[l] + 4);
     }
-    p.bytes = c.off;
+    p.bytes = p.min_bytes = c.off;
   } else {
     for (int l = 0; l < n; ++l) {
-      const size_t b = plan_fwd(nullptr, M, h, o[l], r[l]).bytes;
-      if (b > p.bytes) p.bytes = b;
+      const FwdPlan f = plan_fwd(nullptr, M, h, o[l], r[l]);
+      p.bytes = std::max(p.bytes, f.bytes);
+      p.min_bytes = std::max(p.min_bytes, f.min_bytes);
     }
   }
   return p;
@@ -264,7 +298,7 @@ struct ListWs {
   float* part[qlora::kListMax];
   float* lpart[qlora::kListMax];
   bool few;
-  size_t bytes;
+  size_t bytes, min_bytes;                   // reported / accepted, see FwdPlan
 };
 ListWs plan_list(void* ws, bool bwd, int64_t M, int32_t n, const int64_t* h, const int64_t* o, const int32_t* r) {
   ListWs p{};
@@ -278,11 +312,12 @@ ListWs plan_list(void* ws, bool bwd, int64_t M, int32_t n, const int64_t* h, con
       p.part[l] = c.take<float>(p.plan.part_floats[l]);
       p.lpart[l] = c.take<float>(p.plan.lpart_floats[l]);
     }
-    p.bytes = c.off;
+    p.bytes = p.min_bytes = c.off;
   } else {
     for (int l = 0; l < n; ++l) {
-      const size_t b = bwd ? plan_bwd(nullptr, M, h[l], o[l], r[l]).bytes : plan_fwd(nullptr, M, h[l], o[l], r[l]).bytes;
-      if (b > p.bytes) p.bytes = b;
+      const FwdPlan f = plan_fwd(nullptr, M, h[l], o[l], r[l]);
+      p.bytes = std::max(p.bytes, bwd ? plan_bwd(nullptr, M, h[l], o[l], r[l]).bytes : f.bytes);
+      p.min_bytes = std::max(p.min_bytes, bwd ? plan_bwd(nullptr, M, h[l], o[l], r[l], true, false).bytes : f.min_bytes);
     }
   }
   return p;
@@ -467,7 +502,7 @@ qlora_status linear_fwd_impl(const uint16_t* X, const qlora_nf4_view* Wq, const 
   if (!X || !Y || !workspace) return QLORA_ERR_NULL;
   if (r > 0 && (!L1 || !L2)) return QLORA_ERR_NULL;
   const FwdPlan p = plan_fwd(workspace, M, h, o, r, keep_mask == nullptr && streams_few(Wq));
-  if (workspace_bytes < p.bytes) return QLORA_ERR_WORKSPACE;
+  if (workspace_bytes < p.min_bytes) return QLORA_ERR_WORKSPACE;
   if (!aligned16(X) || !aligned16(Y) || !aligned16(workspace) || !aligned16(L1) || !aligned16(L2) ||
       !aligned16(T_save))
     return QLORA_ERR_ALIGN;
@@ -480,6 +515,14 @@ qlora_status linear_fwd_impl(const uint16_t* X, const qlora_nf4_view* Wq, const 
     QL_TRY(qlora::launch_fewtok_fwd(X, (int)M, W, p.fpart, p.fsplits, L1, L2, r, s, p.lpart, (unsigned*)workspace, Y,
                                     T_save, st));
     return QLORA_OK;
+  }
+  if (streams_mid(Wq)) {
+    const MidWs mid = plan_mid((char*)workspace + qlora::kWorkspaceHeaderBytes,
+                               std::min(workspace_bytes, p.bytes) - qlora::kWorkspaceHeaderBytes, false, M, h, o, r);
+    if (mid.plan.ok) {
+      QL_TRY(qlora::launch_mid(false, X, (int)M, W, mid.plan, L1, L2, r, s, keep_mask, mid.part, mid.lpart, mid.xpack, Y, T_save, st));
+      return QLORA_OK;
+    }
   }
   if (r > 0) {
     // T = X L1 (Eq. 3): split-K partials, then Ts = bf16(s T) (rank zero-padded) and T_save = [hi | lo] of T
@@ -553,7 +596,7 @@ qlora_status qlora_linear_fwd_multi(const uint16_t* X, int32_t n, const qlora_nf
     for (int l = 0; l < n; ++l)
       if (!streams_few(&Wq[l])) return QLORA_ERR_UNSUPPORTED;      // the streaming kernels read 4-bit indices and double-quantised constants
   const MultiPlan p = plan_fwd_multi(workspace, M, n, h, o, r);
-  if (workspace_bytes < p.bytes) return QLORA_ERR_WORKSPACE;
+  if (workspace_bytes < p.min_bytes) return QLORA_ERR_WORKSPACE;
   if (!p.few) {
     for (int l = 0; l < n; ++l)
       if (qlora_status st = qlora_linear_fwd(X, &Wq[l], r[l] > 0 ? L1[l] : nullptr, r[l] > 0 ? L2[l] : nullptr, s[l], M,
@@ -670,7 +713,9 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
   if (r > 0 && (!L1 || !L2)) return QLORA_ERR_NULL;
   const bool want1 = dL1 || aL1, want2 = dL2 || aL2;
   if ((want1 || want2) && !X) return QLORA_ERR_NULL;
-  const BwdPlan p = plan_bwd(workspace, M, h, o, r, keep_mask == nullptr && streams_few(Wq));
+  const bool allow_few = keep_mask == nullptr && streams_few(Wq);
+  BwdPlan p = plan_bwd(workspace, M, h, o, r, allow_few);
+  if (workspace_bytes < p.bytes) p = plan_bwd(workspace, M, h, o, r, allow_few, false);
   if (workspace_bytes < p.bytes) return QLORA_ERR_WORKSPACE;
   if (!aligned16(dY) || !aligned16(X) || !aligned16(workspace) || !aligned16(L1) || !aligned16(L2) ||
       !aligned16(T_saved) || !aligned16(dX) || !aligned16(dL1) || !aligned16(dL2) || !aligned16(aL1) || !aligned16(aL2))
@@ -678,7 +723,13 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
   hipStream_t st = (hipStream_t)hip_stream;
   const qlora::NF4Dev W = to_dev(Wq);
 
-  if (p.few && dX) {
+  // a few hundred tokens: decode inside the product; the finalize step applies the dropout mask to the adapter's term
+  const MidWs mid = !p.few && dX && streams_mid(Wq)
+                        ? plan_mid(p.Wd, p.wd_bytes, true, M, h, o, r) : MidWs{};
+  if (mid.plan.ok) {
+    QL_TRY(qlora::launch_mid(true, dY, (int)M, W, mid.plan, L1, L2, r, s, keep_mask, mid.part, mid.lpart, mid.xpack, dX,
+                             (r > 0 && want1) ? p.Uhl : nullptr, st));
+  } else if (p.few && dX) {
     // few tokens: one launch streams the packed weight once; U = dY L2^T comes from extra workgroups, is applied
     // by each slab's last arriver and left as a [hi | lo] pair for dL1
     QL_TRY(qlora::launch_fewtok_bwd(dY, (int)M, W, p.fpart, p.fsplits, L1, L2, r, s, p.lpart, (unsigned*)workspace, dX,
@@ -688,7 +739,7 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
     QL_TRY(qlora::launch_small_gemm(dY, o, false, L2, o, false, 0, 0, (int)M, r, (int)o, p.part, p.sU, st));
     QL_TRY(qlora::launch_small_finalize(p.part, p.sU, (int)M, r, p.Us, p.rp, p.rp, s, p.Uhl, nullptr, st));
   }
-  if (!p.few && dX) {
+  if (!p.few && dX && !mid.plan.ok) {
     const uint16_t* B1 = L1;
     if (r > 0 && p.L1p) { QL_TRY(qlora::launch_copy_pad(L1, (int)h, r, p.L1p, p.rp, st)); B1 = p.L1p; }
     const int K1 = r > 0 ? p.rp : 0;
@@ -901,7 +952,7 @@ qlora_status list_impl(bool bwd, int32_t n, const uint16_t* const* In, const qlo
       if (!streams_few(&Wq[l]) || Wq[l].dtype != Wq[0].dtype) return QLORA_ERR_UNSUPPORTED;   // one decode table per launch
   const ListWs p = plan_list(workspace, bwd, M, n, h, o, r);
   if (M <= qlora::kFewTokens && !p.few) return QLORA_ERR_UNSUPPORTED;
-  if (workspace_bytes < p.bytes) return QLORA_ERR_WORKSPACE;
+  if (workspace_bytes < p.min_bytes) return QLORA_ERR_WORKSPACE;
   if (!p.few) {
     for (int l = 0; l < n; ++l) {
       const uint16_t* l1 = r[l] > 0 ? L1[l] : nullptr;

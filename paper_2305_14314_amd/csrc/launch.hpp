@@ -131,6 +131,32 @@ hipError_t launch_fewtok_fwd_multi(const uint16_t* X, int M, int n, const FewLay
                                    hipStream_t st);
 hipError_t launch_workspace_init(void* workspace, hipStream_t st);
 
+// midtok.hip: tens to hundreds of tokens, 4-bit weights (with or without Double Quantization): the weight is decoded inside
+// the product, whose work is one line of equal ranges over the compute units, and a last kernel sums a tile's partials and
+// adds the adapter's term.  The plan uses at most `room` bytes of workspace; ok = false: not for this path.
+constexpr int kMidTokens = 512;
+// `units` units in tiles of `ups`, cut into `wgs` ranges whose sizes differ by at most one.
+struct MidLine {
+  int units, ups, wgs;
+  __host__ __device__ int start(int rho) const { return (int)((int64_t)units * rho / wgs); }
+  // the range that holds unit u: the largest rho with start(rho) <= u
+  __host__ __device__ int rho_of(int u) const { return (int)((((int64_t)u + 1) * wgs - 1) / units); }
+  __host__ __device__ int contributors(int tile) const { return rho_of((tile + 1) * ups - 1) - rho_of(tile * ups) + 1; }
+};
+struct MidPlan {
+  bool ok, pack;                             // pack: the token operand is first copied into fragment order
+  int MF, KW, n_tg, n_slabs, steps, n_lparts, chunk, max_contrib;
+  MidLine line;
+  size_t part_floats, lpart_floats, pack_elems;
+};
+MidPlan mid_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room);
+//   forward: out (M x o) = X dequant(W) + scale (mask o X L1) L2, hl (M x 2r or NULL) = [hi | lo] of mask o X L1;
+//   backward: X is dY (M x o), out (M x h) = dY dequant(W)^T + scale mask o ((dY L2^T) L1^T), hl = [hi | lo] of dY L2^T.
+//   mask: keep-bits over M x h elements, or NULL.
+hipError_t launch_mid(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const MidPlan& p, const uint16_t* L1,
+                      const uint16_t* L2, int r, float scale, const uint8_t* mask, float* part, float* lpart, uint16_t* xpack,
+                      uint16_t* out, uint16_t* hl, hipStream_t st);
+
 // fewlist.hip: the same two products for a LIST of independent layers (each with its own token rows) in one
 // persistent launch.  The work of all layers is one line of units (forward: 16 weight rows x 256 columns; backward:
 // 256 rows x 128 columns) and workgroup rho of `grid` takes units [start[rho], start[rho + 1]); the first n_adapter

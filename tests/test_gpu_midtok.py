@@ -1,0 +1,108 @@
+"""Forward and input gradient at tens to hundreds of tokens, where the weight is decoded inside a product that is split
+along its contraction: against the fp64 oracle at the edges of its tiles (16 tokens, groups of at most 128, slabs of 128
+outputs, steps of 32 / 128), with and without an adapter, under dropout, for the other 4-bit types and for weights
+without Double Quantization."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import dev_bf16, dev_f32, host_bits, upload_quant
+from test_gpu_dropout import _mask
+from test_gpu_fused_bwd import _dx, fused  # noqa: F401
+from test_gpu_linear import _check
+
+pytestmark = pytest.mark.gpu
+
+
+# token tiles 2 .. 8 per group, one to five groups, a remainder of one token; h and o with a 64-wide remainder (half a slab
+# forward and backward, half a step backward), one step, many splits; ranks none, below 32, above 64, the largest
+@pytest.mark.parametrize("M,h,o,r", [(17, 64, 64, 16), (33, 320, 192, 16), (48, 1024, 1088, 64), (49, 192, 128, 0),
+                                      (64, 2048, 320, 48), (65, 128, 448, 32), (81, 576, 1024, 64), (97, 64, 2112, 16),
+                                      (112, 320, 320, 80), (113, 1088, 64, 64), (128, 512, 704, 256), (129, 448, 512, 64),
+                                      (257, 2048, 1024, 64), (334, 320, 1536, 0), (511, 704, 192, 144), (512, 1024, 1024, 64)])
+def test_midtok_forward_backward(oracle, synth, M, h, o, r):
+    import paper_2305_14314_amd as ql
+    s = 0.5
+    q = oracle.nf4_quantize(synth.normal_f32((h, o), synth.SIGMA_W, 500 + M))
+    What, Wq = oracle.nf4_dequant(q), upload_quant(q)
+    X, dY = synth.normal_bf16((M, h), 1.0, 501 + M), synth.normal_bf16((M, o), 1.0, 502 + M)
+    L1 = synth.normal_bf16((h, r), 0.05, 503 + M) if r else None
+    L2 = synth.normal_bf16((r, o), 0.05, 504 + M) if r else None
+    d = lambda a: None if a is None else dev_bf16(a)
+    print(f"case mid M={M} h={h} o={o} r={r}", flush=True)
+    ws = ql.workspace_alloc(max(ql.qlora_linear_fwd_sizes(M, h, o, r), ql.qlora_linear_bwd_sizes(M, h, o, r)) + 4096)
+    ws[ql.binding.WORKSPACE_HEADER_BYTES:].fill_(0x7F)          # stale contents: NaN-ish everywhere
+    fb, bb = ql.qlora_linear_fwd_sizes(M, h, o, r), ql.qlora_linear_bwd_sizes(M, h, o, r)
+    T = torch.full((M, 2 * r), float("nan"), dtype=torch.bfloat16, device="cuda") if r else None
+    Y = ql.qlora_linear_fwd(d(X), Wq, d(L1), d(L2), s, T_save=T, workspace=ws[:fb])
+    assert int((ws[fb:] != 0x7F).sum()) == 0                    # nothing behind the reported size
+    dX, dL1, dL2 = ql.qlora_linear_bwd(d(dY), d(X), Wq, d(L1), d(L2), s, T_saved=T, workspace=ws[:bb])
+    assert int((ws[max(fb, bb):] != 0x7F).sum()) == 0
+    torch.cuda.synchronize()
+    _check(host_bits(Y), oracle.linear_fwd(X, What, L1, L2, s), "Y")
+    _check(host_bits(dX), oracle.linear_bwd_dx(dY, What, L1, L2, s), "dX")
+    if r:
+        r1, r2 = oracle.linear_bwd_dl(dY, X, L1, L2, s)
+        _check(host_bits(dL1), r1, "dL1", few_terms=M < 64)
+        _check(host_bits(dL2), r2, "dL2", few_terms=M < 64)
+
+
+@pytest.mark.parametrize("M,h,o,r,p", [(3, 320, 192, 16, 0.5), (40, 448, 320, 64, 0.1), (130, 192, 576, 48, 0.1),
+                                        (512, 320, 448, 64, 0.3)])
+def test_midtok_dropout(oracle, synth, M, h, o, r, p):
+    """The mask enters T and, in the input gradient, the adapter's term only -- exactly: one rounding per element."""
+    import paper_2305_14314_amd as ql
+    q = oracle.nf4_quantize(synth.normal_f32((h, o), synth.SIGMA_W, 600 + M))
+    What, Wq = oracle.nf4_dequant(q), upload_quant(q)
+    X, dY = synth.normal_bf16((M, h), 1.0, 601 + M), synth.normal_bf16((M, o), 1.0, 602 + M)
+    L1, L2 = synth.normal_bf16((h, r), 0.2, 603 + M), synth.normal_bf16((r, o), 0.2, 604 + M)
+    keep, dmask = _mask(M, h, p, 605 + M)
+    D = oracle.dropout_multipliers(keep, p)
+    print(f"case mid dropout M={M} h={h} o={o} r={r} p={p}", flush=True)
+    Y = ql.qlora_linear_fwd_dropout(dev_bf16(X), Wq, dev_bf16(L1), dev_bf16(L2), 1.0, dmask, p)
+    dX, _, _ = ql.qlora_linear_bwd_dropout(dev_bf16(dY), dev_bf16(X), Wq, dev_bf16(L1), dev_bf16(L2), 1.0, dmask, p)
+    torch.cuda.synchronize()
+    _check(host_bits(Y), oracle.linear_fwd(X, What, L1, L2, 1.0, D=D), "Y")
+    ref = oracle.linear_bwd_dx(dY, What, L1, L2, 1.0, D=D)
+    _check(host_bits(dX), ref, "dX")
+    got = (host_bits(dX).astype(np.uint32) << 16).view(np.float32).astype(np.float64).reshape(ref.shape)
+    # half a bf16 step (2^-8 of the value at most), plus the fp32 sums and the 16 bits U keeps; two roundings would be twice that
+    assert np.all(np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + 2e-4 * np.sqrt((ref ** 2).mean()))
+
+
+@pytest.mark.parametrize("kind,dtype,dq", [("nf4", 0, 0), ("fp4_e2m1", 1, 256), ("int4", 3, 0)])
+@pytest.mark.parametrize("M", [2, 60, 200])
+def test_midtok_types(oracle, synth, kind, dtype, dq, M):
+    import paper_2305_14314_amd as ql
+    if M == 2 and dq:
+        M = 18                                                  # double-quantised weights take the streaming kernels up to 16
+    h, o, r, s = 320, 448, 32, 1.0
+    table = oracle.codebook4(kind)
+    W = synth.normal_f32((h, o), synth.SIGMA_W, 700)
+    q = oracle.nf4_quantize(W, dq_blocksize=dq, table=table)
+    What = oracle.nf4_dequant(q)
+    Wq = ql.qlora_nf4_quantize(dev_f32(W), dq_blocksize=dq, dtype=dtype)
+    X, dY = synth.normal_bf16((M, h), 1.0, 701), synth.normal_bf16((M, o), 1.0, 702)
+    L1, L2 = synth.normal_bf16((h, r), 0.05, 703), synth.normal_bf16((r, o), 0.05, 704)
+    print(f"case mid {kind} dq={dq} M={M}", flush=True)
+    Y = ql.qlora_linear_fwd(dev_bf16(X), Wq, dev_bf16(L1), dev_bf16(L2), s)
+    dX, _, _ = ql.qlora_linear_bwd(dev_bf16(dY), dev_bf16(X), Wq, dev_bf16(L1), dev_bf16(L2), s)
+    torch.cuda.synchronize()
+    _check(host_bits(Y), oracle.linear_fwd(X, What, L1, L2, s), "Y")
+    _check(host_bits(dX), oracle.linear_bwd_dx(dY, What, L1, L2, s), "dX")
+
+
+# The fused backward GEMM is reached above 512 tokens only: its ragged shapes there, the same bits as the two-kernel form
+@pytest.mark.parametrize("M,h,o,r", [(520, 64, 64, 0), (600, 320, 1536, 0), (529, 704, 128, 16), (513, 320, 64, 0)])
+def test_fused_backward_above_mid(oracle, synth, fused, M, h, o, r):  # noqa: F811
+    ql = fused
+    L = synth.make_layer(0, 0, M=M, h=h, o=o, r=max(r, 1))
+    q = oracle.nf4_quantize(L["W"])
+    Wq, X, dY = upload_quant(q), dev_bf16(L["X"]), dev_bf16(L["dY"])
+    L1, L2 = (dev_bf16(L["L1"]), dev_bf16(L["L2"])) if r else (None, None)
+    print(f"fused bwd: M {M} h {h} o {o} r {r}", flush=True)
+    a, b = _dx(ql, 0, dY, X, Wq, L1, L2, L["s"]), _dx(ql, 1, dY, X, Wq, L1, L2, L["s"])
+    ref = oracle.linear_bwd_dx(L["dY"], oracle.nf4_dequant(q), L["L1"] if r else None, L["L2"] if r else None, L["s"])
+    _check(host_bits(b), ref, "fused dX")
+    if r == 0:
+        assert torch.equal(a, b)

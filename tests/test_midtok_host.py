@@ -1,0 +1,39 @@
+"""Host-side checks of the path for tens to hundreds of tokens: its work partition, and the operand hazards of its
+inline-asm MFMAs in the generated code."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2305_14314_amd", "csrc")
+CHECKS = os.path.join(ROOT, "tests", "host_checks")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+pytestmark = pytest.mark.skipif(not (os.path.exists(HIPCC) or shutil.which(HIPCC)), reason="hipcc not available")
+
+
+def test_mid_plan_tiles_the_work(tmp_path):
+    from paper_2305_14314_amd import binding, build
+    if not os.path.exists(binding.LIB_PATH):
+        build.build(verbose=False)
+    exe, pkg = str(tmp_path / "mid_plan_check"), os.path.dirname(binding.LIB_PATH)
+    subprocess.run([HIPCC, "--offload-arch=gfx950", "-O2", "-std=c++17", "-x", "hip", "-I", CSRC,
+                    os.path.join(CHECKS, "mid_plan_check.cpp"), "-o", exe, "-L", pkg, "-lqlora_hip", "-Wl,-rpath," + pkg],
+                   check=True, capture_output=True)
+    out = subprocess.run([exe], check=False, capture_output=True, text=True, timeout=300).stdout
+    assert out.startswith("OK "), out
+    assert int(out.split()[1]) > 3000
+
+
+def test_mid_mfma_operands_are_written_in_time(tmp_path):
+    from paper_2305_14314_amd import build
+    asm = str(tmp_path / "midtok.s")
+    subprocess.run([HIPCC, *build.FLAGS, "-x", "hip", "--cuda-device-only", "-S", os.path.join(CSRC, "midtok.hip"), "-o", asm],
+                   check=True, capture_output=True)
+    out = subprocess.run([sys.executable, os.path.join(CHECKS, "mfma_operand_check.py"), asm], check=False, capture_output=True,
+                         text=True).stdout
+    assert out.startswith("OK "), out
+    assert int(out.split()[1]) > 3000
