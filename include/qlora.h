@@ -85,13 +85,13 @@ int qlora_last_hip_error(void);
  * Without Double Quantization (dq_blocksize = 0; Section 3 prices the fp32 constants at 32/64 = 0.5 bit per
  * parameter, 4.5 bit in all): `c1` holds the n fp32 first-level constants c2 themselves, in flattened block order,
  * and c2_code / c2_mean are not read (may be NULL).  Such a weight is accepted by quantise, dequantise and the
- * linear-layer calls, which then take the large-GEMM path at any M -- the few-token streaming kernels read
+ * linear-layer calls, which take the paths for more tokens at M <= 16 too -- the few-token streaming kernels read
  * double-quantised constants; the sizes qlora_linear_fwd_sizes / _bwd_sizes report cover that plan -- and refused with
  * QLORA_ERR_UNSUPPORTED by qlora_linear_fwd_multi at M <= 16.
  *
  * 8-bit integers (dtype = QLORA_INT8; Eq. 1 and Eq. 2 as printed): `packed` holds one signed byte per weight,
  * rows*cols bytes in flattened order, the constants are stored as above (with or without Double Quantization).
- * Accepted and refused exactly like a weight without Double Quantization: large-GEMM path at any M.
+ * Accepted and refused exactly like a weight without Double Quantization: dequantise + GEMM path at any M.
  */
 typedef struct {
   const uint8_t* packed;
@@ -220,10 +220,11 @@ qlora_status qlora_nf4_dequant(const qlora_nf4_view* Wq, uint16_t* W_bf16, void*
 qlora_status qlora_workspace_init(void* workspace, size_t workspace_bytes, void* hip_stream);
 
 /* Workspace (bytes) qlora_linear_fwd / qlora_linear_bwd need for this shape
- * (header included), whatever the weight's data type: at M <= 16 a 4-bit
- * double-quantised weight takes the streaming kernels and any other weight
- * (QLORA_INT8, dq_blocksize = 0) the dequantise + GEMM plan; the larger of
- * the two sizes is reported. */
+ * (header included), whatever the weight's data type and the path it takes:
+ * the streaming kernels (4-bit double-quantised, M <= 16), the product that
+ * decodes the weight itself (4-bit, M <= 512) or dequantise + GEMM.  The
+ * largest is reported; a call also accepts the smaller size of the dequantise
+ * + GEMM plan and then splits the second kind of product less. */
 qlora_status qlora_linear_fwd_sizes(int64_t M, int64_t h, int64_t o, int32_t r, size_t* workspace_bytes);
 qlora_status qlora_linear_bwd_sizes(int64_t M, int64_t h, int64_t o, int32_t r, size_t* workspace_bytes);
 
@@ -234,8 +235,8 @@ qlora_status qlora_linear_bwd_sizes(int64_t M, int64_t h, int64_t o, int32_t r, 
  * r must be a multiple of 16 and at most 256.  T_save (M x 2r bf16, may be NULL)
  * receives T = X * L1 for the backward pass as a pair of bf16 matrices side by
  * side: columns [0, r) hold bf16(T), columns [r, 2r) hold bf16(T - bf16(T)).  Any M >= 1 is accepted: a few
- * tokens (M <= 16) take a bandwidth-bound streaming path, larger M the MFMA
- * GEMM path. */
+ * tokens (M <= 16) take a bandwidth-bound streaming path, up to 512 a product that
+ * decodes the weight itself, larger M the MFMA GEMM on a dequantised copy. */
 qlora_status qlora_linear_fwd(const uint16_t* X, const qlora_nf4_view* Wq,
                               const uint16_t* L1, const uint16_t* L2, float s,
                               int64_t M, int32_t r,
@@ -280,7 +281,7 @@ qlora_status qlora_linear_bwd_acc(const uint16_t* dY, const uint16_t* X, const q
  * e / 8 for e = m*h + k, 1 = kept; the same mask must be passed to the forward and the backward call of a step.
  * 0 <= p < 1 (else QLORA_ERR_SHAPE); keep_mask may be NULL only when r = 0, where the calls are the plain ones.
  * T_save / T_saved hold (B o X) * L1 for the 0/1 mask B, as a [hi | lo] pair (the 1/(1-p) is applied with s).
- * These calls always take the large-GEMM path (no few-token streaming kernel); workspaces are sized by
+ * These calls take the paths for more than a few tokens at any M (no streaming kernel); workspaces are sized by
  * qlora_linear_dropout_sizes (either out-pointer may be NULL).  The backward call takes both kinds of adapter
  * gradient outputs of qlora_linear_bwd and qlora_linear_bwd_acc; any of them may be NULL.  Everything else --
  * layouts, alignment, ownership, errors, tolerance -- as for qlora_linear_fwd / qlora_linear_bwd. */
@@ -407,8 +408,8 @@ qlora_status qlora_hbm_probe(int32_t mode, const void* src, void* dst, int64_t b
  * dequantised weight): mode 0 dequantises the weight into the workspace and multiplies; mode 1 decodes the weight's
  * tiles inside the product (codes and block constants go from HBM to the matrix cores' LDS tiles, the bf16 weight is
  * never in HBM).  The decoded tiles are the same bits either way; the adapter term is added first instead of last in
- * mode 1, so outputs may differ in the last bf16 bit.  Mode 1 applies to 4-bit types with cols % 64 == 0 and r <= 64
- * and falls back to mode 0 otherwise.  mode < 0 only queries.  Returns the previous mode.  Process-wide. */
+ * mode 1, so outputs may differ in the last bf16 bit.  Mode 1 applies above 512 tokens (below, 4-bit weights are
+ * decoded inside the product in either mode) to 4-bit types with cols % 64 == 0 and r <= 64 and falls back to mode 0 otherwise.  mode < 0 only queries.  Returns the previous mode.  Process-wide. */
 int32_t qlora_bwd_fused_dequant(int32_t mode);
 
 /* Testing aid: how many times a slab's last contributor polls for the adapter's partial sums before it hands the
