@@ -36,7 +36,8 @@
 //    sub-step; reads, MFMAs and waits are volatile asm so that this order is the program order, with
 //    hand-placed s_waitcnt (the compiler's automatic waits cannot tell a DMA into one slot from a read of another
 //    across the loop back-edge and would drain all DMAs every iteration).
-//  * LDS rows are 128 bytes (64 k); the eight 16-byte chunks of row r sit at chunk ^ ((r >> 1) & 7).  LDS has 64
+//  * LDS rows are 128 bytes (64 k); the eight 16-byte chunks of row r sit at chunk ^ ((r >> 1) & 7) on the token side (and
+//    at chunk ^ b_swizzle(r) on the weight side, whose fragments take rows in another order).  LDS has 64
 //    banks: a ds_read_b128 is served 16 lanes (256 bytes) per cycle -- the 16 rows of one operand tile at one
 //    logical chunk -- which alternate between the two halves of the bank space while the swizzle spreads the 8
 //    rows of each half over its 8 sixteen-byte groups: no bank conflicts (counter-checked).
@@ -133,6 +134,11 @@ __device__ __forceinline__ uint32_t code_dword(uint64_t a, uint64_t b, int d) {
 #define QL_LDS_WRITE(addr, data, imm) \
   asm volatile("ds_write_b128 %0, %1 offset:%2\n\ts_nop 1" ::"v"(addr), "v"(data), "n"(imm))
 
+// The 16-byte chunks of row r of a weight-side tile sit at chunk ^ b_swizzle(r): the 16 rows 8a + 4b + c (a, c = 0 .. 3, b
+// fixed) that a fragment read takes at one logical chunk alternate between the two halves of the bank space (c % 2) and
+// cover all eight 16-byte groups of each.  Rows 32 apart agree.
+__device__ __forceinline__ int b_swizzle(int r) { return (((r >> 3) & 3) << 1) | ((r >> 1) & 1); }
+
 #define QL_LDS_READ(dst, addr, imm) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(imm))
 __device__ __forceinline__ void wait_frags(Frags<4>& f) {
   asm volatile("s_waitcnt lgkmcnt(0)"
@@ -205,7 +211,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
   for (int j = 0; j < NB; ++j) {
     const int r = (NW * j + wave) * 8 + (lane >> 3);
     b_rows[j] = (n0 + r < p.N) ? r : p.N - 1 - n0;
-    b_chunk[j] = ((lane & 7) ^ ((r >> 1) & 7)) * 8;
+    b_chunk[j] = ((lane & 7) ^ b_swizzle(r)) * 8;
   }
   Dma<NA> da;
   Dma<NB> db;
@@ -238,7 +244,10 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
   const int wm = wave / (NW / 2), wn = wave % (NW / 2);
   // MFMA 16x16x32: lane (i = lane % 16, g = lane / 16) holds row i of a 16-row operand tile at k = 8 g .. 8 g + 7 of
   // the 32-wide sub-step kk, i.e. logical chunk 4 kk + g.  16-row tiles are 2 KB apart and share the swizzle.
-  const int a_row = wm * 128 + (lane & 15), b_row = wn * WN + (lane & 15), g4 = lane >> 4;
+  // On the weight side two consecutive operand tiles take 32 rows between them: row i of tile 2q + b is row
+  // 32 q + 8 (i / 4) + 4 b + i % 4 of the wave's columns, so that a lane's four accumulators of both tiles are eight
+  // neighbouring output columns (16-byte stores).  b_swizzle() spreads the rows of either tile over the banks.
+  const int a_row = wm * 128 + (lane & 15), b_row = wn * WN + 8 * ((lane & 15) >> 2) + (lane & 3), g4 = lane >> 4;
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
   // FUSED: this lane's row of the weight tiles (clamped to the matrix like the DMA rows), its two buffers, the
   // table value of its lane, and where the row lies in a slot: chunk d at (wbase ^ 16 d), the XOR being the swizzle.
@@ -254,7 +263,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
     c_voff = (int)fused_const_offset(rc, 0, p.KT0);
     tabv = p.tab[lane & 15];
 #pragma unroll
-    for (int w = 0; w < 3; ++w) wbase[w] = lds0 + w * 65536 + tid * 128 + ((tid >> 1) & 7) * 16;
+    for (int w = 0; w < 3; ++w) wbase[w] = lds0 + w * 65536 + tid * 128 + b_swizzle(tid) * 16;
   }
   // step of segment 0 behind tile t of the fused order (t >= KT1), clamped to the last
   auto seg0_step = [&](int t) { return fused_seg0_step(t, KT, p.KT1); };
@@ -264,10 +273,10 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
 #pragma unroll
     for (int w = 0; w < 3; ++w) {
       baseA[kk][w] = lds0 + w * 65536 + a_row * 128 + (((4 * kk + g4) ^ ((a_row >> 1) & 7)) * 16);
-      baseB[kk][w] = lds0 + w * 65536 + b_row * 128 + (((4 * kk + g4) ^ ((b_row >> 1) & 7)) * 16);
+      baseB[kk][w] = lds0 + w * 65536 + b_row * 128 + (((4 * kk + g4) ^ b_swizzle(b_row)) * 16);
     }
 #define QL_READ_A(dst, slot, kk, i) QL_LDS_READ(dst, baseA[kk][(slot) >> 1], ((slot) & 1) * kSlot + (i) * 2048)
-#define QL_READ_B(dst, slot, kk, i) QL_LDS_READ(dst, baseB[kk][(slot) >> 1], ((slot) & 1) * kSlot + (i) * 2048)
+#define QL_READ_B(dst, slot, kk, i) QL_LDS_READ(dst, baseB[kk][(slot) >> 1], ((slot) & 1) * kSlot + ((i) >> 1) * 4096 + ((i) & 1) * 512)
 
   f32x4 acc[8][NI];
 #pragma unroll
@@ -279,11 +288,12 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
   // The MFMAs below are inline asm, invisible to the compiler's hazard recogniser: a vector-ALU write of an
   // accumulator register needs 2 wait states before an MFMA reads it as its addend.  Pin every initialisation
   // in front of a few idle cycles (without this the compiler sank the zeroing of one accumulator right in front
-  // of its first MFMA, which then read the register's old contents).
+  // of its first MFMA, which then read the register's old contents): volatile statements keep their order.
 #pragma unroll
   for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int j = 0; j < NI; ++j) asm volatile("s_nop 3" : "+a"(acc[i][j]));
+    for (int j = 0; j < NI; ++j) asm volatile("" : "+a"(acc[i][j]));
+  asm volatile("s_nop 3");
 
   // ---- prologue: A(0) B(0) A(1) B(1) A(2) into slots 0 .. 4 ---------------------------------------
   Codes U = {}, L = {};                                      // FUSED: rows of tiles in use / landing (see QL_ITER)
@@ -490,33 +500,38 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
                  "v"(lk[23]), "v"(lk[24]), "v"(lk[25]), "v"(lk[26]), "v"(lk[27]), "v"(lk[28]), "v"(lk[29]), "v"(lk[30]),
                  "v"(lk[31]));
   }
-  // likewise the other way: an MFMA's result may be read by the vector ALU only 18 wait states after its issue
+  // likewise the other way: an MFMA's result may be read by the vector ALU only 18 wait states after its issue.  Once for
+  // all 64 accumulator tiles, every one of which is read behind its own statement below (idle cycles in every statement
+  // cost 2.7 us per output tile)
+  asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3");
 #pragma unroll
   for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int j = 0; j < NI; ++j) asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3" : "+a"(acc[i][j]));
+    for (int j = 0; j < NI; ++j) asm volatile("" : "+a"(acc[i][j]));
 
   // ---- epilogue: one rounding to bf16 ------------------------------------------------------------
   // The MFMAs take the weight-side fragment as their first operand, so an accumulator tile is the TRANSPOSE of
-  // the output tile: lane (j = lane % 16, g = lane / 16) holds output row 16 mi + j and the four consecutive
-  // columns 16 ni + 4 g .. + 3, which go out as one 8-byte store (a quarter of the store instructions of the
-  // untransposed tile, whose lanes hold four rows of one column).  One 64-bit base per lane; tiles that lie wholly
-  // inside M (all but the last tile-row) skip the per-row bound checks.  N % 4 == 0: a group of four columns is
+  // the output tile: lane (j = lane % 16, g = lane / 16) holds output row 16 mi + j and, of the 32 columns that tiles 2q
+  // and 2q + 1 share, the eight consecutive ones 32 q + 8 g .. + 7, which go out as one 16-byte store (half the store
+  // instructions of 8-byte ones, and whole 64-byte sectors).  One 64-bit base per lane; tiles that lie wholly
+  // inside M (all but the last tile-row) skip the per-row bound checks.  N % 8 == 0: a group of eight columns is
   // inside or outside as a whole.
   const bool rows_inside = m0 + BM <= p.M;
   const int m_lane = m0 + wm * 128 + (lane & 15);            // first row this lane stores
-  const int n_lane = n0 + wn * WN + 4 * g4;                  // its first column
+  const int n_lane = n0 + wn * WN + 8 * g4;                  // its first column
   uint16_t* const cb = p.C + (int64_t)m_lane * p.ldc + n_lane;
 #pragma unroll
   for (int mi = 0; mi < 8; ++mi) {
     if (!rows_inside && m_lane + mi * 16 >= p.M) continue;
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni) {
-      if (n_lane + ni * 16 >= p.N) continue;
-      uint2 q;
-      q.x = pack_bf16x2(acc[mi][ni][0], acc[mi][ni][1]);
-      q.y = pack_bf16x2(acc[mi][ni][2], acc[mi][ni][3]);
-      *(uint2*)(cb + (int64_t)(mi * 16) * p.ldc + ni * 16) = q;
+    for (int q = 0; q < NI / 2; ++q) {
+      if (n_lane + q * 32 >= p.N) continue;
+      uint4 v;
+      v.x = pack_bf16x2(acc[mi][2 * q][0], acc[mi][2 * q][1]);
+      v.y = pack_bf16x2(acc[mi][2 * q][2], acc[mi][2 * q][3]);
+      v.z = pack_bf16x2(acc[mi][2 * q + 1][0], acc[mi][2 * q + 1][1]);
+      v.w = pack_bf16x2(acc[mi][2 * q + 1][2], acc[mi][2 * q + 1][3]);
+      *(uint4*)(cb + (int64_t)(mi * 16) * p.ldc + q * 32) = v;
     }
   }
 }
@@ -527,7 +542,7 @@ hipError_t launch_gemm_nt(const uint16_t* A0, const uint16_t* B0, int64_t lda0, 
                           const uint16_t* A1, const uint16_t* B1, int64_t lda1, int64_t ldb1, int K1,
                           uint16_t* C, int64_t ldc, int M, int N, hipStream_t st) {
   if (K0 <= 0 || K0 % BK != 0 || K1 < 0 || K1 % BK != 0) return hipErrorInvalidValue;
-  if (N % 4 != 0 || ldc % 4 != 0 || ((uintptr_t)C & 7u)) return hipErrorInvalidValue;    // 8-byte output stores
+  if (N % 8 != 0 || ldc % 8 != 0 || ((uintptr_t)C & 15u)) return hipErrorInvalidValue;   // 16-byte output stores
   // a tile's rows are addressed with 32-bit byte offsets from its first row
   const int64_t ld_max = std::max(std::max(lda0, ldb0), std::max(K1 ? lda1 : 0, K1 ? ldb1 : 0));
   if (256 * ld_max * 2 + (int64_t)(K0 > K1 ? K0 : K1) * 2 >= (1ll << 31)) return hipErrorInvalidValue;
@@ -626,7 +641,7 @@ hipError_t launch_gemm_nt_fused(const uint16_t* A0, const uint8_t* Bq, const flo
                                 int K0, const uint16_t* A1, const uint16_t* B1, int64_t lda1, int64_t ldb1, int K1,
                                 uint16_t* C, int64_t ldc, int M, int N, hipStream_t st) {
   if (!gemm_nt_fused_fits(K0, K1, N) || !Bq || !Bc || !tab16) return hipErrorInvalidValue;
-  if (N % 4 != 0 || ldc % 4 != 0 || ((uintptr_t)C & 7u) || ((uintptr_t)Bq & 15u) || ((uintptr_t)Bc & 3u))
+  if (N % 8 != 0 || ldc % 8 != 0 || ((uintptr_t)C & 15u) || ((uintptr_t)Bq & 15u) || ((uintptr_t)Bc & 3u))
     return hipErrorInvalidValue;
   const int64_t ld_max = std::max(lda0, std::max(K1 ? lda1 : 0, K1 ? ldb1 : 0));
   if (256 * ld_max * 2 + (int64_t)(K0 > K1 ? K0 : K1) * 2 >= (1ll << 31)) return hipErrorInvalidValue;
