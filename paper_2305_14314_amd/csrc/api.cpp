@@ -13,6 +13,8 @@
 #include "common.hpp"
 #include "launch.hpp"
 
+#define QL_TRY(expr) do { if (hipError_t e_ = (expr)) return hip_status(e_); } while (0)
+
 namespace {
 
 // ---- optional event bracket around the main GEMM launches (benchmark aid) ----
@@ -167,14 +169,104 @@ MidWs plan_mid(void* buf, size_t room, bool bwd, int64_t M, int64_t h, int64_t o
   return m;
 }
 
+// Floats of the split-K partials of the largest of a layer's skinny products, each in a launch of its own.
+size_t small_part_floats(int64_t M, int64_t h, int64_t o, int32_t r) {
+  const size_t u = (size_t)qlora::small_job_splits((int)M, r, (int)o, 0) * M * r;
+  const size_t t = (size_t)qlora::small_job_splits((int)M, r, (int)h, 0) * M * r;
+  const size_t l1 = (size_t)qlora::small_job_splits((int)h, r, (int)M, 0) * h * r;
+  const size_t l2 = (size_t)qlora::small_job_splits(r, (int)o, (int)M, 0) * r * o;
+  return std::max(std::max(u, t), std::max(l1, l2));
+}
+
+// The skinny products of a call, several to a launch.  Their partials are carved from a pool; a job that finds no room
+// (or no place in the list) first sends off what is collected.  A product of at most four K-steps takes no splits and
+// finishes in its own epilogue where its outputs allow (bf16 or accumulated gradients): dL1 and dL2 of 256 tokens at
+// 1024 x 1024 take 6.7 us so (32 workgroups), and a finalize launch alone takes 4.9.  At eight K-steps (512 tokens,
+// 4096 x 4096) it is 19.5 us against 8.2 + 4.9 in four splits: the chain of K-steps is what such a workgroup waits for.
+struct SmallBatch {
+  qlora::SmallJobs jobs{};
+  qlora::FinList fin{};
+  char* pool; size_t room, used = 0;
+  hipStream_t st;
+  SmallBatch(void* p, size_t bytes, hipStream_t s) : pool((char*)p), room(bytes), st(s) {}
+
+  // `tiles`: output tiles of the products that share the launch, counted from the layers' shapes alone: the order of a
+  // sum, and with it every bit of a result, does not depend on which outputs a call wants or on the room it has.
+  hipError_t add(qlora::SmallJob j, int tiles) {
+    const bool can_direct = !j.fin.hl && (!j.fin.out0 || j.fin.w0 == j.J);
+    j.direct = can_direct && (j.K + 63) / 64 <= 4;
+    j.fin.splits = j.direct ? 1 : qlora::small_job_splits(j.I, j.J, j.K, tiles - qlora::small_tiles(j.I, j.J));
+    for (int turn = 0; turn < 2; ++turn) {
+      const size_t need = j.direct ? 0 : (size_t)j.fin.splits * j.I * j.J * sizeof(float);
+      if (jobs.n < qlora::kSmallMax && (j.direct || fin.n < qlora::kFinMax) && used + need <= room) {
+        j.fin.part = (const float*)(pool + used);
+        used += align_up(need, 256);
+        if (!j.direct) {
+          j.fin.I = j.I; j.fin.J = j.J;
+          fin.add(j.fin);
+        }
+        jobs.j[jobs.n++] = j;
+        return hipSuccess;
+      }
+      if (turn == 0)
+        if (hipError_t e = finish()) return e;
+    }
+    return hipErrorInvalidValue;             // the pool holds any one product: not reached
+  }
+  hipError_t launch() {                      // the products; their finalize jobs stay in `fin` for the caller to place
+    const hipError_t e = qlora::launch_small_jobs(jobs, st);
+    jobs.n = 0;
+    return e;
+  }
+  hipError_t finish() {
+    if (hipError_t e = launch()) return e;
+    const hipError_t e = qlora::launch_fin(fin, st);
+    fin = qlora::FinList{};
+    used = 0;
+    return e;
+  }
+};
+qlora::SmallJob job_t(const uint16_t* X, int64_t h, const uint16_t* L1, int64_t M, int r, const uint8_t* mask) {
+  qlora::SmallJob j{};
+  j.kind = qlora::kSmallT; j.A = X; j.lda = h; j.B = L1; j.ldb = r; j.amask = mask; j.I = (int)M; j.J = r; j.K = (int)h;
+  return j;
+}
+qlora::SmallJob job_u(const uint16_t* dY, int64_t ldy, const uint16_t* L2, int64_t o, int64_t M, int r) {
+  qlora::SmallJob j{};
+  j.kind = qlora::kSmallU; j.A = dY; j.lda = ldy; j.B = L2; j.ldb = o; j.I = (int)M; j.J = r; j.K = (int)o;
+  return j;
+}
+qlora::SmallJob job_dl1(const uint16_t* X, int64_t h, const uint16_t* Uhl, int64_t M, int r, float s, const uint8_t* mask,
+                        uint16_t* dL1, float* acc) {
+  qlora::SmallJob j{};
+  j.kind = qlora::kSmallDL1; j.A = X; j.lda = h; j.B = Uhl; j.ldb = 2 * r; j.hl_off = r; j.amask = mask;
+  j.I = (int)h; j.J = r; j.K = (int)M;
+  j.fin.out0 = dL1; j.fin.ld0 = r; j.fin.w0 = r; j.fin.scale0 = s; j.fin.acc = acc;
+  return j;
+}
+qlora::SmallJob job_dl2(const uint16_t* Thl, const uint16_t* dY, int64_t ldy, int64_t o, int64_t M, int r, float s,
+                        uint16_t* dL2, float* acc) {
+  qlora::SmallJob j{};
+  j.kind = qlora::kSmallDL2; j.A = Thl; j.lda = 2 * r; j.hl_off = r; j.B = dY; j.ldb = ldy;
+  j.I = r; j.J = (int)o; j.K = (int)M;
+  j.fin.out0 = dL2; j.fin.ld0 = o; j.fin.w0 = (int)o; j.fin.scale0 = s; j.fin.acc = acc;
+  return j;
+}
+qlora::FinJob fin_pad(const uint16_t* src, int64_t rows, int r, uint16_t* dst, int64_t ld, int width) {
+  qlora::FinJob f{};
+  f.src = src; f.I = (int)rows; f.J = r; f.out0 = dst; f.ld0 = ld; f.w0 = width;
+  return f;
+}
+
 struct FwdPlan {
   uint16_t* Wt;      // o x (h + rp)   dequantised weight, transposed (K-contiguous for the forward), and behind it in
                      //                every row L2^T with the rank zero-padded to a multiple of 64: both K segments
   uint16_t* Ts;      // M x rp    bf16(s * X L1)
   float* part;       // split-K partials of X L1
+  size_t part_bytes;
   float* fpart;      // few-token path: split partials of X What
   float* lpart;      // few-token path: partials of X L1
-  int rp, splits, fsplits, n_lparts;
+  int rp, fsplits, n_lparts;
   bool few;
   size_t bytes;      // what the size queries report
   size_t min_bytes;  // what a call accepts
@@ -194,9 +286,10 @@ FwdPlan plan_fwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allo
   }
   p.Wt = c.take<uint16_t>((size_t)(h + (r > 0 ? p.rp : 0)) * o);
   if (r > 0) {
-    p.splits = qlora::small_gemm_splits((int)M, r, (int)h);
+    const size_t pe = (size_t)qlora::small_job_splits((int)M, r, (int)h, 0) * M * r;
+    p.part_bytes = pe * sizeof(float);
     p.Ts = c.take<uint16_t>((size_t)M * p.rp);
-    p.part = c.take<float>((size_t)p.splits * M * r);
+    p.part = c.take<float>(pe);
   }
   p.min_bytes = c.off;
   p.bytes = qlora::kWorkspaceHeaderBytes + mid_region(c.off - qlora::kWorkspaceHeaderBytes, false, M, h, o, r);
@@ -209,10 +302,11 @@ struct BwdPlan {
   uint16_t* Us;      // M x rp    bf16(s * dY L2^T)
   uint16_t* Uhl;     // M x 2r    dY L2^T as a [hi | lo] bf16 pair
   uint16_t* Thl;     // M x 2r    X L1 as a [hi | lo] pair, recomputed when the caller saved none
-  float* part;       // split-K partials, reused by the four skinny products
+  float* part;       // split-K partials of any one skinny product
+  size_t part_bytes;
   float* fpart;      // few-token path: split partials of dY What^T
   float* lpart;      // few-token path: partials of dY L2^T
-  int rp, sU, sT, sL1, sL2, fsplits, n_lparts;
+  int rp, fsplits, n_lparts;
   bool few;
   size_t wd_bytes;   // of the region at Wd
   size_t bytes;
@@ -234,19 +328,13 @@ BwdPlan plan_bwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allo
     p.Wd = (uint16_t*)c.take<char>(p.wd_bytes);
   }
   if (r > 0) {
-    p.sU = qlora::small_gemm_splits((int)M, r, (int)o);
-    p.sT = qlora::small_gemm_splits((int)M, r, (int)h);
-    p.sL1 = qlora::small_gemm_splits((int)h, r, (int)M);
-    p.sL2 = qlora::small_gemm_splits(r, (int)o, (int)M);
-    size_t pe = (size_t)p.sU * M * r;
-    if ((size_t)p.sT * M * r > pe) pe = (size_t)p.sT * M * r;
-    if ((size_t)p.sL1 * h * r > pe) pe = (size_t)p.sL1 * h * r;
-    if ((size_t)p.sL2 * r * o > pe) pe = (size_t)p.sL2 * r * o;
+    const size_t pe = small_part_floats(M, h, o, r);
     p.L1p = (r % 64 && !p.few) ? c.take<uint16_t>((size_t)h * p.rp) : nullptr;
     p.Us = c.take<uint16_t>((size_t)M * p.rp);
     p.Uhl = c.take<uint16_t>((size_t)M * 2 * r);
     p.Thl = c.take<uint16_t>((size_t)M * 2 * r);
     p.part = c.take<float>(pe);
+    p.part_bytes = pe * sizeof(float);
   }
   p.bytes = c.off;
   return p;
@@ -484,7 +572,6 @@ qlora_status qlora_workspace_init(void* workspace, size_t workspace_bytes, void*
   return hip_status(qlora::launch_workspace_init(workspace, (hipStream_t)hip_stream));
 }
 
-#define QL_TRY(expr) do { if (hipError_t e_ = (expr)) return hip_status(e_); } while (0)
 
 }  // extern "C"
 
@@ -524,13 +611,17 @@ qlora_status linear_fwd_impl(const uint16_t* X, const qlora_nf4_view* Wq, const 
       return QLORA_OK;
     }
   }
+  SmallBatch batch(p.part, p.part_bytes, st);
   if (r > 0) {
-    // T = X L1 (Eq. 3): split-K partials, then Ts = bf16(s T) (rank zero-padded) and T_save = [hi | lo] of T
-    QL_TRY(qlora::launch_small_gemm(X, h, false, L1, r, true, 0, 0, (int)M, r, (int)h, p.part, p.splits, st, keep_mask));
-    QL_TRY(qlora::launch_small_finalize(p.part, p.splits, (int)M, r, p.Ts, p.rp, p.rp, s, T_save, nullptr, st));
+    // T = X L1 (Eq. 3): split-K partials, then (in the dequantise launch) Ts = bf16(s T) (rank zero-padded) and
+    // T_save = [hi | lo] of T
+    qlora::SmallJob t = job_t(X, h, L1, M, r, keep_mask);
+    t.fin.out0 = p.Ts; t.fin.ld0 = p.rp; t.fin.w0 = p.rp; t.fin.scale0 = s; t.fin.hl = T_save;
+    QL_TRY(batch.add(t, qlora::small_tiles((int)M, r)));
+    QL_TRY(batch.launch());
   }
   const int64_t ldw = h + (r > 0 ? p.rp : 0);               // one row of Wt: What^T[n][0 .. h), then L2^T[n][0 .. rp)
-  QL_TRY(qlora::launch_dequant_t(W, p.Wt, ldw, st, r > 0 ? L2 : nullptr, r, r > 0 ? p.rp : 0));
+  QL_TRY(qlora::launch_dequant_t(W, p.Wt, ldw, st, r > 0 ? L2 : nullptr, r, r > 0 ? p.rp : 0, 0, &batch.fin));
   // Y = X What + Ts L2 (Eq. 5): the adapter term is the second K segment of the same accumulators
   QL_TRY(gemm_nt_timed(X, p.Wt, h, ldw, (int)h, p.Ts, p.Wt + h, p.rp, ldw, r > 0 ? p.rp : 0, Y, o, (int)M, (int)o,
                                st));
@@ -619,7 +710,8 @@ struct StackPlan {
   uint16_t* Wt;      // (sum o) x (h + Rp): row n of layer l = What_l^T[n], then L2_l^T[n] in the layer's rank columns
   uint16_t* Ts;      // M x Rp: [s_0 X L1_0 | s_1 X L1_1 | ...], every layer's rank zero-padded to a multiple of 64
   float* part;       // split-K partials of one X L1 at a time
-  int Rp, off[QLORA_MULTI_MAX], rp[QLORA_MULTI_MAX], splits[QLORA_MULTI_MAX];
+  size_t part_bytes;
+  int Rp, off[QLORA_MULTI_MAX], rp[QLORA_MULTI_MAX];
   int64_t N;
   size_t bytes;
 };
@@ -632,14 +724,12 @@ StackPlan plan_fwd_stacked(void* ws, int64_t M, int32_t n, int64_t h, const int6
     p.off[l] = p.Rp;
     p.rp[l] = r[l] > 0 ? (r[l] + 63) / 64 * 64 : 0;
     p.Rp += p.rp[l];
-    if (r[l] > 0) {
-      p.splits[l] = qlora::small_gemm_splits((int)M, r[l], (int)h);
-      pe = std::max(pe, (size_t)p.splits[l] * M * r[l]);
-    }
+    if (r[l] > 0) pe = std::max(pe, (size_t)qlora::small_job_splits((int)M, r[l], (int)h, 0) * M * r[l]);
   }
   p.Wt = c.take<uint16_t>((size_t)(h + p.Rp) * p.N);
   if (p.Rp > 0) {
     p.Ts = c.take<uint16_t>((size_t)M * p.Rp);
+    p.part_bytes = pe * sizeof(float);
     p.part = c.take<float>(pe);
   }
   p.bytes = c.off;
@@ -679,17 +769,28 @@ qlora_status qlora_linear_fwd_stacked(const uint16_t* X, int32_t n, const qlora_
   if (workspace_bytes < p.bytes) return QLORA_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)hip_stream;
   const int64_t ldw = h + p.Rp;
+  // T_l = X L1_l (Eq. 3) of all layers in one launch, scaled and rounded into the layers' rank columns of Ts by the first
+  // layer's dequantise launch.  The partials lie where the last layer's dequantised weight will (written later), or, with
+  // one layer or little room there, in the plan's own buffer.
+  char* last = (char*)(p.Wt + (p.N - o[n - 1]) * ldw);
+  const size_t last_bytes = n > 1 ? (size_t)o[n - 1] * ldw * sizeof(uint16_t) / 256 * 256 : 0;
+  char* pool = (char*)align_up((size_t)last, 256);
+  const size_t pool_bytes = last_bytes > 256 ? last_bytes - 256 : 0;
+  const bool big = pool_bytes > p.part_bytes;
+  SmallBatch batch(big ? pool : (char*)p.part, big ? pool_bytes : p.part_bytes, st);
+  int tiles = 0;
+  for (int l = 0; l < n; ++l) tiles += r[l] > 0 ? qlora::small_tiles((int)M, r[l]) : 0;
+  for (int l = 0; l < n; ++l) {
+    if (r[l] == 0) continue;
+    qlora::SmallJob t = job_t(X, h, L1[l], M, r[l], nullptr);
+    t.fin.out0 = p.Ts + p.off[l]; t.fin.ld0 = p.Rp; t.fin.w0 = p.rp[l]; t.fin.scale0 = s[l]; t.fin.hl = T_save ? T_save[l] : nullptr;
+    QL_TRY(batch.add(t, tiles));
+  }
+  QL_TRY(batch.launch());
   int64_t n0 = 0;
   for (int l = 0; l < n; ++l) {
-    if (r[l] > 0) {
-      // T_l = X L1_l (Eq. 3), scaled and rounded into its rank columns of Ts
-      QL_TRY(qlora::launch_small_gemm(X, h, false, L1[l], r[l], true, 0, 0, (int)M, r[l], (int)h, p.part, p.splits[l], st,
-                                      nullptr));
-      QL_TRY(qlora::launch_small_finalize(p.part, p.splits[l], (int)M, r[l], p.Ts + p.off[l], p.Rp, p.rp[l], s[l],
-                                          T_save ? T_save[l] : nullptr, nullptr, st));
-    }
     QL_TRY(qlora::launch_dequant_t(to_dev(&Wq[l]), p.Wt + n0 * ldw, ldw, st, r[l] > 0 ? L2[l] : nullptr, r[l], p.Rp,
-                                   p.off[l]));
+                                   p.off[l], l == 0 ? &batch.fin : nullptr));
     n0 += o[l];
   }
   // Y[:, layer l's columns] = X What_l + s_l (X L1_l) L2_l (Eq. 5 per layer)
@@ -726,6 +827,7 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
   // a few hundred tokens: decode inside the product; the finalize step applies the dropout mask to the adapter's term
   const MidWs mid = !p.few && dX && streams_mid(Wq)
                         ? plan_mid(p.Wd, p.wd_bytes, true, M, h, o, r) : MidWs{};
+  qlora::FinList fin{};
   if (mid.plan.ok) {
     QL_TRY(qlora::launch_mid(true, dY, (int)M, W, mid.plan, L1, L2, r, s, keep_mask, mid.part, mid.lpart, mid.xpack, dX,
                              (r > 0 && want1) ? p.Uhl : nullptr, st));
@@ -736,12 +838,16 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
                                     (r > 0 && want1) ? p.Uhl : nullptr, st));
   } else if (r > 0 && (dX || want1)) {
     // U = dY L2^T: Us = bf16(s U) feeds the adapter segment of dX, the [hi | lo] pair of U feeds dL1
-    QL_TRY(qlora::launch_small_gemm(dY, o, false, L2, o, false, 0, 0, (int)M, r, (int)o, p.part, p.sU, st));
-    QL_TRY(qlora::launch_small_finalize(p.part, p.sU, (int)M, r, p.Us, p.rp, p.rp, s, p.Uhl, nullptr, st));
+    SmallBatch batch(p.part, p.part_bytes, st);
+    qlora::SmallJob u = job_u(dY, o, L2, o, M, r);
+    u.fin.out0 = p.Us; u.fin.ld0 = p.rp; u.fin.w0 = p.rp; u.fin.scale0 = s; u.fin.hl = p.Uhl;
+    QL_TRY(batch.add(u, qlora::small_tiles((int)M, r)));
+    QL_TRY(batch.launch());
+    fin = batch.fin;
   }
   if (!p.few && dX && !mid.plan.ok) {
     const uint16_t* B1 = L1;
-    if (r > 0 && p.L1p) { QL_TRY(qlora::launch_copy_pad(L1, (int)h, r, p.L1p, p.rp, st)); B1 = p.L1p; }
+    if (r > 0 && p.L1p) { fin.add(fin_pad(L1, h, r, p.L1p, p.rp, p.rp)); B1 = p.L1p; }
     const int K1 = r > 0 ? p.rp : 0;
     if (g_bwd_fused.load(std::memory_order_relaxed) && W.dtype != qlora::kTypeInt8 && o % 64 == 0 &&
         qlora::gemm_nt_fused_fits((int)o, K1, (int)h)) {
@@ -749,32 +855,39 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
       // What takes the h x o / 64 block constants and the 16 values of the data type instead
       float* consts = (float*)p.Wd;
       float* tab16 = consts + ((size_t)h * (o / 64) + 15) / 16 * 16;
+      QL_TRY(qlora::launch_fin(fin, st));
       QL_TRY(qlora::launch_block_consts(W, consts, tab16, st));
       QL_TRY(gemm_nt_fused_timed(dY, W.packed, W.dq ? consts : W.c1, tab16, o, (int)o, p.Us, B1, p.rp, p.rp, K1, dX, h,
                                  (int)M, (int)h, st));
     } else {
-      QL_TRY(qlora::launch_dequant(W, p.Wd, st));
+      QL_TRY(qlora::launch_dequant(W, p.Wd, st, 0, &fin));
       // dX = dY What^T + Us L1^T
       QL_TRY(gemm_nt_timed(dY, p.Wd, o, o, (int)o, p.Us, B1, p.rp, p.rp, K1, dX, h, (int)M, (int)h, st));
     }
     // LoRA dropout: a dropped input element gets no gradient through the adapter
     if (r > 0 && keep_mask) QL_TRY(qlora::launch_dropout_dx_fix(dX, (int)M, (int)h, keep_mask, p.Us, p.rp, L1, r, st));
+  } else {
+    QL_TRY(qlora::launch_fin(fin, st));
   }
-  if (want1) {
-    // dL1 = s X^T U: contraction over the tokens, both operands stored token-major; U enters as hi + lo
-    QL_TRY(qlora::launch_small_gemm(X, h, true, p.Uhl, 2 * r, true, 2, r, (int)h, r, (int)M, p.part, p.sL1, st, keep_mask));
-    QL_TRY(qlora::launch_small_finalize(p.part, p.sL1, (int)h, r, dL1, r, r, s, nullptr, aL1, st));
-  }
-  if (want2) {
+  if (want1 || want2) {
+    // The dequantised weight (or what else lay there) is done with: its place takes the partials of both gradients.
+    const bool big = p.wd_bytes > p.part_bytes;
+    SmallBatch batch(big ? (void*)p.Wd : (void*)p.part, big ? p.wd_bytes : p.part_bytes, st);
     const uint16_t* T = T_saved;
-    if (!T) {                                               // gradient checkpointing: recompute T = X L1
-      QL_TRY(qlora::launch_small_gemm(X, h, false, L1, r, true, 0, 0, (int)M, r, (int)h, p.part, p.sT, st, keep_mask));
-      QL_TRY(qlora::launch_small_finalize(p.part, p.sT, (int)M, r, nullptr, 0, 0, 0.0f, p.Thl, nullptr, st));
+    const bool need_t = want2 && !T;                        // gradient checkpointing: recompute T = X L1
+    const int tiles = qlora::small_tiles((int)h, r) + qlora::small_tiles(r, (int)o);
+    if (need_t) {
+      qlora::SmallJob t = job_t(X, h, L1, M, r, keep_mask);
+      t.fin.hl = p.Thl;
+      QL_TRY(batch.add(t, qlora::small_tiles((int)M, r)));        // split as in the forward
       T = p.Thl;
     }
+    // dL1 = s X^T U: contraction over the tokens, both operands stored token-major; U enters as hi + lo
+    if (want1) QL_TRY(batch.add(job_dl1(X, h, p.Uhl, M, r, s, keep_mask, dL1, aL1), tiles));
+    if (need_t) QL_TRY(batch.finish());
     // dL2 = s T^T dY with T as hi + lo rows
-    QL_TRY(qlora::launch_small_gemm(T, 2 * r, true, dY, o, true, 1, r, r, (int)o, (int)M, p.part, p.sL2, st));
-    QL_TRY(qlora::launch_small_finalize(p.part, p.sL2, r, (int)o, dL2, o, (int)o, s, nullptr, aL2, st));
+    if (want2) QL_TRY(batch.add(job_dl2(T, dY, o, o, M, r, s, dL2, aL2), tiles));
+    QL_TRY(batch.finish());
   }
   return QLORA_OK;
 }
@@ -820,6 +933,8 @@ struct StackBwdPlan {
   uint16_t* Uhl;     // M x 2 r_max: one layer's dY L2^T as a [hi | lo] pair, for its dL1
   uint16_t* Thl;     // M x 2 r_max: one layer's X L1, recomputed when the caller saved none
   float* part;       // split-K partials, reused by every skinny product
+  size_t part_bytes;
+  int r_max;
   int Rp, off[QLORA_MULTI_MAX], rp[QLORA_MULTI_MAX];
   int64_t N;
   size_t bytes;
@@ -829,6 +944,7 @@ StackBwdPlan plan_bwd_stacked(void* ws, int64_t M, int32_t n, int64_t h, const i
   Carver c(ws);
   size_t pe = 0;
   int r_max = 0;
+  p.r_max = 0;
   for (int l = 0; l < n; ++l) {
     p.N += o[l];
     p.off[l] = p.Rp;
@@ -836,10 +952,7 @@ StackBwdPlan plan_bwd_stacked(void* ws, int64_t M, int32_t n, int64_t h, const i
     p.Rp += p.rp[l];
     r_max = std::max(r_max, (int)r[l]);
     if (r[l] > 0) {
-      pe = std::max(pe, (size_t)qlora::small_gemm_splits((int)M, r[l], (int)o[l]) * M * r[l]);
-      pe = std::max(pe, (size_t)qlora::small_gemm_splits((int)M, r[l], (int)h) * M * r[l]);
-      pe = std::max(pe, (size_t)qlora::small_gemm_splits((int)h, r[l], (int)M) * h * r[l]);
-      pe = std::max(pe, (size_t)qlora::small_gemm_splits(r[l], (int)o[l], (int)M) * r[l] * o[l]);
+      pe = std::max(pe, small_part_floats(M, h, o[l], r[l]));
     }
   }
   p.Wd = c.take<uint16_t>((size_t)h * p.N);
@@ -848,7 +961,9 @@ StackBwdPlan plan_bwd_stacked(void* ws, int64_t M, int32_t n, int64_t h, const i
     p.Us = c.take<uint16_t>((size_t)M * p.Rp);
     p.Uhl = c.take<uint16_t>((size_t)M * 2 * r_max);
     p.Thl = c.take<uint16_t>((size_t)M * 2 * r_max);
+    p.part_bytes = pe * sizeof(float);
     p.part = c.take<float>(pe);
+    p.r_max = r_max;
   }
   p.bytes = c.off;
   return p;
@@ -892,37 +1007,55 @@ qlora_status qlora_linear_bwd_stacked(const uint16_t* dY, const uint16_t* X, int
   if (workspace_bytes < p.bytes) return QLORA_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)hip_stream;
   const int64_t N = p.N;
-  int64_t n0 = 0;
-  for (int l = 0; l < n; ++l) {
-    const uint16_t* dYl = dY + n0;                           // layer l's columns of dY, row stride N
-    const int rl = r[l];
-    if (rl > 0) {
-      // U_l = dY_l L2_l^T: bf16(s_l U_l) into the layer's rank columns of Us, the [hi | lo] pair for dL1
-      const int sU = qlora::small_gemm_splits((int)M, rl, (int)o[l]);
-      QL_TRY(qlora::launch_small_gemm(dYl, N, false, L2[l], o[l], false, 0, 0, (int)M, rl, (int)o[l], p.part, sU, st));
-      QL_TRY(qlora::launch_small_finalize(p.part, sU, (int)M, rl, p.Us + p.off[l], p.Rp, p.rp[l], s[l], p.Uhl, nullptr, st));
-      QL_TRY(qlora::launch_copy_pad(L1[l], (int)h, rl, p.L1s + p.off[l], p.rp[l], st, p.Rp));
-      if (dL1 && dL1[l]) {                                   // dL1_l = s_l X^T U_l
-        const int sL1 = qlora::small_gemm_splits((int)h, rl, (int)M);
-        QL_TRY(qlora::launch_small_gemm(X, h, true, p.Uhl, 2 * rl, true, 2, rl, (int)h, rl, (int)M, p.part, sL1, st));
-        QL_TRY(qlora::launch_small_finalize(p.part, sL1, (int)h, rl, dL1[l], rl, rl, s[l], nullptr, nullptr, st));
+  // The skinny products come first, all layers together, while the place of the dequantised weights is free for their
+  // pairs U, T and their partials; without the room there, layer by layer in the plan's own buffers.
+  const size_t pair = align_up((size_t)M * 2 * std::max(p.r_max, 1) * sizeof(uint16_t), 256);
+  const size_t wd_bytes = (size_t)h * N * sizeof(uint16_t) / 256 * 256;
+  const bool together = wd_bytes > 2 * n * pair + p.part_bytes;
+  int64_t col[QLORA_MULTI_MAX], n0 = 0;
+  for (int l = 0; l < n; ++l) { col[l] = n0; n0 += o[l]; }
+  for (int l0 = 0, l1; l0 < n; l0 = l1) {
+    l1 = together ? n : l0 + 1;
+    auto uhl = [&](int l) { return together ? (uint16_t*)((char*)p.Wd + l * pair) : p.Uhl; };
+    auto thl = [&](int l) { return together ? (uint16_t*)((char*)p.Wd + (n + l) * pair) : p.Thl; };
+    SmallBatch batch(together ? (char*)p.Wd + 2 * n * pair : (char*)p.part, together ? wd_bytes - 2 * n * pair : p.part_bytes, st);
+    auto want1 = [&](int l) { return r[l] > 0 && dL1 && dL1[l]; };
+    auto want2 = [&](int l) { return r[l] > 0 && dL2 && dL2[l]; };
+    auto need_t = [&](int l) { return want2(l) && !(T_saved && T_saved[l]); };
+    int tiles_tu = 0, tiles_dl = 0;          // of all layers' T (or U), and of their dL1 and dL2
+    for (int l = 0; l < n; ++l)
+      if (r[l] > 0) {
+        tiles_tu += qlora::small_tiles((int)M, r[l]);
+        tiles_dl += qlora::small_tiles((int)h, r[l]) + qlora::small_tiles(r[l], (int)o[l]);
       }
-      if (dL2 && dL2[l]) {                                   // dL2_l = s_l T_l^T dY_l
-        const uint16_t* T = T_saved ? T_saved[l] : nullptr;
-        if (!T) {
-          const int sT = qlora::small_gemm_splits((int)M, rl, (int)h);
-          QL_TRY(qlora::launch_small_gemm(X, h, false, L1[l], rl, true, 0, 0, (int)M, rl, (int)h, p.part, sT, st));
-          QL_TRY(qlora::launch_small_finalize(p.part, sT, (int)M, rl, nullptr, 0, 0, 0.0f, p.Thl, nullptr, st));
-          T = p.Thl;
-        }
-        const int sL2 = qlora::small_gemm_splits(rl, (int)o[l], (int)M);
-        QL_TRY(qlora::launch_small_gemm(T, 2 * rl, true, dYl, N, true, 1, rl, rl, (int)o[l], (int)M, p.part, sL2, st));
-        QL_TRY(qlora::launch_small_finalize(p.part, sL2, rl, (int)o[l], dL2[l], o[l], (int)o[l], s[l], nullptr, nullptr, st));
+    for (int l = l0; l < l1; ++l) {
+      if (r[l] == 0) continue;
+      // U_l = dY_l L2_l^T: bf16(s_l U_l) into the layer's rank columns of Us, the [hi | lo] pair for dL1
+      qlora::SmallJob u = job_u(dY + col[l], N, L2[l], o[l], M, r[l]);   // layer l's columns of dY, row stride N
+      u.fin.out0 = p.Us + p.off[l]; u.fin.ld0 = p.Rp; u.fin.w0 = p.rp[l]; u.fin.scale0 = s[l]; u.fin.hl = uhl(l);
+      QL_TRY(batch.add(u, tiles_tu));
+      if (need_t(l)) {
+        qlora::SmallJob t = job_t(X, h, L1[l], M, r[l], nullptr);
+        t.fin.hl = thl(l);
+        QL_TRY(batch.add(t, tiles_tu));
       }
     }
-    QL_TRY(qlora::launch_dequant(to_dev(&Wq[l]), p.Wd + n0, st, N));
-    n0 += o[l];
+    QL_TRY(batch.launch());
+    for (int l = l0; l < l1; ++l)
+      if (r[l] > 0) {
+        if (batch.fin.n == qlora::kFinMax) QL_TRY(batch.finish());
+        batch.fin.add(fin_pad(L1[l], h, r[l], p.L1s + p.off[l], p.Rp, p.rp[l]));
+      }
+    QL_TRY(batch.finish());
+    for (int l = l0; l < l1; ++l) {
+      if (want1(l)) QL_TRY(batch.add(job_dl1(X, h, uhl(l), M, r[l], s[l], nullptr, dL1[l], nullptr), tiles_dl));     // s_l X^T U_l
+      if (want2(l))                                                                                        // s_l T_l^T dY_l
+        QL_TRY(batch.add(job_dl2(need_t(l) ? thl(l) : T_saved[l], dY + col[l], N, o[l], M, r[l], s[l], dL2[l], nullptr),
+                         tiles_dl));
+    }
+    QL_TRY(batch.finish());
   }
+  for (int l = 0; l < n; ++l) QL_TRY(qlora::launch_dequant(to_dev(&Wq[l]), p.Wd + col[l], st, N));
   // dX = sum over the layers of dY_l What_l^T + Us_l L1_l^T: one product, contraction over all outputs, then all ranks
   QL_TRY(gemm_nt_timed(dY, p.Wd, N, N, (int)N, p.Us, p.L1s, p.Rp, p.Rp, p.Rp, dX, h, (int)M, (int)h, st));
   return QLORA_OK;

@@ -2,11 +2,17 @@
 // double-quantised constants -> bf16 weights.  HBM-bound: 0.516 B read + 2 B written per element.
 // One lane decodes one packed dword (8 weights of one 64-block) and stores 16 bytes.
 #include "common.hpp"
+#include "fin.hpp"
 #include "launch.hpp"
 
 namespace qlora {
 
 constexpr int kDeqThreads = 256;
+static_assert(kDeqThreads == kFinThreads, "finalize workgroups share the launch");
+// A launch may carry the finalize step of the skinny products that precede it on the stream (FIN): its first workgroups,
+// done long before the others; a launch of its own costs 4.8 us.
+template <bool FIN> struct FinArg { FinList f; };
+template <> struct FinArg<false> {};
 
 // The 16 values of the data type into LDS: NF4 from constants; another type (Section 4) from the argument, copied
 // by one thread with constant indices (a lane-indexed read of a by-value argument would go through scratch).
@@ -27,11 +33,16 @@ __device__ __forceinline__ float s8_to_f32(uint32_t p, int j) { return (float)((
 
 // I8: 8-bit integers, Eq. 2 as printed: w = q * absmax / 127, as bf16(fl32(q * fl32(c2 / 127))).  A lane then reads
 // 8 bytes instead of 4; `packed` and `n_dwords` count in lane-sized units (8 weights) either way.
-template <bool DQ, bool I8, bool GAP>
+template <bool DQ, bool I8, bool GAP, bool FIN>
 __global__ __launch_bounds__(kDeqThreads) void dequant_nf4_kernel(
     const void* __restrict__ packed_v, const uint8_t* __restrict__ code, const float* __restrict__ c1,
     const float* __restrict__ mean_ptr, uint4* __restrict__ out, int64_t n_dwords, uint32_t rows, uint32_t bpr,
-    const int dtype, const Table4 tab, const int64_t row_gap) {
+    const int dtype, const Table4 tab, const int64_t row_gap, const FinArg<FIN> fin) {
+  int bid = blockIdx.x, n_bid = gridDim.x;
+  if constexpr (FIN) {
+    if (bid < fin.f.blocks()) { fin_block<4>(fin.f, bid); return; }
+    bid -= fin.f.blocks(); n_bid -= fin.f.blocks();
+  }
   // GAP: the output rows are row_gap 16-byte groups apart (a wider buffer: several weights side by side); else back to back
   constexpr bool dq = DQ;                                    // Double Quantization, or the fp32 constants as they are
   const uint32_t* __restrict__ packed = (const uint32_t*)packed_v;
@@ -42,8 +53,8 @@ __global__ __launch_bounds__(kDeqThreads) void dequant_nf4_kernel(
   __syncthreads();
   const float mean = dq ? *mean_ptr : 0.0f;
 
-  const int64_t stride = (int64_t)gridDim.x * kDeqThreads;
-  for (int64_t d = (int64_t)blockIdx.x * kDeqThreads + threadIdx.x; d < n_dwords; d += stride) {
+  const int64_t stride = (int64_t)n_bid * kDeqThreads;
+  for (int64_t d = (int64_t)bid * kDeqThreads + threadIdx.x; d < n_dwords; d += stride) {
     uint32_t p, ph = 0;
     if constexpr (I8) {
       const uint2 pp = ((const uint2*)packed_v)[d];
@@ -85,25 +96,35 @@ __global__ __launch_bounds__(kDeqThreads) void dequant_nf4_kernel(
 // writes, for each of its 8 columns, the 8 k-consecutive bf16 as one 16-byte store, so stores
 // form 128-byte runs along k.  No LDS staging of data.
 //
-// Workgroup rows beyond the weight's (blockIdx.y >= ceil(h / 64)) transpose the adapter's L2 (r x o, bf16) the same
+// Workgroup rows beyond the weight's (row_id >= ceil(h / 64)) transpose the adapter's L2 (r x o, bf16) the same
 // way into columns h + col0 .. h + col0 + r - 1 of `out` and write zeros to the rest of columns h .. h + rp - 1, so
 // that one buffer of row stride ld_out >= h + rp holds both K segments of the forward product's weight-side operand
 // and no launch of its own is spent on a 1 MB transpose.  (col0 > 0: several layers stacked along n share the adapter
 // segment block-diagonally: a layer's rows hold its own L2^T in its own columns and zeros in the others'.)
-template <bool DQ, bool I8>
+template <bool DQ, bool I8, bool FIN>
 __global__ __launch_bounds__(kDeqThreads) void dequant_nf4_t_kernel(
     const void* __restrict__ packed_v, const uint8_t* __restrict__ code, const float* __restrict__ c1,
     const float* __restrict__ mean_ptr, uint16_t* __restrict__ out, int h, int o, int64_t ld_out, const int dtype,
-    const Table4 tab, const uint16_t* __restrict__ L2, int r, int col0) {
+    const Table4 tab, const uint16_t* __restrict__ L2, int r, int col0, const FinArg<FIN> fin) {
   constexpr bool dq = DQ;
+  int row_id = blockIdx.y;                                   // workgroup row; the finalize workgroups fill the first ones
+  if constexpr (FIN) {
+    const int fin_rows = (fin.f.blocks() + (int)gridDim.x - 1) / (int)gridDim.x;
+    if (row_id < fin_rows) {
+      const int b = row_id * (int)gridDim.x + (int)blockIdx.x;
+      if (b < fin.f.blocks()) fin_block<4>(fin.f, b);
+      return;
+    }
+    row_id -= fin_rows;
+  }
   const uint32_t* __restrict__ packed = (const uint32_t*)packed_v;
   const int w_rows = (h + 63) >> 6;                          // workgroup rows of the weight
-  if ((int)blockIdx.y >= w_rows) {
+  if (row_id >= w_rows) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int kg = lane >> 3, ng = lane & 7;
     const int n_blk = blockIdx.x * 4 + wave;
     if (n_blk * 64 >= o) return;
-    const int t_base = ((int)blockIdx.y - w_rows) * 64 + kg * 8;
+    const int t_base = (row_id - w_rows) * 64 + kg * 8;
     const int n_first = n_blk * 64 + ng * 8;
     uint4 row[8];                                            // row[j] = L2[t_base + j][n_first .. n_first + 7]
 #pragma unroll
@@ -137,7 +158,7 @@ __global__ __launch_bounds__(kDeqThreads) void dequant_nf4_t_kernel(
   const int kg = lane >> 3, ng = lane & 7;
   const int n_blk = blockIdx.x * 4 + wave;                  // 64-column block index within a row
   if (n_blk * 64 >= o) return;
-  const int k_base = blockIdx.y * 64 + kg * 8;
+  const int k_base = row_id * 64 + kg * 8;
   const int blocks_per_row = o >> 6;
 
   uint32_t p[8], ph[8];
@@ -178,18 +199,24 @@ __global__ __launch_bounds__(kDeqThreads) void dequant_nf4_t_kernel(
 }
 
 hipError_t launch_dequant_t(const NF4Dev& w, uint16_t* out, int64_t ld_out, hipStream_t st, const uint16_t* L2, int r,
-                            int rp, int col0) {
+                            int rp, int col0, const FinList* fin) {
   const int h = (int)w.rows, o = (int)w.cols;
   if (L2 == nullptr) { r = 0; col0 = 0; }                    // rp > 0 without an adapter: the segment is all zeros
   if (rp % 64 != 0 || col0 < 0 || col0 + r > rp || ld_out < h + rp || ld_out % 8 != 0) return hipErrorInvalidValue;
-  dim3 grid((unsigned)((o + 255) / 256), (unsigned)((h + 63) / 64 + rp / 64));
+  const bool with_fin = fin && fin->n > 0;
+  const unsigned gx = (unsigned)((o + 255) / 256);
+  const unsigned fin_rows = with_fin ? ((unsigned)fin->blocks() + gx - 1) / gx : 0;
+  dim3 grid(gx, (unsigned)((h + 63) / 64 + rp / 64) + fin_rows);
   const bool i8 = w.dtype == kTypeInt8;
+#define QL_DEQ_T2(DQ, I8, FIN, FARG)                                                                            \
+  hipLaunchKernelGGL((dequant_nf4_t_kernel<DQ, I8, FIN>), grid, dim3(kDeqThreads), 0, st, (const void*)w.packed, w.code, \
+                     w.c1, w.mean, out, h, o, ld_out, w.dtype, table4_host(w.dtype), L2, r, col0, FARG)
 #define QL_DEQ_T(DQ, I8)                                                                                        \
-  hipLaunchKernelGGL((dequant_nf4_t_kernel<DQ, I8>), grid, dim3(kDeqThreads), 0, st, (const void*)w.packed, w.code, \
-                     w.c1, w.mean, out, h, o, ld_out, w.dtype, table4_host(w.dtype), L2, r, col0)
+  do { if (with_fin) QL_DEQ_T2(DQ, I8, true, FinArg<true>{*fin}); else QL_DEQ_T2(DQ, I8, false, FinArg<false>{}); } while (0)
   if (w.dq) { if (i8) QL_DEQ_T(true, true); else QL_DEQ_T(true, false); }
   else      { if (i8) QL_DEQ_T(false, true); else QL_DEQ_T(false, false); }
 #undef QL_DEQ_T
+#undef QL_DEQ_T2
   return hipGetLastError();
 }
 
@@ -229,26 +256,31 @@ hipError_t launch_block_consts(const NF4Dev& w, float* consts, float* tab16, hip
   return hipGetLastError();
 }
 
-hipError_t launch_dequant(const NF4Dev& w, uint16_t* out, hipStream_t st, int64_t ld_out) {
+hipError_t launch_dequant(const NF4Dev& w, uint16_t* out, hipStream_t st, int64_t ld_out, const FinList* fin) {
   if (ld_out == 0) ld_out = w.cols;
   if (ld_out < w.cols || ld_out % 8 != 0) return hipErrorInvalidValue;
+  const bool gap = ld_out != w.cols, with_fin = fin && fin->n > 0;
+  if (gap && with_fin) return hipErrorInvalidValue;
   const int64_t n_dwords = w.rows * w.cols / 8;
   int64_t blocks = (n_dwords + kDeqThreads - 1) / kDeqThreads;
   const int64_t cap = 256 * 32;
   if (blocks > cap) blocks = cap;
+  if (with_fin) blocks += fin->blocks();
   const bool i8 = w.dtype == kTypeInt8;
-#define QL_DEQ(DQ, I8, GAP)                                                                                 \
-  hipLaunchKernelGGL((dequant_nf4_kernel<DQ, I8, GAP>), dim3((unsigned)blocks), dim3(kDeqThreads), 0, st,   \
+#define QL_DEQ2(DQ, I8, GAP, FIN, FARG)                                                                     \
+  hipLaunchKernelGGL((dequant_nf4_kernel<DQ, I8, GAP, FIN>), dim3((unsigned)blocks), dim3(kDeqThreads), 0, st,   \
                      (const void*)w.packed, w.code, w.c1, w.mean, (uint4*)out, n_dwords, (uint32_t)w.rows,  \
-                     (uint32_t)(w.cols / 64), w.dtype, table4_host(w.dtype), (ld_out - w.cols) / 8)
-  if (ld_out != w.cols) {
-    if (w.dq) { if (i8) QL_DEQ(true, true, true); else QL_DEQ(true, false, true); }
-    else      { if (i8) QL_DEQ(false, true, true); else QL_DEQ(false, false, true); }
-  } else {
-    if (w.dq) { if (i8) QL_DEQ(true, true, false); else QL_DEQ(true, false, false); }
-    else      { if (i8) QL_DEQ(false, true, false); else QL_DEQ(false, false, false); }
-  }
+                     (uint32_t)(w.cols / 64), w.dtype, table4_host(w.dtype), (ld_out - w.cols) / 8, FARG)
+#define QL_DEQ(DQ, I8)                                                                                      \
+  do {                                                                                                      \
+    if (gap) QL_DEQ2(DQ, I8, true, false, FinArg<false>{});                                                 \
+    else if (with_fin) QL_DEQ2(DQ, I8, false, true, FinArg<true>{*fin});                                    \
+    else QL_DEQ2(DQ, I8, false, false, FinArg<false>{});                                                    \
+  } while (0)
+  if (w.dq) { if (i8) QL_DEQ(true, true); else QL_DEQ(true, false); }
+  else      { if (i8) QL_DEQ(false, true); else QL_DEQ(false, false); }
 #undef QL_DEQ
+#undef QL_DEQ2
   return hipGetLastError();
 }
 

@@ -31,12 +31,15 @@ hipError_t launch_quantize_static(const float* W, int64_t rows, int64_t cols, ui
 
 // dequant.hip
 //   out[k][n] = dequant(W)[k][n] with row stride ld_out elements (0: cols; else >= cols and a multiple of 8)
-hipError_t launch_dequant(const NF4Dev& w, uint16_t* out, hipStream_t st, int64_t ld_out = 0);
+//   fin (only with ld_out = 0): finalize jobs that ride in the launch; they and the dequantisation must not touch one
+//   another's buffers
+struct FinList;
+hipError_t launch_dequant(const NF4Dev& w, uint16_t* out, hipStream_t st, int64_t ld_out = 0, const FinList* fin = nullptr);
 // out[n][k] = dequant(W)[k][n] with row stride ld_out (elements); requires h % 8 == 0.
 // rp > 0 (a multiple of 64, ld_out >= h + rp): the same launch also writes the adapter segment, columns h .. h + rp - 1:
 // out[n][h + col0 + t] = L2[t][n] for t < r (L2: r x o bf16, col0 + r <= rp; NULL: none) and zeros elsewhere.
 hipError_t launch_dequant_t(const NF4Dev& w, uint16_t* out, int64_t ld_out, hipStream_t st,
-                            const uint16_t* L2 = nullptr, int r = 0, int rp = 0, int col0 = 0);
+                            const uint16_t* L2 = nullptr, int r = 0, int rp = 0, int col0 = 0, const FinList* fin = nullptr);
 
 // gemm.hip: C[M x N] = A0 B0^T + A1 B1^T, all operands K-contiguous bf16, K0 and K1 multiples of 64.
 hipError_t launch_gemm_nt(const uint16_t* A0, const uint16_t* B0, int64_t lda0, int64_t ldb0, int K0,
@@ -73,26 +76,47 @@ hipError_t launch_mfma_probe(int mode, int iters, float* out, hipStream_t st);
 hipError_t launch_hbm_probe(int mode, const void* src, void* dst, int64_t bytes, uint32_t* sink, int wgs_per_cu,
                             hipStream_t st);
 
-// small.hip: skinny GEMMs of the LoRA branch with split-K fp32 partials, and layout helpers.
-//   part[split][I x J] = A(i,k) B(k,j);  ta: A stored [k][i] instead of [i][k];  tb: B stored [k][j] instead of [j][k].
-//   hl = 1 / 2: A / B is a [hi | lo] pair (the lo half hl_off elements behind the hi half) and enters as hi + lo;
-//   supported: (ta, tb, hl) = (0,1,0), (0,0,0), (1,1,1), (1,1,2).
-int small_gemm_splits(int I, int J, int K);
-//   amask (LoRA dropout; only with (0,1,0) and (1,1,2), lda % 8 == 0): elements of A whose keep-bit -- bit e % 8 of byte
-//   e / 8, e the element's offset from A -- is clear enter as zero.
-hipError_t launch_small_gemm(const uint16_t* A, int64_t lda, bool ta, const uint16_t* B, int64_t ldb, bool tb, int hl,
-                             int64_t hl_off, int I, int J, int K, float* part, int splits, hipStream_t st,
-                             const uint8_t* amask = nullptr);
+// small.hip: skinny GEMMs of the LoRA branch with split-K fp32 partials; several of them share a launch.
+//   part[split][I x J] = A(i,k) B(k,j), the four products of a layer by what they compute:
+//   T = X L1: A [i][k], B [k][j];  U = dY L2^T: A [i][k], B [j][k];  dL1 = X^T U: A [k][i], B a [hi | lo] pair [k][j];
+//   dL2 = T^T dY: A a [hi | lo] pair [k][i], B [k][j].  A pair's lo half lies hl_off elements behind its hi half.
+enum SmallKind { kSmallT = 0, kSmallU = 1, kSmallDL1 = 2, kSmallDL2 = 3 };
+// What becomes of a product's sum (see fin.hpp); with `src` a plain padded copy.
+struct FinJob {
+  const float* part; int splits, I, J;
+  uint16_t* out0; int64_t ld0; int w0; float scale0;
+  uint16_t* hl; float* acc;
+  const uint16_t* src;
+};
+constexpr int kFinMax = 12;
+struct FinList {
+  int n;
+  int first[kFinMax + 1];                    // first workgroup of each job; [n] = their number
+  FinJob j[kFinMax];
+  int add(const FinJob& job);
+  __host__ __device__ int blocks() const { return first[n]; }
+};
+struct SmallJob {
+  const uint16_t* A; int64_t lda;
+  const uint16_t* B; int64_t ldb;
+  int64_t hl_off;
+  const uint8_t* amask;                      // LoRA dropout (T, dL1; lda % 8 == 0): elements of A whose keep-bit -- bit e % 8 of byte e / 8, e the offset from A -- is clear enter as zero
+  int kind, I, J, K, k_per_split;            // k_per_split: filled by the launcher
+  int direct;                                // one split: the finalize step (out0 with w0 = J, acc) in the product's epilogue
+  FinJob fin;                                // part, splits and the outputs; I, J: filled by the launcher
+};
+constexpr int kSmallMax = 8;
+struct SmallJobs { int n; int first[kSmallMax]; SmallJob j[kSmallMax]; };
+static_assert(sizeof(SmallJobs) <= 2048 && sizeof(FinList) <= 1024, "kernel arguments");
+int small_tiles(int I, int J);
+//   splits of a job that shares its launch with `other_tiles` output tiles of other jobs
+int small_job_splits(int I, int J, int K, int other_tiles);
+hipError_t launch_small_jobs(SmallJobs& jobs, hipStream_t st);
+hipError_t launch_fin(const FinList& f, hipStream_t st);
 //   LoRA dropout: dX[m][k] -= sum_t Us[m][t] L1[k][t] (bf16 operands, fp32 sum, one more rounding to bf16) wherever the
 //   keep-bit of element (m, k) is clear.  dX is M x h, Us M x ld_us (first r columns used), L1 h x r.
 hipError_t launch_dropout_dx_fix(uint16_t* dX, int M, int h, const uint8_t* mask, const uint16_t* Us, int ld_us,
                                  const uint16_t* L1, int r, hipStream_t st);
-//   Sums the splits, then writes out0 = bf16(scale0 * sum) (w0 columns, zeros beyond J) and/or
-//   hl = [bf16(sum) | bf16(sum - bf16(sum))] (row stride 2 J) and/or adds scale0 * sum to the fp32 matrix acc (I x J).
-hipError_t launch_small_finalize(const float* part, int splits, int I, int J, uint16_t* out0, int64_t ld0, int w0,
-                                 float scale0, uint16_t* hl, float* acc, hipStream_t st);
-//   dst[row][0 .. Cp) = src[row][0 .. C) then zeros; dst rows ld_dst elements apart (0: Cp)
-hipError_t launch_copy_pad(const uint16_t* src, int R, int C, uint16_t* dst, int Cp, hipStream_t st, int64_t ld_dst = 0);
 
 // fewtok.hip: few-token (M <= 16) streaming path, one launch per call: fp32 split partials of the frozen product,
 // partials of the adapter's inner product, and the output written by the last workgroup to arrive at each slab

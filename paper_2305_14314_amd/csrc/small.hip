@@ -3,7 +3,12 @@
 // rank (<= 256), so these are bound by streaming X or dY from HBM, not by MFMA.
 //
 //   part[split][I x J] (fp32) = sum over this split's K range of A(i,k) * B(k,j)
-//   finalize: out = bf16(scale * sum over splits) and/or the sum as a [hi | lo] pair of bf16 matrices
+//   finalize (fin.hpp): out = bf16(scale * sum over splits) and/or the sum as a [hi | lo] pair of bf16 matrices; a job of
+//   one split does it in the product's own epilogue
+//
+// Up to eight such products (of one or more layers) share a launch, and so do their finalize steps, which may also ride in
+// a dequantise launch.  A stacked q / k / v forward + backward at 2000 tokens (5120 x 5120, rank 64) spent 204 of 770 us in
+// 28 launches of 5 - 12 us here; it takes 95 us in 5 now, and a launch streams X or dY at 2.6 - 3.1 TB/s.
 //
 // Such a pair carries 16 significant bits of an intermediate (T or U) into the adapter gradients.  Where it is
 // an operand (HL = 1: A, HL = 2: B) the kernel loads both halves' tiles and issues two MFMAs per fragment of
@@ -21,7 +26,10 @@
 // of 16 lanes, lane c supplies the address of an 8-byte chunk and lane i receives element i % 4 of the chunks
 // i / 4, i / 4 + 4, i / 4 + 8, i / 4 + 12 -- so with lane c pointing at (k0 + c / 4, rows R0 + 4 (c % 4) .. +3),
 // lane i ends up with row R0 + i at k0 .. k0 + 3, which is half an MFMA fragment (8 gathers of 16 bits before).
+#include <algorithm>
+
 #include "common.hpp"
+#include "fin.hpp"
 #include "launch.hpp"
 
 namespace qlora {
@@ -30,15 +38,6 @@ constexpr int ST = 64;                       // tile edge in I, J and K
 constexpr int kSmallThreads = 256;
 constexpr int kTPitch = 72;                  // elements per k-row of a row-index-contracted tile: 4 consecutive k-rows hit distinct banks
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
-
-struct SmallArgs {
-  const uint16_t* A; int64_t lda;
-  const uint16_t* B; int64_t ldb;
-  int64_t hl_off;            // HL != 0: element offset of the pair's lo half from its hi half (same row)
-  const uint8_t* amask;      // MASK: keep-bits of A's elements in storage order, one bit each
-  float* part;
-  int I, J, K, k_per_split;
-};
 
 typedef __attribute__((address_space(3))) char lds_char;
 
@@ -115,20 +114,20 @@ __device__ __forceinline__ bf16x8 small_frag(const lds_char* tile, int row, int 
   }
 }
 
+constexpr int kSmallTile = ST * kTPitch * 2;  // bytes of one operand tile in LDS
 template <bool TA, bool TB, int HL, bool MASK>
-__global__ __launch_bounds__(kSmallThreads) void small_gemm_kernel(const SmallArgs p) {
+__device__ __forceinline__ void small_gemm_body(const SmallJob& p, int local, char* smem) {
   static_assert(HL == 0 || (HL == 1 && TA) || (HL == 2 && TB), "a [hi | lo] operand is stored token-major");
   static_assert(!MASK || HL != 1, "the masked operand is X itself");
-  __shared__ __attribute__((aligned(16))) char sA_[ST * kTPitch * 2];
-  __shared__ __attribute__((aligned(16))) char sB_[ST * kTPitch * 2];
-  __shared__ __attribute__((aligned(16))) char sC_[HL ? ST * kTPitch * 2 : 16];
-  lds_char* sA = (lds_char*)sA_;
-  lds_char* sB = (lds_char*)sB_;
-  lds_char* sC = (lds_char*)sC_;
+  lds_char* sA = (lds_char*)smem;
+  lds_char* sB = (lds_char*)(smem + kSmallTile);
+  lds_char* sC = (lds_char*)(smem + 2 * kSmallTile);
+  const int gi = (p.I + ST - 1) / ST, gj = (p.J + ST - 1) / ST;
+  const int bi = local % gi, bj = local / gi % gj, split = local / (gi * gj);
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int i0 = blockIdx.x * ST, j0 = blockIdx.y * ST;
-  const int k_begin = blockIdx.z * p.k_per_split;
+  const int i0 = bi * ST, j0 = bj * ST;
+  const int k_begin = split * p.k_per_split;
   const int k_end = (k_begin + p.k_per_split < p.K) ? k_begin + p.k_per_split : p.K;
   const int wi = wave >> 1, wj = wave & 1;
   const int a_row = wi * 32 + (lane & 31), b_row = wj * 32 + (lane & 31), half = lane >> 5;
@@ -185,97 +184,96 @@ __global__ __launch_bounds__(kSmallThreads) void small_gemm_kernel(const SmallAr
     if (k0 + ST < k_end) step(R1, k0 + 3 * ST);
   }
 
-  float* out = p.part + (int64_t)blockIdx.z * p.I * p.J;
   const int j = j0 + wj * 32 + (lane & 31);
-  if (j < p.J) {
+  if (j >= p.J) return;
+  if (p.direct) {                                            // one split: what the finalize step would do, right here
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int i = i0 + wi * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-      if (i < p.I) out[(int64_t)i * p.J + j] = acc[v];
+      if (i >= p.I) continue;
+      if (p.fin.out0) p.fin.out0[(int64_t)i * p.fin.ld0 + j] = bf16_bits(acc[v] * p.fin.scale0);
+      if (p.fin.acc) p.fin.acc[(int64_t)i * p.J + j] += acc[v] * p.fin.scale0;
     }
+    return;
+  }
+  float* out = const_cast<float*>(p.fin.part) + (int64_t)split * p.I * p.J;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int i = i0 + wi * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
+    if (i < p.I) out[(int64_t)i * p.J + j] = acc[v];
   }
 }
 
-// Reduces the split partials in a fixed order (deterministic) and writes up to two bf16 outputs.
-//   sum(i, j)  = sum over splits of part[s][i][j]
-//   out0[i][j] = bf16(scale0 * sum) for j < J, zero for J <= j < w0                    (row stride ld0)
-//   hl[i][j]   = bf16(sum),  hl[i][J + j] = bf16(sum - hl[i][j])                       (row stride 2 J)
-//   acc[i][j] += scale0 * sum                                      (fp32, row stride J: gradient accumulation)
-__global__ void small_finalize_kernel(const float* __restrict__ part, int splits, int I, int J,
-                                      uint16_t* __restrict__ out0, int64_t ld0, int w0, float scale0,
-                                      uint16_t* __restrict__ hl, float* __restrict__ acc) {
-  const int wmax = (out0 && w0 > J) ? w0 : J;
-  const int64_t total = (int64_t)I * wmax;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int i = (int)(e / wmax), j = (int)(e % wmax);
-    float s = 0.0f;
-    if (j < J) {
-#pragma unroll 8
-      for (int sp = 0; sp < splits; ++sp) s += part[(int64_t)sp * I * J + (int64_t)i * J + j];
-    }
-    if (out0 && j < w0) out0[(int64_t)i * ld0 + j] = bf16_bits(s * scale0);
-    if (acc && j < J) acc[(int64_t)i * J + j] += s * scale0;
-    if (hl && j < J) {
-      const uint16_t hi = bf16_bits(s);
-      hl[(int64_t)i * 2 * J + j] = hi;
-      hl[(int64_t)i * 2 * J + J + j] = bf16_bits(s - bf16_lo_to_f32(hi));
-    }
-  }
+// Several products in one launch: workgroup b belongs to the last job whose first workgroup is <= b.  KINDS: the kinds that
+// occur (1 << kind), so that a launch carries no code it cannot reach.
+template <int KINDS, bool MASK>
+__global__ __launch_bounds__(kSmallThreads) void small_jobs_kernel(const SmallJobs jobs) {
+  __shared__ __attribute__((aligned(16))) char smem[((KINDS & 12) ? 3 : 2) * kSmallTile];
+  int q = 0;
+  while (q + 1 < jobs.n && (int)blockIdx.x >= jobs.first[q + 1]) ++q;
+  const SmallJob& p = jobs.j[q];
+  const int local = blockIdx.x - jobs.first[q];
+  if ((KINDS & 1) && p.kind == kSmallT) small_gemm_body<false, true, 0, MASK>(p, local, smem);
+  if ((KINDS & 2) && p.kind == kSmallU) small_gemm_body<false, false, 0, false>(p, local, smem);
+  if ((KINDS & 4) && p.kind == kSmallDL1) small_gemm_body<true, true, 2, MASK>(p, local, smem);
+  if ((KINDS & 8) && p.kind == kSmallDL2) small_gemm_body<true, true, 1, false>(p, local, smem);
 }
 
-// dst[row][0..Cp) = src[row][0..C) followed by zeros
-__global__ void copy_pad_kernel(const uint16_t* __restrict__ src, int R, int C, uint16_t* __restrict__ dst, int Cp,
-                                int64_t ld_dst) {
-  const int64_t total = (int64_t)R * Cp;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int row = (int)(e / Cp), c = (int)(e % Cp);
-    dst[(int64_t)row * ld_dst + c] = (c < C) ? src[(int64_t)row * C + c] : (uint16_t)0;
-  }
-}
+__global__ __launch_bounds__(kFinThreads) void fin_kernel(const FinList f) { fin_block(f, blockIdx.x); }
 
-int small_gemm_splits(int I, int J, int K) {
-  const int tiles = ((I + ST - 1) / ST) * ((J + ST - 1) / ST);
+// ~2 workgroups per CU over all jobs of a launch: every further split adds an fp32 partial tile to write and read back,
+// and past this point that traffic costs more than the extra loads in flight gain (measured: 256 -> +30 %, 1024 -> +8 %
+// time).
+int small_job_splits(int I, int J, int K, int other_tiles) {
   const int ksteps = (K + ST - 1) / ST;
-  // ~2 workgroups per CU: every further split adds an fp32 partial tile to write and read back, and past this
-  // point that traffic costs more than the extra loads in flight gain (measured: 256 -> +30 %, 1024 -> +8 % time)
-  int splits = (512 + tiles - 1) / tiles;
-  if (splits > ksteps) splits = ksteps;
-  if (splits > 64) splits = 64;
-  if (splits < 1) splits = 1;
-  return splits;
+  const int tiles = ((I + ST - 1) / ST) * ((J + ST - 1) / ST) + other_tiles;
+  return std::max(1, std::min(std::min((512 + tiles - 1) / tiles, 64), ksteps));
 }
+int small_tiles(int I, int J) { return ((I + ST - 1) / ST) * ((J + ST - 1) / ST); }
 
-hipError_t launch_small_gemm(const uint16_t* A, int64_t lda, bool ta, const uint16_t* B, int64_t ldb, bool tb, int hl,
-                             int64_t hl_off, int I, int J, int K, float* part, int splits, hipStream_t st,
-                             const uint8_t* amask) {
-  SmallArgs a;
-  a.A = A; a.lda = lda; a.B = B; a.ldb = ldb; a.hl_off = hl_off; a.part = part; a.I = I; a.J = J; a.K = K;
-  a.amask = amask;
-  if (amask && lda % 8 != 0) return hipErrorInvalidValue;
-  const int ksteps = (K + ST - 1) / ST;
-  a.k_per_split = ((ksteps + splits - 1) / splits) * ST;
-  dim3 grid((unsigned)((I + ST - 1) / ST), (unsigned)((J + ST - 1) / ST), (unsigned)splits);
-  dim3 block(kSmallThreads);
-  if (amask) {
-    if (!ta && tb && hl == 0) hipLaunchKernelGGL((small_gemm_kernel<false, true, 0, true>), grid, block, 0, st, a);
-    else if (ta && tb && hl == 2) hipLaunchKernelGGL((small_gemm_kernel<true, true, 2, true>), grid, block, 0, st, a);
-    else return hipErrorInvalidValue;
+hipError_t launch_small_jobs(SmallJobs& jobs, hipStream_t st) {
+  if (jobs.n == 0) return hipSuccess;
+  int kinds = 0, wgs = 0;
+  bool mask = false;
+  for (int q = 0; q < jobs.n; ++q) {
+    SmallJob& p = jobs.j[q];
+    const int ksteps = (p.K + ST - 1) / ST;
+    p.k_per_split = (ksteps + p.fin.splits - 1) / p.fin.splits * ST;
+    p.fin.I = p.I; p.fin.J = p.J;
+    if (p.direct && (p.fin.splits != 1 || p.fin.hl || (p.fin.out0 && p.fin.w0 != p.J))) return hipErrorInvalidValue;
+    if (p.amask && (p.lda % 8 != 0 || (p.kind != kSmallT && p.kind != kSmallDL1))) return hipErrorInvalidValue;
+    kinds |= 1 << p.kind;
+    mask |= p.amask != nullptr;
+    jobs.first[q] = wgs;
+    wgs += small_tiles(p.I, p.J) * p.fin.splits;
   }
-  else if (!ta && tb && hl == 0) hipLaunchKernelGGL((small_gemm_kernel<false, true, 0, false>), grid, block, 0, st, a);
-  else if (!ta && !tb && hl == 0) hipLaunchKernelGGL((small_gemm_kernel<false, false, 0, false>), grid, block, 0, st, a);
-  else if (ta && tb && hl == 1) hipLaunchKernelGGL((small_gemm_kernel<true, true, 1, false>), grid, block, 0, st, a);
-  else if (ta && tb && hl == 2) hipLaunchKernelGGL((small_gemm_kernel<true, true, 2, false>), grid, block, 0, st, a);
-  else return hipErrorInvalidValue;
+  if (mask)                                                  // one mask for a launch: every T and dL1 job brings it
+    for (int q = 0; q < jobs.n; ++q)
+      if ((jobs.j[q].kind == kSmallT || jobs.j[q].kind == kSmallDL1) && !jobs.j[q].amask) return hipErrorInvalidValue;
+#define QL_SMALL(KINDS)                                                                                             \
+  case KINDS:                                                                                                       \
+    if (mask) hipLaunchKernelGGL((small_jobs_kernel<KINDS, true>), dim3((unsigned)wgs), dim3(kSmallThreads), 0, st, jobs); \
+    else hipLaunchKernelGGL((small_jobs_kernel<KINDS, false>), dim3((unsigned)wgs), dim3(kSmallThreads), 0, st, jobs);     \
+    break;
+  switch (kinds) {
+    QL_SMALL(1) QL_SMALL(2) QL_SMALL(3) QL_SMALL(4) QL_SMALL(5) QL_SMALL(8) QL_SMALL(12)
+    default: return hipErrorInvalidValue;
+  }
+#undef QL_SMALL
   return hipGetLastError();
 }
 
-hipError_t launch_small_finalize(const float* part, int splits, int I, int J, uint16_t* out0, int64_t ld0, int w0,
-                                 float scale0, uint16_t* hl, float* acc, hipStream_t st) {
-  const int wmax = (out0 && w0 > J) ? w0 : J;
-  int64_t blocks = ((int64_t)I * wmax + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  hipLaunchKernelGGL(small_finalize_kernel, dim3((unsigned)blocks), dim3(256), 0, st, part, splits, I, J, out0, ld0, w0,
-                     scale0, hl, acc);
+int FinList::add(const FinJob& job) {
+  j[n] = job;
+  const int64_t quads = (int64_t)job.I * std::max(job.out0 ? job.w0 : 0, job.J) / 4;
+  const int blocks = (int)std::min<int64_t>((quads + kFinThreads - 1) / kFinThreads, 1024);
+  first[n + 1] = first[n] + blocks;
+  return ++n;
+}
+
+hipError_t launch_fin(const FinList& f, hipStream_t st) {
+  if (f.n == 0) return hipSuccess;
+  hipLaunchKernelGGL(fin_kernel, dim3((unsigned)f.blocks()), dim3(kFinThreads), 0, st, f);
   return hipGetLastError();
 }
 
@@ -366,15 +364,6 @@ hipError_t launch_dropout_dx_fix(uint16_t* dX, int M, int h, const uint8_t* mask
   const int64_t n = (int64_t)M * h / 8;
   hipLaunchKernelGGL(dropout_dx_fix_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, dX, n, h, mask, Us,
                      ld_us, L1, r);
-  return hipGetLastError();
-}
-
-hipError_t launch_copy_pad(const uint16_t* src, int R, int C, uint16_t* dst, int Cp, hipStream_t st, int64_t ld_dst) {
-  if (ld_dst == 0) ld_dst = Cp;
-  if (ld_dst < Cp) return hipErrorInvalidValue;
-  int64_t blocks = ((int64_t)R * Cp + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  hipLaunchKernelGGL(copy_pad_kernel, dim3((unsigned)blocks), dim3(256), 0, st, src, R, C, dst, Cp, ld_dst);
   return hipGetLastError();
 }
 

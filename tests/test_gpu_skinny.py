@@ -1,0 +1,55 @@
+"""GPU parity of the skinny adapter products where their batching changes course: eight products and twelve finalize jobs
+of four layers in a launch, layers too small to lend their weight's place (one layer at a time), the largest contraction
+that finishes in the product's own epilogue (256 tokens) and the smallest that does not, ranks that are padded."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import bits_f64, dev_bf16, host_bits, upload_quant
+from test_gpu_linear import _check
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("save", [False, True])
+@pytest.mark.parametrize("M,h,outs,ranks", [(520, 704, [1024, 320, 768, 64], [16, 96, 80, 32]),
+                                            (1500, 64, [64, 128], [16, 48]), (256, 192, [64, 320, 128], [64, 0, 144]),
+                                            (257, 192, [64, 320, 128], [64, 0, 144]), (700, 128, [192], [256])])
+def test_stacked_batches(oracle, synth, M, h, outs, ranks, save):
+    import paper_2305_14314_amd as ql
+    n, ss = len(outs), [0.5, 1.0, 0.25, 2.0][:len(outs)]
+    print(f"case skinny batches M={M} h={h} o={outs} r={ranks} save={save}", flush=True)
+    hX, hdY = synth.normal_bf16((M, h), 1.0, 9000 + M), synth.normal_bf16((M, sum(outs)), 1.0, 9001 + M)
+    Wqs, Whats, hL1, hL2 = [], [], [], []
+    for l, (o, r) in enumerate(zip(outs, ranks)):
+        q = oracle.nf4_quantize(synth.normal_f32((h, o), synth.SIGMA_W, 9100 + l))
+        Wqs.append(upload_quant(q))
+        Whats.append(oracle.nf4_dequant(q))
+        hL1.append(synth.normal_bf16((h, r), 0.05, 9200 + l) if r else None)
+        hL2.append(synth.normal_bf16((r, o), 0.05, 9300 + l) if r else None)
+    L1s = [dev_bf16(a) if a is not None else None for a in hL1]
+    L2s = [dev_bf16(a) if a is not None else None for a in hL2]
+    X, dY = dev_bf16(hX), dev_bf16(hdY)
+    Ts = [torch.empty((M, 2 * r), dtype=torch.bfloat16, device="cuda") if r else None for r in ranks]
+    ws = ql.workspace_alloc(ql.qlora_linear_fwd_stacked_sizes(M, h, outs, ranks))
+    ws[ql.binding.WORKSPACE_HEADER_BYTES:].fill_(0x7F)
+    Y = ql.qlora_linear_fwd_stacked(X, Wqs, L1s, L2s, ss, T_saves=Ts, workspace=ws)
+    ws = ql.workspace_alloc(ql.qlora_linear_bwd_stacked_sizes(M, h, outs, ranks))
+    ws[ql.binding.WORKSPACE_HEADER_BYTES:].fill_(0x7F)
+    dX, dL1s, dL2s = ql.qlora_linear_bwd_stacked(dY, X, Wqs, L1s, L2s, ss, T_saveds=Ts if save else None, workspace=ws)
+    torch.cuda.synchronize()
+    Yh, n0, ref_dx = host_bits(Y), 0, 0.0
+    for l, (o, r) in enumerate(zip(outs, ranks)):
+        dYl = np.ascontiguousarray(hdY[:, n0:n0 + o])
+        _check(Yh[:, n0:n0 + o], oracle.linear_fwd(hX, Whats[l], hL1[l], hL2[l], ss[l]), f"layer {l} Y")
+        ref_dx = ref_dx + oracle.linear_bwd_dx(dYl, Whats[l], hL1[l], hL2[l], ss[l])
+        if r:
+            t = host_bits(Ts[l])
+            want = bits_f64(hX) @ bits_f64(hL1[l])
+            # hi + lo: 16 significant bits, and an fp32 sum of h terms
+            assert np.abs(bits_f64(t[:, :r]) + bits_f64(t[:, r:]) - want).max() <= 2.0 ** -14 * np.abs(want).max() + 1e-6
+            r1, r2 = oracle.linear_bwd_dl(dYl, hX, hL1[l], hL2[l], ss[l])
+            _check(host_bits(dL1s[l]), r1, f"layer {l} dL1")
+            _check(host_bits(dL2s[l]), r2, f"layer {l} dL2")
+        n0 += o
+    _check(host_bits(dX), ref_dx, "dX")
