@@ -55,7 +55,7 @@ namespace qlora {
 
 namespace {
 
-constexpr int BM = 256, BK = 64, NSLOT = 5;                  // BN is 256, or 128 for the tail launch (template parameter)
+constexpr int BM = 256, BK = 64, NSLOT = 5;                  // BN is 256, 192 or 128 (template parameter)
 constexpr int kSlot = BM * BK * 2;                           // 32 KB: one 256-row operand tile
 constexpr int GM = 4;                                       // tile-rows per raster group
 constexpr int kMainWaves = 4;                                // waves per workgroup of the main (BN = 256) kernel
@@ -145,6 +145,11 @@ __device__ __forceinline__ void wait_frags(Frags<4>& f) {
                : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.a[4]), "+v"(f.a[5]), "+v"(f.a[6]),
                  "+v"(f.a[7]), "+v"(f.b[0]), "+v"(f.b[1]), "+v"(f.b[2]), "+v"(f.b[3]));
 }
+__device__ __forceinline__ void wait_frags(Frags<6>& f) {
+  asm volatile("s_waitcnt lgkmcnt(0)"
+               : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.a[4]), "+v"(f.a[5]), "+v"(f.a[6]),
+                 "+v"(f.a[7]), "+v"(f.b[0]), "+v"(f.b[1]), "+v"(f.b[2]), "+v"(f.b[3]), "+v"(f.b[4]), "+v"(f.b[5]));
+}
 __device__ __forceinline__ void wait_frags(Frags<8>& f) {
   asm volatile("s_waitcnt lgkmcnt(0)"
                : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.a[4]), "+v"(f.a[5]), "+v"(f.a[6]),
@@ -156,10 +161,9 @@ __device__ __forceinline__ void wait_frags(Frags<8>& f) {
 // ones three MFMAs before the wait that needs them, and every sub-step began with an exposed LDS latency.
 #define QL_MFMA(c, a, b) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b))
 
-// BN = 256 is the main configuration.  BN = 128 serves the columns left over when the 256-wide tiles do not fill
-// a whole number of rounds of the 256 CUs: half-width tiles finish that last, partly filled round in half the time.
-// NW = waves per workgroup, laid out 2 x NW/2: wave tiles are 128 x 128 (main configuration, 4 waves) or 128 x 64
-// (the half-width tail).
+// BN = 256 is the main configuration; 192 and 128 serve outputs, or their last columns, that fill the rounds of the
+// 256 CUs better with them (gemm_cut).  NW = waves per workgroup, laid out 2 x NW/2: wave tiles are 128 x 128, 128 x 96
+// or 128 x 64.
 //
 // FUSED: the weight-side tiles of K segment 0 are never in HBM as bf16.  Lane l of wave w owns row 64 w + l of every
 // such tile: it loads the row's 32 bytes of codes and its block constant two steps ahead, looks the 64 values up
@@ -170,9 +174,9 @@ __device__ __forceinline__ void wait_frags(Frags<8>& f) {
 // produces is a decoded one; its weight-side tile is the only one a DMA still brings.
 template <int BN, int NW, bool FUSED>
 __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
-  constexpr int WN = BN / (NW / 2);                          // wave tile width: 64, or 128 for 4 waves on a 256-wide tile
+  constexpr int WN = BN / (NW / 2);                          // wave tile width
   constexpr int NI = WN / 16;                                // MFMA columns per wave
-  static_assert(NI == 4 || NI == 8, "wave tiles are 128 x 64 or 128 x 128");
+  static_assert(NI == 4 || NI == 6 || NI == 8, "wave tiles are 128 x 64, 128 x 96 or 128 x 128");
   constexpr int NA = 32 / NW, NB = (BN / 8) / NW;            // DMA instructions per wave, step and operand
   constexpr int PER = (FUSED ? NA : NA + NB) / 2;            // DMA instructions per wave and sub-step
   static_assert((NA + NB) % 2 == 0 && PER <= 8, "DMA instructions are spread evenly over the two sub-steps");
@@ -536,6 +540,40 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
   }
 }
 
+// How an output of tiles_m tile-rows is cut into columns: `wide` 256-wide tile columns from the left, then `rest` columns of
+// rest_width in a launch of their own.
+struct GemmCut { int wide, rest, rest_width; };
+// One workgroup per CU: tiles run in rounds of 256, and a narrower tile costs less than its share is worth only where it
+// fills a round better.  Measured per K-step of 64 (a launch's time / rounds / steps): a round of 256-wide tiles takes
+// 1.05 us nearly empty and 1.36 us full (the board's power limit), 192-wide 0.86 / 1.05, 128-wide 0.66 / 0.79; a second
+// launch about 3 us.  The cut of the least cost by these figures is taken (of
+// about equal ones, the one of more 256-wide tiles).  dX of a stacked q / k / v at 2000 tokens
+// (5120 columns, K 15552: 160 tiles of 256) 264 -> 234 us with 216 tiles of 192; 1024 x 4096 (K 4160) 69 -> 43 us and
+// 600 x 8192 (K 8256) 132 -> 86 us with 128-wide tiles; 4096 x 5120 (K 5184) 193 -> 162 and 1500 x 11008 (K 4160)
+// 156 -> 124 us with 192-wide ones; 4096 x 8192 (K 8256), two full rounds, 351 us against 382 (192) and 388 (128).
+GemmCut gemm_cut(int tiles_m, int N, int steps) {
+  struct Cost { int width, empty, full; };                   // of a round, in 0.01 us per K-step
+  constexpr Cost kWide = {256, 105, 136}, kNarrow[2] = {{192, 86, 105}, {128, 66, 79}};
+  constexpr int kCUs = 256, kLaunch = 300;
+  auto cost = [&](const Cost& c, int cols) {
+    const int64_t tiles = (int64_t)cols * tiles_m, last = tiles % kCUs;
+    return (tiles / kCUs * c.full + (last ? c.empty + (c.full - c.empty) * last / kCUs : 0)) * steps;
+  };
+  const int tiles_n = (N + 255) / 256;
+  GemmCut best = {tiles_n, 0, 256};
+  int64_t best_cost = cost(kWide, tiles_n);
+  auto consider = [&](int wide) {
+    for (const Cost& c : kNarrow) {
+      const int rest = (N - wide * 256 + c.width - 1) / c.width;
+      const int64_t t = cost(kWide, wide) + cost(c, rest) + (wide > 0 ? kLaunch : 0);
+      if (t * 101 < best_cost * 100) { best_cost = t; best = {wide, rest, c.width}; }
+    }
+  };
+  for (int wide = tiles_n - 1; wide > 0 && wide >= tiles_n - kCUs; --wide) consider(wide);   // a round has at most 256 columns
+  consider(0);
+  return best;
+}
+
 }  // namespace
 
 hipError_t launch_gemm_nt(const uint16_t* A0, const uint16_t* B0, int64_t lda0, int64_t ldb0, int K0,
@@ -552,24 +590,17 @@ hipError_t launch_gemm_nt(const uint16_t* A0, const uint16_t* B0, int64_t lda0, 
   a.A1 = A1; a.B1 = B1; a.lda1 = lda1; a.ldb1 = ldb1; a.KT1 = K1 / BK;
   a.C = C; a.ldc = ldc; a.M = M; a.N = N;
   a.tiles_m = (M + BM - 1) / BM;
-  const int tiles_n = (N + 255) / 256;
-  // One workgroup per CU: tiles run in rounds of 256.  When the last round would be at most half full and is made
-  // of whole tile columns, those columns go to a second launch with half-width tiles (twice as many workgroups,
-  // half the time each) instead of occupying a full round.
-  constexpr int kCUs = 256;
-  const int total = a.tiles_m * tiles_n;
-  const int rem = total % kCUs;
-  int tail_cols = 0;
-  if (total > kCUs && rem > 0 && 2 * rem <= kCUs && rem % a.tiles_m == 0) tail_cols = rem / a.tiles_m;
-  a.n_begin = 0;
-  a.tiles_n = tiles_n - tail_cols;
-  hipLaunchKernelGGL((gemm_nt_kernel<256, kMainWaves, false>), dim3((unsigned)(a.tiles_m * a.tiles_n)),
-                     dim3(kMainWaves * 64), 0, st, a);
-  if (tail_cols > 0) {
-    a.n_begin = a.tiles_n * 256;
-    a.tiles_n = (N - a.n_begin + 127) / 128;
-    hipLaunchKernelGGL((gemm_nt_kernel<128, 4, false>), dim3((unsigned)(a.tiles_m * a.tiles_n)), dim3(256), 0, st, a);
-  }
+  const GemmCut cut = gemm_cut(a.tiles_m, N, a.KT0 + a.KT1);
+  auto launch = [&](int width, int n_begin, int tiles_n) {
+    a.n_begin = n_begin;
+    a.tiles_n = tiles_n;
+    const dim3 grid((unsigned)(a.tiles_m * tiles_n)), block(256);
+    if (width == 256) hipLaunchKernelGGL((gemm_nt_kernel<256, kMainWaves, false>), grid, block, 0, st, a);
+    else if (width == 192) hipLaunchKernelGGL((gemm_nt_kernel<192, 4, false>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((gemm_nt_kernel<128, 4, false>), grid, block, 0, st, a);
+  };
+  if (cut.wide > 0) launch(256, 0, cut.wide);
+  if (cut.rest > 0) launch(cut.rest_width, cut.wide * 256, cut.rest);
   return hipGetLastError();
 }
 
