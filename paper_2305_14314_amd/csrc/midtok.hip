@@ -5,7 +5,7 @@
 // Why its own path: with 256 x 256 tiles a product of a few hundred tokens has 4 .. 100 tiles for 256 compute units, and
 // the pass that dequantises the weight moves five times the bytes of the packed weight (2.5 against 0.5 per weight).
 // Whole forward call, dequantise + GEMM against this: 4096 x 11008 at 40 tokens 108 -> 22 us, 5120 x 13824 at 333 tokens
-// 158 -> 90 us; forward + backward 1024 x 1024 at 256 tokens 96 -> 60 us, 4096 x 4096 at 512 tokens 220 -> 114 us.
+// 158 -> 90 us; forward + backward 1024 x 1024 at 256 tokens 96 -> 51 us, 4096 x 4096 at 512 tokens 220 -> 107 us.
 //
 // Two or three launches on the caller's stream:
 //   pre       (more than 64 tokens) the token operand in MFMA-fragment order, so that the main kernel's operand loads
@@ -734,12 +734,13 @@ void launch_main(const MidArgs& a, hipStream_t st) {
 }  // namespace
 
 namespace {
-// One of the two launch shapes: kw = 4, one wave per SIMD with tiles of up to 128 tokens, or kw = 8, two waves per SIMD with
-// tiles of up to 64.  Per unit of work the first is faster (a decoded fragment meets twice the tokens), the second has the
-// cheaper fixed part (half the partials).
-MidPlan plan_shape(bool bwd, int kw, int64_t M, int64_t K, int64_t N, int r, size_t room, double* us) {
+// One of the launch shapes: kw = 4, one wave per SIMD with tiles of up to `group` = 128 or 64 tokens, or kw = 8, two waves
+// per SIMD with tiles of up to 64.  Per unit of work tiles of 128 tokens are fastest (a decoded fragment meets twice the
+// tokens); tiles of 64 have the cheaper fixed part and give a small layer twice the workgroups (dX of
+// 1024 x 1024 at 256 tokens: main kernel 16.5 -> 12.7 us with 128 workgroups instead of 64; 4096 x 4096 at 128 tokens, the
+// three kernels together: 37.1 -> 33.8; 4096 x 4096 at 512 tokens, where both fill the chip: 48.3, and 51.5 with 64).
+MidPlan plan_shape(bool bwd, int kw, int group, int64_t M, int64_t K, int64_t N, int r, size_t room, double* us) {
   MidPlan p{};
-  const int group = kw == 4 ? 128 : 64;
   const int n_tg = (int)((M + group - 1) / group);
   p.KW = kw;
   p.MF = (int)((M + 16 * n_tg - 1) / (16 * n_tg));
@@ -762,10 +763,10 @@ MidPlan plan_shape(bool bwd, int kw, int64_t M, int64_t K, int64_t N, int r, siz
   // The number of workgroups (at most one per compute unit, and what the workspace has room for): the smallest estimated
   // time in microseconds of the longest workgroup -- its units, and the ends of its segments -- plus the partials' way
   // through memory.  Measured (main kernel, r = 64): kw = 4 with 8 token tiles 28.5 at 16 steps a wave, 56.4 at 43;
-  // kw = 8 with 4 tiles 29.5 at 16, 66.8 at 43; a workgroup whose range crosses into a second tile pays a second end
+  // (4 token tiles 31.8 at 32); kw = 8 with 4 tiles 29.5 at 16, 66.8 at 43; a workgroup whose range crosses into a second tile pays a second end
   // (4096 x 11008 at 40 tokens: 21.3 with ranges that cross, 17.4 with every tile in two equal parts).  All in closed form:
   // a call plans on the host every time.
-  const double step = (bwd ? 2.0 : 1.0) * (kw == 4 ? 0.30 + 0.0875 * p.MF : 0.55 + 0.20 * p.MF);
+  const double step = (bwd ? 2.0 : 1.0) * (kw == 4 ? 0.38 + 0.0775 * p.MF : 0.55 + 0.20 * p.MF);
   const double seg_end = 2.0 + 0.75 * p.MF, tile_us = p.MF * 16 * kSlab * 4 / 4.0e6;
   const int64_t units = tiles * ups, most = std::min<int64_t>(256 - std::min(items, 128), units);
   const size_t one = (size_t)M * N * 4;
@@ -786,10 +787,20 @@ MidPlan mid_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room) 
   const int64_t K = bwd ? o : h, N = bwd ? h : o;
   if (M < 1 || M > kMidTokens || o > (1 << 24) || h > (1 << 24) || (M + 127) * K * 2 >= (1ll << 31) || h * o / 2 >= (1ll << 31))
     return MidPlan{};                                        // 32-bit buffer offsets
-  double us8 = 0, us4 = 0;
-  const MidPlan p8 = bwd ? MidPlan{} : plan_shape(bwd, 8, M, K, N, r, room, &us8);
-  const MidPlan p4 = bwd || M > kMidUnpacked ? plan_shape(bwd, 4, M, K, N, r, room, &us4) : MidPlan{};
-  return p4.ok && (!p8.ok || us4 < us8) ? p4 : p8;
+  // the least estimated time; of equal ones the first
+  MidPlan best{};
+  double best_us = 0;
+  auto consider = [&](int kw, int group) {
+    double us = 0;
+    const MidPlan p = plan_shape(bwd, kw, group, M, K, N, r, room, &us);
+    if (p.ok && (!best.ok || us < best_us)) { best = p; best_us = us; }
+  };
+  if (!bwd) consider(8, 64);
+  if (bwd || M > kMidUnpacked) {
+    consider(4, 128);
+    if (M > 64) consider(4, 64);                             // below, tiles of 128 hold all tokens anyway
+  }
+  return best;
 }
 
 hipError_t launch_mid(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const MidPlan& p, const uint16_t* L1,
