@@ -1,19 +1,23 @@
 // Blockwise NF4 quantisation with Double Quantization (arXiv 2305.14314, Eq. 1 and Section 3).
 //
-// Four launches on the caller's stream, no host synchronisation:
+// Three launches on the caller's stream, no host synchronisation:
 //   zero_bins      clears the 256 exponent bins used for the exact mean
 //   quantize_nf4   per 64-block: absmax (DPP row reduce), reciprocal, nearest NF4 index (32-bucket table
 //                  in LDS plus one comparison), nibble pack;
 //                  writes the fp32 constant c2 to scratch and adds it to the exponent bins
-//   dq_mean        exact sum of all c2 from the bins, divided by n, rounded once to fp32
-//   dq_encode      per run of 256 constants: c2 - mean, absmax -> c1, E4M3 codes
+//   dq_encode      exact sum of all c2 from the bins, divided by n, rounded once to fp32 (every workgroup for itself: the
+//                  2 KB of bins and a few dozen operations, against 5.5 us for a launch of its own; the two
+//                  steps together took 11.4 us at 11008 x 4096 and take 7.1); then per run of
+//                  256 constants: c2 - mean, absmax -> c1, E4M3 codes
 //
 // The mean is exact and independent of summation order: every fp32 constant is
 // mantissa * 2^(exponent), the mantissas are summed per exponent in 64-bit integers
 // (integer atomics commute), and the bins are combined in multi-word integer arithmetic.
+#include <algorithm>
 #include <mutex>
 
 #include "common.hpp"
+#include "dq_mean.hpp"
 #include "launch.hpp"
 
 namespace qlora {
@@ -108,99 +112,52 @@ __global__ __launch_bounds__(kQThreads) void quantize_nf4_kernel(
   if (mine) atomicAdd(&bins[threadIdx.x], mine);
 }
 
-// Single wave.  sum = SUM_e bins[e] * 2^(e-1) in units of 2^-149, as 12 x 32-bit limbs;
-// mean = round_to_nearest_even_fp32(sum / n).  Only the non-empty bins (found with wave ballots)
-// and the non-zero limbs are visited, so the serial part is a few dozen operations.
-__global__ __launch_bounds__(64) void dq_mean_kernel(const unsigned long long* __restrict__ bins,
-                                                     uint32_t n, float* __restrict__ mean_out) {
-  __shared__ unsigned long long lb[256];
-  unsigned long long present[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const unsigned long long v = bins[q * 64 + threadIdx.x];
-    lb[q * 64 + threadIdx.x] = v;
-    present[q] = __ballot(v != 0ull);
-  }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-
-  constexpr int L = 12;
-  uint32_t acc[L];
-  for (int k = 0; k < L; ++k) acc[k] = 0;
-  int top_limb = -1;
-  for (int q = 0; q < 4; ++q) {
-    unsigned long long mask = present[q];
-    while (mask) {
-      const int e = q * 64 + __builtin_ctzll(mask);
-      mask &= mask - 1;
-      if (e < 1 || e > 254) continue;                       // exponent 255 (inf/nan) never occurs: inputs are finite
-      const unsigned long long b = lb[e];
-      const int sh = e - 1, limb = sh >> 5, off = sh & 31;
-      // b < 2^56; b << off spans at most three limbs
-      const uint32_t p0 = (uint32_t)(b << off);
-      const unsigned long long hi = off ? (b >> (32 - off)) : (b >> 32);
-      const uint32_t parts[3] = {p0, (uint32_t)hi, (uint32_t)(hi >> 32)};
-      unsigned long long carry = 0;
-      for (int k = 0; k < L - limb; ++k) {
-        const unsigned long long t = (unsigned long long)acc[limb + k] + (k < 3 ? parts[k] : 0u) + carry;
-        acc[limb + k] = (uint32_t)t;
-        carry = t >> 32;
-        if (t && limb + k > top_limb) top_limb = limb + k;
-        if (k >= 2 && carry == 0) break;
-      }
-    }
-  }
-  uint32_t q[L];
-  for (int k = 0; k < L; ++k) q[k] = 0;
-  unsigned long long rem = 0;
-  for (int k = top_limb; k >= 0; --k) {                      // long division by n < 2^32
-    const unsigned long long cur = (rem << 32) | acc[k];
-    q[k] = (uint32_t)(cur / n);
-    rem = cur % n;
-  }
-  int top = -1;
-  for (int k = top_limb; k >= 0; --k)
-    if (q[k]) { top = k * 32 + 31 - __builtin_clz(q[k]); break; }
-  // keep the 24 leading bits of q (all of q if it is shorter), round on the rest and on rem/n
-  const int drop = top >= 24 ? top - 23 : 0;
-  auto bit = [&](int i) -> uint32_t { return (q[i >> 5] >> (i & 31)) & 1u; };
-  uint32_t kept = 0;
-  for (int i = top; i >= drop; --i) kept = (kept << 1) | bit(i);
-  bool half, sticky;
-  if (drop == 0) {
-    half = 2 * rem >= n;
-    sticky = 2 * rem > n;
-  } else {
-    half = bit(drop - 1) != 0;
-    sticky = rem != 0;
-    for (int i = drop - 2; i >= 0 && !sticky; --i) sticky = bit(i) != 0;
-  }
-  if (half && (sticky || (kept & 1u))) ++kept;              // kept <= 2^24
-  // result = kept * 2^(drop - 149) with kept <= 2^24: with drop = 0 the integer is the bit pattern itself
-  // (subnormals and the first binades); each further dropped bit raises the exponent field by one.
-  *mean_out = __builtin_bit_cast(float, kept + ((uint32_t)drop << 23));
-}
-
-// One workgroup per run of 256 first-level constants.
+// A run of 256 first-level constants at a time; the constants of a workgroup's first run are in flight while it works out
+// the mean.
+constexpr int kEncWgs = 1024;
 __global__ __launch_bounds__(kDqBlock) void dq_encode_kernel(const float* __restrict__ c2, int64_t n,
-                                                             const float* __restrict__ mean_ptr,
-                                                             uint8_t* __restrict__ code,
+                                                             const unsigned long long* __restrict__ bins,
+                                                             float* __restrict__ mean_out, uint8_t* __restrict__ code,
                                                              float* __restrict__ c1, uint32_t rows, uint32_t bpr) {
-  __shared__ float wmax[kDqBlock / 64];
-  const int64_t b = (int64_t)blockIdx.x * kDqBlock + threadIdx.x;
-  const float mean = *mean_ptr;
-  const float d = (b < n) ? __fsub_rn(c2[b], mean) : 0.0f;  // centred constant
-  const float m = wave_max(__builtin_fabsf(d));
-  if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
+  __shared__ float wmax[2][kDqBlock / 64];
+  __shared__ unsigned long long lb[256], present[4];
+  __shared__ float mean_s;
+  static_assert(kDqBlock == 256, "one bin per thread");
+  const int64_t runs = (n + kDqBlock - 1) / kDqBlock;
+  auto load = [&](int64_t run) {
+    const int64_t b = run * kDqBlock + threadIdx.x;
+    return c2[b < n ? b : 0];
+  };
+  float next = load(blockIdx.x);
+  const unsigned long long v = bins[threadIdx.x];
+  lb[threadIdx.x] = v;
+  const unsigned long long some = __ballot(v != 0ull);
+  if ((threadIdx.x & 63) == 0) present[threadIdx.x >> 6] = some;
   __syncthreads();
-  const float amax = __builtin_fmaxf(__builtin_fmaxf(wmax[0], wmax[1]), __builtin_fmaxf(wmax[2], wmax[3]));
-  float rc1 = (amax < __FLT_MIN__) ? 0.0f : __fdiv_rn(kF8Max, amax);
-  if (__builtin_isinf(rc1)) rc1 = 0.0f;
-  if (b < n) {                                               // runs follow the flattened order, storage is column-group-major
-    const uint32_t row = (uint32_t)b / bpr, blk = (uint32_t)b - row * bpr;
-    code[code_pos(rows, (int)bpr, row, (int)blk)] = (uint8_t)e4m3_encode(__fmul_rn(d, rc1));
+  if (threadIdx.x == 0) {
+    mean_s = mean_from_bins(lb, present, (uint32_t)n);
+    if (blockIdx.x == 0) *mean_out = mean_s;
   }
-  if (threadIdx.x == 0) c1[blockIdx.x] = amax;
+  __syncthreads();
+  const float mean = mean_s;
+  int par = 0;
+  for (int64_t run = blockIdx.x; run < runs; run += gridDim.x, par ^= 1) {
+    const float c = next;
+    const int64_t b = run * kDqBlock + threadIdx.x;
+    if (run + gridDim.x < runs) next = load(run + gridDim.x);
+    const float d = (b < n) ? __fsub_rn(c, mean) : 0.0f;    // centred constant
+    const float m = wave_max(__builtin_fabsf(d));
+    if ((threadIdx.x & 63) == 0) wmax[par][threadIdx.x >> 6] = m;
+    __syncthreads();                                         // two sets in turn: one barrier per run is enough
+    const float amax = __builtin_fmaxf(__builtin_fmaxf(wmax[par][0], wmax[par][1]), __builtin_fmaxf(wmax[par][2], wmax[par][3]));
+    float rc1 = (amax < __FLT_MIN__) ? 0.0f : __fdiv_rn(kF8Max, amax);
+    if (__builtin_isinf(rc1)) rc1 = 0.0f;
+    if (b < n) {                                             // runs follow the flattened order, storage is column-group-major
+      const uint32_t row = (uint32_t)b / bpr, blk = (uint32_t)b - row * bpr;
+      code[code_pos(rows, (int)bpr, row, (int)blk)] = (uint8_t)e4m3_encode(__fmul_rn(d, rc1));
+    }
+    if (threadIdx.x == 0) c1[run] = amax;
+  }
 }
 
 hipError_t launch_quantize(const float* W, int64_t rows, int64_t cols, uint8_t* packed, uint8_t* code, float* c1,
@@ -227,9 +184,8 @@ hipError_t launch_quantize(const float* W, int64_t rows, int64_t cols, uint8_t* 
     hipLaunchKernelGGL(quantize_nf4_kernel<1>, dim3((unsigned)blocks), dim3(kQThreads), 0, st, (const float4*)W,
                        n_vec4, (void*)packed, c2, bins, thr);
   if (!dq) return hipGetLastError();
-  hipLaunchKernelGGL(dq_mean_kernel, dim3(1), dim3(64), 0, st, bins, (uint32_t)n, mean);
-  const int64_t n1 = (n + kDqBlock - 1) / kDqBlock;
-  hipLaunchKernelGGL(dq_encode_kernel, dim3((unsigned)n1), dim3(kDqBlock), 0, st, c2, n, mean, code, c1,
+  const int64_t n1 = std::min<int64_t>((n + kDqBlock - 1) / kDqBlock, kEncWgs);
+  hipLaunchKernelGGL(dq_encode_kernel, dim3((unsigned)n1), dim3(kDqBlock), 0, st, c2, n, bins, mean, code, c1,
                      (uint32_t)rows, (uint32_t)(cols / kBlock));
   return hipGetLastError();
 }
