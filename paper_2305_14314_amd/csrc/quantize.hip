@@ -22,18 +22,16 @@
 
 namespace qlora {
 
-// Loads in flight: kQUnroll float4 per lane, kQWgsPerCu workgroups per CU (grid-stride beyond that).  Measured on
-// 8192 x 22016 tensors read cold (GB/s of algorithmic bytes): unroll x workgroups 2 x 6 and 3 x 4: 4.42 - 4.45;
-// 1 x 6: 4.40; 2 x 8: 4.28; 4 x 16 (the first choice): 4.06; 2 x 32: 3.83 -- past ~48 KB in flight per CU more requests
-// only queue up in front of the memory channels.
-#ifndef QL_Q_UNROLL
-#define QL_Q_UNROLL 2
-#endif
-#ifndef QL_Q_WGS_PER_CU
-#define QL_Q_WGS_PER_CU 6
-#endif
+// Loads in flight: kQUnroll float4 per lane, kQWgsPerCu workgroups per CU (grid-stride beyond that).  What counts is few
+// workgroups with many loads each: every workgroup pays the decision table, and with many of them the last round over a
+// matrix is uneven.  Whole call, us, on 4096 x 11008 / 5120 x 5120 / 8192 x 8192 / 8192 x 22016 read cold, unroll x
+// workgroups: 2 x 6 (the earlier choice) 65 / 48 / 90 / 193; 4 x 4: 60 / 45 / 88 / 200; 6 x 3: 60 / 41 / 89 / 196; 8 x 2:
+// 58 / 39 / 89 / 193, with non-temporal loads (the weights are read once) 59 / 39 / 89 / 190; 8 x 3: 60 / 40 / 86 / 199;
+// 10 x 2: 58 / 38 / 87 / 202; 12 x 2: 61 / 40 / 91 / 209; 16 x 1: 72 / 47 / 106 / 237.  Matrices of 2 M weights or fewer
+// take 25 - 26 us with any of them.
+constexpr int kQUnroll = 8, kQWgsPerCu = 2;
 constexpr int kQThreads = 256;
-constexpr int kQUnroll = QL_Q_UNROLL;
+typedef __attribute__((ext_vector_type(4))) float q_f32x4;
 
 __global__ void zero_bins_kernel(unsigned long long* bins) { bins[threadIdx.x] = 0ull; }
 
@@ -60,17 +58,17 @@ __global__ __launch_bounds__(kQThreads) void quantize_nf4_kernel(
   // kQUnroll independent float4 loads are issued before any is used.
   const int64_t stride = (int64_t)gridDim.x * kQThreads;
   for (int64_t v0 = (int64_t)blockIdx.x * kQThreads + threadIdx.x; v0 < n_vec4; v0 += kQUnroll * stride) {
-    float4 wv[kQUnroll];
+    q_f32x4 wv[kQUnroll];
 #pragma unroll
     for (int u = 0; u < kQUnroll; ++u) {
       const int64_t v = v0 + u * stride;
-      wv[u] = W[v < n_vec4 ? v : v0];                        // clamped: no branch around the load
+      wv[u] = __builtin_nontemporal_load((const q_f32x4*)W + (v < n_vec4 ? v : v0));   // clamped: no branch around the load
     }
 #pragma unroll
     for (int u = 0; u < kQUnroll; ++u) {
       const int64_t v = v0 + u * stride;
       if (v >= n_vec4) break;                                 // whole 16-lane rows drop out together
-      const float4 w = wv[u];
+      const q_f32x4 w = wv[u];
       float amax = __builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(w.x), __builtin_fabsf(w.y)),
                                    __builtin_fmaxf(__builtin_fabsf(w.z), __builtin_fabsf(w.w)));
       amax = row16_max(amax);                                 // c2 of this lane's block
@@ -171,7 +169,7 @@ hipError_t launch_quantize(const float* W, int64_t rows, int64_t cols, uint8_t* 
   float* c2 = dq ? (float*)((char*)scratch + 256 * sizeof(unsigned long long)) : c1;
   const int64_t n_vec4 = elems / 4;
   int64_t blocks = (n_vec4 + kQThreads - 1) / kQThreads;
-  const int64_t cap = 256 * QL_Q_WGS_PER_CU;                         // workgroups per CU
+  const int64_t cap = 256 * kQWgsPerCu;
   if (blocks > cap) blocks = cap;
   hipLaunchKernelGGL(zero_bins_kernel, dim3(1), dim3(256), 0, st, bins);
   if (dtype == 0)
