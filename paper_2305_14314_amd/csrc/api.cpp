@@ -112,8 +112,8 @@ qlora_status check_view(const qlora_nf4_view* v) {
   return QLORA_OK;
 }
 
-// The few-token streaming kernels read 4-bit indices and double-quantised constants; every other storage goes
-// through dequantise + GEMM whatever the token count.
+// The few-token streaming kernels read 4-bit indices and double-quantised constants; every other storage takes the paths
+// for more tokens whatever the token count.
 inline bool streams_few(const qlora_nf4_view* v) { return v->dq_blocksize != 0 && v->dtype != qlora::kTypeInt8; }
 
 // The kernels for tens to hundreds of tokens decode 4-bit indices, with or without Double Quantization.
@@ -930,9 +930,9 @@ struct StackBwdPlan {
   uint16_t* Wd;      // h x (sum o): the dequantised weights side by side
   uint16_t* L1s;     // h x Rp: the layers' L1, every rank zero-padded to a multiple of 64
   uint16_t* Us;      // M x Rp: bf16(s_l dY_l L2_l^T) in layer l's rank columns
-  uint16_t* Uhl;     // M x 2 r_max: one layer's dY L2^T as a [hi | lo] pair, for its dL1
-  uint16_t* Thl;     // M x 2 r_max: one layer's X L1, recomputed when the caller saved none
-  float* part;       // split-K partials, reused by every skinny product
+  uint16_t* Uhl;     // M x 2 r_max: one layer's dY L2^T as a [hi | lo] pair, for its dL1 } where the layers go one by one:
+  uint16_t* Thl;     // M x 2 r_max: one layer's X L1, recomputed when none was saved    } otherwise all of this lies
+  float* part;       // split-K partials, reused by every skinny product                 } at Wd until it is written
   size_t part_bytes;
   int r_max;
   int Rp, off[QLORA_MULTI_MAX], rp[QLORA_MULTI_MAX];
@@ -944,16 +944,13 @@ StackBwdPlan plan_bwd_stacked(void* ws, int64_t M, int32_t n, int64_t h, const i
   Carver c(ws);
   size_t pe = 0;
   int r_max = 0;
-  p.r_max = 0;
   for (int l = 0; l < n; ++l) {
     p.N += o[l];
     p.off[l] = p.Rp;
     p.rp[l] = r[l] > 0 ? (r[l] + 63) / 64 * 64 : 0;
     p.Rp += p.rp[l];
     r_max = std::max(r_max, (int)r[l]);
-    if (r[l] > 0) {
-      pe = std::max(pe, small_part_floats(M, h, o[l], r[l]));
-    }
+    if (r[l] > 0) pe = std::max(pe, small_part_floats(M, h, o[l], r[l]));
   }
   p.Wd = c.take<uint16_t>((size_t)h * p.N);
   if (p.Rp > 0) {
