@@ -203,9 +203,14 @@ hipError_t launch_dequant_t(const NF4Dev& w, uint16_t* out, int64_t ld_out, hipS
   const int h = (int)w.rows, o = (int)w.cols;
   if (L2 == nullptr) { r = 0; col0 = 0; }                    // rp > 0 without an adapter: the segment is all zeros
   if (rp % 64 != 0 || col0 < 0 || col0 + r > rp || ld_out < h + rp || ld_out % 8 != 0) return hipErrorInvalidValue;
-  const bool with_fin = fin && fin->n > 0;
+  bool with_fin = fin && fin->n > 0;
   const unsigned gx = (unsigned)((o + 255) / 256);
-  const unsigned fin_rows = with_fin ? ((unsigned)fin->blocks() + gx - 1) / gx : 0;
+  unsigned fin_rows = with_fin ? ((unsigned)fin->blocks() + gx - 1) / gx : 0;
+  if (with_fin && (h + 63) / 64 + rp / 64 + (int)fin_rows > 65535) {   // more rows than a grid has: a launch of its own
+    if (hipError_t e = launch_fin(*fin, st)) return e;
+    with_fin = false;
+    fin_rows = 0;
+  }
   dim3 grid(gx, (unsigned)((h + 63) / 64 + rp / 64) + fin_rows);
   const bool i8 = w.dtype == kTypeInt8;
 #define QL_DEQ_T2(DQ, I8, FIN, FARG)                                                                            \
