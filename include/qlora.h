@@ -282,7 +282,8 @@ qlora_status qlora_linear_bwd_acc(const uint16_t* dY, const uint16_t* X, const q
  * 0 <= p < 1 (else QLORA_ERR_SHAPE); keep_mask may be NULL only when r = 0, where the calls are the plain ones.
  * T_save / T_saved hold (B o X) * L1 for the 0/1 mask B, as a [hi | lo] pair (the 1/(1-p) is applied with s).
  * These calls take the paths for more than a few tokens at any M (no streaming kernel); workspaces are sized by
- * qlora_linear_dropout_sizes (either out-pointer may be NULL).  The backward call takes both kinds of adapter
+ * qlora_linear_dropout_sizes (either out-pointer may be NULL; with r = 0 it reports the size of a 4-bit double-quantised
+ * weight, which streams at M <= 16 -- any other weight then needs qlora_linear_fwd_sizes / _bwd_sizes).  The backward call takes both kinds of adapter
  * gradient outputs of qlora_linear_bwd and qlora_linear_bwd_acc; any of them may be NULL.  Everything else --
  * layouts, alignment, ownership, errors, tolerance -- as for qlora_linear_fwd / qlora_linear_bwd. */
 qlora_status qlora_linear_dropout_sizes(int64_t M, int64_t h, int64_t o, int32_t r, size_t* fwd_bytes,

@@ -289,15 +289,22 @@ def qlora_linear_bwd_sizes(M, h, o, r) -> int:
 WORKSPACE_HEADER_BYTES = 16384
 
 
-def _fwd_bytes(Wq, M, h, o, r):
-    """Workspace of a forward call: a weight without Double Quantization always takes the large-GEMM path."""
-    few = Wq.dq_blocksize and Wq.dtype != INT8
-    return qlora_linear_fwd_sizes(M, h, o, r) if few else qlora_linear_dropout_sizes(M, h, o, r)[0]
+def _plan_bytes(Wq, M, h, o, r, dropout, k):
+    """Workspace of a forward (k = 0) or backward (k = 1) call.  Only 4-bit double-quantised weights stream at a few tokens.
+    For any other weight, and under dropout, the size query of the dropout calls is the plan's -- but without an adapter
+    that query reports the streaming plan, and the plain queries, which cover both, are what such a weight needs."""
+    streams = Wq.dq_blocksize and Wq.dtype != INT8
+    if (not dropout) if streams else r == 0:
+        return (qlora_linear_fwd_sizes, qlora_linear_bwd_sizes)[k](M, h, o, r)
+    return qlora_linear_dropout_sizes(M, h, o, r)[k]
 
 
-def _bwd_bytes(Wq, M, h, o, r):
-    few = Wq.dq_blocksize and Wq.dtype != INT8
-    return qlora_linear_bwd_sizes(M, h, o, r) if few else qlora_linear_dropout_sizes(M, h, o, r)[1]
+def _fwd_bytes(Wq, M, h, o, r, dropout=False):
+    return _plan_bytes(Wq, M, h, o, r, dropout, 0)
+
+
+def _bwd_bytes(Wq, M, h, o, r, dropout=False):
+    return _plan_bytes(Wq, M, h, o, r, dropout, 1)
 
 
 def qlora_workspace_init(workspace, stream=None):
@@ -557,7 +564,7 @@ def qlora_linear_fwd_dropout(X, Wq: NF4Weight, L1, L2, s, keep_mask, p, Y=None, 
     if Y is None:
         Y = torch.empty((M, o), dtype=torch.bfloat16, device=X.device)
     if workspace is None:
-        workspace = workspace_alloc(qlora_linear_dropout_sizes(M, h, o, r)[0], X.device, stream)
+        workspace = workspace_alloc(_fwd_bytes(Wq, M, h, o, r, True), X.device, stream)
     v = Wq.view()
     _check(lib().qlora_linear_fwd_dropout(_ptr(X), byref(v), _ptr(L1), _ptr(L2), float(s), M, r, _ptr(keep_mask),
                                           float(p), _ptr(Y), _ptr(T_save), _ptr(workspace), workspace.numel(),
@@ -581,7 +588,7 @@ def qlora_linear_bwd_dropout(dY, X, Wq: NF4Weight, L1, L2, s, keep_mask, p, T_sa
         if dL2 is None:
             dL2 = torch.empty((r, o), dtype=torch.bfloat16, device=dev)
     if workspace is None:
-        workspace = workspace_alloc(qlora_linear_dropout_sizes(M, h, o, r)[1], dev, stream)
+        workspace = workspace_alloc(_bwd_bytes(Wq, M, h, o, r, True), dev, stream)
     v = Wq.view()
     _check(lib().qlora_linear_bwd_dropout(_ptr(dY), _ptr(X), byref(v), _ptr(L1), _ptr(L2), float(s), M, r,
                                           _ptr(keep_mask), float(p), _ptr(T_saved), _ptr(dX), _ptr(dL1), _ptr(dL2),

@@ -165,6 +165,32 @@ def test_dropout_arguments_are_rejected_on_the_host(L):
     assert f0 <= qlora_linear_fwd_sizes(4, 1024, 1024, 0) and b0 <= qlora_linear_bwd_sizes(4, 1024, 1024, 0)
 
 
+@pytest.mark.parametrize("dtype,dq", [(0, 0), (3, 0), (4, 256), (4, 0), (0, 256)])
+@pytest.mark.parametrize("M", [1, 5, 16, 17])
+@pytest.mark.parametrize("r", [0, 16])
+def test_default_workspace_is_accepted(L, dtype, dq, M, r):
+    """The workspace that the binding allocates by itself is large enough for the call it is made for: with a weight that
+    does not stream at a few tokens too, with and without an adapter.  A misaligned workspace is refused after the size
+    check, so nothing is launched."""
+    from types import SimpleNamespace
+    from paper_2305_14314_amd import binding
+    h, o = 1024, 1088
+    W = SimpleNamespace(dq_blocksize=dq, dtype=dtype)
+    v = binding.qlora_nf4_view(0x1000, 0x1000, 0x1000, 0x1000, h, o, 64, dq, dtype)
+    fake, odd, lo = ctypes.c_void_p(0x1000), ctypes.c_void_p(0x1008), ctypes.c_void_p(0x1000 if r else 0)
+    ref = ctypes.byref(v)
+    for dropout in (False, True):
+        fb, bb = binding._fwd_bytes(W, M, h, o, r, dropout), binding._bwd_bytes(W, M, h, o, r, dropout)
+        if dropout:
+            got = (L.qlora_linear_fwd_dropout(fake, ref, lo, lo, 1.0, M, r, lo, 0.1, fake, None, odd, fb, None),
+                   L.qlora_linear_bwd_dropout(fake, fake, ref, lo, lo, 1.0, M, r, lo, 0.1, None, fake, None, None, None, None,
+                                              odd, bb, None))
+        else:
+            got = (L.qlora_linear_fwd(fake, ref, lo, lo, 1.0, M, r, fake, None, odd, fb, None),
+                   L.qlora_linear_bwd(fake, fake, ref, lo, lo, 1.0, M, r, None, fake, None, None, odd, bb, None))
+        assert got == (-5, -5), (dropout, got)
+
+
 def test_data_type_tables_and_their_validation(L, oracle):
     """The library's tables of the 4-bit data types equal the oracle's bit for bit (host call, no GPU), unknown
     types are refused, and a view carries its type."""

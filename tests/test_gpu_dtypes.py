@@ -194,3 +194,24 @@ def test_int8_linear(oracle, synth, dq_blocksize, M, h, o, r):
         with pytest.raises(ql.QloraError) as e:
             ql.qlora_linear_fwd_multi(X, [Wq], [L1], [L2], [s], workspace=ws)
         assert e.value.status == -3
+
+
+@pytest.mark.parametrize("kind,dq", [("nf4", 0), ("int8", 256), ("int8", 0)])
+def test_no_adapter_at_few_tokens_default_workspace(oracle, synth, kind, dq):
+    """r = 0 and a few tokens on weights that do not stream: the workspace the binding allocates serves the call."""
+    import paper_2305_14314_amd as ql
+    M, h, o = 5, 1024, 1088
+    W = synth.normal_f32((h, o), synth.SIGMA_W, 9400)
+    if kind == "int8":
+        What = oracle.int8_dequant(oracle.int8_quantize(W, dq_blocksize=dq))
+        Wq = ql.qlora_quantize_int8(dev_f32(W), dq_blocksize=dq)
+    else:
+        What = oracle.nf4_dequant(oracle.nf4_quantize(W, dq_blocksize=dq))
+        Wq = ql.qlora_nf4_quantize(dev_f32(W), dq_blocksize=dq)
+    X, dY = synth.normal_bf16((M, h), 1.0, 9401), synth.normal_bf16((M, o), 1.0, 9402)
+    print(f"case r=0 {kind} dq={dq}", flush=True)
+    Y = ql.qlora_linear_fwd(dev_bf16(X), Wq, None, None, 1.0)
+    dX, _, _ = ql.qlora_linear_bwd(dev_bf16(dY), None, Wq, None, None, 1.0)
+    torch.cuda.synchronize()
+    _check(host_bits(Y), oracle.linear_fwd(X, What, None, None, 1.0), "Y")
+    _check(host_bits(dX), oracle.linear_bwd_dx(dY, What, None, None, 1.0), "dX")
