@@ -409,8 +409,10 @@ qlora_status qlora_hbm_probe(int32_t mode, const void* src, void* dst, int64_t b
  * dequantised weight): mode 0 dequantises the weight into the workspace and multiplies; mode 1 decodes the weight's
  * tiles inside the product (codes and block constants go from HBM to the matrix cores' LDS tiles, the bf16 weight is
  * never in HBM).  The decoded tiles are the same bits either way; the adapter term is added first instead of last in
- * mode 1, so outputs may differ in the last bf16 bit.  Mode 1 applies above 512 tokens (below, 4-bit weights are
- * decoded inside the product in either mode) to 4-bit types with cols % 64 == 0 and r <= 64 and falls back to mode 0 otherwise.  mode < 0 only queries.  Returns the previous mode.  Process-wide. */
+ * mode 1, so outputs may differ in the last bf16 bit.  Mode 1 applies to 4-bit types with cols % 64 == 0 and r <= 64 and
+ * falls back to mode 0 otherwise.  Neither form runs where the few-token streaming kernels do, and in mode 0 a 4-bit
+ * weight at up to 512 tokens takes the product described at qlora_linear_fwd instead.  mode < 0 only queries.
+ * Returns the previous mode.  Process-wide. */
 int32_t qlora_bwd_fused_dequant(int32_t mode);
 
 /* Testing aid: how many times a slab's last contributor polls for the adapter's partial sums before it hands the

@@ -824,8 +824,11 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
   hipStream_t st = (hipStream_t)hip_stream;
   const qlora::NF4Dev W = to_dev(Wq);
 
+  const int K1 = r > 0 ? p.rp : 0;
+  const bool fused = !p.few && dX && g_bwd_fused.load(std::memory_order_relaxed) && W.dtype != qlora::kTypeInt8 && o % 64 == 0 &&
+                     qlora::gemm_nt_fused_fits((int)o, K1, (int)h);
   // a few hundred tokens: decode inside the product; the finalize step applies the dropout mask to the adapter's term
-  const MidWs mid = !p.few && dX && streams_mid(Wq)
+  const MidWs mid = !p.few && dX && !fused && streams_mid(Wq)
                         ? plan_mid(p.Wd, p.wd_bytes, true, M, h, o, r) : MidWs{};
   qlora::FinList fin{};
   if (mid.plan.ok) {
@@ -848,9 +851,7 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
   if (!p.few && dX && !mid.plan.ok) {
     const uint16_t* B1 = L1;
     if (r > 0 && p.L1p) { fin.add(fin_pad(L1, h, r, p.L1p, p.rp, p.rp)); B1 = p.L1p; }
-    const int K1 = r > 0 ? p.rp : 0;
-    if (g_bwd_fused.load(std::memory_order_relaxed) && W.dtype != qlora::kTypeInt8 && o % 64 == 0 &&
-        qlora::gemm_nt_fused_fits((int)o, K1, (int)h)) {
+    if (fused) {
       // dX = Us L1^T + dY What^T with What decoded tile by tile inside the product: the workspace that would hold
       // What takes the h x o / 64 block constants and the 16 values of the data type instead
       float* consts = (float*)p.Wd;

@@ -29,13 +29,25 @@ def _dx(ql, mode, dY, X, Wq, L1, L2, s):
     return dX
 
 
+def _gemm_launches(ql, call):
+    """The call's result, and how many launches of the main GEMM (either form) it made."""
+    ql.qlora_profile_gemm(True)
+    try:
+        ql.qlora_profile_gemm_read()
+        out = call()
+        return out, ql.qlora_profile_gemm_read()[1]
+    finally:
+        ql.qlora_profile_gemm(False)
+
+
 # h = 64 .. 1024 rows of W (the output columns of the product, ragged against the 256-wide tiles), o = 64 .. 1536: 1 to
 # 32 K-steps (shorter and longer than the prefetch ring and the unrolled loop), ranks below and at 64, none, and 128
 # (two adapter steps: that call takes the two-kernel form whatever the mode)
-@pytest.mark.parametrize("M,h,o,r", [(256, 1024, 1024, 16), (300, 448, 576, 32), (17, 128, 320, 64), (65, 64, 64, 0),
-                                      (513, 256, 192, 64), (257, 320, 1536, 0), (40, 704, 128, 16), (1024, 512, 832, 64),
-                                      (33, 320, 64, 16), (128, 960, 2048, 64),
-                                      (96, 384, 256, 128)])
+# All token counts lie above 512: up to there the form without the switch may be another product altogether.
+@pytest.mark.parametrize("M,h,o,r", [(768, 1024, 1024, 16), (556, 448, 576, 32), (529, 128, 320, 64), (577, 64, 64, 0),
+                                      (513, 256, 192, 64), (769, 320, 1536, 0), (552, 704, 128, 16), (1024, 512, 832, 64),
+                                      (545, 320, 64, 16), (640, 960, 2048, 64),
+                                      (608, 384, 256, 128)])
 def test_fused_backward_matches(oracle, synth, fused, M, h, o, r):
     ql = fused
     print(f"fused bwd: M {M} h {h} o {o} r {r}", flush=True)
@@ -46,8 +58,9 @@ def test_fused_backward_matches(oracle, synth, fused, M, h, o, r):
     X, dY = dev_bf16(L["X"]), dev_bf16(L["dY"])
     L1 = dev_bf16(L["L1"]) if r else None
     L2 = dev_bf16(L["L2"]) if r else None
-    a = _dx(ql, 0, dY, X, Wq, L1, L2, L["s"])
-    b = _dx(ql, 1, dY, X, Wq, L1, L2, L["s"])
+    a, n0 = _gemm_launches(ql, lambda: _dx(ql, 0, dY, X, Wq, L1, L2, L["s"]))
+    b, n1 = _gemm_launches(ql, lambda: _dx(ql, 1, dY, X, Wq, L1, L2, L["s"]))
+    assert n0 == 1 and n1 == 1
     ref = oracle.linear_bwd_dx(L["dY"], What, L["L1"] if r else None, L["L2"] if r else None, L["s"])
     rms = np.sqrt((ref ** 2).mean())
     for tag, got in (("two kernels", a), ("fused", b)):
@@ -67,7 +80,7 @@ def test_fused_backward_matches(oracle, synth, fused, M, h, o, r):
 def test_fused_backward_other_types_and_plain_constants(oracle, synth, fused, dtype_name):
     """The other 4-bit data types (their table goes through the same lookup) and weights without Double Quantization."""
     ql = fused
-    M, h, o, r = 130, 320, 384, 16
+    M, h, o, r = 642, 320, 384, 16
     L = synth.make_layer(0, 0, M=M, h=h, o=o, r=r)
     W = torch.from_numpy(L["W"]).cuda()
     X, dY, L1, L2 = dev_bf16(L["X"]), dev_bf16(L["dY"]), dev_bf16(L["L1"]), dev_bf16(L["L2"])
@@ -88,7 +101,7 @@ def test_fused_backward_under_dropout_and_accumulation(synth, fused):
     """The other callers of the backward product: LoRA dropout (the input-gradient fix-up runs behind either form) and
     fp32 gradient accumulation; both forms against each other."""
     ql = fused
-    M, h, o, r = 200, 384, 512, 32
+    M, h, o, r = 712, 384, 512, 32
     L = synth.make_layer(0, 0, M=M, h=h, o=o, r=r)
     Wq = ql.qlora_nf4_quantize(torch.from_numpy(L["W"]).cuda())
     X, dY, L1, L2 = dev_bf16(L["X"]), dev_bf16(L["dY"]), dev_bf16(L["L1"]), dev_bf16(L["L2"])
@@ -109,3 +122,23 @@ def test_fused_backward_under_dropout_and_accumulation(synth, fused):
     for k in (0, 3):
         ga, gb = bits_f64(host_bits(res[0][k])), bits_f64(host_bits(res[1][k]))
         assert np.all(np.abs(ga - gb) <= 2.0 ** -7 * np.abs(ga) + 1e-4 * np.sqrt((ga ** 2).mean()))
+
+
+@pytest.mark.parametrize("M,h,o,r", [(17, 1024, 1088, 0), (65, 64, 64, 0), (200, 448, 2048, 16), (512, 1024, 1024, 64)])
+def test_fused_mode_is_honoured_at_few_hundred_tokens(oracle, synth, fused, M, h, o, r):
+    """Mode 1 selects the fused product at every token count that does not stream: one launch of it, the oracle's values,
+    and without an adapter the bits of the same rows in a call of more tokens (a row's contraction does not depend on
+    the others)."""
+    ql = fused
+    L = synth.make_layer(0, 0, M=M + 513, h=h, o=o, r=max(r, 1))
+    q = oracle.nf4_quantize(L["W"])
+    Wq, X, dY = upload_quant(q), dev_bf16(L["X"]), dev_bf16(L["dY"])
+    L1, L2 = (dev_bf16(L["L1"]), dev_bf16(L["L2"])) if r else (None, None)
+    print(f"fused bwd below 512: M {M} h {h} o {o} r {r}", flush=True)
+    b, n = _gemm_launches(ql, lambda: _dx(ql, 1, dY[:M].contiguous(), X[:M].contiguous(), Wq, L1, L2, L["s"]))
+    assert n == 1
+    ref = oracle.linear_bwd_dx(L["dY"][:M], oracle.nf4_dequant(q), L["L1"] if r else None, L["L2"] if r else None, L["s"])
+    err = np.abs(bits_f64(host_bits(b)).reshape(ref.shape) - ref).max()
+    assert err <= TOL * np.sqrt((ref ** 2).mean())
+    if r == 0:
+        assert torch.equal(b, _dx(ql, 1, dY, X, Wq, None, None, L["s"])[:M])
