@@ -179,10 +179,11 @@ size_t small_part_floats(int64_t M, int64_t h, int64_t o, int32_t r) {
 }
 
 // The skinny products of a call, several to a launch.  Their partials are carved from a pool; a job that finds no room
-// (or no place in the list) first sends off what is collected.  A product of at most four K-steps takes no splits and
-// finishes in its own epilogue where its outputs allow (bf16 or accumulated gradients): dL1 and dL2 of 256 tokens at
+// (or no place in the list) first sends off what is collected.  An adapter gradient of at most four K-steps takes no splits
+// and is finished in the product's epilogue: dL1 and dL2 of 256 tokens at
 // 1024 x 1024 take 6.7 us so (32 workgroups), and a finalize launch alone takes 4.9.  At eight K-steps (512 tokens,
 // 4096 x 4096) it is 19.5 us against 8.2 + 4.9 in four splits: the chain of K-steps is what such a workgroup waits for.
+// T and U never do, although a T that nobody saves could: Y would differ in bits from that of a call that saves it.
 struct SmallBatch {
   qlora::SmallJobs jobs{};
   qlora::FinList fin{};
@@ -193,8 +194,7 @@ struct SmallBatch {
   // `tiles`: output tiles of the products that share the launch, counted from the layers' shapes alone: the order of a
   // sum, and with it every bit of a result, does not depend on which outputs a call wants or on the room it has.
   hipError_t add(qlora::SmallJob j, int tiles) {
-    const bool can_direct = !j.fin.hl && (!j.fin.out0 || j.fin.w0 == j.J);
-    j.direct = can_direct && (j.K + 63) / 64 <= 4;
+    j.direct = (j.kind == qlora::kSmallDL1 || j.kind == qlora::kSmallDL2) && (j.K + 63) / 64 <= 4;
     j.fin.splits = j.direct ? 1 : qlora::small_job_splits(j.I, j.J, j.K, tiles - qlora::small_tiles(j.I, j.J));
     for (int turn = 0; turn < 2; ++turn) {
       const size_t need = j.direct ? 0 : (size_t)j.fin.splits * j.I * j.J * sizeof(float);
@@ -880,7 +880,7 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
     if (need_t) {
       qlora::SmallJob t = job_t(X, h, L1, M, r, keep_mask);
       t.fin.hl = p.Thl;
-      QL_TRY(batch.add(t, qlora::small_tiles((int)M, r)));        // split as in the forward
+      QL_TRY(batch.add(t, qlora::small_tiles((int)M, r)));   // split as in a forward call that multiplies by the dequantised weight
       T = p.Thl;
     }
     // dL1 = s X^T U: contraction over the tokens, both operands stored token-major; U enters as hi + lo

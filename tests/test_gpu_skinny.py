@@ -53,3 +53,24 @@ def test_stacked_batches(oracle, synth, M, h, outs, ranks, save):
             _check(host_bits(dL2s[l]), r2, f"layer {l} dL2")
         n0 += o
     _check(host_bits(dX), ref_dx, "dX")
+
+
+@pytest.mark.parametrize("kind,M,h", [("nf4", 4000, 256), ("nf4", 4000, 64), ("int8", 500, 256), ("stacked", 4000, 256)])
+def test_saving_t_does_not_change_y(synth, kind, M, h):
+    """Inference and training forward give the same bits: the order in which T = X L1 is summed does not depend on whether
+    the call saves it (four K-steps and fewer, where a product without splits is possible)."""
+    import paper_2305_14314_amd as ql
+    o, r = 512, 64
+    W = torch.from_numpy(synth.normal_f32((h, o), synth.SIGMA_W, 9500)).cuda()
+    Wq = ql.qlora_quantize_int8(W) if kind == "int8" else ql.qlora_nf4_quantize(W)
+    X = dev_bf16(synth.normal_bf16((M, h), 1.0, 9501))
+    L1, L2 = dev_bf16(synth.normal_bf16((h, r), 0.5, 9502)), dev_bf16(synth.normal_bf16((r, o), 0.5, 9503))
+    T = torch.empty((M, 2 * r), dtype=torch.bfloat16, device="cuda")
+    print(f"case Y with and without T_save: {kind} M={M} h={h}", flush=True)
+    if kind == "stacked":
+        f = lambda t: ql.qlora_linear_fwd_stacked(X, [Wq, Wq], [L1, L1], [L2, L2], [1.0, 1.0], T_saves=[t, None])
+    else:
+        f = lambda t: ql.qlora_linear_fwd(X, Wq, L1, L2, 1.0, T_save=t)
+    a, b = f(None), f(T)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b)
