@@ -17,14 +17,11 @@ constexpr int kFinThreads = 256;
 //   acc[i][j] += scale0 * sum                                      (fp32, row stride J: gradient accumulation)
 // A job with `src` instead copies: out0[i][j] = src[i][j] (bf16, row stride J) for j < J, zero for J <= j < w0.
 template <int UNROLL = 8>
-__device__ __forceinline__ void fin_block(const FinList& f, int block) {
-  int q = 0;
-  while (q + 1 < f.n && block >= f.first[q + 1]) ++q;
-  const FinJob& p = f.j[q];
+__device__ __forceinline__ void fin_job(const FinJob& p, int block, int blocks) {
   const int wq = ((p.out0 && p.w0 > p.J) ? p.w0 : p.J) >> 2;
-  const int64_t total = (int64_t)p.I * wq, stride = (int64_t)(f.first[q + 1] - f.first[q]) * kFinThreads;
+  const int64_t total = (int64_t)p.I * wq, stride = (int64_t)blocks * kFinThreads;
   const int64_t plane = (int64_t)p.I * p.J;
-  for (int64_t e = (int64_t)(block - f.first[q]) * kFinThreads + threadIdx.x; e < total; e += stride) {
+  for (int64_t e = (int64_t)block * kFinThreads + threadIdx.x; e < total; e += stride) {
     const int i = (int)(e / wq), j = 4 * (int)(e - (int64_t)i * wq);
     const bool in = j < p.J;
     if (p.src) {
@@ -61,6 +58,14 @@ __device__ __forceinline__ void fin_block(const FinList& f, int block) {
       *(uint2*)(p.hl + (int64_t)i * 2 * p.J + p.J + j) = lo;
     }
   }
+}
+
+// The same for workgroup `block` of a list's.
+template <int UNROLL = 8>
+__device__ __forceinline__ void fin_block(const FinList& f, int block) {
+  int q = 0;
+  while (q + 1 < f.n && block >= f.first[q + 1]) ++q;
+  fin_job<UNROLL>(f.j[q], block - f.first[q], f.first[q + 1] - f.first[q]);
 }
 
 }  // namespace qlora

@@ -102,7 +102,7 @@ struct SmallJob {
   int64_t hl_off;
   const uint8_t* amask;                      // LoRA dropout (T, dL1; lda % 8 == 0): elements of A whose keep-bit -- bit e % 8 of byte e / 8, e the offset from A -- is clear enter as zero
   int kind, I, J, K, k_per_split;            // k_per_split: filled by the launcher
-  int direct;                                // one split: the finalize step (out0 with w0 = J, acc) in the product's epilogue
+  int direct;                                // dL1, dL2 in one split: the finalize step (out0 with w0 = J, acc) in the product's epilogue
   FinJob fin;                                // part, splits and the outputs; I, J: filled by the launcher
 };
 constexpr int kSmallMax = 8;

@@ -114,9 +114,25 @@ __device__ __forceinline__ bf16x8 small_frag(const lds_char* tile, int row, int 
   }
 }
 
+// What the loop over K reads of a job, held in scalar registers.  A job is read through an index into the kernel's arguments,
+// and the compiler would rather read it again in front of every predicated load than keep it: eight scalar loads and their
+// waits per two K-steps (U of 4096 tokens by 16384 outputs at rank 128, under the profiler: 51 us so, 43 with them held).
+struct SmallOperands { const uint16_t *A, *B; const uint8_t* amask; int64_t lda, ldb, hl_off; int I, J, K, k_per_split; };
+template <typename T> __device__ __forceinline__ T* pin(T* q) {
+  uint64_t u = (uint64_t)q;
+  asm volatile("" : "+s"(u));
+  return (T*)(__attribute__((address_space(1))) T*)u;        // still known to be global memory
+}
+__device__ __forceinline__ SmallOperands pin_operands(const SmallJob& j) {
+  SmallOperands p{pin(j.A), pin(j.B), pin(j.amask), j.lda, j.ldb, j.hl_off, j.I, j.J, j.K, j.k_per_split};
+  asm volatile("" : "+s"(p.lda), "+s"(p.ldb), "+s"(p.hl_off), "+s"(p.I), "+s"(p.J), "+s"(p.K), "+s"(p.k_per_split));
+  return p;
+}
+
 constexpr int kSmallTile = ST * kTPitch * 2;  // bytes of one operand tile in LDS
 template <bool TA, bool TB, int HL, bool MASK>
-__device__ __forceinline__ void small_gemm_body(const SmallJob& p, int local, char* smem) {
+__device__ __forceinline__ void small_gemm_body(const SmallJob& job, int local, char* smem) {
+  const SmallOperands p = pin_operands(job);
   static_assert(HL == 0 || (HL == 1 && TA) || (HL == 2 && TB), "a [hi | lo] operand is stored token-major");
   static_assert(!MASK || HL != 1, "the masked operand is X itself");
   lds_char* sA = (lds_char*)smem;
@@ -186,17 +202,17 @@ __device__ __forceinline__ void small_gemm_body(const SmallJob& p, int local, ch
 
   const int j = j0 + wj * 32 + (lane & 31);
   if (j >= p.J) return;
-  if (p.direct) {                                            // one split: what the finalize step would do, right here
+  if (HL != 0 && job.direct) {                               // one split: what the finalize step would do, right here
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int i = i0 + wi * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
       if (i >= p.I) continue;
-      if (p.fin.out0) p.fin.out0[(int64_t)i * p.fin.ld0 + j] = bf16_bits(acc[v] * p.fin.scale0);
-      if (p.fin.acc) p.fin.acc[(int64_t)i * p.J + j] += acc[v] * p.fin.scale0;
+      if (job.fin.out0) job.fin.out0[(int64_t)i * job.fin.ld0 + j] = bf16_bits(acc[v] * job.fin.scale0);
+      if (job.fin.acc) job.fin.acc[(int64_t)i * p.J + j] += acc[v] * job.fin.scale0;
     }
     return;
   }
-  float* out = const_cast<float*>(p.fin.part) + (int64_t)split * p.I * p.J;
+  float* out = const_cast<float*>(job.fin.part) + (int64_t)split * p.I * p.J;
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
     const int i = i0 + wi * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
@@ -204,21 +220,39 @@ __device__ __forceinline__ void small_gemm_body(const SmallJob& p, int local, ch
   }
 }
 
+template <int KIND, bool MASK>
+__device__ __forceinline__ void small_gemm_kind(const SmallJob& p, int local, char* smem) {
+  if constexpr (KIND == kSmallT) small_gemm_body<false, true, 0, MASK>(p, local, smem);
+  if constexpr (KIND == kSmallU) small_gemm_body<false, false, 0, false>(p, local, smem);
+  if constexpr (KIND == kSmallDL1) small_gemm_body<true, true, 2, MASK>(p, local, smem);
+  if constexpr (KIND == kSmallDL2) small_gemm_body<true, true, 1, false>(p, local, smem);
+}
+constexpr int small_lds(int kinds) { return ((kinds & 12) ? 3 : 2) * kSmallTile; }
+
+// One product: its job alone is the argument (a list is 1.4 KB to hand over and three dependent reads to find the job in:
+// 0.4 us a launch).
+template <int KIND, bool MASK>
+__global__ __launch_bounds__(kSmallThreads) void small_job_kernel(const SmallJob job) {
+  __shared__ __attribute__((aligned(16))) char smem[small_lds(1 << KIND)];
+  small_gemm_kind<KIND, MASK>(job, blockIdx.x, smem);
+}
+
 // Several products in one launch: workgroup b belongs to the last job whose first workgroup is <= b.  KINDS: the kinds that
 // occur (1 << kind), so that a launch carries no code it cannot reach.
 template <int KINDS, bool MASK>
 __global__ __launch_bounds__(kSmallThreads) void small_jobs_kernel(const SmallJobs jobs) {
-  __shared__ __attribute__((aligned(16))) char smem[((KINDS & 12) ? 3 : 2) * kSmallTile];
+  __shared__ __attribute__((aligned(16))) char smem[small_lds(KINDS)];
   int q = 0;
   while (q + 1 < jobs.n && (int)blockIdx.x >= jobs.first[q + 1]) ++q;
   const SmallJob& p = jobs.j[q];
   const int local = blockIdx.x - jobs.first[q];
-  if ((KINDS & 1) && p.kind == kSmallT) small_gemm_body<false, true, 0, MASK>(p, local, smem);
-  if ((KINDS & 2) && p.kind == kSmallU) small_gemm_body<false, false, 0, false>(p, local, smem);
-  if ((KINDS & 4) && p.kind == kSmallDL1) small_gemm_body<true, true, 2, MASK>(p, local, smem);
-  if ((KINDS & 8) && p.kind == kSmallDL2) small_gemm_body<true, true, 1, false>(p, local, smem);
+  if ((KINDS & 1) && p.kind == kSmallT) small_gemm_kind<kSmallT, MASK>(p, local, smem);
+  if ((KINDS & 2) && p.kind == kSmallU) small_gemm_kind<kSmallU, MASK>(p, local, smem);
+  if ((KINDS & 4) && p.kind == kSmallDL1) small_gemm_kind<kSmallDL1, MASK>(p, local, smem);
+  if ((KINDS & 8) && p.kind == kSmallDL2) small_gemm_kind<kSmallDL2, MASK>(p, local, smem);
 }
 
+__global__ __launch_bounds__(kFinThreads) void fin_job_kernel(const FinJob job) { fin_job(job, blockIdx.x, gridDim.x); }
 __global__ __launch_bounds__(kFinThreads) void fin_kernel(const FinList f) { fin_block(f, blockIdx.x); }
 
 // ~2 workgroups per CU over all jobs of a launch: every further split adds an fp32 partial tile to write and read back,
@@ -240,7 +274,8 @@ hipError_t launch_small_jobs(SmallJobs& jobs, hipStream_t st) {
     const int ksteps = (p.K + ST - 1) / ST;
     p.k_per_split = (ksteps + p.fin.splits - 1) / p.fin.splits * ST;
     p.fin.I = p.I; p.fin.J = p.J;
-    if (p.direct && (p.fin.splits != 1 || p.fin.hl || (p.fin.out0 && p.fin.w0 != p.J))) return hipErrorInvalidValue;
+    if (p.direct && ((p.kind != kSmallDL1 && p.kind != kSmallDL2) || p.fin.splits != 1 || p.fin.hl || (p.fin.out0 && p.fin.w0 != p.J)))
+      return hipErrorInvalidValue;
     if (p.amask && (p.lda % 8 != 0 || (p.kind != kSmallT && p.kind != kSmallDL1))) return hipErrorInvalidValue;
     kinds |= 1 << p.kind;
     mask |= p.amask != nullptr;
@@ -250,15 +285,25 @@ hipError_t launch_small_jobs(SmallJobs& jobs, hipStream_t st) {
   if (mask)                                                  // one mask for a launch: every T and dL1 job brings it
     for (int q = 0; q < jobs.n; ++q)
       if ((jobs.j[q].kind == kSmallT || jobs.j[q].kind == kSmallDL1) && !jobs.j[q].amask) return hipErrorInvalidValue;
-#define QL_SMALL(KINDS)                                                                                             \
-  case KINDS:                                                                                                       \
-    if (mask) hipLaunchKernelGGL((small_jobs_kernel<KINDS, true>), dim3((unsigned)wgs), dim3(kSmallThreads), 0, st, jobs); \
-    else hipLaunchKernelGGL((small_jobs_kernel<KINDS, false>), dim3((unsigned)wgs), dim3(kSmallThreads), 0, st, jobs);     \
-    break;
-  switch (kinds) {
-    QL_SMALL(1) QL_SMALL(2) QL_SMALL(3) QL_SMALL(4) QL_SMALL(5) QL_SMALL(8) QL_SMALL(12)
-    default: return hipErrorInvalidValue;
+  const dim3 grid((unsigned)wgs), block(kSmallThreads);
+#define QL_SMALL_ONE(KIND, MASK)                                                                                     \
+  case 2 * (1 << KIND) + MASK: hipLaunchKernelGGL((small_job_kernel<KIND, MASK>), grid, block, 0, st, jobs.j[0]); break;
+#define QL_SMALL(KINDS, MASK)                                                                                        \
+  case 2 * KINDS + MASK: hipLaunchKernelGGL((small_jobs_kernel<KINDS, MASK>), grid, block, 0, st, jobs); break;
+  if (jobs.n == 1) {
+    switch (2 * kinds + mask) {
+      QL_SMALL_ONE(kSmallT, 0) QL_SMALL_ONE(kSmallT, 1) QL_SMALL_ONE(kSmallU, 0) QL_SMALL_ONE(kSmallDL1, 0)
+      QL_SMALL_ONE(kSmallDL1, 1) QL_SMALL_ONE(kSmallDL2, 0)
+      default: return hipErrorInvalidValue;
+    }
+  } else {                                                   // a layer's T with dL1, dL1 with dL2; the same of stacked layers (no mask)
+    switch (2 * kinds + mask) {
+      QL_SMALL(1, 0) QL_SMALL(2, 0) QL_SMALL(3, 0) QL_SMALL(4, 0) QL_SMALL(5, 0) QL_SMALL(5, 1) QL_SMALL(8, 0) QL_SMALL(12, 0)
+      QL_SMALL(12, 1)
+      default: return hipErrorInvalidValue;
+    }
   }
+#undef QL_SMALL_ONE
 #undef QL_SMALL
   return hipGetLastError();
 }
@@ -273,7 +318,9 @@ int FinList::add(const FinJob& job) {
 
 hipError_t launch_fin(const FinList& f, hipStream_t st) {
   if (f.n == 0) return hipSuccess;
-  hipLaunchKernelGGL(fin_kernel, dim3((unsigned)f.blocks()), dim3(kFinThreads), 0, st, f);
+  const dim3 grid((unsigned)f.blocks()), block(kFinThreads);
+  if (f.n == 1) hipLaunchKernelGGL(fin_job_kernel, grid, block, 0, st, f.j[0]);
+  else hipLaunchKernelGGL(fin_kernel, grid, block, 0, st, f);
   return hipGetLastError();
 }
 
