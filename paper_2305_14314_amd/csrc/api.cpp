@@ -191,11 +191,12 @@ struct SmallBatch {
   hipStream_t st;
   SmallBatch(void* p, size_t bytes, hipStream_t s) : pool((char*)p), room(bytes), st(s) {}
 
-  // `tiles`: output tiles of the products that share the launch, counted from the layers' shapes alone: the order of a
-  // sum, and with it every bit of a result, does not depend on which outputs a call wants or on the room it has.
-  hipError_t add(qlora::SmallJob j, int tiles) {
+  // `tiles`: output tiles of the products that share the launch (0: this one alone), counted from the layers' shapes: the
+  // order of a sum, and with it every bit of what is summed here, does not depend on which outputs a call wants or on the
+  // room it has.
+  hipError_t add(qlora::SmallJob j, int tiles, int floor = 0) {
     j.direct = (j.kind == qlora::kSmallDL1 || j.kind == qlora::kSmallDL2) && (j.K + 63) / 64 <= 4;
-    j.fin.splits = j.direct ? 1 : qlora::small_job_splits(j.I, j.J, j.K, tiles - qlora::small_tiles(j.I, j.J));
+    j.fin.splits = j.direct ? 1 : qlora::small_job_splits(j.I, j.J, j.K, std::max(tiles - qlora::small_tiles(j.I, j.J), 0), floor);
     for (int turn = 0; turn < 2; ++turn) {
       const size_t need = j.direct ? 0 : (size_t)j.fin.splits * j.I * j.J * sizeof(float);
       if (jobs.n < qlora::kSmallMax && (j.direct || fin.n < qlora::kFinMax) && used + need <= room) {
@@ -226,6 +227,21 @@ struct SmallBatch {
     return e;
   }
 };
+// How dL1 and dL2 of a layer are split (the last two arguments of SmallBatch::add).  They share a launch where `room`, which
+// depends on the shape alone, holds their partials -- with a floor under the smaller one's workgroups if it holds those too;
+// otherwise each is split as in the launch of its own that it gets.  (4096 x 1024 at rank 256 and 4096 tokens, which does not
+// fit: 74 us with the splits of a shared launch, 65 so.  Four or more gradients of stacked layers leave no such tail: no
+// floor there, whose partials would send some of them off in a second launch.)
+struct DlSplit { int tiles, floor; };
+DlSplit dl_split(int64_t M, int64_t h, int64_t o, int r, size_t room) {
+  const int t1 = qlora::small_tiles((int)h, r), t2 = qlora::small_tiles(r, (int)o);
+  auto fits = [&](int floor) {
+    return align_up((size_t)qlora::small_job_splits((int)h, r, (int)M, t2, floor) * h * r * sizeof(float), 256) +
+               align_up((size_t)qlora::small_job_splits(r, (int)o, (int)M, t1, floor) * r * o * sizeof(float), 256) <= room;
+  };
+  if (fits(qlora::kSmallFloor)) return {t1 + t2, qlora::kSmallFloor};
+  return {fits(0) ? t1 + t2 : 0, 0};
+}
 qlora::SmallJob job_t(const uint16_t* X, int64_t h, const uint16_t* L1, int64_t M, int r, const uint8_t* mask) {
   qlora::SmallJob j{};
   j.kind = qlora::kSmallT; j.A = X; j.lda = h; j.B = L1; j.ldb = r; j.amask = mask; j.I = (int)M; j.J = r; j.K = (int)h;
@@ -816,6 +832,7 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
   if ((want1 || want2) && !X) return QLORA_ERR_NULL;
   const bool allow_few = keep_mask == nullptr && streams_few(Wq);
   BwdPlan p = plan_bwd(workspace, M, h, o, r, allow_few);
+  const size_t full_wd = p.wd_bytes;                         // whatever room this call brings
   if (workspace_bytes < p.bytes) p = plan_bwd(workspace, M, h, o, r, allow_few, false);
   if (workspace_bytes < p.bytes) return QLORA_ERR_WORKSPACE;
   if (!aligned16(dY) || !aligned16(X) || !aligned16(workspace) || !aligned16(L1) || !aligned16(L2) ||
@@ -876,7 +893,7 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
     SmallBatch batch(big ? (void*)p.Wd : (void*)p.part, big ? p.wd_bytes : p.part_bytes, st);
     const uint16_t* T = T_saved;
     const bool need_t = want2 && !T;                        // gradient checkpointing: recompute T = X L1
-    const int tiles = qlora::small_tiles((int)h, r) + qlora::small_tiles(r, (int)o);
+    const DlSplit split = dl_split(M, h, o, r, std::max(full_wd, p.part_bytes));
     if (need_t) {
       qlora::SmallJob t = job_t(X, h, L1, M, r, keep_mask);
       t.fin.hl = p.Thl;
@@ -884,10 +901,10 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
       T = p.Thl;
     }
     // dL1 = s X^T U: contraction over the tokens, both operands stored token-major; U enters as hi + lo
-    if (want1) QL_TRY(batch.add(job_dl1(X, h, p.Uhl, M, r, s, keep_mask, dL1, aL1), tiles));
+    if (want1) QL_TRY(batch.add(job_dl1(X, h, p.Uhl, M, r, s, keep_mask, dL1, aL1), split.tiles, split.floor));
     if (need_t) QL_TRY(batch.finish());
     // dL2 = s T^T dY with T as hi + lo rows
-    if (want2) QL_TRY(batch.add(job_dl2(T, dY, o, o, M, r, s, dL2, aL2), tiles));
+    if (want2) QL_TRY(batch.add(job_dl2(T, dY, o, o, M, r, s, dL2, aL2), split.tiles, split.floor));
     QL_TRY(batch.finish());
   }
   return QLORA_OK;

@@ -109,8 +109,9 @@ constexpr int kSmallMax = 8;
 struct SmallJobs { int n; int first[kSmallMax]; SmallJob j[kSmallMax]; };
 static_assert(sizeof(SmallJobs) <= 2048 && sizeof(FinList) <= 1024, "kernel arguments");
 int small_tiles(int I, int J);
-//   splits of a job that shares its launch with `other_tiles` output tiles of other jobs
-int small_job_splits(int I, int J, int K, int other_tiles);
+//   splits of a job that shares its launch with `other_tiles` output tiles of other jobs; never more than without any
+constexpr int kSmallFloor = 256;             // workgroups a job of a shared launch should have of its own
+int small_job_splits(int I, int J, int K, int other_tiles, int floor = 0);
 hipError_t launch_small_jobs(SmallJobs& jobs, hipStream_t st);
 hipError_t launch_fin(const FinList& f, hipStream_t st);
 //   LoRA dropout: dX[m][k] -= sum_t Us[m][t] L1[k][t] (bf16 operands, fp32 sum, one more rounding to bf16) wherever the

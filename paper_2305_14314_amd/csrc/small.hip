@@ -257,11 +257,12 @@ __global__ __launch_bounds__(kFinThreads) void fin_kernel(const FinList f) { fin
 
 // ~2 workgroups per CU over all jobs of a launch: every further split adds an fp32 partial tile to write and read back,
 // and past this point that traffic costs more than the extra loads in flight gain (measured: 256 -> +30 %, 1024 -> +8 %
-// time).
-int small_job_splits(int I, int J, int K, int other_tiles) {
-  const int ksteps = (K + ST - 1) / ST;
-  const int tiles = ((I + ST - 1) / ST) * ((J + ST - 1) / ST) + other_tiles;
-  return std::max(1, std::min(std::min((512 + tiles - 1) / tiles, 64), ksteps));
+// time).  `floor`: the job's own workgroups are not fewer than that.  Without it the small one of two unlike gradients is
+// left with a few long chains that outlast the launch: dL1 and dL2 of 16384 x 64 at rank 128 and 4096 tokens (512 and 2
+// tiles, one split each) 115 us, with dL2 in 64 splits 78; 8192 x 2048, rank 256 98 -> 89; 5120 x 13824, rank 16 66 -> 62.
+int small_job_splits(int I, int J, int K, int other_tiles, int floor) {
+  const int ksteps = (K + ST - 1) / ST, own = small_tiles(I, J), tiles = own + other_tiles;
+  return std::max(1, std::min(std::min(std::max((512 + tiles - 1) / tiles, (floor + own - 1) / own), 64), ksteps));
 }
 int small_tiles(int I, int J) { return ((I + ST - 1) / ST) * ((J + ST - 1) / ST); }
 
