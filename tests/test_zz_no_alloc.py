@@ -2,6 +2,7 @@
 results are those of qlora_nf4_quantize bit for bit, on two calls in a row (the second on a smaller tensor, so the
 shared device array still holds the first call's constants), and sizes beyond its limit are refused."""
 import ctypes
+import gc
 
 import pytest
 import torch
@@ -29,6 +30,7 @@ def test_static_scratch_matches_the_scratch_argument(dq):
         out = q.nf4_alloc(h, o, dev, dq_blocksize=dq)
         for t in (out.packed, out.code, out.c1, out.mean):
             t.view(torch.uint8).fill_(0xA5)
+        gc.collect()                                                   # earlier tests' tensors in cycles: not freed in between
         before = torch.cuda.memory_allocated(dev)
         q.qlora_nf4_quantize_static(W, out)
         torch.cuda.synchronize()
