@@ -154,13 +154,14 @@ size_t mid_bytes(const qlora::MidPlan& p) {
   return align_up(p.part_floats * sizeof(float), 256) + align_up(p.lpart_floats * sizeof(float), 256) + align_up(p.pack_elems * 2, 256);
 }
 // bytes of the region that holds either the dequantised weight (`base` bytes) or the buffers of this path
-size_t mid_region(size_t base, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r) {
+size_t mid_region(size_t base, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r, bool fix = false) {
   const qlora::MidPlan p = qlora::mid_plan(bwd, M, h, o, r, std::max(base, kMidRoom));
-  return p.ok ? std::max(base, mid_bytes(p)) : base;
+  return p.ok && qlora::mid_pays(p, bwd, M, h, o, r, fix) ? std::max(base, mid_bytes(p)) : base;
 }
-MidWs plan_mid(void* buf, size_t room, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r) {
+MidWs plan_mid(void* buf, size_t room, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r, bool fix = false) {
   MidWs m{};
   m.plan = qlora::mid_plan(bwd, M, h, o, r, room);
+  m.plan.ok = m.plan.ok && qlora::mid_pays(m.plan, bwd, M, h, o, r, fix);
   if (!m.plan.ok) return m;
   char* p = (char*)buf;
   m.part = (float*)p; p += align_up(m.plan.part_floats * sizeof(float), 256);
@@ -327,8 +328,9 @@ struct BwdPlan {
   size_t wd_bytes;   // of the region at Wd
   size_t bytes;
 };
-// roomy: the region at Wd also holds the buffers of the path for tens to hundreds of tokens (what the size queries report)
-BwdPlan plan_bwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allow_few = true, bool roomy = true) {
+// roomy: the region at Wd also holds the buffers of the path for tens to hundreds of tokens (what the size queries report);
+// fix: of a dropout call, which takes that path more often
+BwdPlan plan_bwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allow_few = true, bool roomy = true, bool fix = false) {
   BwdPlan p{};
   Carver c(ws);
   p.rp = (r + 63) / 64 * 64;
@@ -340,7 +342,7 @@ BwdPlan plan_bwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allo
     p.lpart = c.take<float>((size_t)p.n_lparts * M * r + 4);
   } else {
     p.wd_bytes = (size_t)h * o * sizeof(uint16_t);
-    if (roomy) p.wd_bytes = mid_region(p.wd_bytes, true, M, h, o, r);
+    if (roomy) p.wd_bytes = mid_region(p.wd_bytes, true, M, h, o, r, fix);
     p.Wd = (uint16_t*)c.take<char>(p.wd_bytes);
   }
   if (r > 0) {
@@ -658,7 +660,7 @@ qlora_status qlora_linear_dropout_sizes(int64_t M, int64_t h, int64_t o, int32_t
   if (qlora_status st = check_linear(M, h, o, r)) return st;
   // without an adapter there is nothing to drop and the calls are the plain ones, few-token path included
   if (fwd_bytes) *fwd_bytes = plan_fwd(nullptr, M, h, o, r, r == 0).bytes;
-  if (bwd_bytes) *bwd_bytes = plan_bwd(nullptr, M, h, o, r, r == 0).bytes;
+  if (bwd_bytes) *bwd_bytes = plan_bwd(nullptr, M, h, o, r, r == 0, true, r > 0).bytes;
   return QLORA_OK;
 }
 
@@ -831,7 +833,8 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
   const bool want1 = dL1 || aL1, want2 = dL2 || aL2;
   if ((want1 || want2) && !X) return QLORA_ERR_NULL;
   const bool allow_few = keep_mask == nullptr && streams_few(Wq);
-  BwdPlan p = plan_bwd(workspace, M, h, o, r, allow_few);
+  const bool fix = keep_mask != nullptr;
+  BwdPlan p = plan_bwd(workspace, M, h, o, r, allow_few, true, fix);
   const size_t full_wd = p.wd_bytes;                         // whatever room this call brings
   if (workspace_bytes < p.bytes) p = plan_bwd(workspace, M, h, o, r, allow_few, false);
   if (workspace_bytes < p.bytes) return QLORA_ERR_WORKSPACE;
@@ -846,7 +849,7 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
                      qlora::gemm_nt_fused_fits((int)o, K1, (int)h);
   // a few hundred tokens: decode inside the product; the finalize step applies the dropout mask to the adapter's term
   const MidWs mid = !p.few && dX && !fused && streams_mid(Wq)
-                        ? plan_mid(p.Wd, p.wd_bytes, true, M, h, o, r) : MidWs{};
+                        ? plan_mid(p.Wd, p.wd_bytes, true, M, h, o, r, fix) : MidWs{};
   qlora::FinList fin{};
   if (mid.plan.ok) {
     QL_TRY(qlora::launch_mid(true, dY, (int)M, W, mid.plan, L1, L2, r, s, keep_mask, mid.part, mid.lpart, mid.xpack, dX,

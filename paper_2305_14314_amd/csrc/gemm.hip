@@ -551,19 +551,21 @@ struct GemmCut { int wide, rest, rest_width; };
 // (5120 columns, K 15552: 160 tiles of 256) 264 -> 234 us with 216 tiles of 192; 1024 x 4096 (K 4160) 69 -> 43 us and
 // 600 x 8192 (K 8256) 132 -> 86 us with 128-wide tiles; 4096 x 5120 (K 5184) 193 -> 162 and 1500 x 11008 (K 4160)
 // 156 -> 124 us with 192-wide ones; 4096 x 8192 (K 8256), two full rounds, 351 us against 382 (192) and 388 (128).
+struct RoundCost { int width, empty, full; };                // of a round, in 0.01 us per K-step
+constexpr RoundCost kWide = {256, 105, 136}, kNarrow[2] = {{192, 86, 105}, {128, 66, 79}};
+constexpr int kCUs = 256;
+int64_t rounds_cost(const RoundCost& c, int64_t tiles, int64_t steps) {
+  const int64_t last = tiles % kCUs;
+  return (tiles / kCUs * c.full + (last ? c.empty + (c.full - c.empty) * last / kCUs : 0)) * steps;
+}
 GemmCut gemm_cut(int tiles_m, int N, int steps) {
-  struct Cost { int width, empty, full; };                   // of a round, in 0.01 us per K-step
-  constexpr Cost kWide = {256, 105, 136}, kNarrow[2] = {{192, 86, 105}, {128, 66, 79}};
-  constexpr int kCUs = 256, kLaunch = 300;
-  auto cost = [&](const Cost& c, int cols) {
-    const int64_t tiles = (int64_t)cols * tiles_m, last = tiles % kCUs;
-    return (tiles / kCUs * c.full + (last ? c.empty + (c.full - c.empty) * last / kCUs : 0)) * steps;
-  };
+  constexpr int kLaunch = 300;
+  auto cost = [&](const RoundCost& c, int cols) { return rounds_cost(c, (int64_t)cols * tiles_m, steps); };
   const int tiles_n = (N + 255) / 256;
   GemmCut best = {tiles_n, 0, 256};
   int64_t best_cost = cost(kWide, tiles_n);
   auto consider = [&](int wide) {
-    for (const Cost& c : kNarrow) {
+    for (const RoundCost& c : kNarrow) {
       const int rest = (N - wide * 256 + c.width - 1) / c.width;
       const int64_t t = cost(kWide, wide) + cost(c, rest) + (wide > 0 ? kLaunch : 0);
       if (t * 101 < best_cost * 100) { best_cost = t; best = {wide, rest, c.width}; }
@@ -575,6 +577,13 @@ GemmCut gemm_cut(int tiles_m, int N, int steps) {
 }
 
 }  // namespace
+
+double gemm_rounds_us(int64_t M, int64_t N, int64_t steps) {
+  const int64_t tiles_m = (M + BM - 1) / BM;
+  int64_t best = rounds_cost(kWide, (N + 255) / 256 * tiles_m, steps);
+  for (const RoundCost& c : kNarrow) best = std::min(best, rounds_cost(c, (N + c.width - 1) / c.width * tiles_m, steps));
+  return 0.01 * (double)best;
+}
 
 hipError_t launch_gemm_nt(const uint16_t* A0, const uint16_t* B0, int64_t lda0, int64_t ldb0, int K0,
                           const uint16_t* A1, const uint16_t* B1, int64_t lda1, int64_t ldb1, int K1,

@@ -45,6 +45,8 @@ hipError_t launch_dequant_t(const NF4Dev& w, uint16_t* out, int64_t ld_out, hipS
 hipError_t launch_gemm_nt(const uint16_t* A0, const uint16_t* B0, int64_t lda0, int64_t ldb0, int K0,
                           const uint16_t* A1, const uint16_t* B1, int64_t lda1, int64_t ldb1, int K1,
                           uint16_t* C, int64_t ldc, int M, int N, hipStream_t st);
+// Estimated time of the product from the measured costs of a tile round (whole outputs of one tile width), `steps` K-steps.
+double gemm_rounds_us(int64_t M, int64_t N, int64_t steps);
 
 // The same product with the weight-side operand of segment 0 decoded inside the kernel: Bq = N rows of K0 / 2 bytes of
 // 4-bit codes, Bc = N x K0 / 64 fp32 block constants, tab16 = the data type's 16 values (all device memory).  The
@@ -173,8 +175,11 @@ struct MidPlan {
   int MF, KW, n_tg, n_slabs, steps, n_lparts, chunk, max_contrib;
   MidLine line;
   size_t part_floats, lpart_floats, pack_elems;
+  double us;                                 // estimate of the main kernel's time
 };
 MidPlan mid_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room);
+// Is the plan worth taking, or is the weight dequantised and multiplied sooner?  fix: that path would need the dropout fix-up.
+bool mid_pays(const MidPlan& p, bool bwd, int64_t M, int64_t h, int64_t o, int r, bool fix);
 //   forward: out (M x o) = X dequant(W) + scale (mask o X L1) L2, hl (M x 2r or NULL) = [hi | lo] of mask o X L1;
 //   backward: X is dY (M x o), out (M x h) = dY dequant(W)^T + scale mask o ((dY L2^T) L1^T), hl = [hi | lo] of dY L2^T.
 //   mask: keep-bits over M x h elements, or NULL.

@@ -793,7 +793,7 @@ MidPlan mid_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room) 
   auto consider = [&](int kw, int group) {
     double us = 0;
     const MidPlan p = plan_shape(bwd, kw, group, M, K, N, r, room, &us);
-    if (p.ok && (!best.ok || us < best_us)) { best = p; best_us = us; }
+    if (p.ok && (!best.ok || us < best_us)) { best = p; best.us = best_us = us; }
   };
   if (!bwd) consider(8, 64);
   if (bwd || M > kMidUnpacked) {
@@ -801,6 +801,22 @@ MidPlan mid_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room) 
     if (M > 64) consider(4, 64);                             // below, tiles of 128 hold all tokens anyway
   }
   return best;
+}
+
+// Both sides from their parts, in microseconds, fitted to 1645 calls of either path (1 .. 512 tokens, contractions of 64 ..
+// 22016, 64 .. 65536 outputs, ranks 0 .. 256; each estimate within 20 % on nine calls of ten).  Decoding inside the product
+// loses where the contraction is short (its partials are then as large as the product: dX with K = 64, N = 16384 at 384 tokens
+// 43 us against 12) or the rank large (K = 1024, N = 8192, rank 256 at 512 tokens 66 against 32); it wins where the weight is
+// what counts (K = 22016, N = 8192, rank 64 at 256 tokens 117 against 421).  Near the line either will do: it is drawn where
+// the estimates differ by a fifth, so that of those calls none is more than a quarter slower than its better path and seven
+// of them slower than 3 % than inside the product.
+bool mid_pays(const MidPlan& p, bool bwd, int64_t M, int64_t h, int64_t o, int r, bool fix) {
+  const double K = (double)(bwd ? o : h), N = (double)(bwd ? h : o), MN = 1e-6 * (double)M * N;
+  const double mid = 6.5 + 0.88 * p.us + (p.pack ? 4.3 + 0.053 * r : 0.027 * r) + 0.35 * p.max_contrib * MN + 0.0034 * r * MN +
+                     3.3e-8 * (double)M * K * r;
+  const double gemm = 9.7 + 0.7 * gemm_rounds_us(M, (int64_t)N, ((int64_t)K + (r + 63) / 64 * 64) / 64) + 0.62e-6 * K * N +
+                      0.6 * MN + (r > 0 ? 3.6 + 1e-6 * r * (0.2 * N + 3.8 * K) : 0.0) + (fix ? 5.5 + 2.2 * MN : 0.0);
+  return mid <= 1.2 * gemm;
 }
 
 hipError_t launch_mid(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const MidPlan& p, const uint16_t* L1,

@@ -8,7 +8,7 @@ import torch
 
 from gpu_util import dev_bf16, dev_f32, host_bits, upload_quant
 from test_gpu_dropout import _mask
-from test_gpu_fused_bwd import _dx, fused  # noqa: F401
+from test_gpu_fused_bwd import _dx, _gemm_launches, fused  # noqa: F401
 from test_gpu_linear import _check
 
 pytestmark = pytest.mark.gpu
@@ -39,6 +39,33 @@ def test_midtok_forward_backward(oracle, synth, M, h, o, r):
     dX, dL1, dL2 = ql.qlora_linear_bwd(d(dY), d(X), Wq, d(L1), d(L2), s, T_saved=T, workspace=ws[:bb])
     assert int((ws[max(fb, bb):] != 0x7F).sum()) == 0
     torch.cuda.synchronize()
+    _check(host_bits(Y), oracle.linear_fwd(X, What, L1, L2, s), "Y")
+    _check(host_bits(dX), oracle.linear_bwd_dx(dY, What, L1, L2, s), "dX")
+    if r:
+        r1, r2 = oracle.linear_bwd_dl(dY, X, L1, L2, s)
+        _check(host_bits(dL1), r1, "dL1", few_terms=M < 64)
+        _check(host_bits(dL2), r2, "dL2", few_terms=M < 64)
+
+
+# Contractions long enough, either way, for the product that decodes the weight (the small layers above may be dequantised
+# instead): the same edges, and no launch of the main GEMM.
+@pytest.mark.parametrize("M,h,o,r", [(49, 1088, 1024, 0), (64, 2048, 1088, 48), (65, 1024, 2112, 32), (81, 1600, 1088, 64),
+                                      (97, 1600, 2112, 16), (112, 2048, 1344, 80), (113, 1088, 2048, 64),
+                                      (128, 2752, 3136, 256), (129, 2048, 1088, 64), (334, 1536, 2112, 0),
+                                      (511, 2752, 3136, 144), (512, 2112, 1600, 64)])
+def test_midtok_is_reached(oracle, synth, M, h, o, r):
+    import paper_2305_14314_amd as ql
+    s = 0.5
+    q = oracle.nf4_quantize(synth.normal_f32((h, o), synth.SIGMA_W, 800 + M))
+    What, Wq = oracle.nf4_dequant(q), upload_quant(q)
+    X, dY = synth.normal_bf16((M, h), 1.0, 801 + M), synth.normal_bf16((M, o), 1.0, 802 + M)
+    L1 = synth.normal_bf16((h, r), 0.05, 803 + M) if r else None
+    L2 = synth.normal_bf16((r, o), 0.05, 804 + M) if r else None
+    d = lambda a: None if a is None else dev_bf16(a)
+    print(f"case mid reached M={M} h={h} o={o} r={r}", flush=True)
+    Y, n = _gemm_launches(ql, lambda: ql.qlora_linear_fwd(d(X), Wq, d(L1), d(L2), s))
+    (dX, dL1, dL2), m = _gemm_launches(ql, lambda: ql.qlora_linear_bwd(d(dY), d(X), Wq, d(L1), d(L2), s))
+    assert n == 0 and m == 0
     _check(host_bits(Y), oracle.linear_fwd(X, What, L1, L2, s), "Y")
     _check(host_bits(dX), oracle.linear_bwd_dx(dY, What, L1, L2, s), "dX")
     if r:

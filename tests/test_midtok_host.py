@@ -15,17 +15,26 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 pytestmark = pytest.mark.skipif(not (os.path.exists(HIPCC) or shutil.which(HIPCC)), reason="hipcc not available")
 
 
-def test_mid_plan_tiles_the_work(tmp_path):
+def _run_check(tmp_path, name):
     from paper_2305_14314_amd import binding, build
     if not os.path.exists(binding.LIB_PATH):
         build.build(verbose=False)
-    exe, pkg = str(tmp_path / "mid_plan_check"), os.path.dirname(binding.LIB_PATH)
+    exe, pkg = str(tmp_path / name), os.path.dirname(binding.LIB_PATH)
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-O2", "-std=c++17", "-x", "hip", "-I", CSRC,
-                    os.path.join(CHECKS, "mid_plan_check.cpp"), "-o", exe, "-L", pkg, "-lqlora_hip", "-Wl,-rpath," + pkg],
+                    os.path.join(CHECKS, name + ".cpp"), "-o", exe, "-L", pkg, "-lqlora_hip", "-Wl,-rpath," + pkg],
                    check=True, capture_output=True)
-    out = subprocess.run([exe], check=False, capture_output=True, text=True, timeout=300).stdout
+    return subprocess.run([exe], check=False, capture_output=True, text=True, timeout=300).stdout
+
+
+def test_mid_plan_tiles_the_work(tmp_path):
+    out = _run_check(tmp_path, "mid_plan_check")
     assert out.startswith("OK "), out
     assert int(out.split()[1]) > 3000
+
+
+def test_mid_is_taken_where_it_is_faster(tmp_path):
+    out = _run_check(tmp_path, "mid_choice_check")
+    assert out.startswith("OK "), out
 
 
 def test_mid_mfma_operands_are_written_in_time(tmp_path):
