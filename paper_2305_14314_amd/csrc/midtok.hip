@@ -847,21 +847,31 @@ hipError_t launch_mid(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const
     a.x_bytes = (uint32_t)((int64_t)M * a.K * 2);
     a.n_items = items;
   }
-#define QL_MID_4(MF)                                                           \
-  case 40 + MF:                                                                \
-    if (bwd) launch_main<MF, 4, true, true>(a, st);                            \
-    else launch_main<MF, 4, false, true>(a, st);                               \
-    break;
-  if ((bwd && p.KW != 4) || (p.KW == 4 && !p.pack)) return hipErrorInvalidValue;
-  switch (10 * p.KW + p.MF) {
-    case 81: if (p.pack) return hipErrorInvalidValue; launch_main<1, 8, false, false>(a, st); break;
-    case 82: if (p.pack) launch_main<2, 8, false, true>(a, st); else launch_main<2, 8, false, false>(a, st); break;
-    case 83: if (p.pack) launch_main<3, 8, false, true>(a, st); else launch_main<3, 8, false, false>(a, st); break;
-    case 84: if (!p.pack) return hipErrorInvalidValue; launch_main<4, 8, false, true>(a, st); break;
-    QL_MID_4(2) QL_MID_4(3) QL_MID_4(4) QL_MID_4(5) QL_MID_4(6) QL_MID_4(7) QL_MID_4(8)
-    default: return hipErrorInvalidValue;
+  // what mid_plan makes of 1 .. 512 tokens; packed forward operands have three token tiles at least
+#define QL_MID_BWD(MF) case 40 + MF: launch_main<MF, 4, true, true>(a, st); break;
+#define QL_MID_FWD(MF) case 40 + MF: launch_main<MF, 4, false, true>(a, st); break;
+  if (bwd) {
+    switch (10 * p.KW + p.MF) {
+      QL_MID_BWD(2) QL_MID_BWD(3) QL_MID_BWD(4) QL_MID_BWD(5) QL_MID_BWD(6) QL_MID_BWD(7) QL_MID_BWD(8)
+      default: return hipErrorInvalidValue;
+    }
+  } else if (p.pack) {
+    switch (10 * p.KW + p.MF) {
+      case 83: launch_main<3, 8, false, true>(a, st); break;
+      case 84: launch_main<4, 8, false, true>(a, st); break;
+      QL_MID_FWD(3) QL_MID_FWD(4) QL_MID_FWD(5) QL_MID_FWD(6) QL_MID_FWD(7) QL_MID_FWD(8)
+      default: return hipErrorInvalidValue;
+    }
+  } else {
+    switch (10 * p.KW + p.MF) {
+      case 81: launch_main<1, 8, false, false>(a, st); break;
+      case 82: launch_main<2, 8, false, false>(a, st); break;
+      case 83: launch_main<3, 8, false, false>(a, st); break;
+      default: return hipErrorInvalidValue;
+    }
   }
-#undef QL_MID_4
+#undef QL_MID_FWD
+#undef QL_MID_BWD
   if (hipError_t e = hipGetLastError()) return e;
   MidFinArgs f{};
   f.part = part; f.line = p.line; f.MF = p.MF; f.n_tg = p.n_tg; f.M = M; f.N = a.N; f.lpart = lpart; f.n_lparts = a.n_lparts; f.r = r;

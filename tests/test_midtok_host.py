@@ -37,6 +37,11 @@ def test_mid_is_taken_where_it_is_faster(tmp_path):
     assert out.startswith("OK "), out
 
 
+def test_mid_plans_have_kernels(tmp_path):
+    out = _run_check(tmp_path, "mid_variants_check")
+    assert out == "OK 18\n", out
+
+
 def test_mid_mfma_operands_are_written_in_time(tmp_path):
     from paper_2305_14314_amd import build
     asm = str(tmp_path / "midtok.s")
