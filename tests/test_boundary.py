@@ -191,6 +191,48 @@ def test_default_workspace_is_accepted(L, dtype, dq, M, r):
         assert got == (-5, -5), (dropout, got)
 
 
+def accepted_workspace(L, bwd, M, h, o, r):
+    """The smallest workspace (bytes) the call accepts for a 4-bit double-quantised weight, by bisection: a misaligned
+    workspace is refused after the size check, so nothing is launched."""
+    from paper_2305_14314_amd import binding
+    v = binding.qlora_nf4_view(0x1000, 0x1000, 0x1000, 0x1000, h, o, 64, 256)
+    fake, odd, lo = ctypes.c_void_p(0x1000), ctypes.c_void_p(0x1008), ctypes.c_void_p(0x1000 if r else 0)
+    sizes = binding.qlora_linear_bwd_sizes if bwd else binding.qlora_linear_fwd_sizes
+
+    def ok(n):
+        if bwd:
+            st = L.qlora_linear_bwd(fake, fake, ctypes.byref(v), lo, lo, 1.0, M, r, None, fake, None, None, odd, n, None)
+        else:
+            st = L.qlora_linear_fwd(fake, ctypes.byref(v), lo, lo, 1.0, M, r, fake, None, odd, n, None)
+        assert st in (-4, -5), st
+        return st == -5
+
+    bad, good = 0, sizes(M, h, o, r)
+    assert ok(good)
+    while good - bad > 1:
+        mid = (bad + good) // 2
+        bad, good = (bad, mid) if ok(mid) else (mid, good)
+    return good
+
+
+@pytest.mark.parametrize("M,h,o,r", [(256, 1024, 1024, 64), (40, 448, 2112, 16), (512, 1088, 2048, 48), (100, 2048, 1088, 0),
+                                     (600, 1024, 1024, 16)])
+def test_dequantise_plan_is_all_a_call_needs(L, M, h, o, r):
+    """Whatever the size queries report, the bytes of the dequantise + GEMM plan are accepted: the weight (and L2 beside it
+    in the forward), the adapter's intermediates and the partials of the largest skinny product."""
+    up = lambda n: (n + 255) // 256 * 256
+    tiles = lambda I, J: -(-I // 64) * -(-J // 64)
+    part = lambda I, J, K: min(-(-512 // tiles(I, J)), 64, -(-K // 64)) * I * J
+    rp = -(-r // 64) * 64
+    fwd = 16384 + up((h + rp) * o * 2)
+    bwd = 16384 + up(h * o * 2)
+    if r:
+        fwd += up(M * rp * 2) + up(part(M, r, h) * 4)
+        bwd += (up(h * rp * 2) if r % 64 else 0) + up(M * rp * 2) + 2 * up(M * 4 * r) + \
+            up(max(part(M, r, o), part(M, r, h), part(h, r, M), part(r, o, M)) * 4)
+    assert (accepted_workspace(L, False, M, h, o, r), accepted_workspace(L, True, M, h, o, r)) == (fwd, bwd)
+
+
 def test_data_type_tables_and_their_validation(L, oracle):
     """The library's tables of the 4-bit data types equal the oracle's bit for bit (host call, no GPU), unknown
     types are refused, and a view carries its type."""

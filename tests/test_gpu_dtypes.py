@@ -1,12 +1,13 @@
 """GPU parity for the other 4-bit data types of the paper's comparison (Int4, Float4 E2M1, Float4 E3M0): the same
 kernels with another 16-value table.  Quantisation and dequantisation bit-exact against the oracle (ties and
-duplicate values included), the linear layer within the GEMM tolerance on both the large-GEMM and the few-token
-path."""
+duplicate values included), the linear layer within the GEMM tolerance on every path: dequantise + GEMM, the product
+that decodes the weight and the few-token kernels."""
 import numpy as np
 import pytest
 import torch
 
 from gpu_util import code_to_flat, dev_bf16, dev_f32, host_bits, host_u8, host_u32, upload_quant
+from test_gpu_fused_bwd import _gemm_launches
 from test_gpu_linear import _check
 
 pytestmark = pytest.mark.gpu
@@ -49,10 +50,11 @@ def test_quantize_dequant_bit_exact(oracle, synth, kind, dtype):
 
 
 @pytest.mark.parametrize("kind,dtype", KINDS)
-@pytest.mark.parametrize("M,h,o,r", [(300, 448, 576, 32), (5, 192, 320, 16), (16, 1024, 1024, 64)])
+@pytest.mark.parametrize("M,h,o,r", [(600, 448, 576, 32), (300, 448, 576, 32), (5, 192, 320, 16), (16, 1024, 1024, 64)])
 def test_linear_other_types(oracle, synth, kind, dtype, M, h, o, r):
-    """Forward and backward on a weight of another data type: M = 300 takes the dequantise + GEMM path, M = 5 and 16
-    the few-token streaming kernels (8- and 16-token variants), all against the oracle on its own dequantised weight."""
+    """Forward and backward on a weight of another data type: M = 600 takes the dequantise + GEMM path, M = 300 may take the
+    product that decodes the weight, M = 5 and 16 the few-token streaming kernels (8- and 16-token variants), all against
+    the oracle on its own dequantised weight."""
     import paper_2305_14314_amd as ql
     s = 0.5
     table = oracle.codebook4(kind)
@@ -64,8 +66,9 @@ def test_linear_other_types(oracle, synth, kind, dtype, M, h, o, r):
     hL1, hL2 = synth.normal_bf16((h, r), 0.05, 9103), synth.normal_bf16((r, o), 0.05, 9104)
     X, dY, L1, L2 = dev_bf16(hX), dev_bf16(hdY), dev_bf16(hL1), dev_bf16(hL2)
     print(f"case {kind} linear M={M} h={h} o={o} r={r}", flush=True)
-    Y = ql.qlora_linear_fwd(X, Wq, L1, L2, s)
-    dX, dL1, dL2 = ql.qlora_linear_bwd(dY, X, Wq, L1, L2, s)
+    Y, n_fwd = _gemm_launches(ql, lambda: ql.qlora_linear_fwd(X, Wq, L1, L2, s))
+    (dX, dL1, dL2), n_bwd = _gemm_launches(ql, lambda: ql.qlora_linear_bwd(dY, X, Wq, L1, L2, s))
+    assert M <= 512 or (n_fwd, n_bwd) == (1, 1)
     Ym = ql.qlora_linear_fwd_multi(X, [Wq, Wq], [L1, None], [L2, None], [s, 1.0])
     torch.cuda.synchronize()
     _check(host_bits(Y), oracle.linear_fwd(hX, What, hL1, hL2, s), f"{kind} Y")
@@ -87,8 +90,9 @@ def test_linear_other_types(oracle, synth, kind, dtype, M, h, o, r):
 @pytest.mark.parametrize("kind,dtype", [("nf4", 0), ("int4", 3)])
 def test_without_double_quantization(oracle, synth, kind, dtype):
     """dq_blocksize = 0: the fp32 constants are kept (4.5 bit per parameter).  Quantise and dequantise bit-exact; the
-    linear layer at 300 and at 5 tokens (the latter through the large-GEMM path: the streaming kernels read
-    double-quantised constants) against the oracle; the several-layers forward refuses such a weight at few tokens."""
+    linear layer at 600 tokens (dequantise + GEMM), 300 and 5 (the product that decodes the weight, or dequantise + GEMM:
+    the streaming kernels read double-quantised constants) against the oracle; the several-layers forward refuses such a
+    weight at few tokens."""
     import paper_2305_14314_amd as ql
     table = oracle.codebook4(kind)
     h, o, r, s = 448, 576, 32, 0.5
@@ -103,12 +107,13 @@ def test_without_double_quantization(oracle, synth, kind, dtype):
     np.testing.assert_array_equal(host_bits(ql.qlora_nf4_dequant(Wq)), What)
     hL1, hL2 = synth.normal_bf16((h, r), 0.05, 9201), synth.normal_bf16((r, o), 0.05, 9202)
     L1, L2 = dev_bf16(hL1), dev_bf16(hL2)
-    for M in (300, 5):
+    for M in (600, 300, 5):
         print(f"case no-DQ {kind} M={M}", flush=True)
         hX, hdY = synth.normal_bf16((M, h), 1.0, 9203 + M), synth.normal_bf16((M, o), 1.0, 9204 + M)
         X, dY = dev_bf16(hX), dev_bf16(hdY)
-        Y = ql.qlora_linear_fwd(X, Wq, L1, L2, s)
-        dX, dL1, dL2 = ql.qlora_linear_bwd(dY, X, Wq, L1, L2, s)
+        Y, n_fwd = _gemm_launches(ql, lambda: ql.qlora_linear_fwd(X, Wq, L1, L2, s))
+        (dX, dL1, dL2), n_bwd = _gemm_launches(ql, lambda: ql.qlora_linear_bwd(dY, X, Wq, L1, L2, s))
+        assert M <= 512 or (n_fwd, n_bwd) == (1, 1)
         torch.cuda.synchronize()
         _check(host_bits(Y), oracle.linear_fwd(hX, What, hL1, hL2, s), f"no-DQ {kind} M={M} Y")
         _check(host_bits(dX), oracle.linear_bwd_dx(hdY, What, hL1, hL2, s), f"no-DQ {kind} M={M} dX")

@@ -233,12 +233,14 @@ def test_random_shapes(oracle, synth, M, h, o, r):
     _run_case(oracle, ql, L, f"random M={M} h={h} o={o} r={r}", with_lora=r > 0)
 
 
-def test_training_step_graph_replay(synth):
-    """The large-GEMM path under HIP graph capture: forward with T saved, backward with all three gradients, the
-    dropout variants with fp32 accumulation.  Every replay -- with eager work, scribbled workspace and synchronisations
+@pytest.mark.parametrize("M", [600, 300])
+def test_training_step_graph_replay(synth, M):
+    """A training step under HIP graph capture, at 600 tokens on dequantised weights (finalize steps ride in the dequantise
+    launch) and at 300 through the product that decodes the weight: forward with T saved, backward with all three
+    gradients, the dropout variants with fp32 accumulation.  Every replay -- with eager work, scribbled workspace and synchronisations
     in between -- reproduces the eager result bit for bit (the path holds kernels only: nothing a graph replays badly)."""
     import paper_2305_14314_amd as ql
-    M, h, o, r, s, p = 300, 448, 576, 32, 0.5, 0.1
+    h, o, r, s, p = 448, 576, 32, 0.5, 0.1
     Wq = ql.qlora_nf4_quantize(synth.normal_f32_device((h, o), synth.SIGMA_W, 7100))
     L1 = dev_bf16(synth.normal_bf16((h, r), 0.05, 7101))
     L2 = dev_bf16(synth.normal_bf16((r, o), 0.05, 7102))

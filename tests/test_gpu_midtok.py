@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from gpu_util import dev_bf16, dev_f32, host_bits, upload_quant
+from test_boundary import accepted_workspace
 from test_gpu_dropout import _mask
 from test_gpu_fused_bwd import _dx, _gemm_launches, fused  # noqa: F401
 from test_gpu_linear import _check
@@ -133,3 +134,34 @@ def test_fused_backward_above_mid(oracle, synth, fused, M, h, o, r):  # noqa: F8
     _check(host_bits(b), ref, "fused dX")
     if r == 0:
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("M,h,o,r", [(256, 1024, 1024, 64), (64, 4096, 448, 16), (512, 1088, 2048, 48), (200, 1600, 1088, 0)])
+def test_smallest_accepted_workspace(oracle, synth, M, h, o, r):
+    """With the bytes of the dequantise + GEMM plan and no more the calls split less or take that plan: the oracle's values,
+    and nothing written behind them."""
+    import paper_2305_14314_amd as ql
+    s, L = 0.5, ql.binding.lib()
+    nf, nb = accepted_workspace(L, False, M, h, o, r), accepted_workspace(L, True, M, h, o, r)
+    assert nf < ql.qlora_linear_fwd_sizes(M, h, o, r) or nb < ql.qlora_linear_bwd_sizes(M, h, o, r)
+    q = oracle.nf4_quantize(synth.normal_f32((h, o), synth.SIGMA_W, 900 + M))
+    What, Wq = oracle.nf4_dequant(q), upload_quant(q)
+    X, dY = synth.normal_bf16((M, h), 1.0, 901 + M), synth.normal_bf16((M, o), 1.0, 902 + M)
+    L1 = synth.normal_bf16((h, r), 0.05, 903 + M) if r else None
+    L2 = synth.normal_bf16((r, o), 0.05, 904 + M) if r else None
+    d = lambda a: None if a is None else dev_bf16(a)
+    print(f"case smallest workspace M={M} h={h} o={o} r={r}: {nf} {nb}", flush=True)
+    for n, bwd in ((nf, False), (nb, True)):
+        ws = ql.workspace_alloc(n + 4096)
+        ws[ql.binding.WORKSPACE_HEADER_BYTES:].fill_(0x7F)
+        if not bwd:
+            Y = ql.qlora_linear_fwd(d(X), Wq, d(L1), d(L2), s, workspace=ws[:n])
+            _check(host_bits(Y), oracle.linear_fwd(X, What, L1, L2, s), "Y")
+        else:
+            dX, dL1, dL2 = ql.qlora_linear_bwd(d(dY), d(X), Wq, d(L1), d(L2), s, workspace=ws[:n])
+            _check(host_bits(dX), oracle.linear_bwd_dx(dY, What, L1, L2, s), "dX")
+            if r:
+                r1, r2 = oracle.linear_bwd_dl(dY, X, L1, L2, s)
+                _check(host_bits(dL1), r1, "dL1", few_terms=M < 64)
+                _check(host_bits(dL2), r2, "dL2", few_terms=M < 64)
+        assert int((ws[n:] != 0x7F).sum()) == 0
