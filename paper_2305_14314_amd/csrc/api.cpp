@@ -153,10 +153,12 @@ struct MidWs { qlora::MidPlan plan; float* part; float* lpart; uint16_t* xpack; 
 size_t mid_bytes(const qlora::MidPlan& p) {
   return align_up(p.part_floats * sizeof(float), 256) + align_up(p.lpart_floats * sizeof(float), 256) + align_up(p.pack_elems * 2, 256);
 }
-// bytes of the region that holds either the dequantised weight (`base` bytes) or the buffers of this path
-size_t mid_region(size_t base, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r, bool fix = false) {
+// bytes of the region that holds either the dequantised weight (`base` bytes) or the buffers of this path; asked for whether
+// or not the path is taken, because the adapter gradients' partials lie there too (dL1 and dL2 of 1024 x 1024 at rank 128 and
+// 512 tokens share a launch in it: 20.5 us, 24.6 without)
+size_t mid_region(size_t base, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r) {
   const qlora::MidPlan p = qlora::mid_plan(bwd, M, h, o, r, std::max(base, kMidRoom));
-  return p.ok && qlora::mid_pays(p, bwd, M, h, o, r, fix) ? std::max(base, mid_bytes(p)) : base;
+  return p.ok ? std::max(base, mid_bytes(p)) : base;
 }
 MidWs plan_mid(void* buf, size_t room, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r, bool fix = false) {
   MidWs m{};
@@ -229,10 +231,11 @@ struct SmallBatch {
   }
 };
 // How dL1 and dL2 of a layer are split (the last two arguments of SmallBatch::add).  They share a launch where `room`, which
-// depends on the shape alone, holds their partials -- with a floor under the smaller one's workgroups if it holds those too;
-// otherwise each is split as in the launch of its own that it gets.  (4096 x 1024 at rank 256 and 4096 tokens, which does not
-// fit: 74 us with the splits of a shared launch, 65 so.  Four or more gradients of stacked layers leave no such tail: no
-// floor there, whose partials would send some of them off in a second launch.)
+// depends on the shape alone, holds their partials -- with a floor under the smaller one's workgroups if it holds those too.
+// Where it does not, each gets a launch of its own, and its own splits if a shared launch's would leave chains of eight
+// K-steps and more: 4096 x 1024 at rank 256 and 4096 tokens (32 K-steps) 74 us with a shared launch's splits, 65 with its
+// own; 320 x 1088 at rank 64 (3 K-steps) 50 and 53.  The gradients of stacked layers are not held to the floor: over
+// 240 calls none is slower than with separate launches, and its partials would send some off in a second launch.
 struct DlSplit { int tiles, floor; };
 DlSplit dl_split(int64_t M, int64_t h, int64_t o, int r, size_t room) {
   const int t1 = qlora::small_tiles((int)h, r), t2 = qlora::small_tiles(r, (int)o);
@@ -241,7 +244,8 @@ DlSplit dl_split(int64_t M, int64_t h, int64_t o, int r, size_t room) {
                align_up((size_t)qlora::small_job_splits(r, (int)o, (int)M, t1, floor) * r * o * sizeof(float), 256) <= room;
   };
   if (fits(qlora::kSmallFloor)) return {t1 + t2, qlora::kSmallFloor};
-  return {fits(0) ? t1 + t2 : 0, 0};
+  const int64_t chain = (M + 63) / 64 / qlora::small_job_splits((int)h, r, (int)M, t2);
+  return {fits(0) || chain < 8 ? t1 + t2 : 0, 0};
 }
 qlora::SmallJob job_t(const uint16_t* X, int64_t h, const uint16_t* L1, int64_t M, int r, const uint8_t* mask) {
   qlora::SmallJob j{};
@@ -328,9 +332,8 @@ struct BwdPlan {
   size_t wd_bytes;   // of the region at Wd
   size_t bytes;
 };
-// roomy: the region at Wd also holds the buffers of the path for tens to hundreds of tokens (what the size queries report);
-// fix: of a dropout call, which takes that path more often
-BwdPlan plan_bwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allow_few = true, bool roomy = true, bool fix = false) {
+// roomy: the region at Wd also holds the buffers of the path for tens to hundreds of tokens (what the size queries report)
+BwdPlan plan_bwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allow_few = true, bool roomy = true) {
   BwdPlan p{};
   Carver c(ws);
   p.rp = (r + 63) / 64 * 64;
@@ -342,7 +345,7 @@ BwdPlan plan_bwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allo
     p.lpart = c.take<float>((size_t)p.n_lparts * M * r + 4);
   } else {
     p.wd_bytes = (size_t)h * o * sizeof(uint16_t);
-    if (roomy) p.wd_bytes = mid_region(p.wd_bytes, true, M, h, o, r, fix);
+    if (roomy) p.wd_bytes = mid_region(p.wd_bytes, true, M, h, o, r);
     p.Wd = (uint16_t*)c.take<char>(p.wd_bytes);
   }
   if (r > 0) {
@@ -660,7 +663,7 @@ qlora_status qlora_linear_dropout_sizes(int64_t M, int64_t h, int64_t o, int32_t
   if (qlora_status st = check_linear(M, h, o, r)) return st;
   // without an adapter there is nothing to drop and the calls are the plain ones, few-token path included
   if (fwd_bytes) *fwd_bytes = plan_fwd(nullptr, M, h, o, r, r == 0).bytes;
-  if (bwd_bytes) *bwd_bytes = plan_bwd(nullptr, M, h, o, r, r == 0, true, r > 0).bytes;
+  if (bwd_bytes) *bwd_bytes = plan_bwd(nullptr, M, h, o, r, r == 0).bytes;
   return QLORA_OK;
 }
 
@@ -833,8 +836,7 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
   const bool want1 = dL1 || aL1, want2 = dL2 || aL2;
   if ((want1 || want2) && !X) return QLORA_ERR_NULL;
   const bool allow_few = keep_mask == nullptr && streams_few(Wq);
-  const bool fix = keep_mask != nullptr;
-  BwdPlan p = plan_bwd(workspace, M, h, o, r, allow_few, true, fix);
+  BwdPlan p = plan_bwd(workspace, M, h, o, r, allow_few);
   const size_t full_wd = p.wd_bytes;                         // whatever room this call brings
   if (workspace_bytes < p.bytes) p = plan_bwd(workspace, M, h, o, r, allow_few, false);
   if (workspace_bytes < p.bytes) return QLORA_ERR_WORKSPACE;
@@ -849,7 +851,7 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
                      qlora::gemm_nt_fused_fits((int)o, K1, (int)h);
   // a few hundred tokens: decode inside the product; the finalize step applies the dropout mask to the adapter's term
   const MidWs mid = !p.few && dX && !fused && streams_mid(Wq)
-                        ? plan_mid(p.Wd, p.wd_bytes, true, M, h, o, r, fix) : MidWs{};
+                        ? plan_mid(p.Wd, p.wd_bytes, true, M, h, o, r, keep_mask != nullptr) : MidWs{};
   qlora::FinList fin{};
   if (mid.plan.ok) {
     QL_TRY(qlora::launch_mid(true, dY, (int)M, W, mid.plan, L1, L2, r, s, keep_mask, mid.part, mid.lpart, mid.xpack, dX,
