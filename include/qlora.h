@@ -91,7 +91,7 @@ int qlora_last_hip_error(void);
  *
  * 8-bit integers (dtype = QLORA_INT8; Eq. 1 and Eq. 2 as printed): `packed` holds one signed byte per weight,
  * rows*cols bytes in flattened order, the constants are stored as above (with or without Double Quantization).
- * Accepted and refused exactly like a weight without Double Quantization: dequantise + GEMM path at any M.
+ * Accepted and refused exactly like a weight without Double Quantization, but on the dequantise + GEMM path at any M.
  */
 typedef struct {
   const uint8_t* packed;
@@ -224,7 +224,11 @@ qlora_status qlora_workspace_init(void* workspace, size_t workspace_bytes, void*
  * the streaming kernels (4-bit double-quantised, M <= 16), the product that
  * decodes the weight itself (4-bit, M <= 512) or dequantise + GEMM.  The
  * largest is reported; a call also accepts the smaller size of the dequantise
- * + GEMM plan and then splits the second kind of product less. */
+ * + GEMM plan and then splits the second kind of product less or takes the
+ * third.  Every call with at least the reported size gives the same bits for
+ * the same arguments; with less the fp32 sums may be formed in another order.
+ * Up to 512 tokens that order depends on M too, so a token's row can differ in
+ * its last bits between calls of different M. */
 qlora_status qlora_linear_fwd_sizes(int64_t M, int64_t h, int64_t o, int32_t r, size_t* workspace_bytes);
 qlora_status qlora_linear_bwd_sizes(int64_t M, int64_t h, int64_t o, int32_t r, size_t* workspace_bytes);
 
@@ -236,7 +240,8 @@ qlora_status qlora_linear_bwd_sizes(int64_t M, int64_t h, int64_t o, int32_t r, 
  * receives T = X * L1 for the backward pass as a pair of bf16 matrices side by
  * side: columns [0, r) hold bf16(T), columns [r, 2r) hold bf16(T - bf16(T)).  Any M >= 1 is accepted: a few
  * tokens (M <= 16) take a bandwidth-bound streaming path, up to 512 a product that
- * decodes the weight itself, larger M the MFMA GEMM on a dequantised copy. */
+ * decodes the weight itself unless an estimate says that the next is faster (short
+ * contractions, large ranks), larger M the MFMA GEMM on a dequantised copy. */
 qlora_status qlora_linear_fwd(const uint16_t* X, const qlora_nf4_view* Wq,
                               const uint16_t* L1, const uint16_t* L2, float s,
                               int64_t M, int32_t r,
@@ -252,7 +257,8 @@ qlora_status qlora_linear_fwd(const uint16_t* X, const qlora_nf4_view* Wq,
  * Each of dX, dL1, dL2 may be NULL and is then not computed.  X is needed only
  * for dL1 / dL2 (may be NULL when both are NULL).  T_saved is the T_save of the
  * forward call or NULL, in which case X * L1 is recomputed (gradient
- * checkpointing).  With r = 0 only dX is produced. */
+ * checkpointing; up to 512 tokens the sum may be formed in another order than
+ * in the forward call).  With r = 0 only dX is produced. */
 qlora_status qlora_linear_bwd(const uint16_t* dY, const uint16_t* X, const qlora_nf4_view* Wq,
                               const uint16_t* L1, const uint16_t* L2, float s,
                               int64_t M, int32_t r, const uint16_t* T_saved,
@@ -325,7 +331,8 @@ qlora_status qlora_linear_fwd_multi(const uint16_t* X, int32_t n, const qlora_nf
  * block-diagonally (layer l's s[l] * X * L1[l] meets only layer l's L2[l]), and the outputs come out side by side:
  *   Y is M x (o[0] + ... + o[n-1]), row-major; layer l's output is the column range starting at o[0] + ... + o[l-1].
  * T_save: NULL, or a host array of n device pointers (entries may be NULL): T_save[l] receives X * L1[l] as the
- * M x 2 r[l] [hi | lo] pair qlora_linear_bwd takes.  Any M >= 1 (few tokens take the same path).  Workspace: the size
+ * M x 2 r[l] [hi | lo] pair qlora_linear_bwd takes.  Any M >= 1 (few tokens take the same path: the weights are always
+ * dequantised).  Workspace: the size
  * qlora_linear_fwd_stacked_sizes reports, (sum o) * (h + sum of the ranks rounded up to 64) bf16 values and a few
  * small buffers; same rules otherwise.  Each layer's output meets the tolerance of qlora_linear_fwd. */
 qlora_status qlora_linear_fwd_stacked_sizes(int64_t M, int32_t n, int64_t h, const int64_t* o, const int32_t* r,

@@ -10,11 +10,14 @@
 //                     p = p - (lr wd) p  [wd != 0];  p = p - lr * (m / bc1) / (sqrt(v / bc2) + eps)
 //                   writes p, m, v, the bf16 copy of p that the linear layers read, and zeroes g when asked to.
 // 34 bytes of HBM traffic per parameter (16 read, 18 written with the bf16 copy and the cleared gradient).  p, m and v are
-// not touched again before the next step and the cleared gradient is only overwritten: they stream past the caches, which
-// are left to the gradient (read by both kernels) and the bf16 copy (read by the next forward).  10 M parameters of one
-// 65B-shaped block at rank 64, the whole step: 73.9 us
-// with ordinary accesses, 62.8 so (sqnorm alone 14.3 -> 7.5: the gradient is still in the last-level cache); only the loads
-// or only the stores past the caches 72 - 74.  16 workgroups per compute unit: 61.6, but 20 us more on first use.
+// not touched again before the next step, and a forward and a backward pass lie between: they and the cleared gradient
+// (which qlora_linear_bwd_acc will read to add to it) stream past the caches, which are left to the gradient (read by both
+// kernels) and the bf16 copy (read by the next forward).  Whole step (norm + update), us, ordinary accesses -> so, on as many
+// sets of buffers in turn as no cache holds (2.1 GB): 2.1 M parameters 19.9 -> 16.9, 4.2 M 33.9 -> 30.6, 10 M (one
+// 65B-shaped block at rank 64) 73.5 -> 69.6, 21 M 154 -> 140, 84 M 694 -> 651.  One set of 10 M again and again (180 MB, all of
+// it in the last-level cache with ordinary accesses) 57.0 -> 61.7: slower, but no training program steps twice without
+// touching anything else.  Three sets in turn 74 -> 64 (sqnorm 14.3 -> 7.5, as part of the gradient is still there); with only
+// the loads or only the stores past the caches 72 - 74.  16 workgroups per compute unit: 61.6, but 20 us more on first use.
 #include "common.hpp"
 #include "launch.hpp"
 

@@ -147,7 +147,7 @@ struct Carver {
 
 // Tens to hundreds of tokens (midtok.hip): its buffers lie where the dequantised weight would.  Small layers need more
 // than that for enough splits: the size queries then report more, and a caller that brings only the dequantise + GEMM
-// plan's bytes is still served, with fewer splits or by that plan.
+// plan's bytes is still served, with fewer splits or by that plan (and other last bits).
 constexpr size_t kMidRoom = (size_t)32 << 20;
 struct MidWs { qlora::MidPlan plan; float* part; float* lpart; uint16_t* xpack; };
 size_t mid_bytes(const qlora::MidPlan& p) {
@@ -600,7 +600,7 @@ namespace {
 // LoRA dropout: the kept elements' 1/(1-p) goes into the adapter's scale, the mask into the operand loads.
 inline float dropout_scale(float s, float p) { return (float)((double)s / (1.0 - (double)p)); }
 
-// The forward pass; keep_mask != NULL: LoRA dropout on the adapter's input (large-GEMM path whatever M).
+// The forward pass; keep_mask != NULL: LoRA dropout on the adapter's input (no streaming kernel whatever M).
 qlora_status linear_fwd_impl(const uint16_t* X, const qlora_nf4_view* Wq, const uint16_t* L1, const uint16_t* L2,
                              float s, int64_t M, int32_t r, const uint8_t* keep_mask, uint16_t* Y, uint16_t* T_save,
                              void* workspace, size_t workspace_bytes, void* hip_stream) {

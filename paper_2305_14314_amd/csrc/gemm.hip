@@ -548,8 +548,8 @@ struct GemmCut { int wide, rest, rest_width; };
 // 1.05 us nearly empty and 1.36 us full (the board's power limit), 192-wide 0.86 / 1.05, 128-wide 0.66 / 0.79; a second
 // launch about 3 us.  The cut of the least cost by these figures is taken (of
 // about equal ones, the one of more 256-wide tiles).  dX of a stacked q / k / v at 2000 tokens
-// (5120 columns, K 15552: 160 tiles of 256) 264 -> 234 us with 216 tiles of 192; 1024 x 4096 (K 4160) 69 -> 43 us and
-// 600 x 8192 (K 8256) 132 -> 86 us with 128-wide tiles; 4096 x 5120 (K 5184) 193 -> 162 and 1500 x 11008 (K 4160)
+// (5120 columns, K 15552: 160 tiles of 256) 310 -> 263 us inside the training call with 216 tiles of 192; each alone and
+// repeated: 1024 x 4096 (K 4160) 69 -> 43 us and 600 x 8192 (K 8256) 132 -> 86 us with 128-wide tiles; 4096 x 5120 (K 5184) 193 -> 162 and 1500 x 11008 (K 4160)
 // 156 -> 124 us with 192-wide ones; 4096 x 8192 (K 8256), two full rounds, 351 us against 382 (192) and 388 (128).
 struct RoundCost { int width, empty, full; };                // of a round, in 0.01 us per K-step
 constexpr RoundCost kWide = {256, 105, 136}, kNarrow[2] = {{192, 86, 105}, {128, 66, 79}};

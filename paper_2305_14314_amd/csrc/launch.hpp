@@ -161,6 +161,10 @@ hipError_t launch_workspace_init(void* workspace, hipStream_t st);
 // midtok.hip: tens to hundreds of tokens, 4-bit weights (with or without Double Quantization): the weight is decoded inside
 // the product, whose work is one line of equal ranges over the compute units, and a last kernel sums a tile's partials and
 // adds the adapter's term.  The plan uses at most `room` bytes of workspace; ok = false: not for this path.
+// Up to kMidTokens mid_pays() weighs a plan against dequantise + GEMM; above, that path is taken unweighed.  There neither is
+// better everywhere (us at rank 64, dequantised / decoded inside; K x N at tokens): 4096 x 4096 at 576 forward 58.6 / 55.4, dX
+// 57.0 / 62.1; 5120 x 13824 at 576 119 / 147, at 1024 143 / 267; 8192 x 8192 at 768 121 / 137; but 22016 x 8192 at 768
+// 439 / 306.  The estimate is fitted to calls of up to 512 tokens.
 constexpr int kMidTokens = 512;
 // `units` units in tiles of `ups`, cut into `wgs` ranges whose sizes differ by at most one.
 struct MidLine {

@@ -8,13 +8,13 @@
 // 158 -> 90 us; forward + backward 1024 x 1024 at 256 tokens 96 -> 51 us, 4096 x 4096 at 512 tokens 220 -> 107 us.
 //
 // Two or three launches on the caller's stream:
-//   pre       (more than 64 tokens) the token operand in MFMA-fragment order, so that the main kernel's operand loads
+//   pre       (backward, and forward above 48 tokens) the token operand in MFMA-fragment order, so that the main kernel's operand loads
 //             are whole contiguous kilobytes; beside it the partial sums of the adapter's inner product T = X L1 (U = dY L2^T)
 //   main      the products of all tiles (16 MF tokens x 128 outputs) are one line of units (KW steps of the contraction),
 //             cut into equal ranges, one per workgroup: whatever the shape, every compute unit multiplies the same
 //             amount.  Within a tile a workgroup's waves take the steps in turn, each with the whole tile in
 //             accumulators, and are summed through LDS into one fp32 partial tile.  No barrier in the loop.  Forward at
-//             up to 64 tokens the adapter's partial sums are extra workgroups here and the operand is read as it lies.
+//             up to 48 tokens the adapter's partial sums are extra workgroups here and the operand is read as it lies.
 //   finalize  out = bf16( sum of a tile's partials + s * (sum of T's partials) * L2 ), in a fixed order, one rounding; T
 //             as a [hi | lo] pair of bf16 operands (16 significant bits) on MFMA; writes T_save
 //
@@ -807,9 +807,8 @@ MidPlan mid_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room) 
 // 22016, 64 .. 65536 outputs, ranks 0 .. 256; each estimate within 20 % on nine calls of ten).  Decoding inside the product
 // loses where the contraction is short (its partials are then as large as the product: dX with K = 64, N = 16384 at 384 tokens
 // 43 us against 12) or the rank large (K = 1024, N = 8192, rank 256 at 512 tokens 66 against 32); it wins where the weight is
-// what counts (K = 22016, N = 8192, rank 64 at 256 tokens 117 against 421).  Near the line either will do: it is drawn where
-// the estimates differ by a fifth, so that of those calls none is more than a quarter slower than its better path and seven
-// of them slower than 3 % than inside the product.
+// what counts (K = 22016, N = 8192, rank 64 at 256 tokens 117 against 421).  Near the line either will do: a call goes to the
+// other path where that is faster by a fifth, so that seven of the fitted calls lose more than 3 % by it, the worst 20 %.
 bool mid_pays(const MidPlan& p, bool bwd, int64_t M, int64_t h, int64_t o, int r, bool fix) {
   const double K = (double)(bwd ? o : h), N = (double)(bwd ? h : o), MN = 1e-6 * (double)M * N;
   const double mid = 6.5 + 0.88 * p.us + (p.pack ? 4.3 + 0.053 * r : 0.027 * r) + 0.35 * p.max_contrib * MN + 0.0034 * r * MN +

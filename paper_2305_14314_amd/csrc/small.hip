@@ -3,8 +3,8 @@
 // rank (<= 256), so these are bound by streaming X or dY from HBM, not by MFMA.
 //
 //   part[split][I x J] (fp32) = sum over this split's K range of A(i,k) * B(k,j)
-//   finalize (fin.hpp): out = bf16(scale * sum over splits) and/or the sum as a [hi | lo] pair of bf16 matrices; a job of
-//   one split does it in the product's own epilogue
+//   finalize (fin.hpp): out = bf16(scale * sum over splits) and/or the sum as a [hi | lo] pair of bf16 matrices; dL1 and
+//   dL2 of at most four K-steps do it in the product's own epilogue
 //
 // Up to eight such products (of one or more layers) share a launch, and so do their finalize steps, which may also ride in
 // a dequantise launch.  A stacked q / k / v forward + backward at 2000 tokens (5120 x 5120, rank 64) spent 204 of 770 us in
