@@ -74,3 +74,30 @@ def test_saving_t_does_not_change_y(synth, kind, M, h):
     a, b = f(None), f(T)
     torch.cuda.synchronize()
     assert torch.equal(a, b)
+
+
+# dL1 and dL2 in one launch with a floor under the smaller one's workgroups; in launches of their own with a shared launch's
+# splits (short chains) and with their own; finished in the epilogue
+@pytest.mark.parametrize("M,h,o,r", [(1024, 2048, 2048, 64), (640, 320, 1088, 64), (2048, 2048, 64, 256), (2048, 64, 2048, 256),
+                                      (200, 320, 1088, 48)])
+def test_gradients_alone_and_together(oracle, synth, M, h, o, r):
+    """Each gradient against the oracle, and the same bits whether the call wants the other or not."""
+    import paper_2305_14314_amd as ql
+    s = 0.5
+    hX, hdY = synth.normal_bf16((M, h), 1.0, 9600), synth.normal_bf16((M, o), 1.0, 9601)
+    hL1, hL2 = synth.normal_bf16((h, r), 0.05, 9602), synth.normal_bf16((r, o), 0.05, 9603)
+    Wq = upload_quant(oracle.nf4_quantize(synth.normal_f32((h, o), synth.SIGMA_W, 9604)))
+    X, dY, L1, L2 = (dev_bf16(a) for a in (hX, hdY, hL1, hL2))
+    print(f"case gradients alone and together M={M} h={h} o={o} r={r}", flush=True)
+    _, dL1, dL2 = ql.qlora_linear_bwd(dY, X, Wq, L1, L2, s)
+    got = []
+    for want in ((True, True), (True, False), (False, True)):
+        a1 = torch.zeros((h, r), device="cuda") if want[0] else None
+        a2 = torch.zeros((r, o), device="cuda") if want[1] else None
+        ql.qlora_linear_bwd_acc(dY, X, Wq, L1, L2, s, a1, a2)
+        got.append((a1, a2))
+    torch.cuda.synchronize()
+    r1, r2 = oracle.linear_bwd_dl(hdY, hX, hL1, hL2, s)
+    _check(host_bits(dL1), r1, "dL1")
+    _check(host_bits(dL2), r2, "dL2")
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[2][1])
