@@ -7,17 +7,23 @@
 //   main workgroups    : part[split][m][n] = partial sums of X * What (forward) or dY * What^T (backward)
 //                        over the split's share of the contraction, for a slab of 256 outputs
 //   adapter workgroups : lpart[p][m][j] = partial sums of the adapter's inner product T = X L1 or U = dY L2^T
-//   last arriver       : every workgroup counts itself in at its slab's arrival counter (device-scope atomic
-//                        after a fence); the workgroup that brings in a slab's last split then meets the adapter
+//   last arriver       : every workgroup counts itself in at its slab's arrival counter (device-scope atomic, once
+//                        its partial is stored past the die's L2); the workgroup that brings in a slab's last split then meets the adapter
 //                        workgroups, each of which counts itself in at every slab's handshake word.  Whoever
 //                        completes that count computes
 //                        out = bf16( sum of splits + s * (sum of lpart) * L2 )  resp.  ... * L1^T  -- one rounding.
 //                        The only wait is a bounded poll of the last split for the adapter, so every wave exits
 //                        whatever the scheduling; the sums are taken in a fixed order, so results do not depend
 //                        on who arrives last.
-// The counters live in the zeroed header of the caller's workspace and are reset by the last arriver.  A kernel
-// boundary costs ~3 us of idle GPU plus ~4 us of fixed launch cost here, which a separate reduction kernel
-// would pay on top of a 20-40 us stream.
+// The counters live in the zeroed header of the caller's workspace and are reset by the last arriver.
+//
+// Where the time of a call goes (8192 x 8192, one token, rank 64, clock readings in the kernel, us from its start): table
+// built 1.7, first wave out of the loop 7.4, last 10.0 (the decode's vector and LDS work, ~5.5 each, not the stream of
+// 34.6 MB), partial stored 10.8, slab complete 12.4, partials read 14.3, output 15.5.  The whole call takes 15.7, 20.3 when the
+// way from the loop to the output was fences, partials read in groups of four with the adapter's behind them, and a
+// scalar product over the ranks on a quarter of the threads (10.8 -> 21.6).  4096 x 4096 15.4 -> 11.5; 4096 x 11008
+// 18.6 -> 13.8; 2048 x 8192 at rank 128 24.4 -> 13.1; 12 tokens 8192 x 8192 26.4 -> 19.9; q / k / v 3 x 5120 x 5120 at 4
+// tokens in one launch 21.4 -> 18.3; input gradient 8192 x 8192 26.6 -> 23.1 at one token, 34.7 -> 30.3 at 16.
 //
 // A step of a wave costs address-unit, LDS-lookup, VALU and MFMA time one after the other (a wave issues
 // in order), so workgroups are 16 waves (4 per SIMD, 128 VGPRs each) and every wave keeps 2-3 steps of
@@ -42,26 +48,29 @@ constexpr int kCtrShake = 2048;
 constexpr int kSpinLimit = 64;               // bounded wait (polls) of a slab's last split for the adapter
 
 
-// Counts this workgroup in at *c; true for the workgroup that completes `total` arrivals.  Everything the
-// workgroup stored before the call is visible to the last arriver.  Only thread 0 pays for the device-scope
-// fences (a release is an L2 write-back, an acquire an L2 invalidate on this multi-die part): the barriers
-// order the other threads' stores before its release and their later loads after its acquire.  The partials
-// themselves are stored write-through (relaxed device-scope atomic stores), which leaves the write-back
-// nothing to do: plain stores followed by full fences in every wave measured 8x slower kernels.
-__device__ __forceinline__ bool arrive_last(unsigned* c, unsigned total, volatile int* flag) {
-  __syncthreads();
+// Counts this workgroup in at *c; 0: others are still to come.  The workgroup that completes `total` arrivals gets
+// kLast, and kReady with it when the slab's handshake word (`shake`, looked at in the same round trip) already shows all
+// n_adapter adapter workgroups: their partials may be read at once.  The words go back to zero here: nobody else
+// touches them any more.
+constexpr int kLast = 1, kReady = 2;
+__device__ __forceinline__ int arrive(unsigned* c, unsigned total, unsigned* shake, unsigned n_adapter, int* flag) {
+  all_stored();
   if (threadIdx.x == 0) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     const unsigned old = atomicAdd(c, 1u);
-    const int last = old + 1 == total;
-    if (last) {
-      atomicExch(c, 0u);                                     // nobody else touches this counter any more
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    const unsigned seen = n_adapter > 0u ? agent_word(shake) : 0u;
+    int f = 0;
+    if (old + 1 == total) {
+      agent_zero(c);
+      f = kLast;
+      if (seen == n_adapter) {
+        if (n_adapter > 0u) agent_zero(shake);
+        f |= kReady;
+      }
     }
-    *flag = last;
+    *flag = f;
   }
   __syncthreads();
-  return *flag != 0;
+  return *flag;
 }
 
 // The workgroup that brought in a slab's last split meets the adapter here: the slab's handshake word counts the
@@ -69,28 +78,18 @@ __device__ __forceinline__ bool arrive_last(unsigned* c, unsigned total, volatil
 // hundred KB and are normally long done; when they are a little late (the smallest layers, cold adapter matrices)
 // the split waits for them -- a BOUNDED number of polls, so every wave exits whatever happens -- and only then
 // counts itself in.  Whoever completes the count owns the output stage: true = this workgroup.
-__device__ __forceinline__ bool meet_adapter(unsigned* shake, unsigned n_adapter, volatile int* flag, unsigned early) {
+__device__ __forceinline__ bool meet_adapter(unsigned* shake, unsigned n_adapter, int* flag) {
   __syncthreads();                                           // everybody has read the previous flag
   if (threadIdx.x == 0) {
-    int mine = early == n_adapter;                           // seen complete already (the count cannot change any more)
+    int mine = 0;
     for (int it = 0; !mine && it < kSpinLimit; ++it) {
-      if (__hip_atomic_load(shake, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_adapter) { mine = 1; break; }
-      __builtin_amdgcn_s_sleep(16);
+      if (agent_word(shake) == n_adapter) { mine = 1; break; }
+      __builtin_amdgcn_s_sleep(8);
     }
-    if (mine) {
-      // every adapter workgroup is in, so this arrival is the last: the word only has to go back to zero
-      // (nobody reads it any more), and there is no round trip to wait for
-      __hip_atomic_store(shake, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");     // the adapter's partials
-    } else {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");     // hands the splits' partials on to the adapter workgroup that will be last
-      const unsigned old = atomicAdd(shake, 1u);
-      mine = old == n_adapter;                               // it came in after the last poll after all
-      if (mine) {
-        atomicExch(shake, 0u);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-      }
-    }
+    // complete: this arrival is the last, the word only has to go back to zero and there is no round trip to wait for;
+    // else the splits' partials (all of them stored) are handed on to the adapter workgroup that will be last
+    if (!mine) mine = atomicAdd(shake, 1u) == n_adapter;     // it came in after the last poll after all
+    if (mine) agent_zero(shake);
     *flag = mine;
   }
   __syncthreads();
@@ -100,162 +99,205 @@ __device__ __forceinline__ bool meet_adapter(unsigned* shake, unsigned n_adapter
 // ---- output stage ---------------------------------------------------------------------------------
 // out[m][n] = bf16( sum_s part[s][m][n] + scale * sum_j T[m][j] * B(j, n) ),  T = sum_p lpart[p], for the 256
 // outputs n of one slab; forward: B(j, n) = L2[j][n]; backward: B(j, n) = L1[n][j].  Run by all NT threads of one
-// workgroup: a thread owns one column and four tokens per pass.  Slab 0 also stores T as a [hi | lo] bf16 pair.
+// workgroup; slab 0 also stores T as a [hi | lo] bf16 pair.
+// What it costs is round trips to memory, so everything is requested at once, in the order in which it is needed: the
+// partials of T (`ready`: the adapter's workgroups are known to be done; otherwise `shake` is met first and they are read
+// again, NULL: the caller has done so), the split partials, the first tile of the adapter's outer matrix -- and by as few
+// lanes as there are values, a wave per token: a 16-byte request per lane occupies the address unit for 16 cycles, and with
+// every wave asking for its share of the outputs in MFMA layout (4 of 64 lanes with a value at one token) the requests alone
+// took 1.7 us.  The adapter's product runs on MFMA 16x16x32, a wave 16 (NT = 512: 32) outputs: T is split exactly into
+// three bf16 terms (3 x 8 bits hold fp32's 24), so its products with the bf16 matrix are those of the fp32 value, summed in
+// fp32.  Weight side first: lane (i, g) ends with the four neighbouring outputs 4g .. 4g+3 of token i.
+constexpr int kPendOff = 120 * 1024;         // LDS beyond what the output stage uses
+constexpr int kTileRanks = 64;               // ranks staged at a time
+// forward: this thread's share of a tile of the adapter's outer matrix, rows j0 + e / 32 of L2, columns 8 (e % 32) .. +7 of the slab
+template <int NT> struct OutTile { u32x4 v[2048 / NT]; };
+template <int NT>
+__device__ __forceinline__ void tile_load(OutTile<NT>& t, const FewArgs& p, int slab, int j0) {
+  const uint16_t* src = p.r > 0 ? p.Bmat : p.X;              // without an adapter: any valid bytes
+#pragma unroll
+  for (int it = 0; it < 2048 / NT; ++it) {
+    const int e = it * NT + threadIdx.x, j = j0 + (e >> 5), n = slab * 256 + 8 * (e & 31);
+    const bool ok = j < p.r && n < p.o;
+    const u32x4 v = *(const u32x4*)(src + (ok ? (int64_t)j * p.o + n : 0));
+    t.v[it] = ok ? v : u32x4{0u, 0u, 0u, 0u};
+  }
+}
 template <bool BWD, int NT>
-__device__ void finalize_slab(const FewArgs& p, int slab, char* smem, unsigned* shake, volatile int* flag) {
-  constexpr int RC = 64;                                     // rank columns staged at a time
-  constexpr int kPitch = RC + 8;                             // backward tile row pitch keeps 16-byte alignment
-  constexpr int P = 1024 / NT;                               // passes over the tokens (4 per 256 threads and pass)
-  constexpr int IT = 2048 / NT;                              // an adapter tile is at most 2048 chunks of 16 bytes
-  float* Ts = (float*)smem;                                  // T[j][m], unscaled: 16 KB
-  uint16_t* Bs = (uint16_t*)(smem + 16384);                  // forward [RC][256], backward [256][kPitch]
+__device__ void finalize_slab(const FewArgs& p, int slab, char* smem, bool ready, unsigned* shake, int* flag) {
+  constexpr int RC = kTileRanks;
+  constexpr int W = NT / 64, PW = 16 / W;                    // waves; tokens, and groups of 16 outputs, of a wave
+  constexpr int IT = 2048 / NT;
+  constexpr int kBatch = 8;                                  // partials of one kind in flight
+  constexpr int kPitch = 256 + 8, kPlane = 16 * kPitch, kSumPitch = 256 + 4;
+  uint16_t* Tp = (uint16_t*)smem;                            // [3][16][kPitch]: the terms of T[m][j]
+  uint16_t* Bs = Tp + 3 * kPlane;                            // forward: [RC][kPitch]
+  float* sum = (float*)(Bs + RC * kPitch);                   // [16][kSumPitch]: the adapter's product
+  static_assert((3 * kPlane + RC * kPitch) * 2 + 16 * kSumPitch * 4 <= kPendOff, "LDS map");
   const int N = BWD ? p.h : p.o;
   const int n0 = slab * 256;
-  const int c = threadIdx.x & 255, tq = threadIdx.x >> 8;    // column within the slab, token quad of a pass
-  const int n = n0 + c;
-  const bool n_ok = n < N;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int i = lane & 15, g = lane >> 4;
+  const int rp = (p.r + 31) & ~31;                           // ranks in whole MFMA steps: zeros beyond r on both sides
+  const Rsrc part = agent_rsrc(p.part), lpart = agent_rsrc(p.lpart);
 
-  // Everything that does not depend on the adapter's partials is loaded first: the split partials of this
-  // thread's outputs and the first tile of the adapter's outer matrix.
-  u32x4 stage[IT];
-  int dst[IT];
-  auto stage_load = [&](int j0, int rc) {
-    const int cpr = rc >> 3;                                 // backward: 16-byte chunks per row
+  // A wave takes tokens wave, wave + W; a lane four outputs of the split partials and four ranks of T's.  Past the end of a
+  // batch requests repeat the last: with a branch around each the compiler waits for all before the first is used.
+  const int n = n0 + 4 * lane;                               // N % 64 == 0: four outputs are inside or outside together
+  const bool n_ok = n < N, t_lane = 4 * lane < p.r;
+  f32x4 acc[PW], v[PW][kBatch], lp[PW][kBatch];
+  auto part_load = [&](int u, int s0) {
+    const uint32_t at = (uint32_t)((wave + W * u) * N + (n_ok ? n : 0));
 #pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const int e = it * NT + threadIdx.x;
-      bool ok, inside;
-      int64_t off;
-      if (!BWD) {                                            // row j0 + e / 32 of L2, columns n0 + 8 (e % 32) .. +7
-        const int j = e >> 5, ch = e & 31;
-        inside = j < rc;
-        ok = inside && n0 + 8 * ch < N;
-        off = (int64_t)(j0 + j) * N + n0 + 8 * ch;
-        dst[it] = j * 256 + 8 * ch;
-      } else {                                               // row n0 + cc of L1, rank columns j0 + 8 ch .. +7
-        const int cc = e / cpr, ch = e - cc * cpr;
-        inside = cc < 256;
-        ok = inside && n0 + cc < N;
-        off = (int64_t)(n0 + cc) * p.r + j0 + 8 * ch;
-        dst[it] = cc * kPitch + 8 * ch;
-      }
-      const u32x4 v = *(const u32x4*)(p.Bmat + (ok ? off : 0));
-      stage[it] = ok ? v : u32x4{0u, 0u, 0u, 0u};
-      if (!inside) dst[it] = -1;                             // outside the tile: nothing to store
+    for (int q = 0; q < kBatch; ++q) v[u][q] = agent_load(part, at + (uint32_t)((s0 + q < p.splits ? s0 + q : p.splits - 1) * p.M * N));
+  };
+  auto t_load = [&](int u, int q0) {
+#pragma unroll
+    for (int q = 0; q < kBatch; ++q) {
+      const int qc = q0 + q < p.n_lparts ? q0 + q : (p.n_lparts > 0 ? p.n_lparts - 1 : 0);
+      lp[u][q] = agent_load(lpart, (uint32_t)((qc * p.M + wave + W * u) * p.r + (t_lane ? 4 * lane : 0)));
     }
   };
-  if (p.r > 0) stage_load(0, p.r < RC ? p.r : RC);           // without an adapter Bmat may be NULL: no load at all
-  // a first look at the adapter's count, in flight together with the loads of the split partials below
-  unsigned early = 0u;
-  if (p.r > 0 && shake && threadIdx.x == 0) early = __hip_atomic_load(shake, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-
-  float acc[P][4], lora[P][4];
+  OutTile<NT> tile;
 #pragma unroll
-  for (int q = 0; q < P; ++q) {
-    const int m0 = 4 * tq + q * (NT / 64);
+  for (int u = 0; u < PW; ++u)
+    if (wave + W * u < p.M) {                                // uniform
+      t_load(u, 0);
+      part_load(u, 0);
+    }
+  if (!BWD) tile_load(tile, p, slab, 0);
+  if (p.r > 0) {
+    const bool meet = !ready && shake;
+    if (meet && !meet_adapter(shake, (unsigned)p.n_lparts, flag)) return;   // the adapter came after the bounded wait: the slab is its
 #pragma unroll
-    for (int u = 0; u < 4; ++u) { acc[q][u] = 0.0f; lora[q][u] = 0.0f; }
-    if (m0 < p.M) {                                          // uniform per wave
-      const int64_t nn = n_ok ? n : 0;
-#pragma unroll 4
-      for (int sp = 0; sp < p.splits; ++sp) {
-        const float* ps = p.part + (int64_t)sp * p.M * N + nn;
+    for (int u = 0; u < PW; ++u) {
+      const int m = wave + W * u;
+      if (m >= p.M) continue;
+      if (meet) t_load(u, 0);                                // what was read before may not have been there yet
+      f32x4 t = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int q0 = 0;;) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int m = m0 + u;
-          const float v = ps[(int64_t)(m < p.M ? m : 0) * N];
-          acc[q][u] += m < p.M ? v : 0.0f;
-        }
+        for (int q = 0; q < kBatch; ++q)
+          if (q0 + q < p.n_lparts) t += lp[u][q];
+        q0 += kBatch;
+        if (q0 >= p.n_lparts) break;
+        t_load(u, q0);
       }
+      if (!t_lane) t = f32x4{0.f, 0.f, 0.f, 0.f};
+      uint2 term[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        term[k].x = pack_bf16x2(t[0], t[1]);
+        term[k].y = pack_bf16x2(t[2], t[3]);
+        t[0] -= bf16_lo_to_f32(term[k].x); t[1] -= bf16_hi_to_f32(term[k].x);
+        t[2] -= bf16_lo_to_f32(term[k].y); t[3] -= bf16_hi_to_f32(term[k].y);
+        if (4 * lane < rp) *(uint2*)(Tp + k * kPlane + m * kPitch + 4 * lane) = term[k];
+      }
+      if (p.hl && slab == 0 && t_lane) {
+        *(uint2*)(p.hl + (int64_t)m * 2 * p.r + 4 * lane) = term[0];
+        *(uint2*)(p.hl + (int64_t)m * 2 * p.r + p.r + 4 * lane) = term[1];
+      }
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < PW; ++u) {                             // the splits in their fixed order
+    acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (wave + W * u >= p.M) continue;
+    for (int s0 = 0;;) {
+#pragma unroll
+      for (int q = 0; q < kBatch; ++q)
+        if (s0 + q < p.splits) acc[u] += v[u][q];
+      s0 += kBatch;
+      if (s0 >= p.splits) break;
+      part_load(u, s0);
     }
   }
   if (p.r > 0) {
-    if (shake && !meet_adapter(shake, (unsigned)p.n_lparts, flag, early)) return;         // the adapter came after the bounded wait: the slab is its
-    for (int e = threadIdx.x; e < p.M * p.r; e += NT) {
-      float t = 0.0f;
-      for (int q0 = 0; q0 < p.n_lparts; q0 += 8) {           // 8 loads in flight, then a fixed-order sum
-        float v[8];
+    f32x4 lora[PW];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const bool ok = q0 + q < p.n_lparts;
-          const float x = p.lpart[(int64_t)(ok ? q0 + q : 0) * p.M * p.r + e];
-          v[q] = ok ? x : 0.0f;
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) t += v[q];
-      }
-      const int m = e / p.r, j = e - m * p.r;
-      Ts[j * 16 + m] = t;
-      if (p.hl && slab == 0) {
-        const uint16_t hi = bf16_bits(t);
-        p.hl[(int64_t)m * 2 * p.r + j] = hi;
-        p.hl[(int64_t)m * 2 * p.r + p.r + j] = bf16_bits(t - bf16_lo_to_f32(hi));
-      }
-    }
+    for (int c = 0; c < PW; ++c) lora[c] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int j0 = 0; j0 < p.r; j0 += RC) {
-      const int rc = (p.r - j0 < RC) ? p.r - j0 : RC;
-      if (j0 > 0) {
-        __syncthreads();                                     // previous tile consumed
-        stage_load(j0, rc);
+      if (!BWD) {
+        if (j0 > 0) __syncthreads();                         // previous tile consumed
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+          const int e = it * NT + threadIdx.x;
+          *(u32x4*)(Bs + (e >> 5) * kPitch + 8 * (e & 31)) = tile.v[it];
+        }
+        if (j0 + RC < p.r) tile_load(tile, p, slab, j0 + RC);
       }
+      if (!BWD || j0 == 0) __syncthreads();                  // T, and the tile, visible
 #pragma unroll
-      for (int it = 0; it < IT; ++it)
-        if (dst[it] >= 0) *(u32x4*)(Bs + dst[it]) = stage[it];
-      __syncthreads();                                       // tile and Ts visible
+      for (int t0 = 0; t0 < RC; t0 += 32) {
+        if (j0 + t0 >= rp) break;
+        bf16x8 tt[3];
 #pragma unroll
-      for (int q = 0; q < P; ++q) {
-        const int m0 = 4 * tq + q * (NT / 64);
-        if (m0 < p.M) {
-#pragma unroll 8
-          for (int j = 0; j < rc; ++j) {
-            const float b = bf16_lo_to_f32(BWD ? Bs[c * kPitch + j] : Bs[j * 256 + c]);
-            const f32x4 t = *(const f32x4*)&Ts[(j0 + j) * 16 + m0];
+        for (int k = 0; k < 3; ++k) tt[k] = *(const bf16x8*)(Tp + k * kPlane + i * kPitch + j0 + t0 + 8 * g);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) lora[q][u] = __builtin_fmaf(t[u], b, lora[q][u]);
+        for (int c = 0; c < PW; ++c) {
+          u32x4 w;                                           // ranks t0 + 8g .. +7 of output 16 (wave + W c) + i
+          if (!BWD) {
+            const uint16_t* src = Bs + (t0 + 8 * g) * kPitch + 16 * (wave + W * c) + i;
+#pragma unroll
+            for (int d = 0; d < 4; ++d)
+              w[d] = (uint32_t)src[2 * d * kPitch] | (uint32_t)src[(2 * d + 1) * kPitch] << 16;
+          } else {
+            const int nb = n0 + 16 * (wave + W * c) + i, j = j0 + t0 + 8 * g;
+            const bool ok = nb < N && j < p.r;
+            const u32x4 b = *(const u32x4*)(p.Bmat + (ok ? (int64_t)nb * p.r + j : 0));
+            w = ok ? b : u32x4{0u, 0u, 0u, 0u};
           }
+#pragma unroll
+          for (int k = 0; k < 3; ++k)
+            lora[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), tt[k], lora[c], 0, 0, 0);
         }
       }
     }
+#pragma unroll
+    for (int c = 0; c < PW; ++c) *(f32x4*)(sum + i * kSumPitch + 16 * (wave + W * c) + 4 * g) = lora[c];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PW; ++u)
+      if (wave + W * u < p.M) {
+        const f32x4 l = *(const f32x4*)(sum + (wave + W * u) * kSumPitch + 4 * lane);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) acc[u][d] += p.scale * l[d];
+      }
   }
   if (!n_ok) return;
 #pragma unroll
-  for (int q = 0; q < P; ++q) {
-    const int m0 = 4 * tq + q * (NT / 64);
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (m0 + u < p.M) p.out[(int64_t)(m0 + u) * N + n] = bf16_bits(acc[q][u] + p.scale * lora[q][u]);
-  }
+  for (int u = 0; u < PW; ++u)
+    if (wave + W * u < p.M) {
+      uint2 q;
+      q.x = pack_bf16x2(acc[u][0], acc[u][1]);
+      q.y = pack_bf16x2(acc[u][2], acc[u][3]);
+      *(uint2*)(p.out + (int64_t)(wave + W * u) * N + n) = q;
+    }
 }
 
 // Called by every adapter workgroup after its partial is stored: it counts itself in at every slab's handshake.
 // A slab whose count it completes (the slab's splits gave up waiting: rare) is finished right here.
 template <bool BWD, int NT>
-__device__ void adapter_arrive(const FewArgs& p, char* smem, volatile int* flag) {
-  int* npend = (int*)(smem + 65536);                         // beyond what finalize_slab uses
+__device__ void adapter_arrive(const FewArgs& p, char* smem, int* flag) {
+  int* npend = (int*)(smem + kPendOff);
   int* pend = npend + 1;
+  static_assert(kPendOff + 4 * (1 + kFewMaxSlabs) <= kSmemBytes, "one entry per slab");
   if (threadIdx.x == 0) *npend = 0;
-  __syncthreads();                                           // the partial of this workgroup is stored
+  all_stored();                                              // the partial of this workgroup
   for (int t = threadIdx.x; t < p.n_slabs; t += NT) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     const unsigned old = atomicAdd(p.ctr + kCtrShake + t, 1u);
     if (old == (unsigned)p.n_lparts) {                       // every other adapter workgroup and the slab's splits are in
-      atomicExch(p.ctr + kCtrShake + t, 0u);
+      agent_zero(p.ctr + kCtrShake + t);
       pend[atomicAdd(npend, 1)] = t;
     }
   }
   __syncthreads();
   const int n = *npend;
-  if (n > 0) {
-    if (threadIdx.x == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // everybody counted before us
-    __syncthreads();
-  }
   for (int q = 0; q < n; ++q) {
-    finalize_slab<BWD, NT>(p, pend[q], smem, nullptr, flag);
+    finalize_slab<BWD, NT>(p, pend[q], smem, true, nullptr, flag);
     __syncthreads();
   }
 }
-
-
 
 // ---- forward main ---------------------------------------------------------------------------------
 // W is [h][o], o contiguous.  A workgroup owns a slab of 256 output columns (128 packed bytes per row: one
@@ -338,14 +380,16 @@ __device__ __forceinline__ void fewtok_fwd_body(const FewArgs& p, const int work
     s.c1 = p.c1[(crow * (uint32_t)bpr + (uint32_t)(c_ok ? c_blk : 4 * slab)) >> 8];
   };
 
-  // the first loads are in flight while the decode table is built
+  // A wave's first step is in flight while the decode table is built, the others are asked for behind it: with all of them
+  // in front the requests of 16 waves fill the queues of the memory pipe and the table waits for the first data to arrive.
   const int stride = NW * 16;
   const int kb0 = k_begin + wave * 16;
   FwdStep buf[kDepth];
-#pragma unroll
-  for (int d = 0; d < kDepth; ++d) load_step(buf[d], kb0 + d * stride);
+  load_step(buf[0], kb0);
   init_pair_lut<NT>(lut2, unit, p.dtype, p.tab, (float*)(smem + kStripOff));
   __syncthreads();
+#pragma unroll
+  for (int d = 1; d < kDepth; ++d) load_step(buf[d], kb0 + d * stride);
 
   f32x4 acc[NA][8];
 #pragma unroll
@@ -427,32 +471,35 @@ __device__ __forceinline__ void fewtok_fwd_body(const FewArgs& p, const int work
   // D layout: column slot = lane % 16, rows 4 * (lane / 16) + v.  Row R of accumulator set a is token R % MT of
   // column half (MT == 8 ? R / 8 : a); column within the half = 8 slot + e.  The waves store [MT][256] tiles over
   // the decode table (dead now) and the tiles are summed.
-  float* out = p.part + (int64_t)split * p.M * p.o;
   auto store_tile = [&](float* my) {
 #pragma unroll
     for (int a = 0; a < NA; ++a)
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
-#pragma unroll
-        for (int vv = 0; vv < 4; ++vv) {
-          const int R = 4 * g + vv;
-          const int m = MT == 8 ? (R & 7) : R, half = MT == 8 ? (R >> 3) : a;
-          my[m * 256 + half * 128 + 8 * sl + e] = acc[a][e][vv];
+      for (int vv = 0; vv < 4; ++vv) {
+        const int R = 4 * g + vv;
+        const int m = MT == 8 ? (R & 7) : R, half = MT == 8 ? (R >> 3) : a;
+        if (m < p.M) {
+          float* dst = my + m * 256 + half * 128 + 8 * sl;
+          *(f32x4*)dst = f32x4{acc[a][0][vv], acc[a][1][vv], acc[a][2][vv], acc[a][3][vv]};
+          *(f32x4*)(dst + 4) = f32x4{acc[a][4][vv], acc[a][5][vv], acc[a][6][vv], acc[a][7][vv]};
         }
+      }
   };
   constexpr int kTile = MT * 256;
   __syncthreads();                                           // every wave is done with the decode table
   store_tile(red + wave * kTile);
   __syncthreads();
-  for (int idx = threadIdx.x; idx < p.M * 256; idx += NT) {
-    const int n = slab * 256 + (idx & 255);
-    float t = 0.0f;
+  const Rsrc part = agent_rsrc(p.part);
+  for (int idx = threadIdx.x; idx < p.M * 64; idx += NT) {
+    const int n = slab * 256 + 4 * (idx & 63);
+    f32x4 t = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int w = 0; w < NW; ++w) t += red[w * kTile + idx];
-    if (n < p.o) __hip_atomic_store(out + (int64_t)(idx >> 8) * p.o + n, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int w = 0; w < NW; ++w) t += *(const f32x4*)(red + w * kTile + 4 * idx);
+    if (n < p.o) agent_store(part, (uint32_t)((split * p.M + (idx >> 6)) * p.o + n), t);
   }
-  if (!arrive_last(p.ctr + slab, (unsigned)p.splits, &flag)) return;
-  finalize_slab<false, NT>(p, slab, smem, p.ctr + kCtrShake + slab, &flag);
+  unsigned* shake = p.ctr + kCtrShake + slab;
+  if (const int f = arrive(p.ctr + slab, (unsigned)p.splits, shake, (unsigned)p.n_lparts, &flag))
+    finalize_slab<false, NT>(p, slab, smem, (f & kReady) != 0, shake, &flag);
 }
 
 template <int MT, int NT>
@@ -604,20 +651,22 @@ __global__ __launch_bounds__(kFewThreads) void fewtok_bwd_kernel(const FewArgs p
 #pragma unroll
   for (int u = 0; u < 4; ++u)
 #pragma unroll
-    for (int vv = 0; vv < 4; ++vv) my[(4 * g + vv) * 64 + 16 * u + i] = acc[u][vv];
+    for (int vv = 0; vv < 4; ++vv)
+      if (4 * g + vv < p.M) my[(4 * g + vv) * 64 + 16 * u + i] = acc[u][vv];
   __syncthreads();
-  float* out = p.part + (int64_t)split * p.M * p.h;
-  for (int idx = threadIdx.x; idx < p.M * 256; idx += kFewThreads) {
-    const int m = idx >> 8, rr = idx & 255;
+  const Rsrc part = agent_rsrc(p.part);
+  for (int idx = threadIdx.x; idx < p.M * 64; idx += kFewThreads) {
+    const int m = idx >> 6, rr = 4 * (idx & 63);
     const int row = slab * 256 + rr;
     const float* src = red + (rr >> 6) * (16 * 64) + m * 64 + (rr & 63);
-    float t = 0.0f;
+    f32x4 t = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int c = 0; c < 4; ++c) t += src[c * 4 * 16 * 64];
-    if (row < p.h) __hip_atomic_store(out + (int64_t)m * p.h + row, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int c = 0; c < 4; ++c) t += *(const f32x4*)(src + c * 4 * 16 * 64);
+    if (row < p.h) agent_store(part, (uint32_t)((split * p.M + m) * p.h + row), t);
   }
-  if (!arrive_last(p.ctr + slab, (unsigned)p.splits, &flag)) return;
-  finalize_slab<true, NT>(p, slab, smem, p.ctr + kCtrShake + slab, &flag);
+  unsigned* shake = p.ctr + kCtrShake + slab;
+  if (const int f = arrive(p.ctr + slab, (unsigned)p.splits, shake, (unsigned)p.n_lparts, &flag))
+    finalize_slab<true, NT>(p, slab, smem, (f & kReady) != 0, shake, &flag);
 }
 
 // One 16-wave workgroup occupies a CU (its LDS map is 133 KB), so the launch is sized to fit the 256 CUs

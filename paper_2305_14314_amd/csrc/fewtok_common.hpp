@@ -113,47 +113,93 @@ __device__ __forceinline__ int work_index() {
   return x * (grid >> 3) + (x < (grid & 7) ? x : (grid & 7)) + q;
 }
 
+// ---- between the workgroups of a launch --------------------------------------------------------------
+// Partials travel past the L2 of a die (agent scope: sc1): they are stored so, every wave waits for its stores to be
+// acknowledged before the workgroup is counted in, and they are read so; no fence is needed -- an agent-scope release is
+// a write-back of the die's whole L2, an acquire an invalidation.
+typedef __amdgpu_buffer_rsrc_t Rsrc;
+constexpr int kAgent = 16;                   // cache policy of the buffer instructions: sc1
+__device__ __forceinline__ Rsrc agent_rsrc(const float* p) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, 0x7fffffff, 0x00020000);
+}
+//   four floats at element `at`: the partials of a layer are far below 2 GiB
+__device__ __forceinline__ void agent_store(Rsrc r, uint32_t at, f32x4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, at * 4u, 0, kAgent);
+}
+__device__ __forceinline__ f32x4 agent_load(Rsrc r, uint32_t at) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, at * 4u, 0, kAgent));
+}
+__device__ __forceinline__ void agent_zero(unsigned* p) { __hip_atomic_store(p, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ unsigned agent_word(const unsigned* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// every store of this workgroup has reached the point where all dies see it
+__device__ __forceinline__ void all_stored() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+}
+
 // ---- adapter partials -----------------------------------------------------------------------------
 // Both run on MFMA 16x16x32 with the tokens as one 16-wide dimension and 16 rank columns as the other,
 // kLoraDepth steps of loads in flight, and a cross-wave sum through LDS; one partial slot per workgroup.
+// A call waits for them, so they are short: tokens >= M and rank columns >= r read any valid row and only reach sums that
+// are never stored (no masks), a load is a scalar base and a fixed 32-bit offset, and none is issued past the end (a load
+// in flight holds its registers, and whoever needs them next waits for it).  With 64-bit addresses and masks per element
+// and two steps of loads past the end a partial was stored 11.4 us into a call at 8192 x 8192 (and 9.3 us into one at
+// 4096 x 4096, where the output waited for it); now 5.7 and 4.1.
 //
-// forward: lpart[wg][m][j] = sum over k in [kLoraK * wg, +kLoraK) of X[m][k] * L1[k][j]
+// forward: lpart[wg][m][j] = sum over k in [chunk * wg, +chunk) of X[m][k] * L1[k][j]
 // L1 is [h][r] (rank contiguous), so a fragment of 8 consecutive k for one rank column is gathered from
 // 8 rows: lane (i, g) loads columns 4i .. 4i+3 of rows kb + 8g + j and splits them with byte permutes.
-struct LFwdStep { uint32_t l[8][2]; u32x4 x; };
+struct LFwdStep { uint2 l[8]; u32x4 x; };
+
+// The waves' sums: acc[e][v] of lane (i, g) belongs to token 4g + v and rank column j0 + col(i, e).
+template <int NT, bool BWD>
+__device__ __forceinline__ void lora_store(const FewArgs& p, int wg, int j0, const f32x4 (&acc)[4], float* red) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int i = lane & 15, g = lane >> 4;
+  const Rsrc lpart = agent_rsrc(p.lpart);
+  __syncthreads();                                           // previous chunk's sums have been read
+  float* my = red + wave * (16 * 64);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    if (4 * g + v >= p.M) continue;
+    if (BWD) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) my[(4 * g + v) * 64 + 16 * e + i] = acc[e][v];
+    } else {
+      *(f32x4*)(my + (4 * g + v) * 64 + 4 * i) = f32x4{acc[0][v], acc[1][v], acc[2][v], acc[3][v]};
+    }
+  }
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < p.M * 16; idx += NT) {
+    const int m = idx >> 4, c = (idx & 15) * 4;
+    f32x4 t = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) t += *(const f32x4*)(red + w * 16 * 64 + m * 64 + c);
+    if (j0 + c < p.r) agent_store(lpart, (uint32_t)((wg * p.M + m) * p.r + j0 + c), t);   // r % 16 == 0
+  }
+}
 
 template <int NT>
 __device__ void lora_fwd_partial(const FewArgs& p, int wg, float* red /* [NT / 64][16][64] */) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // wave index is uniform
   const int i = lane & 15, g = lane >> 4;
   const int k_begin = wg * p.lora_chunk;
-  const int k_end = (k_begin + p.lora_chunk < p.h) ? k_begin + p.lora_chunk : p.h;
+  const int k_end = (k_begin + p.lora_chunk < p.h) ? k_begin + p.lora_chunk : p.h;              // multiples of 64
   const int stride = (NT / 64) * 32, kb0 = k_begin + wave * 32; // the waves interleave 32-row steps
-  float* out = p.lpart + (int64_t)wg * p.M * p.r;
+  const uint32_t x_off = (uint32_t)(i < p.M ? i : 0) * (uint32_t)(p.h >> 3) + (uint32_t)g;      // in 16-byte chunks
   for (int j0 = 0; j0 < p.r; j0 += 64) {
-    const bool col_ok = j0 + 4 * i < p.r;                    // r % 16 == 0: the 4 columns are in or out together
+    const uint32_t l_off = (uint32_t)(2 * g * p.r + (j0 + 4 * i < p.r ? (j0 >> 2) + i : 0));    // in 8-byte chunks; r % 16 == 0: 4 columns are in or out together
     auto load_step = [&](LFwdStep& s, int kb) {
-      // loads are unconditional (addresses clamped into the tensor), values are masked afterwards:
-      // a guarded load would become a branch and force a full wait at every join
-      const bool x_ok = i < p.M && kb + 8 * g < k_end;
-      const u32x4 xv = *(const u32x4*)(p.X + (x_ok ? (int64_t)i * p.h + kb + 8 * g : 0));
-      s.x = x_ok ? xv : u32x4{0u, 0u, 0u, 0u};
+      s.x = ((const u32x4*)(p.X + kb))[x_off];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int k = kb + 8 * g + j;
-        const bool ok = col_ok && k < k_end;
-        const uint32_t* src = (const uint32_t*)(p.L + (ok ? (int64_t)k * p.r + j0 + 4 * i : 0));
-        const uint32_t v0 = src[0], v1 = src[1];
-        s.l[j][0] = ok ? v0 : 0u;
-        s.l[j][1] = ok ? v1 : 0u;
-      }
+      for (int j = 0; j < 8; ++j) s.l[j] = ((const uint2*)(p.L + (int64_t)(kb + j) * p.r))[l_off];
     };
     f32x4 acc[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
     LFwdStep buf[kLoraDepth];
 #pragma unroll
-    for (int d = 0; d < kLoraDepth; ++d) load_step(buf[d], kb0 + d * stride);
+    for (int d = 0; d < kLoraDepth; ++d) load_step(buf[d], kb0 + d * stride < k_end ? kb0 + d * stride : k_begin);
     for (int kb = kb0; kb < k_end; kb += kLoraDepth * stride) {
 #pragma unroll
       for (int d = 0; d < kLoraDepth; ++d) {
@@ -165,33 +211,19 @@ __device__ void lora_fwd_partial(const FewArgs& p, int wg, float* red /* [NT / 6
             u32x4 w;
 #pragma unroll
             for (int jp = 0; jp < 4; ++jp)
-              w[jp] = __builtin_amdgcn_perm(buf[d].l[2 * jp + 1][e >> 1], buf[d].l[2 * jp][e >> 1], sel);
+              w[jp] = e >> 1 ? __builtin_amdgcn_perm(buf[d].l[2 * jp + 1].y, buf[d].l[2 * jp].y, sel)
+                             : __builtin_amdgcn_perm(buf[d].l[2 * jp + 1].x, buf[d].l[2 * jp].x, sel);
             acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, __builtin_bit_cast(bf16x8, w), acc[e], 0, 0, 0);
           }
-          load_step(buf[d], kb + (d + kLoraDepth) * stride);
+          if (kb + (d + kLoraDepth) * stride < k_end) load_step(buf[d], kb + (d + kLoraDepth) * stride);
         }
       }
     }
-    __syncthreads();                                         // previous chunk's sums have been read
-    float* my = red + wave * (16 * 64);
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-#pragma unroll
-      for (int vv = 0; vv < 4; ++vv) my[(4 * g + vv) * 64 + 4 * i + e] = acc[e][vv];
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < p.M * 64; idx += NT) {
-      const int m = idx >> 6, c = idx & 63;
-      if (j0 + c < p.r) {
-        float t = 0.0f;
-#pragma unroll
-        for (int w = 0; w < NT / 64; ++w) t += red[w * 16 * 64 + idx];
-        __hip_atomic_store(out + (int64_t)m * p.r + j0 + c, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    }
+    lora_store<NT, false>(p, wg, j0, acc, red);
   }
 }
 
-// backward: lpart[wg][m][j] = sum over n in [kLoraN * wg, +kLoraN) of dY[m][n] * L2[j][n]
+// backward: lpart[wg][m][j] = sum over n in [chunk * wg, +chunk) of dY[m][n] * L2[j][n]
 // Both operands are contiguous along n: fragments are plain 16-byte loads.
 struct LBwdStep { u32x4 l[4]; u32x4 y; };
 
@@ -200,29 +232,24 @@ __device__ void lora_bwd_partial(const FewArgs& p, int wg, float* red /* [NT / 6
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // wave index is uniform
   const int i = lane & 15, g = lane >> 4;
   const int n_begin = wg * p.lora_chunk;
-  const int n_end = (n_begin + p.lora_chunk < p.o) ? n_begin + p.lora_chunk : p.o;
+  const int n_end = (n_begin + p.lora_chunk < p.o) ? n_begin + p.lora_chunk : p.o;              // multiples of 64
   const int stride = (NT / 64) * 32, nb0 = n_begin + wave * 32; // the waves interleave 32-column steps
-  float* out = p.lpart + (int64_t)wg * p.M * p.r;
+  const uint16_t* y_row = p.X + (int64_t)(i < p.M ? i : 0) * p.o + 8 * g;
   for (int j0 = 0; j0 < p.r; j0 += 64) {
-    auto load_step = [&](LBwdStep& s, int nb) {
-      const bool ok = nb + 8 * g < n_end;                    // o % 64 == 0
-      const bool y_ok = i < p.M && ok;
-      const u32x4 yv = *(const u32x4*)(p.X + (y_ok ? (int64_t)i * p.o + nb + 8 * g : 0));
-      s.y = y_ok ? yv : u32x4{0u, 0u, 0u, 0u};
+    const uint16_t* l_row[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int j = j0 + 16 * e + i;
-        const bool l_ok = j < p.r && ok;
-        const u32x4 lv = *(const u32x4*)(p.L + (l_ok ? (int64_t)j * p.o + nb + 8 * g : 0));
-        s.l[e] = l_ok ? lv : u32x4{0u, 0u, 0u, 0u};
-      }
+    for (int e = 0; e < 4; ++e) l_row[e] = p.L + (int64_t)(j0 + 16 * e + i < p.r ? j0 + 16 * e + i : 0) * p.o + 8 * g;
+    auto load_step = [&](LBwdStep& s, int nb) {
+      s.y = *(const u32x4*)(y_row + nb);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s.l[e] = *(const u32x4*)(l_row[e] + nb);
     };
     f32x4 acc[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
     LBwdStep buf[kLoraDepth];
 #pragma unroll
-    for (int d = 0; d < kLoraDepth; ++d) load_step(buf[d], nb0 + d * stride);
+    for (int d = 0; d < kLoraDepth; ++d) load_step(buf[d], nb0 + d * stride < n_end ? nb0 + d * stride : n_begin);
     for (int nb = nb0; nb < n_end; nb += kLoraDepth * stride) {
 #pragma unroll
       for (int d = 0; d < kLoraDepth; ++d) {
@@ -231,26 +258,11 @@ __device__ void lora_bwd_partial(const FewArgs& p, int wg, float* red /* [NT / 6
 #pragma unroll
           for (int e = 0; e < 4; ++e)
             acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ya, __builtin_bit_cast(bf16x8, buf[d].l[e]), acc[e], 0, 0, 0);
-          load_step(buf[d], nb + (d + kLoraDepth) * stride);
+          if (nb + (d + kLoraDepth) * stride < n_end) load_step(buf[d], nb + (d + kLoraDepth) * stride);
         }
       }
     }
-    __syncthreads();
-    float* my = red + wave * (16 * 64);
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-#pragma unroll
-      for (int vv = 0; vv < 4; ++vv) my[(4 * g + vv) * 64 + 16 * e + i] = acc[e][vv];
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < p.M * 64; idx += NT) {
-      const int m = idx >> 6, c = idx & 63;
-      if (j0 + c < p.r) {
-        float t = 0.0f;
-#pragma unroll
-        for (int w = 0; w < NT / 64; ++w) t += red[w * 16 * 64 + idx];
-        __hip_atomic_store(out + (int64_t)m * p.r + j0 + c, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    }
+    lora_store<NT, true>(p, wg, j0, acc, red);
   }
 }
 

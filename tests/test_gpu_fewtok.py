@@ -19,6 +19,16 @@ def test_fewtok_small_shapes(oracle, synth, M, h, o, r):
     _run_case(oracle, ql, L, f"few M={M} h={h} o={o} r={r}", with_lora=r > 0)
 
 
+@pytest.mark.parametrize("M,h,o,r", [(1, 9216, 320, 48), (8, 9216, 320, 240), (9, 17408, 128, 80), (16, 320, 17408, 208),
+                                      (6, 64, 9216, 112)])
+def test_fewtok_output_stage_edges(oracle, synth, M, h, o, r):
+    """Output stage: more partials of T than one batch of requests (8) holds, ranks that do not fill an MFMA step (32) or a
+    staged tile (64), a slab of fewer than 256 outputs, a wave with one and with two tokens."""
+    import paper_2305_14314_amd as ql
+    L = synth.make_layer(0, 0, M=M, h=h, o=o, r=r)
+    _run_case(oracle, ql, L, f"few M={M} h={h} o={o} r={r}", with_lora=True)
+
+
 @pytest.mark.parametrize("layer", [0, 4, 6])
 def test_fewtok_65b_shapes(oracle, synth, layer):
     """Workload 4: 65B-shaped linears at 1, 4 and 16 tokens, forward and dX, all outputs checked."""
