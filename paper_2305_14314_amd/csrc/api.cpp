@@ -409,11 +409,12 @@ struct ListWs {
   bool few;
   size_t bytes, min_bytes;                   // reported / accepted, see FwdPlan
 };
-ListWs plan_list(void* ws, bool bwd, int64_t M, int32_t n, const int64_t* h, const int64_t* o, const int32_t* r) {
+ListWs plan_list(void* ws, bool bwd, int64_t M, int32_t n, const int64_t* h, const int64_t* o, const int32_t* r,
+                 bool compact = false) {
   ListWs p{};
   int hi[qlora::kListMax], oi[qlora::kListMax];
   for (int l = 0; l < n; ++l) { hi[l] = (int)h[l]; oi[l] = (int)o[l]; }
-  if (M <= qlora::kFewTokens) p.plan = qlora::fewlist_plan(bwd, (int)M, n, hi, oi, r);
+  if (M <= qlora::kFewTokens) p.plan = qlora::fewlist_plan(bwd, (int)M, n, hi, oi, r, compact);
   p.few = p.plan.ok;
   if (p.few) {
     Carver c(ws);
@@ -1103,8 +1104,9 @@ qlora_status list_impl(bool bwd, int32_t n, const uint16_t* const* In, const qlo
   if (M <= qlora::kFewTokens)
     for (int l = 0; l < n; ++l)
       if (!streams_few(&Wq[l]) || Wq[l].dtype != Wq[0].dtype) return QLORA_ERR_UNSUPPORTED;   // one decode table per launch
-  const ListWs p = plan_list(workspace, bwd, M, n, h, o, r);
+  ListWs p = plan_list(workspace, bwd, M, n, h, o, r);
   if (M <= qlora::kFewTokens && !p.few) return QLORA_ERR_UNSUPPORTED;
+  if (p.few && workspace_bytes < p.bytes) p = plan_list(workspace, bwd, M, n, h, o, r, true);
   if (workspace_bytes < p.min_bytes) return QLORA_ERR_WORKSPACE;
   if (!p.few) {
     for (int l = 0; l < n; ++l) {

@@ -3,8 +3,8 @@
 // Section 5).  Each layer brings its own token rows; the layers do not depend on each other.
 //
 // Why a list: at a few tokens a layer is 35 - 93 MB of packed weights, i.e. 4 - 12 us of HBM time, while a launch
-// of its own costs 16 - 19 us of fixed time on this machine (dispatch, decode table, pipeline fill, the chain
-// partial -> fence -> count -> last arriver's loads -> output).  Here that is paid once per list:
+// of its own costs 10 us of fixed time on this machine (dispatch, decode table, pipeline fill, the chain partial -> count ->
+// last arriver's loads -> output).  Here that is paid once per list:
 //
 //   * one workgroup per compute unit, alive for the whole list; the byte -> (value, value) decode table is
 //     built once and stays in LDS;
@@ -33,15 +33,14 @@
 // Launch shapes (threads per workgroup, ring depth of the load pipeline) of the three kernels.  The load cursor of the
 // next segment costs registers: with 1024 threads (128 registers a lane) the forward kernel for up to 8 tokens spilled
 // 61 and the backward kernel 103 registers to scratch, which showed as 40 and 97 MiB of HBM writes per launch.  With
-// 512 threads nothing spills.  Measured on the seven linears of a 65B-shaped block, 1 / 4 / 16 tokens, microseconds
-// per launch: backward 1024 threads, depth 2: 207 / 217 / 245; 512 threads, depth 3: 177 / 182 / 209 (depth 4 spills
-// again).  Forward, up to 8 tokens: 1024 threads, depth 3: 174 / 177; 512 threads, depth 4: 175 / 178, depth 6:
-// 179 / 183.  Forward, 16 tokens (512 threads): depth 3, 4, 5: 204, 203, 205.
+// 512 threads nothing spills.  Seven linears of a 65B-shaped block, us per launch: backward at 1 / 4 / 8 tokens depth 2 121.9 /
+// 129.6 / 136.9, 3 123.3 / 130.7 / 138.4, 4 140.6 / 155.4 / 153.0 (spills); forward up to 8 tokens at 1 / 4 depth 3 103.7 /
+// 108.5, 4 104.2 / 108.8, 5 104.7 / 108.9; at 16 tokens 3, 4: 128.5, 129.2.
 #ifndef QL_LIST_FWD8_NT
 #define QL_LIST_FWD8_NT 512
 #endif
 #ifndef QL_LIST_FWD8_DEPTH
-#define QL_LIST_FWD8_DEPTH 4
+#define QL_LIST_FWD8_DEPTH 3
 #endif
 #ifndef QL_LIST_FWD16_DEPTH
 #define QL_LIST_FWD16_DEPTH 3
@@ -50,36 +49,18 @@
 #define QL_LIST_BWD_NCW 2
 #endif
 #ifndef QL_LIST_BWD_DEPTH
-#define QL_LIST_BWD_DEPTH 3
+#define QL_LIST_BWD_DEPTH 2
 #endif
 // Cost model of the partition, in units of streaming one unit (forward 2 KB, backward 16 KB): what the end of a
-// segment costs, what a slab's output stage costs, what an adapter item costs.  From the timing probe of a debug build
-// (forward, one token, 65B block: a unit 0.12 us; reduction + partial store + arrival about 6 us; an output stage about
-// 12 us; an adapter item about 20 us, part of it overlapped; backward units are 8 times larger), then chosen by
-// measurement on the same block (1 / 4 / 16 tokens, us per launch; forward as tail, stage, item): 50, 100, 100: 136 /
-// 146 / 164; 40, 130, 150: 137 / 140 / 166; 60, 160, 100: 136 / 139 / 163; 70, 200, 120: 137 / 138 / 159; 60, 240, 100:
-// 138 / 140 / 161; 30, 100, 60: 141 / 144 / 166 (equal units with a credit of 64 per item, the previous rule: 148 / 154 /
-// 178).  Backward: 6, 12, 12: 170 / 178 / 214; 0, 0, 8: 167 / 174 / 208; 3, 6, 8: 161 / 169 / 204; 2, 4, 6: 161 / 167 / 199;
-// 4, 8, 8: 164 / 170 / 203; 10, 20, 16: 173 / 178 / 210.
-#ifndef QL_LIST_TAIL_FWD
-#define QL_LIST_TAIL_FWD 70
-#endif
-#ifndef QL_LIST_FIN_FWD
-#define QL_LIST_FIN_FWD 200
-#endif
-#ifndef QL_LIST_ITEM_FWD
-#define QL_LIST_ITEM_FWD 120
-#endif
-#ifndef QL_LIST_TAIL_BWD
-#define QL_LIST_TAIL_BWD 2
-#endif
-#ifndef QL_LIST_FIN_BWD
-#define QL_LIST_FIN_BWD 4
-#endif
-#ifndef QL_LIST_ITEM_BWD
-#define QL_LIST_ITEM_BWD 6
-#endif
-
+// segment costs, what a slab's output stage costs, what an adapter item costs; chosen by measurement (seven linears of a block,
+// us per launch; forward as tail, stage, item, 65B-shaped at 1 / 4 / 16 tokens and 7B-shaped at 1 / 16): 30, 70, 40: 104.7 /
+// 109.5 / 130.0, 40.7 / 48.8; 70, 200, 120 (right for the slower output stage before): 106.3 / 111.8 / 134.1, 53.3 / 64.6;
+// 50, 140, 80: 112.0 / 116.9 / 143.2, 46.7 / 57.6; 20, 50, 30: 113.8 / 110.8 / 129.8, 39.9 / 47.8; 0, 0, 20: 110.6 / 116.0 /
+// 147, 40.6 / 49.6.  Backward: 3, 4, 4: 124.0 / 131.5 / 159.2, 43.7 / 56.5; 2, 4, 6: 124.4 / 131.8 / 174.8, 44.8 / 58.2;
+// 1, 2, 4: 122.7 / 129.9 / 174.4, 45.5 / 59.1; 4, 6, 4: 130.0 / 137.2 / 175.1, 46.1 / 59.7.
+// The costs also decide how many workgroups share a slab, i.e. the room the partials take: a call that brings less than its
+// size query reports is planned with the `compact` costs (those of the slower output stage), whose sizes were once
+// reported and stay accepted.
 namespace qlora {
 
 namespace {
@@ -91,13 +72,18 @@ constexpr int kLRed = 64 * 1024;                             // 64 KB: cross-wav
 constexpr int kLUnit = 128 * 1024;                           // float[256]
 constexpr int kLStrip = kLUnit + 1024;                       // float[16 waves][64]
 constexpr int kLPend = kLStrip + 16 * 256;                   // int[1 + kFewMaxSlabs]
-constexpr int kListSmem = kLPend + 4 * (1 + 2048);
-static_assert(kLutBytes <= kLRed && kListSmem <= 160 * 1024, "LDS map");
+constexpr int kLTab = kLPend + 4 * (1 + 2048) + 12;           // int[kListGridMax]: the ranges' starts
+constexpr int kListSmem = kLTab + 4 * kListGridMax;
+static_assert(kLTab % 16 == 0, "read as int4");
+static_assert(kLutBytes <= kLRed && kLRed + kOutStageBytes <= kLUnit && kListSmem <= 160 * 1024, "LDS map");
 
 constexpr int kCtrShake = 2048;                              // [kCtrShake + slab]: handshake of a slab's last contributor with the adapter
 constexpr int kCtrStatus = 2047;                             // sticky: an arrival word was found in a state no call leaves behind
 constexpr unsigned kMask24 = 0x00ffffffu;
 constexpr unsigned kSplitBit = 1u << 23;                     // handshake word: the slab's contributors (bits 0 .. 22: adapter items)
+
+struct ListCosts { int tail, stage, item; };
+constexpr ListCosts kListCosts[2] = {{30, 70, 40}, {3, 4, 4}}, kListCostsCompact[2] = {{70, 200, 120}, {2, 4, 6}};   // forward, backward
 
 struct ListLayer {
   const uint16_t* X;                                         // M x h (forward) or dY, M x o (backward)
@@ -141,242 +127,82 @@ __device__ __forceinline__ bool word_dirty(unsigned w, unsigned nonce, unsigned 
 }
 __device__ __forceinline__ void raise_status(unsigned* hdr) { atomicOr(hdr + kCtrStatus, 1u); }
 
-// Contributor j of `total` arrives at *c; true for the one that completes the mask.  Everything the workgroup
-// stored before the call is visible to the last arriver: thread 0 alone pays for the device-scope fences, the
-// barriers extend them to the workgroup (the partials are stored write-through, so the release has nothing to
-// write back).
-__device__ __forceinline__ bool arrive_mask(const FewArgs& p, unsigned* c, int j, int total, volatile int* flag) {
-  __syncthreads();
+// Contributor j of `total` arrives at *c, once its partial is stored past the die's L2; the one that completes the mask gets
+// kLast, and kReady with it when the slab's handshake word (looked at in the same round trip) already shows all adapter
+// items.  Nobody else touches the words then: they go back to zero.
+__device__ __forceinline__ int arrive_mask(const FewArgs& p, unsigned* c, int j, int total, unsigned* shake, int* flag) {
+  all_stored();
   if (threadIdx.x == 0) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    const unsigned bit = 1u << j, full = (1u << total) - 1u;
+    const unsigned bit = 1u << j, full = (1u << total) - 1u, adapters = (1u << p.n_lparts) - 1u;
     const unsigned old = atomicOr(c, (p.nonce << 24) | bit);
+    const unsigned seen = p.r > 0 ? agent_word(shake) : 0u;
     if (word_dirty(old, p.nonce, full) || (old & bit)) raise_status(p.hdr);
-    const int last = ((old | bit) & kMask24) == full;
-    if (last) {
-      atomicExch(c, 0u);                                     // nobody else touches this word any more
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    int f = 0;
+    if (((old | bit) & kMask24) == full) {
+      agent_zero(c);
+      f = kLast;
+      if (word_dirty(seen, p.nonce, adapters)) raise_status(p.hdr);
+      if (p.r == 0 || (seen & kMask24) == adapters) {
+        if (p.r > 0) agent_zero(shake);
+        f |= kReady;
+      }
     }
-    *flag = last;
+    *flag = f;
   }
   __syncthreads();
-  return *flag != 0;
+  return *flag;
 }
 
 // The workgroup that completed a slab's partials meets the adapter at the slab's handshake word: adapter item q
 // sets bit q there (at every slab of its layer), the slab's side sets kSplitBit.  The adapter's items are the
 // first things the first workgroups do and are normally long done; otherwise the slab's side polls a BOUNDED
 // number of times and then sets its bit and leaves: whoever completes the mask owns the output stage.
-__device__ __forceinline__ bool meet_adapter_mask(const FewArgs& p, unsigned* shake, volatile int* flag, unsigned early) {
+__device__ __forceinline__ bool meet_adapter_mask(const FewArgs& p, unsigned* shake, int* flag) {
   const unsigned adapters = (1u << p.n_lparts) - 1u;
   __syncthreads();                                           // everybody has read the previous flag
   if (threadIdx.x == 0) {
-    if (word_dirty(early, p.nonce, adapters)) raise_status(p.hdr);
-    int mine = (early & kMask24) == adapters;                // seen complete already (the mask cannot change any more)
+    int mine = 0;
     for (int it = 0; !mine && it < p.spin_limit; ++it) {
-      if ((__hip_atomic_load(shake, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kMask24) == adapters) { mine = 1; break; }
+      if ((agent_word(shake) & kMask24) == adapters) { mine = 1; break; }
       __builtin_amdgcn_s_sleep(16);
     }
-    if (mine) {
-      __hip_atomic_store(shake, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // nobody reads it any more
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");     // the adapter's partials
-    } else {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");     // hands the slab's partials on to the adapter item that will be last
+    if (!mine) {                                             // hands the slab's partials on to the adapter item that will be last
       const unsigned old = atomicOr(shake, (p.nonce << 24) | kSplitBit);
       if (word_dirty(old, p.nonce, adapters)) raise_status(p.hdr);
       mine = (old & kMask24) == adapters;                    // it came in after the last poll after all
-      if (mine) {
-        atomicExch(shake, 0u);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-      }
     }
+    if (mine) agent_zero(shake);                             // nobody reads it any more
     *flag = mine;
   }
   __syncthreads();
   return *flag != 0;
 }
 
-// ---- output stage ---------------------------------------------------------------------------------
-// out[m][n] = bf16( sum_j part[j][m][c] + scale * sum_t T[m][t] * B(t, n) ),  T = sum_q lpart[q], for the 256 outputs
-// n = 256 slab + c of one slab; forward: B(t, n) = L2[t][n]; backward: B(t, n) = L1[n][t].  `part` points at the slab's
-// [contrib][M][256] tiles.  Run by all NT threads of one workgroup: a thread owns one column and four tokens per pass.
-// Slab 0 also stores T as a [hi | lo] bf16 pair.  `scratch`: 52 KB of LDS.
+// The output stage of one slab, whose partials are [contrib][M][256] tiles at `part`.  Requests in flight, split partials and
+// partials of T per token: what the registers beside the ring of loads allow (backward 4 and 8: 95 registers spilled at ring
+// depth 3, 139 instead of 124 us for a 65B-shaped block at one token).
 template <bool BWD, int NT>
-__device__ void list_finalize(const FewArgs& p, int slab, const float* part, int contrib, char* scratch, unsigned* shake,
-                              volatile int* flag) {
-  constexpr int RC = 64;                                     // rank columns staged at a time
-  constexpr int kPitch = RC + 8;                             // backward tile row pitch keeps 16-byte alignment
-  constexpr int P = 1024 / NT;                               // passes over the tokens (4 per 256 threads and pass)
-#ifndef QL_LIST_FIN_JB
-#define QL_LIST_FIN_JB 8
-#endif
-#ifndef QL_LIST_FIN_JB_BWD
-#define QL_LIST_FIN_JB_BWD 2
-#endif
-  constexpr int JB = BWD ? QL_LIST_FIN_JB_BWD : QL_LIST_FIN_JB;   // ranks per batch of LDS reads in the adapter product
-  constexpr int IT = 2048 / NT;                              // an adapter tile is at most 2048 chunks of 16 bytes
-  float* Ts = (float*)scratch;                               // T[t][m], unscaled: 16 KB
-  uint16_t* Bs = (uint16_t*)(scratch + 16384);               // forward [RC][256], backward [256][kPitch]
-  const int N = BWD ? p.h : p.o;
-  const int n0 = slab * 256;
-  const int c = threadIdx.x & 255, tq = threadIdx.x >> 8;    // column within the slab, token quad of a pass
-  const int n = n0 + c;
-  const bool n_ok = n < N;
-
-  // everything that does not depend on the adapter's partials is loaded first
-  u32x4 stage[IT];
-  int dst[IT];
-  auto stage_load = [&](int j0, int rc) {
-    const int cpr = rc >> 3;                                 // backward: 16-byte chunks per row
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const int e = it * NT + threadIdx.x;
-      bool ok, inside;
-      int64_t off;
-      if (!BWD) {                                            // row j0 + e / 32 of L2, columns n0 + 8 (e % 32) .. +7
-        const int j = e >> 5, ch = e & 31;
-        inside = j < rc;
-        ok = inside && n0 + 8 * ch < N;
-        off = (int64_t)(j0 + j) * N + n0 + 8 * ch;
-        dst[it] = j * 256 + 8 * ch;
-      } else {                                               // row n0 + cc of L1, rank columns j0 + 8 ch .. +7
-        const int cc = e / cpr, ch = e - cc * cpr;
-        inside = cc < 256;
-        ok = inside && n0 + cc < N;
-        off = (int64_t)(n0 + cc) * p.r + j0 + 8 * ch;
-        dst[it] = cc * kPitch + 8 * ch;
-      }
-      const u32x4 v = *(const u32x4*)(p.Bmat + (ok ? off : 0));
-      stage[it] = ok ? v : u32x4{0u, 0u, 0u, 0u};
-      if (!inside) dst[it] = -1;                             // outside the tile: nothing to store
-    }
-  };
-  if (p.r > 0) stage_load(0, p.r < RC ? p.r : RC);           // without an adapter Bmat may be NULL: no load at all
-  unsigned early = 0u;
-  if (p.r > 0 && shake && threadIdx.x == 0) early = __hip_atomic_load(shake, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-
-  // The loads of a stage are all issued before any is used (clamped addresses, values masked afterwards: no branch
-  // between them), and the sums run in a fixed order: a stage costs one memory round trip, not one per contributor and
-  // pass -- with the loads interleaved with their sums the output stage took 10 us at one token and 26 us at 16.
-  float acc[P][4], lora[P][4];
-#pragma unroll
-  for (int q = 0; q < P; ++q)
-#pragma unroll
-    for (int u = 0; u < 4; ++u) { acc[q][u] = 0.0f; lora[q][u] = 0.0f; }
-#ifndef QL_LIST_FIN_BATCH
-#define QL_LIST_FIN_BATCH 4
-#endif
-  constexpr int CB = QL_LIST_FIN_BATCH;                      // contributors per batch: P * CB * 4 loads in flight
-  for (int sp0 = 0; sp0 < contrib; sp0 += CB) {
-    float v[P][CB][4];
-#pragma unroll
-    for (int q = 0; q < P; ++q) {
-      const int m0 = 4 * tq + q * (NT / 64);
-#pragma unroll
-      for (int b = 0; b < CB; ++b) {
-        const bool ok = m0 < p.M && sp0 + b < contrib;
-        const float* ps = part + (int64_t)(ok ? sp0 + b : 0) * p.M * 256 + c;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[q][b][u] = ps[(ok && m0 + u < p.M ? m0 + u : 0) * 256];
-      }
-    }
-    // Nothing above uses a loaded value; the barrier keeps the scheduler from moving the masks and sums up between
-    // the loads, where each would wait for its own load.
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int q = 0; q < P; ++q) {
-      const int m0 = 4 * tq + q * (NT / 64);
-#pragma unroll
-      for (int b = 0; b < CB; ++b)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc[q][u] += (m0 + u < p.M && sp0 + b < contrib) ? v[q][b][u] : 0.0f;
-    }
-  }
-  if (p.r > 0) {
-    if (shake && !meet_adapter_mask(p, shake, flag, early)) return;   // the adapter comes later: the slab is its
-    const int n_e = p.M * p.r;
-    for (int e0 = threadIdx.x; e0 < n_e; e0 += 2 * NT) {     // two elements of T per thread and turn
-      float t[2] = {0.0f, 0.0f};
-      for (int q0 = 0; q0 < p.n_lparts; q0 += 8) {           // 16 loads in flight, then a fixed-order sum
-        float v[2][8];
-#pragma unroll
-        for (int w = 0; w < 2; ++w) {
-          const int e = e0 + w * NT;
-#pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            const bool ok = e < n_e && q0 + q < p.n_lparts;
-            v[w][q] = p.lpart[(int64_t)(ok ? q0 + q : 0) * n_e + (ok ? e : 0)];
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int w = 0; w < 2; ++w)
-#pragma unroll
-          for (int q = 0; q < 8; ++q) t[w] += (e0 + w * NT < n_e && q0 + q < p.n_lparts) ? v[w][q] : 0.0f;
-      }
-#pragma unroll
-      for (int w = 0; w < 2; ++w) {
-        const int e = e0 + w * NT;
-        if (e < n_e) {
-          const int m = e / p.r, j = e - m * p.r;
-          Ts[j * 16 + m] = t[w];
-          if (p.hl && slab == 0) {
-            const uint16_t hi = bf16_bits(t[w]);
-            p.hl[(int64_t)m * 2 * p.r + j] = hi;
-            p.hl[(int64_t)m * 2 * p.r + p.r + j] = bf16_bits(t[w] - bf16_lo_to_f32(hi));
-          }
-        }
-      }
-    }
-    for (int j0 = 0; j0 < p.r; j0 += RC) {
-      const int rc = (p.r - j0 < RC) ? p.r - j0 : RC;
-      if (j0 > 0) {
-        __syncthreads();                                     // previous tile consumed
-        stage_load(j0, rc);
-      }
-#pragma unroll
-      for (int it = 0; it < IT; ++it)
-        if (dst[it] >= 0) *(u32x4*)(Bs + dst[it]) = stage[it];
-      __syncthreads();                                       // tile and Ts visible
-      // The LDS reads of JB ranks are issued together and the products follow in rank order (the order of the sums
-      // is that of a plain loop over the ranks): read by read, each rank cost one LDS round trip.
-      for (int jb = 0; jb < rc; jb += JB) {
-        float bb[JB];
-        f32x4 tt[P][JB];
-#pragma unroll
-        for (int i = 0; i < JB; ++i) {
-          const int j = jb + i < rc ? jb + i : rc - 1;       // past the tile: a valid row, its product is skipped
-          bb[i] = bf16_lo_to_f32(BWD ? Bs[c * kPitch + j] : Bs[j * 256 + c]);
-#pragma unroll
-          for (int q = 0; q < P; ++q) tt[q][i] = *(const f32x4*)&Ts[(j0 + j) * 16 + 4 * tq + q * (NT / 64)];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 0; q < P; ++q)
-#pragma unroll
-          for (int i = 0; i < JB; ++i)
-            if (jb + i < rc) {
-#pragma unroll
-              for (int u = 0; u < 4; ++u) lora[q][u] = __builtin_fmaf(tt[q][i][u], bb[i], lora[q][u]);
-            }
-      }
-    }
-  }
-  if (!n_ok) return;
-#pragma unroll
-  for (int q = 0; q < P; ++q) {
-    const int m0 = 4 * tq + q * (NT / 64);
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (m0 + u < p.M) p.out[(int64_t)(m0 + u) * N + n] = bf16_bits(acc[q][u] + p.scale * lora[q][u]);
-  }
+__device__ __forceinline__ void list_finalize(const FewArgs& p, int slab, const float* part, int contrib, char* scratch, bool ready,
+                                              unsigned* shake, int* flag) {
+  output_stage<BWD, NT, BWD ? 2 : 4, BWD ? 4 : 8>(p, slab, part, contrib, p.M * 256, 256, scratch, !ready && shake,
+                        [&] { return meet_adapter_mask(p, shake, flag); });
 }
 
-// How many workgroups contribute to a slab, and which of them this one is (both from the partition formula).
+// How many workgroups contribute to a slab, and which of them this one is.  The range that holds a unit is list_rho_of() of
+// it, counted by the lanes of a wave over the starts in LDS: the binary search reads the kernel's arguments eight times,
+// one after the other, twice per segment.
+__device__ __forceinline__ void starts_to_lds(const ListPart& part, int* tab) {
+  if (threadIdx.x < kListGridMax) tab[threadIdx.x] = (int)threadIdx.x < part.grid ? part.start[threadIdx.x] : 0x7fffffff;
+}
+__device__ __forceinline__ int rho_of_wave(const int* tab, int u) {
+  static_assert(kListGridMax == 256, "four starts per lane");
+  const int4 s = *(const int4*)(tab + 4 * (threadIdx.x & 63));
+  return __popcll(__ballot(s.x <= u)) + __popcll(__ballot(s.y <= u)) + __popcll(__ballot(s.z <= u)) + __popcll(__ballot(s.w <= u)) - 1;
+}
 struct Contrib { int j, total; };
-__device__ __forceinline__ Contrib slab_contrib(const ListPart& part, const ListLayer& y, int slab, int rho) {
+__device__ __forceinline__ Contrib slab_contrib(const int* tab, const ListLayer& y, int slab, int rho) {
   const int U0 = y.unit0 + slab * y.ups;
-  const int first = list_rho_of(part, U0), last = list_rho_of(part, U0 + y.ups - 1);
+  const int first = rho_of_wave(tab, U0), last = rho_of_wave(tab, U0 + y.ups - 1);
   return Contrib{rho - first, last - first + 1};
 }
 __device__ __forceinline__ const float* slab_part(const FewArgs& p, const ListLayer& y, int slab) {
@@ -387,31 +213,26 @@ __device__ __forceinline__ const float* slab_part(const FewArgs& p, const ListLa
 // handshake word.  A slab whose mask it completes (the slab's side gave up waiting: rare) is finished right here.
 template <bool BWD, int NT>
 __device__ void list_adapter_arrive(const ListArgs& A, const ListLayer& y, const FewArgs& p, int item, char* scratch,
-                                    int* npend, volatile int* flag) {
+                                    int* npend, int* flag) {
   int* pend = npend + 1;
   const unsigned adapters = (1u << p.n_lparts) - 1u, bit = 1u << item;
   if (threadIdx.x == 0) *npend = 0;
-  __syncthreads();                                           // the partial of this workgroup is stored
+  all_stored();                                              // the partial of this workgroup
   for (int t = threadIdx.x; t < p.n_slabs; t += NT) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     const unsigned old = atomicOr(p.ctr + kCtrShake + t, (p.nonce << 24) | bit);
     if (word_dirty(old, p.nonce, adapters | kSplitBit) || (old & bit)) raise_status(p.hdr);
     if (((old | bit) & kMask24) == (adapters | kSplitBit)) {  // every other adapter item and the slab's side are in
-      atomicExch(p.ctr + kCtrShake + t, 0u);
+      agent_zero(p.ctr + kCtrShake + t);
       pend[atomicAdd(npend, 1)] = t;
     }
   }
   __syncthreads();
   const int n = *npend;
-  if (n > 0) {
-    if (threadIdx.x == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // everybody arrived before us
-    __syncthreads();
-  }
   for (int q = 0; q < n; ++q) {
     const int slab = pend[q];
     const int U0 = y.unit0 + slab * y.ups;
     const int contrib = list_rho_of(A.part, U0 + y.ups - 1) - list_rho_of(A.part, U0) + 1;
-    list_finalize<BWD, NT>(p, slab, slab_part(p, y, slab), contrib, scratch, nullptr, flag);
+    list_finalize<BWD, NT>(p, slab, slab_part(p, y, slab), contrib, scratch, true, nullptr, flag);
     __syncthreads();
   }
 }
@@ -559,6 +380,7 @@ __global__ __launch_bounds__(NT) void fewlist_fwd_kernel(const ListArgs A) {
 #pragma unroll
   for (int d = 0; d < kDepth; ++d) next_load(buf[d]);        // in flight while the decode table is built
   skip_empty();
+  starts_to_lds(A.part, (int*)(smem + kLTab));
   init_pair_lut<NT>(lut2, unit, A.dtype, A.tab, (float*)(smem + kLStrip));
   __syncthreads();
 
@@ -622,11 +444,20 @@ __global__ __launch_bounds__(NT) void fewlist_fwd_kernel(const ListArgs A) {
   };
 
   // D layout: column slot = lane % 16, rows 4 * (lane / 16) + v.  Row R of accumulator set a is token R % MT of
-  // column half (MT == 8 ? R / 8 : a); column within the half = 8 slot + e.
-  auto tile_index = [&](int a, int e, int vv) {
-    const int R = 4 * g + vv;
-    const int m = MT == 8 ? (R & 7) : R, half = MT == 8 ? (R >> 3) : a;
-    return m * 256 + half * 128 + 8 * sl + e;
+  // column half (MT == 8 ? R / 8 : a); column within the half = 8 slot + e: eight neighbours of a lane.
+  auto with_tile = [&](float* my, auto&& f) {
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int vv = 0; vv < 4; ++vv) {
+        const int R = 4 * g + vv;
+        const int m = MT == 8 ? (R & 7) : R, half = MT == 8 ? (R >> 3) : a;
+        if (m < A.M) {
+#pragma unroll
+          for (int e = 0; e < 8; e += 4)
+            f((f32x4*)(my + m * 256 + half * 128 + 8 * sl + e), f32x4{acc[a][e][vv], acc[a][e + 1][vv], acc[a][e + 2][vv], acc[a][e + 3][vv]});
+        }
+      }
   };
 
   for (Seg cs = seg_at(A, u0, u1);; cs = seg_at(A, cs.u_end, u1)) {
@@ -646,42 +477,24 @@ __global__ __launch_bounds__(NT) void fewlist_fwd_kernel(const ListArgs A) {
       skip_empty();
     }
     // ---- the segment's partial: sum over the waves (half of them at a time: the decode table stays) ----
-    if (wave >= HW) {
-      float* my = red + (wave - HW) * kTile;
-#pragma unroll
-      for (int a = 0; a < NA; ++a)
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-#pragma unroll
-          for (int vv = 0; vv < 4; ++vv) my[tile_index(a, e, vv)] = acc[a][e][vv];
-    }
+    if (wave >= HW) with_tile(red + (wave - HW) * kTile, [](f32x4* d, f32x4 t) { *d = t; });
     __syncthreads();
-    if (wave < HW) {
-      float* my = red + wave * kTile;
-#pragma unroll
-      for (int a = 0; a < NA; ++a)
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-#pragma unroll
-          for (int vv = 0; vv < 4; ++vv) {
-            const int ix = tile_index(a, e, vv);
-            my[ix] += acc[a][e][vv];
-          }
-    }
+    if (wave < HW) with_tile(red + wave * kTile, [](f32x4* d, f32x4 t) { *d += t; });
     __syncthreads();
     const ListLayer& y = A.L[cs.l];
     const FewArgs p = layer_args(A, y);
-    const Contrib cb = slab_contrib(A.part, y, cs.slab, rho);
+    const Contrib cb = slab_contrib((const int*)(smem + kLTab), y, cs.slab, rho);
     const float* pslab = slab_part(p, y, cs.slab);
-    float* out = (float*)pslab + (int64_t)cb.j * p.M * 256;
-    for (int idx = threadIdx.x; idx < p.M * 256; idx += NT) {
-      float t = 0.0f;
+    const Rsrc out = agent_rsrc(pslab);
+    for (int idx = threadIdx.x; idx < p.M * 64; idx += NT) {
+      f32x4 t = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int w = 0; w < HW; ++w) t += red[w * kTile + idx];
-      __hip_atomic_store(out + idx, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int w = 0; w < HW; ++w) t += *(const f32x4*)(red + w * kTile + 4 * idx);
+      agent_store(out, (uint32_t)(cb.j * p.M * 256 + 4 * idx), t);
     }
-    if (arrive_mask(p, p.ctr + cs.slab, cb.j, cb.total, &flag))
-      list_finalize<false, NT>(p, cs.slab, pslab, cb.total, smem + kLRed, p.ctr + kCtrShake + cs.slab, &flag);
+    unsigned* shake = p.ctr + kCtrShake + cs.slab;
+    if (const int f = arrive_mask(p, p.ctr + cs.slab, cb.j, cb.total, shake, &flag))
+      list_finalize<false, NT>(p, cs.slab, pslab, cb.total, smem + kLRed, (f & kReady) != 0, shake, &flag);
     if (cs.u_end >= u1) break;
     zero_acc();
     __syncthreads();                                         // the sum area is free again
@@ -784,6 +597,7 @@ __global__ __launch_bounds__(256 * NCW) void fewlist_bwd_kernel(const ListArgs A
 #pragma unroll
   for (int d = 0; d < kDepth; ++d) next_load(buf[d]);        // in flight while the table is built
   skip_empty();
+  starts_to_lds(A.part, (int*)(smem + kLTab));
   init_pair_lut<NT>(lut2, unit, A.dtype, A.tab, (float*)(smem + kLStrip));
   __syncthreads();
 
@@ -853,19 +667,20 @@ __global__ __launch_bounds__(256 * NCW) void fewlist_bwd_kernel(const ListArgs A
     __syncthreads();
     const ListLayer& y = A.L[cs.l];
     const FewArgs p = layer_args(A, y);
-    const Contrib cb = slab_contrib(A.part, y, cs.slab, rho);
+    const Contrib cb = slab_contrib((const int*)(smem + kLTab), y, cs.slab, rho);
     const float* pslab = slab_part(p, y, cs.slab);
-    float* out = (float*)pslab + (int64_t)cb.j * p.M * 256;
-    for (int idx = threadIdx.x; idx < p.M * 256; idx += NT) {
-      const int m = idx >> 8, rr = idx & 255;
+    const Rsrc out = agent_rsrc(pslab);
+    for (int idx = threadIdx.x; idx < p.M * 64; idx += NT) {
+      const int m = idx >> 6, rr = 4 * (idx & 63);
       const float* src = red + (rr >> 6) * (16 * 64) + m * 64 + (rr & 63);
-      float t = 0.0f;
+      f32x4 t = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int q = 0; q < NCW; ++q) t += src[q * 4 * 16 * 64];
-      __hip_atomic_store(out + idx, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int q = 0; q < NCW; ++q) t += *(const f32x4*)(src + q * 4 * 16 * 64);
+      agent_store(out, (uint32_t)(cb.j * p.M * 256 + 4 * idx), t);
     }
-    if (arrive_mask(p, p.ctr + cs.slab, cb.j, cb.total, &flag))
-      list_finalize<true, NT>(p, cs.slab, pslab, cb.total, smem + kLRed, p.ctr + kCtrShake + cs.slab, &flag);
+    unsigned* shake = p.ctr + kCtrShake + cs.slab;
+    if (const int f = arrive_mask(p, p.ctr + cs.slab, cb.j, cb.total, shake, &flag))
+      list_finalize<true, NT>(p, cs.slab, pslab, cb.total, smem + kLRed, (f & kReady) != 0, shake, &flag);
     if (cs.u_end >= u1) break;
 #pragma unroll
     for (int u = 0; u < 4; ++u) acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -878,7 +693,7 @@ __global__ __launch_bounds__(256 * NCW) void fewlist_bwd_kernel(const ListArgs A
 // ---- host side ------------------------------------------------------------------------------------
 // The partition is a pure function of the shapes: the size queries, the launcher and the kernel evaluate the same
 // formulas (list_start / list_rho_of in launch.hpp).
-ListPlan fewlist_plan(bool bwd, int M, int n, const int* h, const int* o, const int* r) {
+ListPlan fewlist_plan(bool bwd, int M, int n, const int* h, const int* o, const int* r, bool compact) {
   ListPlan P{};
   if (n < 1 || n > kListMax || M < 1 || M > kFewTokens) return P;
   int64_t units = 0;
@@ -910,8 +725,8 @@ ListPlan fewlist_plan(bool bwd, int M, int n, const int* h, const int* o, const 
   // range, and runs the slab's output stage), plus kItem for every adapter item it computes first.  Boundaries: the
   // smallest bound T for which a greedy walk (every workgroup takes what fits under T) covers the line with `grid`
   // workgroups.
-  const int kTail = bwd ? QL_LIST_TAIL_BWD : QL_LIST_TAIL_FWD, kFin = bwd ? QL_LIST_FIN_BWD : QL_LIST_FIN_FWD;
-  const int kItem = bwd ? QL_LIST_ITEM_BWD : QL_LIST_ITEM_FWD;
+  const ListCosts costs = (compact ? kListCostsCompact : kListCosts)[bwd];
+  const int kTail = costs.tail, kFin = costs.stage, kItem = costs.item;
   std::vector<int> slab_end;                                 // ascending unit index where each slab ends
   for (int l = 0; l < n; ++l)
     for (int sidx = 0; sidx < P.n_slabs[l]; ++sidx) slab_end.push_back(P.unit0[l] + (sidx + 1) * P.ups[l]);

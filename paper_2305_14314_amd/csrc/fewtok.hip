@@ -52,7 +52,6 @@ constexpr int kSpinLimit = 64;               // bounded wait (polls) of a slab's
 // kLast, and kReady with it when the slab's handshake word (`shake`, looked at in the same round trip) already shows all
 // n_adapter adapter workgroups: their partials may be read at once.  The words go back to zero here: nobody else
 // touches them any more.
-constexpr int kLast = 1, kReady = 2;
 __device__ __forceinline__ int arrive(unsigned* c, unsigned total, unsigned* shake, unsigned n_adapter, int* flag) {
   all_stored();
   if (threadIdx.x == 0) {
@@ -96,183 +95,14 @@ __device__ __forceinline__ bool meet_adapter(unsigned* shake, unsigned n_adapter
   return *flag != 0;
 }
 
-// ---- output stage ---------------------------------------------------------------------------------
-// out[m][n] = bf16( sum_s part[s][m][n] + scale * sum_j T[m][j] * B(j, n) ),  T = sum_p lpart[p], for the 256
-// outputs n of one slab; forward: B(j, n) = L2[j][n]; backward: B(j, n) = L1[n][j].  Run by all NT threads of one
-// workgroup; slab 0 also stores T as a [hi | lo] bf16 pair.
-// What it costs is round trips to memory, so everything is requested at once, in the order in which it is needed: the
-// partials of T (`ready`: the adapter's workgroups are known to be done; otherwise `shake` is met first and they are read
-// again, NULL: the caller has done so), the split partials, the first tile of the adapter's outer matrix -- and by as few
-// lanes as there are values, a wave per token: a 16-byte request per lane occupies the address unit for 16 cycles, and with
-// every wave asking for its share of the outputs in MFMA layout (4 of 64 lanes with a value at one token) the requests alone
-// took 1.7 us.  The adapter's product runs on MFMA 16x16x32, a wave 16 (NT = 512: 32) outputs: T is split exactly into
-// three bf16 terms (3 x 8 bits hold fp32's 24), so its products with the bf16 matrix are those of the fp32 value, summed in
-// fp32.  Weight side first: lane (i, g) ends with the four neighbouring outputs 4g .. 4g+3 of token i.
+// The output stage of one slab; its splits lie [split][token][N].
 constexpr int kPendOff = 120 * 1024;         // LDS beyond what the output stage uses
-constexpr int kTileRanks = 64;               // ranks staged at a time
-// forward: this thread's share of a tile of the adapter's outer matrix, rows j0 + e / 32 of L2, columns 8 (e % 32) .. +7 of the slab
-template <int NT> struct OutTile { u32x4 v[2048 / NT]; };
-template <int NT>
-__device__ __forceinline__ void tile_load(OutTile<NT>& t, const FewArgs& p, int slab, int j0) {
-  const uint16_t* src = p.r > 0 ? p.Bmat : p.X;              // without an adapter: any valid bytes
-#pragma unroll
-  for (int it = 0; it < 2048 / NT; ++it) {
-    const int e = it * NT + threadIdx.x, j = j0 + (e >> 5), n = slab * 256 + 8 * (e & 31);
-    const bool ok = j < p.r && n < p.o;
-    const u32x4 v = *(const u32x4*)(src + (ok ? (int64_t)j * p.o + n : 0));
-    t.v[it] = ok ? v : u32x4{0u, 0u, 0u, 0u};
-  }
-}
 template <bool BWD, int NT>
-__device__ void finalize_slab(const FewArgs& p, int slab, char* smem, bool ready, unsigned* shake, int* flag) {
-  constexpr int RC = kTileRanks;
-  constexpr int W = NT / 64, PW = 16 / W;                    // waves; tokens, and groups of 16 outputs, of a wave
-  constexpr int IT = 2048 / NT;
-  constexpr int kBatch = 8;                                  // partials of one kind in flight
-  constexpr int kPitch = 256 + 8, kPlane = 16 * kPitch, kSumPitch = 256 + 4;
-  uint16_t* Tp = (uint16_t*)smem;                            // [3][16][kPitch]: the terms of T[m][j]
-  uint16_t* Bs = Tp + 3 * kPlane;                            // forward: [RC][kPitch]
-  float* sum = (float*)(Bs + RC * kPitch);                   // [16][kSumPitch]: the adapter's product
-  static_assert((3 * kPlane + RC * kPitch) * 2 + 16 * kSumPitch * 4 <= kPendOff, "LDS map");
+__device__ __forceinline__ void finalize_slab(const FewArgs& p, int slab, char* smem, bool ready, unsigned* shake, int* flag) {
+  static_assert(kOutStageBytes <= kPendOff, "LDS map");
   const int N = BWD ? p.h : p.o;
-  const int n0 = slab * 256;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int i = lane & 15, g = lane >> 4;
-  const int rp = (p.r + 31) & ~31;                           // ranks in whole MFMA steps: zeros beyond r on both sides
-  const Rsrc part = agent_rsrc(p.part), lpart = agent_rsrc(p.lpart);
-
-  // A wave takes tokens wave, wave + W; a lane four outputs of the split partials and four ranks of T's.  Past the end of a
-  // batch requests repeat the last: with a branch around each the compiler waits for all before the first is used.
-  const int n = n0 + 4 * lane;                               // N % 64 == 0: four outputs are inside or outside together
-  const bool n_ok = n < N, t_lane = 4 * lane < p.r;
-  f32x4 acc[PW], v[PW][kBatch], lp[PW][kBatch];
-  auto part_load = [&](int u, int s0) {
-    const uint32_t at = (uint32_t)((wave + W * u) * N + (n_ok ? n : 0));
-#pragma unroll
-    for (int q = 0; q < kBatch; ++q) v[u][q] = agent_load(part, at + (uint32_t)((s0 + q < p.splits ? s0 + q : p.splits - 1) * p.M * N));
-  };
-  auto t_load = [&](int u, int q0) {
-#pragma unroll
-    for (int q = 0; q < kBatch; ++q) {
-      const int qc = q0 + q < p.n_lparts ? q0 + q : (p.n_lparts > 0 ? p.n_lparts - 1 : 0);
-      lp[u][q] = agent_load(lpart, (uint32_t)((qc * p.M + wave + W * u) * p.r + (t_lane ? 4 * lane : 0)));
-    }
-  };
-  OutTile<NT> tile;
-#pragma unroll
-  for (int u = 0; u < PW; ++u)
-    if (wave + W * u < p.M) {                                // uniform
-      t_load(u, 0);
-      part_load(u, 0);
-    }
-  if (!BWD) tile_load(tile, p, slab, 0);
-  if (p.r > 0) {
-    const bool meet = !ready && shake;
-    if (meet && !meet_adapter(shake, (unsigned)p.n_lparts, flag)) return;   // the adapter came after the bounded wait: the slab is its
-#pragma unroll
-    for (int u = 0; u < PW; ++u) {
-      const int m = wave + W * u;
-      if (m >= p.M) continue;
-      if (meet) t_load(u, 0);                                // what was read before may not have been there yet
-      f32x4 t = f32x4{0.f, 0.f, 0.f, 0.f};
-      for (int q0 = 0;;) {
-#pragma unroll
-        for (int q = 0; q < kBatch; ++q)
-          if (q0 + q < p.n_lparts) t += lp[u][q];
-        q0 += kBatch;
-        if (q0 >= p.n_lparts) break;
-        t_load(u, q0);
-      }
-      if (!t_lane) t = f32x4{0.f, 0.f, 0.f, 0.f};
-      uint2 term[3];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        term[k].x = pack_bf16x2(t[0], t[1]);
-        term[k].y = pack_bf16x2(t[2], t[3]);
-        t[0] -= bf16_lo_to_f32(term[k].x); t[1] -= bf16_hi_to_f32(term[k].x);
-        t[2] -= bf16_lo_to_f32(term[k].y); t[3] -= bf16_hi_to_f32(term[k].y);
-        if (4 * lane < rp) *(uint2*)(Tp + k * kPlane + m * kPitch + 4 * lane) = term[k];
-      }
-      if (p.hl && slab == 0 && t_lane) {
-        *(uint2*)(p.hl + (int64_t)m * 2 * p.r + 4 * lane) = term[0];
-        *(uint2*)(p.hl + (int64_t)m * 2 * p.r + p.r + 4 * lane) = term[1];
-      }
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < PW; ++u) {                             // the splits in their fixed order
-    acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (wave + W * u >= p.M) continue;
-    for (int s0 = 0;;) {
-#pragma unroll
-      for (int q = 0; q < kBatch; ++q)
-        if (s0 + q < p.splits) acc[u] += v[u][q];
-      s0 += kBatch;
-      if (s0 >= p.splits) break;
-      part_load(u, s0);
-    }
-  }
-  if (p.r > 0) {
-    f32x4 lora[PW];
-#pragma unroll
-    for (int c = 0; c < PW; ++c) lora[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int j0 = 0; j0 < p.r; j0 += RC) {
-      if (!BWD) {
-        if (j0 > 0) __syncthreads();                         // previous tile consumed
-#pragma unroll
-        for (int it = 0; it < IT; ++it) {
-          const int e = it * NT + threadIdx.x;
-          *(u32x4*)(Bs + (e >> 5) * kPitch + 8 * (e & 31)) = tile.v[it];
-        }
-        if (j0 + RC < p.r) tile_load(tile, p, slab, j0 + RC);
-      }
-      if (!BWD || j0 == 0) __syncthreads();                  // T, and the tile, visible
-#pragma unroll
-      for (int t0 = 0; t0 < RC; t0 += 32) {
-        if (j0 + t0 >= rp) break;
-        bf16x8 tt[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) tt[k] = *(const bf16x8*)(Tp + k * kPlane + i * kPitch + j0 + t0 + 8 * g);
-#pragma unroll
-        for (int c = 0; c < PW; ++c) {
-          u32x4 w;                                           // ranks t0 + 8g .. +7 of output 16 (wave + W c) + i
-          if (!BWD) {
-            const uint16_t* src = Bs + (t0 + 8 * g) * kPitch + 16 * (wave + W * c) + i;
-#pragma unroll
-            for (int d = 0; d < 4; ++d)
-              w[d] = (uint32_t)src[2 * d * kPitch] | (uint32_t)src[(2 * d + 1) * kPitch] << 16;
-          } else {
-            const int nb = n0 + 16 * (wave + W * c) + i, j = j0 + t0 + 8 * g;
-            const bool ok = nb < N && j < p.r;
-            const u32x4 b = *(const u32x4*)(p.Bmat + (ok ? (int64_t)nb * p.r + j : 0));
-            w = ok ? b : u32x4{0u, 0u, 0u, 0u};
-          }
-#pragma unroll
-          for (int k = 0; k < 3; ++k)
-            lora[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), tt[k], lora[c], 0, 0, 0);
-        }
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < PW; ++c) *(f32x4*)(sum + i * kSumPitch + 16 * (wave + W * c) + 4 * g) = lora[c];
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < PW; ++u)
-      if (wave + W * u < p.M) {
-        const f32x4 l = *(const f32x4*)(sum + (wave + W * u) * kSumPitch + 4 * lane);
-#pragma unroll
-        for (int d = 0; d < 4; ++d) acc[u][d] += p.scale * l[d];
-      }
-  }
-  if (!n_ok) return;
-#pragma unroll
-  for (int u = 0; u < PW; ++u)
-    if (wave + W * u < p.M) {
-      uint2 q;
-      q.x = pack_bf16x2(acc[u][0], acc[u][1]);
-      q.y = pack_bf16x2(acc[u][2], acc[u][3]);
-      *(uint2*)(p.out + (int64_t)(wave + W * u) * N + n) = q;
-    }
+  output_stage<BWD, NT, 8, 8>(p, slab, p.part + slab * 256, p.splits, p.M * N, N, smem, !ready && shake,
+                        [&] { return meet_adapter(shake, (unsigned)p.n_lparts, flag); });
 }
 
 // Called by every adapter workgroup after its partial is stored: it counts itself in at every slab's handshake.

@@ -222,7 +222,8 @@ struct ListPlan {
   int n_lparts[kListMax], lora_chunk[kListMax], max_contrib[kListMax];
   size_t part_floats[kListMax], lpart_floats[kListMax];      // sizes of the two partial buffers of every layer
 };
-ListPlan fewlist_plan(bool bwd, int M, int n, const int* h, const int* o, const int* r);
+//   compact: the partition of an earlier cost model, for workspaces of the size it asked for
+ListPlan fewlist_plan(bool bwd, int M, int n, const int* h, const int* o, const int* r, bool compact = false);
 struct ListLayerDesc {
   NF4Dev w;
   const uint16_t* X;                         // forward: X (M x h); backward: dY (M x o)

@@ -260,3 +260,23 @@ def test_list_many_tokens_is_the_single_layer_path(synth):
         torch.cuda.synchronize()
         assert torch.equal(Ys[l].view(torch.int16), Y1.view(torch.int16))
         assert torch.equal(dXs[l].view(torch.int16), dX1.view(torch.int16))
+
+
+@pytest.mark.parametrize("backward,M,shapes,saved", [
+    (False, 7, [(320, 640, 16), (2048, 4096, 16), (8192, 512, 16)], 1053952),
+    (True, 7, [(320, 640, 16), (2048, 4096, 16), (8192, 512, 16)], 1725440)])
+def test_list_accepts_the_smaller_saved_size(oracle, synth, backward, M, shapes, saved):
+    """A workspace of the size that an earlier cost model of the partition asked for is planned by that model: same results
+    within the tolerance, nothing written behind it; a smaller one is refused."""
+    import paper_2305_14314_amd as ql
+    layers = _make_list(oracle, synth, M, shapes, 9900)
+    assert ql.qlora_linear_list_sizes(M, *[list(c) for c in zip(*shapes)], backward) > saved
+    buf = ql.workspace_alloc(saved + 4096)
+    buf[saved:].fill_(0x5a)
+    outs = _run_list(ql, layers, backward, buf[:saved])
+    torch.cuda.synchronize()
+    _check_list(oracle, layers, outs, backward, f"list saved size M={M}")
+    assert int(buf[:HDR].max()) == 0 and ql.qlora_workspace_check(buf[:saved])
+    assert bool((buf[saved:] == 0x5a).all()), "written behind the workspace"
+    with pytest.raises(ql.QloraError):
+        _run_list(ql, layers, backward, buf[:saved - 256])
