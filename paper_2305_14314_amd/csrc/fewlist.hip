@@ -381,7 +381,7 @@ __global__ __launch_bounds__(NT) void fewlist_fwd_kernel(const ListArgs A) {
   for (int d = 0; d < kDepth; ++d) next_load(buf[d]);        // in flight while the decode table is built
   skip_empty();
   starts_to_lds(A.part, (int*)(smem + kLTab));
-  init_pair_lut<NT>(lut2, unit, A.dtype, A.tab, (float*)(smem + kLStrip));
+  init_pair_lut<NT>(lut2, unit, A.dtype, A.tab);
   __syncthreads();
 
   f32x4 acc[NA][8];
@@ -598,7 +598,7 @@ __global__ __launch_bounds__(256 * NCW) void fewlist_bwd_kernel(const ListArgs A
   for (int d = 0; d < kDepth; ++d) next_load(buf[d]);        // in flight while the table is built
   skip_empty();
   starts_to_lds(A.part, (int*)(smem + kLTab));
-  init_pair_lut<NT>(lut2, unit, A.dtype, A.tab, (float*)(smem + kLStrip));
+  init_pair_lut<NT>(lut2, unit, A.dtype, A.tab);
   __syncthreads();
 
   f32x4 acc[4];

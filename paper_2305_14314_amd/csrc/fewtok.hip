@@ -216,7 +216,7 @@ __device__ __forceinline__ void fewtok_fwd_body(const FewArgs& p, const int work
   const int kb0 = k_begin + wave * 16;
   FwdStep buf[kDepth];
   load_step(buf[0], kb0);
-  init_pair_lut<NT>(lut2, unit, p.dtype, p.tab, (float*)(smem + kStripOff));
+  init_pair_lut<NT>(lut2, unit, p.dtype, p.tab);
   __syncthreads();
 #pragma unroll
   for (int d = 1; d < kDepth; ++d) load_step(buf[d], kb0 + d * stride);
@@ -432,7 +432,7 @@ __global__ __launch_bounds__(kFewThreads) void fewtok_bwd_kernel(const FewArgs p
   BwdStep buf[kBwdDepth];
 #pragma unroll
   for (int d = 0; d < kBwdDepth; ++d) load_step(buf[d], kb0 + d * stride);   // in flight while the table is built
-  init_pair_lut<NT>(lut2, unit, p.dtype, p.tab, (float*)(smem + kStripOff));
+  init_pair_lut<NT>(lut2, unit, p.dtype, p.tab);
   __syncthreads();
 
   f32x4 acc[4];

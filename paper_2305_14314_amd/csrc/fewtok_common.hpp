@@ -27,36 +27,32 @@ constexpr int kStripOff = kUnitOff + 1024;                   // float[kWaves][2]
 constexpr int kSmemBytes = kStripOff + kWaves * 256;
 static_assert(kLutBytes <= kRedBytes && kSmemBytes <= 160 * 1024, "LDS map");
 
-// The 16 values (NF4's from constants, another data type's from the arguments: Section 4) are staged in LDS by 16
-// threads first (`stage`, 16 floats) -- a lane-indexed read of a constant array or of a by-value argument is a memory
-// load per element.  Entry e = 32 b + copy of the table belongs to byte b = e / 32; thread t writes entries t, t + NT,
-// ...: their low nibble (t / 32) % 16 is the same for all of them and their high nibble advances by NT / 512 per entry,
-// so a thread reads the stage once for the low value and at compile-time positions for the high ones.
+// Entry e = 32 b + copy of the table belongs to byte b = e / 32; thread t writes the pairs of copies t, t + NT, ... (16 bytes
+// each): byte t / 16 + NT / 16 k, whose low nibble is the same for all of them and whose high nibble is the same for 256
+// threads and advances by NT / 256.  So the low value is picked once per thread from the 16 values in scalar registers (NF4's,
+// or another data type's from the arguments: Section 4) and the high ones are scalar: no memory round trip (a lane-indexed read
+// of a constant array is one), no barrier of its own.  The caller's barrier makes the table visible.
 template <int NT>
-__device__ __forceinline__ void init_pair_lut(f32x2* lut2 /* [256][32] */, float* unit /* [256] */, int dtype,
-                                              const Table4& tab, float* stage) {
-  static_assert(NT == 512 || NT == 1024, "entries per thread and their nibbles are worked out for these two");
-  if (threadIdx.x < 16) {
-    constexpr float t[16] = {QLORA_NF4_VALUES};
-    float v = t[threadIdx.x];
-    if (dtype != 0) {
+__device__ __forceinline__ void init_pair_lut(f32x2* lut2 /* [256][32] */, float* unit /* [256] */, int dtype, const Table4& tab) {
+  static_assert(NT % 256 == 0 && 4096 % NT == 0, "whole high nibbles per pass");
+  constexpr float t[16] = {QLORA_NF4_VALUES};
+  constexpr int H = NT / 256;
+  const int hi_first = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), lo_nibble = (threadIdx.x >> 4) & 15;
+  float v[16], lo = 0.0f;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) v = (int)threadIdx.x == i ? tab.v[i] : v;
-    }
-    stage[threadIdx.x] = v;
+  for (int i = 0; i < 16; ++i) {
+    v[i] = t[i];
+    if (dtype != 0) v[i] = tab.v[i];                         // uniform
+    lo = lo_nibble == i ? v[i] : lo;
   }
-  __syncthreads();
-  const int b0 = threadIdx.x / kLutCopies;                   // byte of this thread's first entry: < NT / 32
-  const float lo = stage[b0 & 15];
 #pragma unroll
-  for (int k = 0; k < 256 * kLutCopies / NT; ++k) {
-    const int hi_nibble = (NT == 512) ? k : 2 * k + (b0 >> 4);
-    f32x2 v;
-    v[0] = lo;
-    v[1] = stage[hi_nibble];
-    lut2[threadIdx.x + NT * k] = v;
+  for (int k = 0; k < 16 / H; ++k) {
+    float hi = v[H * k];
+#pragma unroll
+    for (int q = 1; q < H; ++q) hi = hi_first == q ? v[H * k + q] : hi;
+    *(f32x4*)(lut2 + 2 * (threadIdx.x + NT * k)) = f32x4{lo, hi, lo, hi};
   }
-  if (threadIdx.x < 256) unit[threadIdx.x] = e4m3_unit(threadIdx.x);
+  for (int i = threadIdx.x; i < 256; i += NT) unit[i] = e4m3_unit(i);
 }
 // (value[lo nibble], value[hi nibble]) of byte B (0..3) of packed dword `pk`, from this lane's copy of the table.
 // Entry e of copy c sits at byte offset 256 e + 8 c: the offset is assembled by one byte permute

@@ -4,8 +4,8 @@
 //
 // Why its own path: with 256 x 256 tiles a product of a few hundred tokens has 4 .. 100 tiles for 256 compute units, and
 // the pass that dequantises the weight moves five times the bytes of the packed weight (2.5 against 0.5 per weight).
-// Whole forward call, dequantise + GEMM against this: 4096 x 11008 at 40 tokens 108 -> 22 us, 5120 x 13824 at 333 tokens
-// 158 -> 90 us; forward + backward 1024 x 1024 at 256 tokens 96 -> 51 us, 4096 x 4096 at 512 tokens 220 -> 107 us.
+// Whole forward call, dequantise + GEMM against this: 4096 x 11008 at 40 tokens 108 -> 20 us, 5120 x 13824 at 333 tokens
+// 158 -> 87 us; forward + backward 1024 x 1024 at 256 tokens 96 -> 48 us, 4096 x 4096 at 512 tokens 220 -> 99 us.
 //
 // Two or three launches on the caller's stream:
 //   pre       (backward, and forward above 48 tokens) the token operand in MFMA-fragment order, so that the main kernel's operand loads
@@ -35,6 +35,7 @@ namespace {
 
 using few::kLutCopies;
 using few::kLutBytes;
+using few::init_pair_lut;
 using few::pair_lookup_b;
 using few::work_index;
 
@@ -67,30 +68,6 @@ struct MidArgs {
   int n_lparts, chunk, n_items;              // adapter items this launch computes (32 tokens x chunk), first in the work list
 };
 
-// The decode table of the few-token kernels for any multiple of 256 threads.
-template <int NT>
-__device__ __forceinline__ void init_lut(f32x2* lut2, float* unit, int dtype, const Table4& tab, float* stage) {
-  if (threadIdx.x < 16) {
-    constexpr float t[16] = {QLORA_NF4_VALUES};
-    float v = t[threadIdx.x];
-    if (dtype != 0) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) v = (int)threadIdx.x == i ? tab.v[i] : v;
-    }
-    stage[threadIdx.x] = v;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 256 * kLutCopies / NT; ++k) {
-    const int b = (threadIdx.x + NT * k) / kLutCopies;
-    f32x2 v;
-    v[0] = stage[b & 15];
-    v[1] = stage[b >> 4];
-    lut2[threadIdx.x + NT * k] = v;
-  }
-  for (int c = threadIdx.x; c < 256; c += NT) unit[c] = e4m3_unit(c);
-}
-
 __device__ __forceinline__ u32x4 apply_mask(u32x4 v, uint32_t b) {
 #pragma unroll
   for (int d = 0; d < 4; ++d)
@@ -102,8 +79,8 @@ __device__ __forceinline__ u32x4 apply_mask(u32x4 v, uint32_t b) {
 // One workgroup per 32 tokens and chunk; its KW waves take the chunk's 32-wide steps in turn, two or four steps of
 // loads in flight each (the whole share of a wave for most sizes), and are summed through LDS.
 constexpr int kAdTok = 32;
-template <int KW, bool BWD>
-__device__ void adapter_partial(const MidArgs& p, int item, float* red /* [KW][32][64] */) {
+template <int KW, bool BWD, bool MASKED>
+__device__ __forceinline__ void adapter_partial(const MidArgs& p, int item, float* red /* [KW][32][64] */) {
   constexpr int NT = KW * 64, D = KW == 8 ? 2 : 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int i = lane & 15, g = lane >> 4;
@@ -111,36 +88,37 @@ __device__ void adapter_partial(const MidArgs& p, int item, float* red /* [KW][3
   const int m0 = (item % n_tt) * kAdTok, q = item / n_tt;
   const int k_begin = q * p.chunk, k_end = k_begin + p.chunk < p.K ? k_begin + p.chunk : p.K;   // multiples of 64
   float* out = p.lpart + (int64_t)q * p.M * p.r;
-  struct St { u32x4 x[2]; uint32_t keep[2]; uint32_t l[16]; };   // raw loads only
-  const bool masked = !BWD && p.mask != nullptr;
-  const uint8_t* mask = masked ? p.mask : (const uint8_t*)p.X;   // without a mask: any valid bytes, not used
-  const int ms = masked ? 1 : 0;
-  int64_t xrow[2];
+  // Raw loads only, each a scalar base and a fixed 32-bit offset (64-bit addresses per lane and element cost more than the
+  // loads).  Tokens >= M and rank columns >= r read any valid row and only reach sums that are never stored.
+  struct St { u32x4 x[2]; uint32_t keep[2]; uint32_t l[16]; };
+  uint32_t x_off[2];                                         // in 16-byte chunks of X, which are bytes of the mask
 #pragma unroll
   for (int f = 0; f < 2; ++f) {
     const int m = m0 + 16 * f + i;
-    xrow[f] = (int64_t)(m < p.M ? m : p.M - 1) * p.K + 8 * g;
+    x_off[f] = (uint32_t)(m < p.M ? m : p.M - 1) * (uint32_t)(p.K >> 3) + (uint32_t)g;
   }
   for (int j0 = 0; j0 < p.r; j0 += 64) {
-    const bool col_ok = j0 + 4 * i < p.r;                    // forward: this lane's 4 rank columns
+    const uint32_t l_off = (uint32_t)(2 * g * p.r + (j0 + 4 * i < p.r ? (j0 >> 2) + i : 0));    // forward: in 8-byte chunks
+    const uint16_t* l_row[4];                                // backward: 4 rank columns
+#pragma unroll
+    for (int e = 0; e < 4; ++e) l_row[e] = p.L + (int64_t)(BWD && j0 + 4 * i + e < p.r ? j0 + 4 * i + e : 0) * p.K + 8 * g;
     auto load = [&](St& s, int kb) {
       const int kc = kb < k_end ? kb : k_begin;              // past the end: any valid step, never consumed
 #pragma unroll
       for (int f = 0; f < 2; ++f) {
-        s.x[f] = *(const u32x4*)(p.X + xrow[f] + kc);
-        s.keep[f] = mask[((xrow[f] + kc) >> 3) * ms];
+        s.x[f] = ((const u32x4*)(p.X + kc))[x_off[f]];
+        if (MASKED) s.keep[f] = (p.mask + (kc >> 3))[x_off[f]];
       }
       if (!BWD) {                                            // L1 is [k][j]: 8 rows x 4 columns
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-          const uint2 v = *(const uint2*)(p.L + (int64_t)(kc + 8 * g + j) * p.r + (col_ok ? j0 + 4 * i : 0));
+          const uint2 v = ((const uint2*)(p.L + (int64_t)(kc + j) * p.r))[l_off];
           s.l[2 * j] = v.x; s.l[2 * j + 1] = v.y;
         }
       } else {                                               // L2 is [j][n]: 8 columns of 4 rows
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const int j = j0 + 4 * i + e;
-          const u32x4 v = *(const u32x4*)(p.L + (int64_t)(j < p.r ? j : 0) * p.K + kc + 8 * g);
+          const u32x4 v = *(const u32x4*)(l_row[e] + kc);
 #pragma unroll
           for (int d = 0; d < 4; ++d) s.l[4 * e + d] = v[d];
         }
@@ -154,7 +132,7 @@ __device__ void adapter_partial(const MidArgs& p, int item, float* red /* [KW][3
     auto compute = [&](const St& s) {
       u32x4 x[2];
 #pragma unroll
-      for (int f = 0; f < 2; ++f) x[f] = masked ? apply_mask(s.x[f], s.keep[f]) : s.x[f];
+      for (int f = 0; f < 2; ++f) x[f] = MASKED ? apply_mask(s.x[f], s.keep[f]) : s.x[f];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         u32x4 w;
@@ -206,32 +184,30 @@ __device__ void adapter_partial(const MidArgs& p, int item, float* red /* [KW][3
 // Fragment of 16 tokens x 32 contraction elements = 1 KB: lane (i, g) at byte 16 (16 g + i) holds token i's eight elements
 // of k group g.  Forward: [32-wide step][token tile].  Backward: [64-wide step][phase t][token tile], group g of phase t
 // being columns 16g + 8t .. +7.  Tokens beyond M are zeros.
-constexpr int kPreUnroll = 4;
+// A workgroup of 8 waves packs 16 tokens x 512 contraction elements, a wave 64 of them: two fragments, no index arithmetic
+// beyond one division per workgroup (with a 64-bit division per
+// 16 bytes and adapter partials by 64-bit addresses the launch took 9.8 us for 512 x 4096 at rank 64, 8.0 now; 333 x 5120 8.3 -> 6.1).
+constexpr int kPreK = 512;
 template <bool BWD>
-__global__ __launch_bounds__(512) void mid_pre_kernel(const MidArgs p, uint16_t* __restrict__ Xp, int tiles, int items, int64_t chunks) {
+__global__ __launch_bounds__(512) void mid_pre_kernel(const MidArgs p, uint16_t* __restrict__ Xp, int tiles, int items) {
   __shared__ __attribute__((aligned(16))) char smem[8 * kAdTok * 64 * 4];
   if ((int)blockIdx.x < items) {
-    adapter_partial<8, BWD>(p, blockIdx.x, (float*)smem);
+    if (!BWD && p.mask) adapter_partial<8, BWD, !BWD>(p, blockIdx.x, (float*)smem);
+    else adapter_partial<8, BWD, false>(p, blockIdx.x, (float*)smem);
     return;
   }
-  const int kc_row = p.K >> 3;                               // 8-element chunks per token
-  const int64_t stride = (int64_t)(gridDim.x - items) * 512;
-  for (int64_t q0 = (int64_t)(blockIdx.x - items) * 512 + threadIdx.x; q0 < chunks; q0 += kPreUnroll * stride) {
-    u32x4 v[kPreUnroll];
-    int m[kPreUnroll], c[kPreUnroll];
+  const int n_kb = (p.K + kPreK - 1) / kPreK, at = (int)blockIdx.x - items;
+  const int tile = at / n_kb, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int k0 = (at - tile * n_kb) * kPreK + wave * 64, i = lane & 15, g = lane >> 4;
+  if (k0 >= p.K) return;
+  const int m = 16 * tile + i;
+  const uint16_t* src = p.X + (int64_t)(m < p.M ? m : p.M - 1) * p.K + k0 + (BWD ? 16 : 8) * g;
+  u32x4 v[2];
 #pragma unroll
-    for (int z = 0; z < kPreUnroll; ++z) {                   // independent loads (clamped), then the stores
-      const int64_t q = q0 + z * stride < chunks ? q0 + z * stride : q0;
-      m[z] = (int)(q / kc_row); c[z] = (int)(q - (int64_t)m[z] * kc_row);
-      v[z] = *(const u32x4*)(p.X + (int64_t)(m[z] < p.M ? m[z] : p.M - 1) * p.K + 8 * c[z]);
-    }
+  for (int t = 0; t < 2; ++t) v[t] = *(const u32x4*)(src + (BWD ? 8 : 32) * t);
 #pragma unroll
-    for (int z = 0; z < kPreUnroll; ++z) {
-      const int g = BWD ? (c[z] >> 1) & 3 : c[z] & 3;
-      const int64_t frag = BWD ? ((int64_t)(c[z] >> 3) * 2 + (c[z] & 1)) * tiles + (m[z] >> 4) : (int64_t)(c[z] >> 2) * tiles + (m[z] >> 4);
-      *(u32x4*)(Xp + (frag * 64 + 16 * g + (m[z] & 15)) * 8) = m[z] < p.M ? v[z] : u32x4{0u, 0u, 0u, 0u};
-    }
-  }
+  for (int t = 0; t < 2; ++t)
+    *(u32x4*)(Xp + (((int64_t)(k0 >> 5) + t) * tiles + tile) * 512 + 8 * lane) = m < p.M ? v[t] : u32x4{0u, 0u, 0u, 0u};
 }
 
 // ---- main ---------------------------------------------------------------------------------------------------------------
@@ -264,7 +240,8 @@ __global__ __launch_bounds__(KW * 64) void mid_main_kernel(const MidArgs p) {
   const int work = work_index();
   if constexpr (!PACK) {
     if (work < p.n_items) {
-      adapter_partial<KW, BWD>(p, work, (float*)smem);
+      if (p.mask) adapter_partial<KW, false, true>(p, work, (float*)smem);
+      else adapter_partial<KW, false, false>(p, work, (float*)smem);
       return;
     }
   }
@@ -284,12 +261,14 @@ __global__ __launch_bounds__(KW * 64) void mid_main_kernel(const MidArgs p) {
   const __amdgpu_buffer_rsrc_t c1_rsrc = mid_rsrc(p.c1, 4u * (p.dq ? (n_blocks + 255u) / 256u : n_blocks));
   const int c1_shift = p.dq ? 8 : 0, code_w = p.dq ? 1 : 0;
 
+  // The table comes before the first loads: behind them it would wait until the queues of the memory pipe have room for all
+  // of their requests, i.e. for the first data (ready 5 - 7 us into the kernel that way, 1.2 so).
+  init_pair_lut<NT>(lut2, unit, p.dtype, p.tab);
   const int u_end = p.line.start(rho + 1);
   for (int u = p.line.start(rho); u < u_end;) {
   // ---- one segment: a run of units of one tile ---------------------------------------------------------------------
   const int tile = u / p.line.ups, u0 = u - tile * p.line.ups;
   const int u1 = u0 + (u_end - u) < p.line.ups ? u0 + (u_end - u) : p.line.ups;
-  const bool first_segment = u == p.line.start(rho);
   u += u1 - u0;
   const int tg = tile % p.n_tg, slab = tile / p.n_tg;
   const int s_begin = u0 * KW, s_end = u1 * KW < p.steps ? u1 * KW : p.steps;
@@ -401,7 +380,6 @@ __global__ __launch_bounds__(KW * 64) void mid_main_kernel(const MidArgs p) {
     load_x(xb[d], st0 + (d / kPhases) * KW, d % kPhases);
     __builtin_amdgcn_sched_barrier(0);
   }
-  if (first_segment) init_lut<NT>(lut2, unit, p.dtype, p.tab, (float*)(smem + kMStrip));
   __syncthreads();
 
   float c2[R][8];                                            // constants of the step being decoded / of the next
@@ -590,6 +568,11 @@ __global__ __launch_bounds__(KW * 64) void mid_main_kernel(const MidArgs p) {
 
 // ---- finalize -------------------------------------------------------------------------------------------------------------
 // Workgroup: 16 TF tokens x 256 outputs, a wave 64 of them; lane (i, g) owns outputs 4i .. 4i+3 of tokens 4g + v.
+// Up to kLeanBlocks workgroups everything a workgroup needs is requested at once (see below); with more, occupancy hides the
+// round trips and the registers for that cost more than they save (LEAN).  Whole calls, us, all at once / lean: 4096 x 11008
+// forward at 40 tokens (129 workgroups) 20.5 / 21.5, 4096 x 4096 at 128 (128) 23.6 / 24.2; dX 4096 x 4096 at 512 (512)
+// 41.8 / 40.9, forward 5120 x 13824 at 333 (1134) 87.4 / 84.6.
+constexpr unsigned kLeanBlocks = 256;
 struct MidFinArgs {
   const float* part; int M, N;
   MidLine line; int MF, n_tg;                // which contributors a tile has
@@ -600,7 +583,7 @@ struct MidFinArgs {
   const uint8_t* mask;                       // backward under LoRA dropout: keep-bits of the output elements, or NULL
 };
 
-template <int TF, bool BWD>
+template <int TF, bool BWD, bool LEAN>
 __global__ __launch_bounds__(256) void mid_finalize_kernel(const MidFinArgs p) {
   constexpr int kPitch = 256 + 8;
   __shared__ __attribute__((aligned(16))) uint16_t Th[16 * TF * kPitch], Tl[16 * TF * kPitch];
@@ -611,11 +594,44 @@ __global__ __launch_bounds__(256) void mid_finalize_kernel(const MidFinArgs p) {
   const bool n_ok = nb < p.N;                                // N % 64 == 0: a wave's outputs are inside or outside together
   const int n = (n_ok ? nb : 0) + 4 * i;
 
-  f32x4 sum[TF][4];
+  // What a workgroup waits for is memory round trips: the partials of T, the first fragments of the outer matrix and the
+  // first two partials of the tile are requested together, without branches between them (clamped addresses).
+  const int r4 = p.r >> 2, rp = (p.r + 31) & ~31;
+  constexpr int LB = LEAN ? 4 : 8;                           // partials of T in flight
+  f32x4 lp[LB];
+  auto t_load = [&](int idx, int q0) {
+    const int ml = idx / (rp >> 2), c = idx - ml * (rp >> 2), m = m0 + ml < p.M ? m0 + ml : p.M - 1;
+    const float* src = p.lpart + (int64_t)m * p.r + (c < r4 ? 4 * c : 0);
 #pragma unroll
-  for (int f = 0; f < TF; ++f)
+    for (int q = 0; q < LB; ++q) lp[q] = *(const f32x4*)(src + (int64_t)(q0 + q < p.n_lparts ? q0 + q : p.n_lparts - 1) * p.M * p.r);
+  };
+  constexpr int RB = LEAN ? 1 : 2;                           // steps of 32 ranks in flight
+  struct OutFrag { u32x4 w[4]; };                            // forward: 8 rows x 4 columns as loaded; backward: [e], ranks of output 4i + e
+  OutFrag bf[RB];
+  auto b_load = [&](OutFrag& o, int t0) {
+    if (!BWD) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) sum[f][v] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < 8; ++j) {
+        const int t = t0 + 8 * g + j;
+        const uint2 v = *(const uint2*)(p.B + (int64_t)(t < p.r ? t : 0) * p.N + n);
+        o.w[j >> 1][2 * (j & 1)] = t < p.r ? v.x : 0u;
+        o.w[j >> 1][2 * (j & 1) + 1] = t < p.r ? v.y : 0u;
+      }
+    } else {
+      const bool ok = t0 + 8 * g < p.r;                      // r % 16 == 0: a lane's 8 ranks are inside or outside together
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const u32x4 v = *(const u32x4*)(p.B + (int64_t)(n + e) * p.r + (ok ? t0 + 8 * g : 0));
+        o.w[e] = ok ? v : u32x4{0u, 0u, 0u, 0u};
+      }
+    }
+  };
+  const int n_idx = 16 * TF * (rp >> 2);
+  if (p.r > 0) {                                             // uniform
+    t_load(threadIdx.x < n_idx ? threadIdx.x : 0, 0);
+#pragma unroll
+    for (int k = 0; k < RB; ++k) b_load(bf[k], 32 * k);
+  }
   // a wave's outputs lie in one slab, the workgroup's tokens in one token group (per 16-token tile)
   int contrib[TF];
 #pragma unroll
@@ -624,38 +640,47 @@ __global__ __launch_bounds__(256) void mid_finalize_kernel(const MidFinArgs p) {
     contrib[f] = p.line.contributors(tile);
   }
   const int most = TF == 2 ? max(contrib[0], contrib[TF - 1]) : contrib[0];
-  for (int s = 0; s < most; ++s) {
-    const float* ps = p.part + (int64_t)s * p.M * p.N + n;
-    f32x4 x[TF][4];
+  constexpr int CB = LEAN ? 1 : 2;                           // partials of the tile in flight
+  f32x4 sum[TF][4], x[CB][TF][4];
 #pragma unroll
-    for (int f = 0; f < TF; ++f)
+  for (int f = 0; f < TF; ++f)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int m = m0 + 16 * f + 4 * g + v;
-        x[f][v] = *(const f32x4*)(ps + (int64_t)(m < p.M ? m : p.M - 1) * p.N);
-      }
+    for (int v = 0; v < 4; ++v) sum[f][v] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto x_load = [&](int s0) {
 #pragma unroll
-    for (int f = 0; f < TF; ++f)
+    for (int k = 0; k < CB; ++k) {
+      const float* ps = p.part + (int64_t)(s0 + k < most ? s0 + k : most - 1) * p.M * p.N + n;
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
-        if (s < contrib[f]) sum[f][v] += x[f][v];
-  }
+      for (int f = 0; f < TF; ++f)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int m = m0 + 16 * f + 4 * g + v;
+          x[k][f][v] = *(const f32x4*)(ps + (int64_t)(m < p.M ? m : p.M - 1) * p.N);
+        }
+    }
+  };
+  x_load(0);
+  __builtin_amdgcn_sched_barrier(0);
   f32x4 lora[TF][4];                                         // [tile][e]: tokens 4g .. 4g+3 of output 4i + e
 #pragma unroll
   for (int f = 0; f < TF; ++f)
 #pragma unroll
     for (int e = 0; e < 4; ++e) lora[f][e] = f32x4{0.f, 0.f, 0.f, 0.f};
   if (p.r > 0) {
-    const int r4 = p.r >> 2, rp = (p.r + 31) & ~31;
-    for (int idx = threadIdx.x; idx < 16 * TF * (rp >> 2); idx += 256) {
+    for (int idx = threadIdx.x; idx < n_idx; idx += 256) {
+      if (idx >= 256) t_load(idx, 0);
       const int ml = idx / (rp >> 2), c = idx - ml * (rp >> 2), m = m0 + ml;
-      f32x4 t = f32x4{0.f, 0.f, 0.f, 0.f};
       const bool ok = m < p.M && c < r4;
-      if (ok) {
-        const float* src = p.lpart + (int64_t)m * p.r + 4 * c;
-#pragma unroll 4
-        for (int q = 0; q < p.n_lparts; ++q) t += *(const f32x4*)(src + (int64_t)q * p.M * p.r);
+      f32x4 t = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int q0 = 0;;) {
+#pragma unroll
+        for (int q = 0; q < LB; ++q)
+          if (q0 + q < p.n_lparts) t += lp[q];
+        q0 += LB;
+        if (q0 >= p.n_lparts) break;
+        t_load(idx, q0);
       }
+      if (!ok) t = f32x4{0.f, 0.f, 0.f, 0.f};
       uint2 hi, lo;
       hi.x = pack_bf16x2(t[0], t[1]); hi.y = pack_bf16x2(t[2], t[3]);
       lo.x = pack_bf16x2(t[0] - bf16_lo_to_f32(hi.x), t[1] - bf16_hi_to_f32(hi.x));
@@ -668,43 +693,44 @@ __global__ __launch_bounds__(256) void mid_finalize_kernel(const MidFinArgs p) {
       }
     }
     __syncthreads();
-    for (int t0 = 0; t0 < p.r; t0 += 32) {
-      u32x4 w[4];                                            // [e]: ranks t0 + 8g .. +7 of output 4i + e
-      if (!BWD) {
-        uint2 row[8];
+    for (int tb = 0; tb < p.r; tb += 32 * RB) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int t = t0 + 8 * g + j;
-          const uint2 v = *(const uint2*)(p.B + (int64_t)(t < p.r ? t : 0) * p.N + n);
-          row[j] = t < p.r ? v : uint2{0u, 0u};
-        }
+      for (int k = 0; k < RB; ++k) {
+        const int t0 = tb + 32 * k;
+        if (t0 >= p.r) break;
+        u32x4 w[4];                                          // [e]: ranks t0 + 8g .. +7 of output 4i + e
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
+          if (BWD) { w[e] = bf[k].w[e]; continue; }
           const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
 #pragma unroll
-          for (int jp = 0; jp < 4; ++jp)
-            w[e][jp] = (e >> 1) ? __builtin_amdgcn_perm(row[2 * jp + 1].y, row[2 * jp].y, sel)
-                                : __builtin_amdgcn_perm(row[2 * jp + 1].x, row[2 * jp].x, sel);
+          for (int jp = 0; jp < 4; ++jp) w[e][jp] = __builtin_amdgcn_perm(bf[k].w[jp][2 + (e >> 1)], bf[k].w[jp][e >> 1], sel);
         }
-      } else {
-        const bool ok = t0 + 8 * g < p.r;                    // r % 16 == 0: a lane's 8 ranks are inside or outside together
+        if (t0 + 32 * RB < p.r) b_load(bf[k], t0 + 32 * RB);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const u32x4 v = *(const u32x4*)(p.B + (int64_t)(n + e) * p.r + (ok ? t0 + 8 * g : 0));
-          w[e] = ok ? v : u32x4{0u, 0u, 0u, 0u};
-        }
-      }
+        for (int f = 0; f < TF; ++f) {
+          const bf16x8 th = *(const bf16x8*)(Th + (16 * f + i) * kPitch + t0 + 8 * g);
+          const bf16x8 tl = *(const bf16x8*)(Tl + (16 * f + i) * kPitch + t0 + 8 * g);
 #pragma unroll
-      for (int f = 0; f < TF; ++f) {
-        const bf16x8 th = *(const bf16x8*)(Th + (16 * f + i) * kPitch + t0 + 8 * g);
-        const bf16x8 tl = *(const bf16x8*)(Tl + (16 * f + i) * kPitch + t0 + 8 * g);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          lora[f][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(th, __builtin_bit_cast(bf16x8, w[e]), lora[f][e], 0, 0, 0);
-          lora[f][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tl, __builtin_bit_cast(bf16x8, w[e]), lora[f][e], 0, 0, 0);
+          for (int e = 0; e < 4; ++e) {
+            lora[f][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(th, __builtin_bit_cast(bf16x8, w[e]), lora[f][e], 0, 0, 0);
+            lora[f][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tl, __builtin_bit_cast(bf16x8, w[e]), lora[f][e], 0, 0, 0);
+          }
         }
       }
     }
+  }
+  for (int s0 = 0;;) {                                       // the partials in their fixed order
+#pragma unroll
+    for (int k = 0; k < CB; ++k)
+#pragma unroll
+      for (int f = 0; f < TF; ++f)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (s0 + k < contrib[f]) sum[f][v] += x[k][f][v];
+    s0 += CB;
+    if (s0 >= most) break;
+    x_load(s0);
   }
   if (!n_ok) return;
 #pragma unroll
@@ -807,11 +833,12 @@ MidPlan mid_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room) 
 // 22016, 64 .. 65536 outputs, ranks 0 .. 256; each estimate within 20 % on nine calls of ten).  Decoding inside the product
 // loses where the contraction is short (its partials are then as large as the product: dX with K = 64, N = 16384 at 384 tokens
 // 43 us against 12) or the rank large (K = 1024, N = 8192, rank 256 at 512 tokens 66 against 32); it wins where the weight is
-// what counts (K = 22016, N = 8192, rank 64 at 256 tokens 117 against 421).  Near the line either will do: a call goes to the
+// what counts (K = 22016, N = 8192, rank 64 at 256 tokens 117 against 421).  The constant of the first estimate was 6.5 when the
+// three kernels took 2 - 4 us longer to start.  Near the line either will do: a call goes to the
 // other path where that is faster by a fifth, so that seven of the fitted calls lose more than 3 % by it, the worst 20 %.
 bool mid_pays(const MidPlan& p, bool bwd, int64_t M, int64_t h, int64_t o, int r, bool fix) {
   const double K = (double)(bwd ? o : h), N = (double)(bwd ? h : o), MN = 1e-6 * (double)M * N;
-  const double mid = 6.5 + 0.88 * p.us + (p.pack ? 4.3 + 0.053 * r : 0.027 * r) + 0.35 * p.max_contrib * MN + 0.0034 * r * MN +
+  const double mid = 4.0 + 0.88 * p.us + (p.pack ? 4.3 + 0.053 * r : 0.027 * r) + 0.35 * p.max_contrib * MN + 0.0034 * r * MN +
                      3.3e-8 * (double)M * K * r;
   const double gemm = 9.7 + 0.7 * gemm_rounds_us(M, (int64_t)N, ((int64_t)K + (r + 63) / 64 * 64) / 64) + 0.62e-6 * K * N +
                       0.6 * MN + (r > 0 ? 3.6 + 1e-6 * r * (0.2 * N + 3.8 * K) : 0.0) + (fix ? 5.5 + 2.2 * MN : 0.0);
@@ -836,10 +863,9 @@ hipError_t launch_mid(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const
     a.x_step = tiles * 1024 * (bwd ? 2 : 1);
     a.x_bytes = (uint32_t)(p.pack_elems * 2);
     a.x_sub = tiles * 1024;
-    const int64_t chunks = (int64_t)tiles * 16 * (a.K / 8);
-    const unsigned grid = (unsigned)(items + std::min<int64_t>((chunks + 512 * kPreUnroll - 1) / (512 * kPreUnroll), 512));
-    if (bwd) hipLaunchKernelGGL(mid_pre_kernel<true>, dim3(grid), dim3(512), 0, st, a, xpack, tiles, items, chunks);
-    else hipLaunchKernelGGL(mid_pre_kernel<false>, dim3(grid), dim3(512), 0, st, a, xpack, tiles, items, chunks);
+    const unsigned grid = (unsigned)(items + tiles * ((a.K + kPreK - 1) / kPreK));
+    if (bwd) hipLaunchKernelGGL(mid_pre_kernel<true>, dim3(grid), dim3(512), 0, st, a, xpack, tiles, items);
+    else hipLaunchKernelGGL(mid_pre_kernel<false>, dim3(grid), dim3(512), 0, st, a, xpack, tiles, items);
   } else {
     a.Xf = (const char*)X;
     a.x_step = 64;
@@ -878,10 +904,11 @@ hipError_t launch_mid(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const
   const unsigned gx = (unsigned)((a.N + 255) / 256);
   const bool two = (int64_t)gx * ((M + 31) / 32) >= 1024;
   const dim3 grid(gx, (unsigned)(two ? (M + 31) / 32 : (M + 15) / 16));
-  if (bwd) { if (two) hipLaunchKernelGGL((mid_finalize_kernel<2, true>), grid, dim3(256), 0, st, f);
-             else hipLaunchKernelGGL((mid_finalize_kernel<1, true>), grid, dim3(256), 0, st, f); }
-  else     { if (two) hipLaunchKernelGGL((mid_finalize_kernel<2, false>), grid, dim3(256), 0, st, f);
-             else hipLaunchKernelGGL((mid_finalize_kernel<1, false>), grid, dim3(256), 0, st, f); }
+  const bool lean = grid.x * grid.y > kLeanBlocks;
+  auto launch = [&](auto T, auto D, auto L) { hipLaunchKernelGGL((mid_finalize_kernel<T.value, D.value, L.value>), grid, dim3(256), 0, st, f); };
+  auto pick = [&](auto T, auto D) { if (lean) launch(T, D, std::true_type{}); else launch(T, D, std::false_type{}); };
+  if (two) { if (bwd) pick(Int<2>{}, std::true_type{}); else pick(Int<2>{}, std::false_type{}); }
+  else     { if (bwd) pick(Int<1>{}, std::true_type{}); else pick(Int<1>{}, std::false_type{}); }
   return hipGetLastError();
 }
 
