@@ -55,9 +55,8 @@ namespace qlora {
 
 namespace {
 
-constexpr int BM = 256, BK = 64, NSLOT = 5;                  // BN is 256, 192 or 128 (template parameter)
-constexpr int kSlot = BM * BK * 2;                           // 32 KB: one 256-row operand tile
-constexpr int GM = 4;                                       // tile-rows per raster group
+constexpr int BK = 64;                                       // BM is 256 or 128, BN 256, 192 or 128 (template parameters)
+constexpr int kMainRows = 256, kHalfRows = 128;
 constexpr int kMainWaves = 4;                                // waves per workgroup of the main (BN = 256) kernel
 
 typedef __attribute__((address_space(3))) char lchar;
@@ -73,7 +72,7 @@ struct GemmArgs {
   const uint8_t* Bq; const float* Bc; const float* tab;
 };
 
-template <int NI> struct Frags { bf16x8 a[8], b[NI]; };      // 16-row / 16-column MFMA operand tiles of one 32-wide sub-step
+template <int MI, int NI> struct Frags { bf16x8 a[MI], b[NI]; };   // 16-row / 16-column MFMA operand tiles of one 32-wide sub-step
 
 // One operand's DMA state.  The tile's rows are addressed through a buffer resource based at the tile's first
 // row: a per-lane byte offset that never changes (row * ld + chunk) plus a scalar byte offset that advances by one
@@ -140,17 +139,21 @@ __device__ __forceinline__ uint32_t code_dword(uint64_t a, uint64_t b, int d) {
 __device__ __forceinline__ int b_swizzle(int r) { return (((r >> 3) & 3) << 1) | ((r >> 1) & 1); }
 
 #define QL_LDS_READ(dst, addr, imm) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(imm))
-__device__ __forceinline__ void wait_frags(Frags<4>& f) {
+__device__ __forceinline__ void wait_frags(Frags<4, 4>& f) {
+  asm volatile("s_waitcnt lgkmcnt(0)"
+               : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.b[0]), "+v"(f.b[1]), "+v"(f.b[2]), "+v"(f.b[3]));
+}
+__device__ __forceinline__ void wait_frags(Frags<8, 4>& f) {
   asm volatile("s_waitcnt lgkmcnt(0)"
                : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.a[4]), "+v"(f.a[5]), "+v"(f.a[6]),
                  "+v"(f.a[7]), "+v"(f.b[0]), "+v"(f.b[1]), "+v"(f.b[2]), "+v"(f.b[3]));
 }
-__device__ __forceinline__ void wait_frags(Frags<6>& f) {
+__device__ __forceinline__ void wait_frags(Frags<8, 6>& f) {
   asm volatile("s_waitcnt lgkmcnt(0)"
                : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.a[4]), "+v"(f.a[5]), "+v"(f.a[6]),
                  "+v"(f.a[7]), "+v"(f.b[0]), "+v"(f.b[1]), "+v"(f.b[2]), "+v"(f.b[3]), "+v"(f.b[4]), "+v"(f.b[5]));
 }
-__device__ __forceinline__ void wait_frags(Frags<8>& f) {
+__device__ __forceinline__ void wait_frags(Frags<8, 8>& f) {
   asm volatile("s_waitcnt lgkmcnt(0)"
                : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.a[4]), "+v"(f.a[5]), "+v"(f.a[6]),
                  "+v"(f.a[7]), "+v"(f.b[0]), "+v"(f.b[1]), "+v"(f.b[2]), "+v"(f.b[3]), "+v"(f.b[4]), "+v"(f.b[5]),
@@ -172,16 +175,29 @@ __device__ __forceinline__ void wait_frags(Frags<8>& f) {
 // to it -- and writes the row into the slot a DMA would have filled, all of it between the MFMAs of the step
 // before the tile is read.  The adapter segment (at most one step) then comes FIRST, so that every tile the loop
 // produces is a decoded one; its weight-side tile is the only one a DMA still brings.
-template <int BN, int NW, bool FUSED>
-__global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
-  constexpr int WN = BN / (NW / 2);                          // wave tile width
-  constexpr int NI = WN / 16;                                // MFMA columns per wave
-  static_assert(NI == 4 || NI == 6 || NI == 8, "wave tiles are 128 x 64, 128 x 96 or 128 x 128");
-  constexpr int NA = 32 / NW, NB = (BN / 8) / NW;            // DMA instructions per wave, step and operand
+//
+// BM = 128 (BN = 128): wave tiles 64 x 64 and a ring of five 16 KB slots, so that two workgroups share a CU and one's waits are
+// the other's work.  Twice the operand bytes per product of the 256 x 256 tile; it serves outputs with too few of the larger
+// tiles (gemm_cut).
+//
+// NSLOT slots: tile n of the order A(0) B(0) A(1) ... sits in slot n % NSLOT; at step k the slots of step k take B(k + LEAD) and
+// A(k + LEAD + 1).  With one workgroup of 128 x 128 tiles per CU nothing covers the loads' latency but the ring: nine slots.
+template <int BM, int BN, int NW, bool FUSED, int NSLOT>
+__device__ __forceinline__ void gemm_nt_body(const GemmArgs& p) {
+  constexpr int LEAD = (NSLOT - 1) / 2;
+  static_assert((NSLOT == 5 || NSLOT == 9) && (NSLOT == 5 || !FUSED), "the loops are unrolled for these");
+  constexpr int WM = BM / 2, WN = BN / (NW / 2);             // wave tile
+  constexpr int MI = WM / 16, NI = WN / 16;                  // MFMA rows and columns per wave
+  static_assert((MI == 8 && (NI == 4 || NI == 6 || NI == 8)) || (MI == 4 && NI == 4 && !FUSED), "wave tiles 128 x 64, 128 x 96, 128 x 128, 64 x 64");
+  constexpr int kSlot = BM * BK * 2;                         // one operand tile of the ring (weight side: at most as large)
+  static_assert(BN <= BM, "both operands' tiles fit a slot");
+  constexpr int kWin = 2 * kSlot;                            // two slots share a base register, the second by an immediate
+  constexpr int GM = 4 * kMainRows / BM;                     // tile-rows per raster group: 1024 rows
+  constexpr int NA = (BM / 8) / NW, NB = (BN / 8) / NW;      // DMA instructions per wave, step and operand
   constexpr int PER = (FUSED ? NA : NA + NB) / 2;            // DMA instructions per wave and sub-step
-  static_assert((NA + NB) % 2 == 0 && PER <= 8, "DMA instructions are spread evenly over the two sub-steps");
+  static_assert((NA + NB) % 2 == 0 && PER <= MI, "DMA instructions are spread evenly over the two sub-steps");
   static_assert(!FUSED || (BN == 256 && NW == 4), "fused tiles: 256 rows, one per lane of the workgroup");
-  __shared__ __attribute__((aligned(1024))) char smem[NSLOT * kSlot];             // 160 KB
+  __shared__ __attribute__((aligned(1024))) char smem[NSLOT * kSlot];             // 160 KB (BM = 256), 80 KB (128)
   lchar* const lds = (lchar*)smem;
 
   const int tid = threadIdx.x;
@@ -251,7 +267,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
   // On the weight side two consecutive operand tiles take 32 rows between them: row i of tile 2q + b is row
   // 32 q + 8 (i / 4) + 4 b + i % 4 of the wave's columns, so that a lane's four accumulators of both tiles are eight
   // neighbouring output columns (16-byte stores).  b_swizzle() spreads the rows of either tile over the banks.
-  const int a_row = wm * 128 + (lane & 15), b_row = wn * WN + 8 * ((lane & 15) >> 2) + (lane & 3), g4 = lane >> 4;
+  const int a_row = wm * WM + (lane & 15), b_row = wn * WN + 8 * ((lane & 15) >> 2) + (lane & 3), g4 = lane >> 4;
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
   // FUSED: this lane's row of the weight tiles (clamped to the matrix like the DMA rows), its two buffers, the
   // table value of its lane, and where the row lies in a slot: chunk d at (wbase ^ 16 d), the XOR being the swizzle.
@@ -267,24 +283,25 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
     c_voff = (int)fused_const_offset(rc, 0, p.KT0);
     tabv = p.tab[lane & 15];
 #pragma unroll
-    for (int w = 0; w < 3; ++w) wbase[w] = lds0 + w * 65536 + tid * 128 + b_swizzle(tid) * 16;
+    for (int w = 0; w < 3; ++w) wbase[w] = lds0 + w * kWin + tid * 128 + b_swizzle(tid) * 16;
   }
   // step of segment 0 behind tile t of the fused order (t >= KT1), clamped to the last
   auto seg0_step = [&](int t) { return fused_seg0_step(t, KT, p.KT1); };
-  uint32_t baseA[2][3], baseB[2][3];
+  constexpr int NWIN = (NSLOT + 1) / 2;
+  uint32_t baseA[2][NWIN], baseB[2][NWIN];
 #pragma unroll
   for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-    for (int w = 0; w < 3; ++w) {
-      baseA[kk][w] = lds0 + w * 65536 + a_row * 128 + (((4 * kk + g4) ^ ((a_row >> 1) & 7)) * 16);
-      baseB[kk][w] = lds0 + w * 65536 + b_row * 128 + (((4 * kk + g4) ^ b_swizzle(b_row)) * 16);
+    for (int w = 0; w < NWIN; ++w) {
+      baseA[kk][w] = lds0 + w * kWin + a_row * 128 + (((4 * kk + g4) ^ ((a_row >> 1) & 7)) * 16);
+      baseB[kk][w] = lds0 + w * kWin + b_row * 128 + (((4 * kk + g4) ^ b_swizzle(b_row)) * 16);
     }
 #define QL_READ_A(dst, slot, kk, i) QL_LDS_READ(dst, baseA[kk][(slot) >> 1], ((slot) & 1) * kSlot + (i) * 2048)
 #define QL_READ_B(dst, slot, kk, i) QL_LDS_READ(dst, baseB[kk][(slot) >> 1], ((slot) & 1) * kSlot + ((i) >> 1) * 4096 + ((i) & 1) * 512)
 
-  f32x4 acc[8][NI];
+  f32x4 acc[MI][NI];
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NI; ++j)
 #pragma unroll
@@ -294,7 +311,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
   // in front of a few idle cycles (without this the compiler sank the zeroing of one accumulator right in front
   // of its first MFMA, which then read the register's old contents): volatile statements keep their order.
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NI; ++j) asm volatile("" : "+a"(acc[i][j]));
   asm volatile("s_nop 3");
@@ -363,7 +380,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
     seek(da, a_rows, a_chunk, NA, m0, 0, true);
     seek(db, b_rows, b_chunk, NB, n0, 0, false);
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
+    for (int s = 0; s < LEAD; ++s) {
 #pragma unroll
       for (int j = 0; j < NA; ++j) QL_DMA16(da, lds + (2 * s) * kSlot, j);
 #pragma unroll
@@ -372,16 +389,16 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
       advance(db, b_rows, b_chunk, NB, n0, s, false);
     }
 #pragma unroll
-    for (int j = 0; j < NA; ++j) QL_DMA16(da, lds + 4 * kSlot, j);
-    advance(da, a_rows, a_chunk, NA, m0, 2, true);
-    // A(0), B(0) landed; A(1), B(1), A(2) (2 NA + NB instructions) in flight
-    wait_vmcnt<2 * NA + NB>();
+    for (int j = 0; j < NA; ++j) QL_DMA16(da, lds + (2 * LEAD) * kSlot, j);
+    advance(da, a_rows, a_chunk, NA, m0, LEAD, true);
+    // A(0), B(0) landed; A(1), B(1), ..., A(LEAD) in flight
+    wait_vmcnt<LEAD * NA + (LEAD - 1) * NB>();
     asm volatile("s_barrier" ::: "memory");
   }
 
-  Frags<NI> f0, f1;
+  Frags<MI, NI> f0, f1;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < MI; ++i) {
     QL_READ_A(f0.a[i], 0, 0, i);
     if (i < NI) QL_READ_B(f0.b[i], 1, 0, i);
   }
@@ -415,13 +432,13 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
     wait_frags(cur);                                                                                        \
     u32x4 ob = {0u, 0u, 0u, 0u};                                                                            \
     float pr[2] = {0.0f, 0.0f};                                                                             \
-    _Pragma("unroll") for (int i_ = 0; i_ < 8; ++i_) {                                                      \
+    _Pragma("unroll") for (int i_ = 0; i_ < MI; ++i_) {                                                     \
       _Pragma("unroll") for (int nj_ = 0; nj_ < NI; ++nj_) {                                                \
         const int ni_ = (i_ & 1) ? NI - 1 - nj_ : nj_;       /* serpentine: consecutive MFMAs share an operand */ \
         QL_MFMA(acc[i_][ni_], cur.b[ni_], cur.a[i_]);        /* D = (B tile) (A tile)^T: see the epilogue */      \
-        const int r_ = i_ * NI + nj_;                        /* MFMA number; reads 0 .. 7 + NI: a[], then b[] */ \
-        if (r_ < 8) QL_READ_A(nxt.a[r_ & 7], sa, kk, r_ & 7);                                               \
-        else if (r_ < 8 + NI) QL_READ_B(nxt.b[(r_ - 8) % NI], sb, kk, (r_ - 8) % NI);                       \
+        const int r_ = i_ * NI + nj_;                        /* MFMA number; reads 0 .. MI - 1 + NI: a[], then b[] */ \
+        if (r_ < MI) QL_READ_A(nxt.a[r_ % MI], sa, kk, r_ % MI);                                            \
+        else if (r_ < MI + NI) QL_READ_B(nxt.b[(r_ - MI) % NI], sb, kk, (r_ - MI) % NI);                    \
         if constexpr (FUSED) {                                                                              \
           if (dec_) { QL_DEC(r_, db_, cb_, cc_, s0_, s1_) }                                                 \
         }                                                                                                   \
@@ -437,7 +454,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
   {                                                                                                         \
     constexpr int sa_ = ((S0) + 2) % NSLOT, sb_ = ((S0) + 3) % NSLOT, fa_ = (S0) % NSLOT, fb_ = ((S0) + 1) % NSLOT; \
     wait_frags(f1);                                           /* this wave has read all it needs of step k */ \
-    wait_vmcnt<NA>();                                         /* its part of A(k+1), B(k+1) has landed      */ \
+    wait_vmcnt<(LEAD - 1) * NA + (LEAD - 2) * NB>();          /* its part of A(k+1), B(k+1) has landed      */ \
     if constexpr (FUSED) {                                                                                  \
       /* tile k+2: its first half was looked up during the previous sub-step; U moves on to tile k+3, */    \
       /* whose row, asked for a step ago, that wait has covered                                       */    \
@@ -456,33 +473,45 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
       if constexpr (!FUSED) db.soff += BK * 2;                                                              \
       da.soff += BK * 2;                                                                                    \
     } else {                                                                                                \
-      if constexpr (!FUSED) advance(db, b_rows, b_chunk, NB, n0, k + 2, false);                             \
-      advance(da, a_rows, a_chunk, NA, m0, k + 3, true);                                                    \
+      if constexpr (!FUSED) advance(db, b_rows, b_chunk, NB, n0, k + LEAD, false);                          \
+      advance(da, a_rows, a_chunk, NA, m0, k + LEAD + 1, true);                                             \
     }                                                                                                       \
     ++k;                                                                                                    \
   }
 
   QL_HEAD(0, 1)                                               // step 0, sub-step 0 (no DMA: the ring is full)
   int k = 0;                                                 // f1 holds the fragments of the last sub-step of step k
-  // Steady state: every tile requested and every state advanced in these five iterations stays inside K segment 0
-  // (the last advance moves A to step k + 8 < KT0), so the DMA state advances by one scalar add and no iteration
-  // carries the branches and register copies of the segment switch.
-#pragma unroll 1
-  while (k + 8 < (FUSED ? KT : p.KT0)) {
-    QL_ITER(0, true) QL_ITER(2, true) QL_ITER(4, true) QL_ITER(1, true) QL_ITER(3, true)
+  // Steady state: every tile requested and every state advanced in these NSLOT iterations stays inside K segment 0
+  // (the last advance moves A to step k + NSLOT + LEAD + 1 < KT0), so the DMA state advances by one scalar add and no
+  // iteration carries the branches and register copies of the segment switch.
+#define QL_ROUND(FAST)                                                                                      \
+  if constexpr (NSLOT == 5) {                                                                               \
+    QL_ITER(0, FAST) QL_ITER(2, FAST) QL_ITER(4, FAST) QL_ITER(1, FAST) QL_ITER(3, FAST)                    \
+  } else {                                                                                                  \
+    QL_ITER(0, FAST) QL_ITER(2, FAST) QL_ITER(4, FAST) QL_ITER(6, FAST) QL_ITER(8, FAST)                    \
+    QL_ITER(1, FAST) QL_ITER(3, FAST) QL_ITER(5, FAST) QL_ITER(7, FAST)                                     \
   }
 #pragma unroll 1
-  while (k + 5 < KT) {
-    QL_ITER(0, false) QL_ITER(2, false) QL_ITER(4, false) QL_ITER(1, false) QL_ITER(3, false)
-  }
+  while (k + NSLOT + LEAD + 1 < (FUSED ? KT : p.KT0)) { QL_ROUND(true) }
+#pragma unroll 1
+  while (k + NSLOT < KT) { QL_ROUND(false) }
   if (k + 1 < KT) QL_ITER(0, false)
   if (k + 1 < KT) QL_ITER(2, false)
   if (k + 1 < KT) QL_ITER(4, false)
-  if (k + 1 < KT) QL_ITER(1, false)
+  if constexpr (NSLOT == 5) {
+    if (k + 1 < KT) QL_ITER(1, false)
+  } else {
+    if (k + 1 < KT) QL_ITER(6, false)
+    if (k + 1 < KT) QL_ITER(8, false)
+    if (k + 1 < KT) QL_ITER(1, false)
+    if (k + 1 < KT) QL_ITER(3, false)
+    if (k + 1 < KT) QL_ITER(5, false)
+  }
+#undef QL_ROUND
   // the last sub-step of the last step; its fragments are in f1
   wait_frags(f1);
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni) QL_MFMA(acc[i][ni], f1.b[ni], f1.a[i]);
 #undef QL_ITER
@@ -509,7 +538,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
   // cost 2.7 us per output tile)
   asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3");
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NI; ++j) asm volatile("" : "+a"(acc[i][j]));
 
@@ -521,11 +550,11 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
   // inside M (all but the last tile-row) skip the per-row bound checks.  N % 8 == 0: a group of eight columns is
   // inside or outside as a whole.
   const bool rows_inside = m0 + BM <= p.M;
-  const int m_lane = m0 + wm * 128 + (lane & 15);            // first row this lane stores
+  const int m_lane = m0 + wm * WM + (lane & 15);             // first row this lane stores
   const int n_lane = n0 + wn * WN + 8 * g4;                  // its first column
   uint16_t* const cb = p.C + (int64_t)m_lane * p.ldc + n_lane;
 #pragma unroll
-  for (int mi = 0; mi < 8; ++mi) {
+  for (int mi = 0; mi < MI; ++mi) {
     if (!rows_inside && m_lane + mi * 16 >= p.M) continue;
 #pragma unroll
     for (int q = 0; q < NI / 2; ++q) {
@@ -540,46 +569,65 @@ __global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) {
   }
 }
 
+template <int BN, int NW, bool FUSED>
+__global__ __launch_bounds__(NW * 64) void gemm_nt_kernel(const GemmArgs p) { gemm_nt_body<kMainRows, BN, NW, FUSED, 5>(p); }
+template <int NSLOT>
+__global__ __launch_bounds__(256, NSLOT == 5 ? 2 : 1) void gemm_nt_half_kernel(const GemmArgs p) { gemm_nt_body<kHalfRows, 128, 4, false, NSLOT>(p); }
+
+
 // How an output of tiles_m tile-rows is cut into columns: `wide` 256-wide tile columns from the left, then `rest` columns of
 // rest_width in a launch of their own.
-struct GemmCut { int wide, rest, rest_width; };
 // One workgroup per CU: tiles run in rounds of 256, and a narrower tile costs less than its share is worth only where it
 // fills a round better.  Measured per K-step of 64 (a launch's time / rounds / steps): a round of 256-wide tiles takes
 // 1.05 us nearly empty and 1.36 us full (the board's power limit), 192-wide 0.86 / 1.05, 128-wide 0.66 / 0.79; a second
-// launch about 3 us.  The cut of the least cost by these figures is taken (of
+// launch about 3 us.  Tiles of 128 x 128 take 0.45 / 0.57 in a round of 256 (nine slots), 0.58 / 0.84 in a round of 512, two to
+// a CU (five slots).  The cut of the least cost by these figures is taken (of
 // about equal ones, the one of more 256-wide tiles).  dX of a stacked q / k / v at 2000 tokens
 // (5120 columns, K 15552: 160 tiles of 256) 310 -> 263 us inside the training call with 216 tiles of 192; each alone and
 // repeated: 1024 x 4096 (K 4160) 69 -> 43 us and 600 x 8192 (K 8256) 132 -> 86 us with 128-wide tiles; 4096 x 5120 (K 5184) 193 -> 162 and 1500 x 11008 (K 4160)
 // 156 -> 124 us with 192-wide ones; 4096 x 8192 (K 8256), two full rounds, 351 us against 382 (192) and 388 (128).
+// With 128 x 128 tiles, whole calls: 600 tokens 4096 x 4096 forward 56.7 -> 44.1 us (with the five-slot ring 51.0), 1024
+// tokens dX 4096 x 11008 177 -> 142 (146), 900 tokens dX 1536 x 3072 44.8 -> 35.0 (38.9), 1024 tokens 1024 x 1024 24.5 -> 19.4
+// (20.6); where the larger tiles fill their rounds they lose: 4096 tokens 4096 x 4096 117 against 135.
+struct GemmCut { int wide, rest, rest_width, half; };        // half: the whole output in that many columns of 128 x 128 tiles
 struct RoundCost { int width, empty, full; };                // of a round, in 0.01 us per K-step
 constexpr RoundCost kWide = {256, 105, 136}, kNarrow[2] = {{192, 86, 105}, {128, 66, 79}};
+constexpr RoundCost kHalf1 = {0, 45, 57}, kHalf2 = {0, 58, 84};   // 128 x 128: up to one, up to two workgroups per CU
 constexpr int kCUs = 256;
-int64_t rounds_cost(const RoundCost& c, int64_t tiles, int64_t steps) {
-  const int64_t last = tiles % kCUs;
-  return (tiles / kCUs * c.full + (last ? c.empty + (c.full - c.empty) * last / kCUs : 0)) * steps;
+int64_t rounds_cost(const RoundCost& c, int64_t tiles, int64_t steps, int64_t per_round = kCUs) {
+  const int64_t last = tiles % per_round;
+  return (tiles / per_round * c.full + (last ? c.empty + (c.full - c.empty) * last / per_round : 0)) * steps;
 }
-GemmCut gemm_cut(int tiles_m, int N, int steps) {
+int64_t half_cost(int64_t M, int64_t N, int64_t steps) {
+  const int64_t tiles = (M + kHalfRows - 1) / kHalfRows * ((N + 127) / 128);
+  return tiles <= kCUs ? rounds_cost(kHalf1, tiles, steps) : rounds_cost(kHalf2, tiles, steps, 2 * kCUs);
+}
+GemmCut gemm_cut(int M, int N, int steps) {
   constexpr int kLaunch = 300;
+  const int tiles_m = (M + kMainRows - 1) / kMainRows;
   auto cost = [&](const RoundCost& c, int cols) { return rounds_cost(c, (int64_t)cols * tiles_m, steps); };
   const int tiles_n = (N + 255) / 256;
-  GemmCut best = {tiles_n, 0, 256};
+  GemmCut best = {tiles_n, 0, 256, 0};
   int64_t best_cost = cost(kWide, tiles_n);
   auto consider = [&](int wide) {
     for (const RoundCost& c : kNarrow) {
       const int rest = (N - wide * 256 + c.width - 1) / c.width;
       const int64_t t = cost(kWide, wide) + cost(c, rest) + (wide > 0 ? kLaunch : 0);
-      if (t * 101 < best_cost * 100) { best_cost = t; best = {wide, rest, c.width}; }
+      if (t * 101 < best_cost * 100) { best_cost = t; best = {wide, rest, c.width, 0}; }
     }
   };
   for (int wide = tiles_n - 1; wide > 0 && wide >= tiles_n - kCUs; --wide) consider(wide);   // a round has at most 256 columns
   consider(0);
+  const int half_n = (N + 127) / 128;
+  const int64_t t = half_cost(M, N, steps);
+  if (t * 101 < best_cost * 100) best = {0, 0, 0, half_n};
   return best;
 }
 
 }  // namespace
 
 double gemm_rounds_us(int64_t M, int64_t N, int64_t steps) {
-  const int64_t tiles_m = (M + BM - 1) / BM;
+  const int64_t tiles_m = (M + kMainRows - 1) / kMainRows;
   int64_t best = rounds_cost(kWide, (N + 255) / 256 * tiles_m, steps);
   for (const RoundCost& c : kNarrow) best = std::min(best, rounds_cost(c, (N + c.width - 1) / c.width * tiles_m, steps));
   return 0.01 * (double)best;
@@ -598,16 +646,20 @@ hipError_t launch_gemm_nt(const uint16_t* A0, const uint16_t* B0, int64_t lda0, 
   a.A0 = A0; a.B0 = B0; a.lda0 = lda0; a.ldb0 = ldb0; a.KT0 = K0 / BK;
   a.A1 = A1; a.B1 = B1; a.lda1 = lda1; a.ldb1 = ldb1; a.KT1 = K1 / BK;
   a.C = C; a.ldc = ldc; a.M = M; a.N = N;
-  a.tiles_m = (M + BM - 1) / BM;
-  const GemmCut cut = gemm_cut(a.tiles_m, N, a.KT0 + a.KT1);
+  const GemmCut cut = gemm_cut(M, N, a.KT0 + a.KT1);
   auto launch = [&](int width, int n_begin, int tiles_n) {
     a.n_begin = n_begin;
     a.tiles_n = tiles_n;
+    const int rows = width == kHalf1.width ? kHalfRows : kMainRows;
+    a.tiles_m = (M + rows - 1) / rows;
     const dim3 grid((unsigned)(a.tiles_m * tiles_n)), block(256);
     if (width == 256) hipLaunchKernelGGL((gemm_nt_kernel<256, kMainWaves, false>), grid, block, 0, st, a);
     else if (width == 192) hipLaunchKernelGGL((gemm_nt_kernel<192, 4, false>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((gemm_nt_kernel<128, 4, false>), grid, block, 0, st, a);
+    else if (width == 128) hipLaunchKernelGGL((gemm_nt_kernel<128, 4, false>), grid, block, 0, st, a);
+    else if (grid.x > kCUs) hipLaunchKernelGGL(gemm_nt_half_kernel<5>, grid, block, 0, st, a);
+    else hipLaunchKernelGGL(gemm_nt_half_kernel<9>, grid, block, 0, st, a);
   };
+  if (cut.half > 0) launch(kHalf1.width, 0, cut.half);
   if (cut.wide > 0) launch(256, 0, cut.wide);
   if (cut.rest > 0) launch(cut.rest_width, cut.wide * 256, cut.rest);
   return hipGetLastError();
@@ -689,7 +741,7 @@ hipError_t launch_gemm_nt_fused(const uint16_t* A0, const uint8_t* Bq, const flo
   a.A0 = A0; a.B0 = nullptr; a.lda0 = lda0; a.ldb0 = 0; a.KT0 = K0 / BK;
   a.A1 = A1; a.B1 = B1; a.lda1 = lda1; a.ldb1 = ldb1; a.KT1 = K1 / BK;
   a.C = C; a.ldc = ldc; a.M = M; a.N = N;
-  a.tiles_m = (M + BM - 1) / BM;
+  a.tiles_m = (M + kMainRows - 1) / kMainRows;
   a.tiles_n = (N + 255) / 256;
   a.n_begin = 0;
   a.Bq = Bq; a.Bc = Bc; a.tab = tab16;

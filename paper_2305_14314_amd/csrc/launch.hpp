@@ -45,7 +45,8 @@ hipError_t launch_dequant_t(const NF4Dev& w, uint16_t* out, int64_t ld_out, hipS
 hipError_t launch_gemm_nt(const uint16_t* A0, const uint16_t* B0, int64_t lda0, int64_t ldb0, int K0,
                           const uint16_t* A1, const uint16_t* B1, int64_t lda1, int64_t ldb1, int K1,
                           uint16_t* C, int64_t ldc, int M, int N, hipStream_t st);
-// Estimated time of the product from the measured costs of a tile round (whole outputs of one tile width), `steps` K-steps.
+// Estimated time of the product from the measured costs of a tile round (whole outputs of one tile width, 256 rows), `steps`
+// K-steps: what mid_pays' estimate is fitted to.
 double gemm_rounds_us(int64_t M, int64_t N, int64_t steps);
 
 // The same product with the weight-side operand of segment 0 decoded inside the kernel: Bq = N rows of K0 / 2 bytes of

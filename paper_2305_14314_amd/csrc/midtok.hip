@@ -833,12 +833,12 @@ MidPlan mid_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room) 
 // 22016, 64 .. 65536 outputs, ranks 0 .. 256; each estimate within 20 % on nine calls of ten).  Decoding inside the product
 // loses where the contraction is short (its partials are then as large as the product: dX with K = 64, N = 16384 at 384 tokens
 // 43 us against 12) or the rank large (K = 1024, N = 8192, rank 256 at 512 tokens 66 against 32); it wins where the weight is
-// what counts (K = 22016, N = 8192, rank 64 at 256 tokens 117 against 421).  The constant of the first estimate was 6.5 when the
-// three kernels took 2 - 4 us longer to start.  Near the line either will do: a call goes to the
+// what counts (K = 22016, N = 8192, rank 64 at 256 tokens 117 against 421).  Both paths have become faster
+// since by about the same (2 - 4 us here, tiles of 128 x 128 there); the line stays where the fit put it.  Near the line either will do: a call goes to the
 // other path where that is faster by a fifth, so that seven of the fitted calls lose more than 3 % by it, the worst 20 %.
 bool mid_pays(const MidPlan& p, bool bwd, int64_t M, int64_t h, int64_t o, int r, bool fix) {
   const double K = (double)(bwd ? o : h), N = (double)(bwd ? h : o), MN = 1e-6 * (double)M * N;
-  const double mid = 4.0 + 0.88 * p.us + (p.pack ? 4.3 + 0.053 * r : 0.027 * r) + 0.35 * p.max_contrib * MN + 0.0034 * r * MN +
+  const double mid = 6.5 + 0.88 * p.us + (p.pack ? 4.3 + 0.053 * r : 0.027 * r) + 0.35 * p.max_contrib * MN + 0.0034 * r * MN +
                      3.3e-8 * (double)M * K * r;
   const double gemm = 9.7 + 0.7 * gemm_rounds_us(M, (int64_t)N, ((int64_t)K + (r + 63) / 64 * 64) / 64) + 0.62e-6 * K * N +
                       0.6 * MN + (r > 0 ? 3.6 + 1e-6 * r * (0.2 * N + 3.8 * K) : 0.0) + (fix ? 5.5 + 2.2 * MN : 0.0);

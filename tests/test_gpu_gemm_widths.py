@@ -13,6 +13,18 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("M,h,o,r", [(513, 64, 64, 0), (700, 192, 448, 16), (520, 64, 10944, 16), (1000, 64, 8256, 16),
                                      (1000, 128, 8320, 0), (1025, 64, 8384, 16), (800, 320, 16448, 16), (4100, 64, 3904, 16)])
 def test_widths(oracle, synth, M, h, o, r):
+    _widths(oracle, synth, M, h, o, r)
+
+
+@pytest.mark.parametrize("M,h,o,r", [(513, 64, 128, 16), (640, 128, 192, 0), (641, 512, 320, 16), (769, 576, 64, 32), (1025, 640, 3520, 16),
+                                     (700, 704, 5504, 0), (2049, 1216, 1984, 48)])
+def test_half_tiles(oracle, synth, M, h, o, r):
+    """Tiles of 128 x 128: one K-step, one to two turns of the nine-slot ring and the segment switch in each of its places, just
+    below and above one workgroup per compute unit, ragged rows and columns."""
+    _widths(oracle, synth, M, h, o, r)
+
+
+def _widths(oracle, synth, M, h, o, r):
     """Forward (output width o) and, with the sides swapped, backward (output width o again, and the adapter's segment)."""
     import paper_2305_14314_amd as ql
     print(f"case widths M={M} h={h} o={o} r={r}", flush=True)
