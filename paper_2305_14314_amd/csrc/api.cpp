@@ -363,7 +363,7 @@ BwdPlan plan_bwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allo
 
 // Several layers on one X.  Few tokens: one launch, every layer with its own partial buffers.  Otherwise the layers
 // run one after the other through the single-layer path, sharing one workspace of the largest size.
-static_assert(QLORA_MULTI_MAX == qlora::kFewMaxLayers, "the header's limit is the kernel's");
+static_assert(QLORA_MULTI_MAX == qlora::kFewMaxLayers && QLORA_MULTI_MAX <= qlora::kDeqMax, "the header's limit is the kernel's");
 struct MultiPlan {
   float* fpart[qlora::kFewMaxLayers];
   float* lpart[qlora::kFewMaxLayers];
@@ -809,12 +809,17 @@ qlora_status qlora_linear_fwd_stacked(const uint16_t* X, int32_t n, const qlora_
     QL_TRY(batch.add(t, tiles));
   }
   QL_TRY(batch.launch());
+  qlora::DeqDesc deq[QLORA_MULTI_MAX];
   int64_t n0 = 0;
   for (int l = 0; l < n; ++l) {
-    QL_TRY(qlora::launch_dequant_t(to_dev(&Wq[l]), p.Wt + n0 * ldw, ldw, st, r[l] > 0 ? L2[l] : nullptr, r[l], p.Rp,
-                                   p.off[l], l == 0 ? &batch.fin : nullptr));
+    deq[l] = qlora::DeqDesc{to_dev(&Wq[l]), p.Wt + n0 * ldw, r[l] > 0 ? L2[l] : nullptr, r[l], p.off[l]};
     n0 += o[l];
   }
+  // in one launch, unless the partials of the T products lie where the last layer's weight will: that layer then follows
+  const int together = qlora::dequant_list_fits(deq, n) ? (big ? n - 1 : n) : 0;
+  if (together > 1) QL_TRY(qlora::launch_dequant_t_list(deq, together, ldw, p.Rp, st, &batch.fin));
+  for (int l = together > 1 ? together : 0; l < n; ++l)
+    QL_TRY(qlora::launch_dequant_t(deq[l].w, deq[l].out, ldw, st, deq[l].L2, deq[l].r, p.Rp, deq[l].col0, l == 0 ? &batch.fin : nullptr));
   // Y[:, layer l's columns] = X What_l + s_l (X L1_l) L2_l (Eq. 5 per layer)
   QL_TRY(gemm_nt_timed(X, p.Wt, h, ldw, (int)h, p.Ts, p.Wt + h, p.Rp, ldw, p.Rp, Y, p.N, (int)M, (int)p.N, st));
   return QLORA_OK;
@@ -1076,7 +1081,11 @@ qlora_status qlora_linear_bwd_stacked(const uint16_t* dY, const uint16_t* X, int
     }
     QL_TRY(batch.finish());
   }
-  for (int l = 0; l < n; ++l) QL_TRY(qlora::launch_dequant(to_dev(&Wq[l]), p.Wd + col[l], st, N));
+  qlora::DeqDesc deq[QLORA_MULTI_MAX];
+  for (int l = 0; l < n; ++l) deq[l] = qlora::DeqDesc{to_dev(&Wq[l]), p.Wd + col[l], nullptr, 0, 0};
+  if (qlora::dequant_list_fits(deq, n)) QL_TRY(qlora::launch_dequant_list(deq, n, N, st));
+  else
+    for (int l = 0; l < n; ++l) QL_TRY(qlora::launch_dequant(deq[l].w, deq[l].out, st, N));
   // dX = sum over the layers of dY_l What_l^T + Us_l L1_l^T: one product, contraction over all outputs, then all ranks
   QL_TRY(gemm_nt_timed(dY, p.Wd, N, N, (int)N, p.Us, p.L1s, p.Rp, p.Rp, p.Rp, dX, h, (int)M, (int)h, st));
   return QLORA_OK;

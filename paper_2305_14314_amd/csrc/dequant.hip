@@ -1,6 +1,11 @@
 // Standalone doubleDequant (arXiv 2305.14314, Eq. 6 and Eq. 2): packed NF4 indices and
 // double-quantised constants -> bf16 weights.  HBM-bound: 0.516 B read + 2 B written per element.
-// One lane decodes one packed dword (8 weights of one 64-block) and stores 16 bytes.
+// One lane decodes one packed dword (8 weights of one 64-block) and stores 16 bytes.  8192 x 8192 38.4 -> 37.1 us and 4096 x 11008
+// 27.3 -> 25.9 without a memory round trip for the value table; the transposing kernel also asks for its data before it builds
+// the tables (a forward call of 1000 tokens through 4096 x 11008 101.4 -> 98.5).  The same in the flat kernel, whose workgroups
+// take several turns, made large weights slower (8192 x 22016 95 -> 115; why was not examined) and stayed out.
+#include <algorithm>
+
 #include "common.hpp"
 #include "fin.hpp"
 #include "launch.hpp"
@@ -14,17 +19,19 @@ static_assert(kDeqThreads == kFinThreads, "finalize workgroups share the launch"
 template <bool FIN> struct FinArg { FinList f; };
 template <> struct FinArg<false> {};
 
-// The 16 values of the data type into LDS: NF4 from constants; another type (Section 4) from the argument, copied
-// by one thread with constant indices (a lane-indexed read of a by-value argument would go through scratch).
+// The 16 values of the data type into LDS, NF4's or (Section 4) those of the argument: picked from scalars by the first wave's
+// lanes (a lane-indexed read of a constant array is a memory round trip, of a by-value argument goes through scratch).
 __device__ __forceinline__ void init_lut16(float* lut, int dtype, const Table4& tab) {
-  if (dtype == 0) {
-    if (threadIdx.x < 16) {
-      constexpr float t[16] = {QLORA_NF4_VALUES};
-      lut[threadIdx.x] = t[threadIdx.x];
-    }
-  } else if (threadIdx.x == 0) {
+  if (threadIdx.x < 64) {
+    constexpr float t[16] = {QLORA_NF4_VALUES};
+    float v = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) lut[i] = tab.v[i];
+    for (int i = 0; i < 16; ++i) {
+      float x = t[i];
+      if (dtype != 0) x = tab.v[i];                          // uniform
+      v = (int)threadIdx.x == i ? x : v;
+    }
+    if (threadIdx.x < 16) lut[threadIdx.x] = v;
   }
 }
 
@@ -33,16 +40,11 @@ __device__ __forceinline__ float s8_to_f32(uint32_t p, int j) { return (float)((
 
 // I8: 8-bit integers, Eq. 2 as printed: w = q * absmax / 127, as bf16(fl32(q * fl32(c2 / 127))).  A lane then reads
 // 8 bytes instead of 4; `packed` and `n_dwords` count in lane-sized units (8 weights) either way.
-template <bool DQ, bool I8, bool GAP, bool FIN>
-__global__ __launch_bounds__(kDeqThreads) void dequant_nf4_kernel(
+template <bool DQ, bool I8, bool GAP>
+__device__ __forceinline__ void dequant_body(
     const void* __restrict__ packed_v, const uint8_t* __restrict__ code, const float* __restrict__ c1,
     const float* __restrict__ mean_ptr, uint4* __restrict__ out, int64_t n_dwords, uint32_t rows, uint32_t bpr,
-    const int dtype, const Table4 tab, const int64_t row_gap, const FinArg<FIN> fin) {
-  int bid = blockIdx.x, n_bid = gridDim.x;
-  if constexpr (FIN) {
-    if (bid < fin.f.blocks()) { fin_block<4>(fin.f, bid); return; }
-    bid -= fin.f.blocks(); n_bid -= fin.f.blocks();
-  }
+    const int dtype, const Table4& tab, const int64_t row_gap, const int bid, const int n_bid) {
   // GAP: the output rows are row_gap 16-byte groups apart (a wider buffer: several weights side by side); else back to back
   constexpr bool dq = DQ;                                    // Double Quantization, or the fp32 constants as they are
   const uint32_t* __restrict__ packed = (const uint32_t*)packed_v;
@@ -90,6 +92,36 @@ __global__ __launch_bounds__(kDeqThreads) void dequant_nf4_kernel(
   }
 }
 
+template <bool DQ, bool I8, bool GAP, bool FIN>
+__global__ __launch_bounds__(kDeqThreads) void dequant_nf4_kernel(
+    const void* __restrict__ packed_v, const uint8_t* __restrict__ code, const float* __restrict__ c1,
+    const float* __restrict__ mean_ptr, uint4* __restrict__ out, int64_t n_dwords, uint32_t rows, uint32_t bpr,
+    const int dtype, const Table4 tab, const int64_t row_gap, const FinArg<FIN> fin) {
+  int bid = blockIdx.x, n_bid = gridDim.x;
+  if constexpr (FIN) {
+    if (bid < fin.f.blocks()) { fin_block<4>(fin.f, bid); return; }
+    bid -= fin.f.blocks(); n_bid -= fin.f.blocks();
+  }
+  dequant_body<DQ, I8, GAP>(packed_v, code, c1, mean_ptr, out, n_dwords, rows, bpr, dtype, tab, row_gap, bid, n_bid);
+}
+
+// Several weights of one height side by side (stacked layers), double-quantised 4-bit ones of one data type: a launch apiece ramps
+// up and drains 2000 workgroups for 18 us of work (q / k / v 3 x 5120 x 5120 at 2000 tokens, forward + backward 638 -> 630 us).
+struct DeqLayer { const uint32_t* packed; const uint8_t* code; const float* c1; const float* mean; uint16_t* out; const uint16_t* L2; int o, r, col0; };
+struct DeqLayers { int n; int first[kDeqMax + 1]; DeqLayer l[kDeqMax]; };     // first: workgroup (column) of each layer, [n] = their number
+__device__ __forceinline__ int deq_layer(const DeqLayers& a, int at) {
+  int l = 0;
+  while (l + 1 < a.n && at >= a.first[l + 1]) ++l;
+  return l;
+}
+__global__ __launch_bounds__(kDeqThreads) void dequant_nf4_list_kernel(const DeqLayers a, uint32_t rows, const int dtype,
+                                                                       const Table4 tab, const int64_t ld_out) {
+  const int l = deq_layer(a, blockIdx.x);
+  const DeqLayer& y = a.l[l];
+  dequant_body<true, false, true>(y.packed, y.code, y.c1, y.mean, (uint4*)y.out, (int64_t)rows * y.o / 8, rows, (uint32_t)(y.o >> 6),
+                                  dtype, tab, (ld_out - y.o) / 8, (int)blockIdx.x - a.first[l], a.first[l + 1] - a.first[l]);
+}
+
 // Transposed variant for the forward GEMM: out[n][k] = dequant(W)[k][n], row stride ld_out >= h.
 // A workgroup owns 64 input rows (k) x 256 columns (n); each wave a 64 x 64 sub-tile, i.e. one
 // 64-block per row.  A lane loads one packed dword (8 n) from each of 8 consecutive rows and
@@ -101,28 +133,18 @@ __global__ __launch_bounds__(kDeqThreads) void dequant_nf4_kernel(
 // that one buffer of row stride ld_out >= h + rp holds both K segments of the forward product's weight-side operand
 // and no launch of its own is spent on a 1 MB transpose.  (col0 > 0: several layers stacked along n share the adapter
 // segment block-diagonally: a layer's rows hold its own L2^T in its own columns and zeros in the others'.)
-template <bool DQ, bool I8, bool FIN>
-__global__ __launch_bounds__(kDeqThreads) void dequant_nf4_t_kernel(
+template <bool DQ, bool I8>
+__device__ __forceinline__ void dequant_t_body(
     const void* __restrict__ packed_v, const uint8_t* __restrict__ code, const float* __restrict__ c1,
     const float* __restrict__ mean_ptr, uint16_t* __restrict__ out, int h, int o, int64_t ld_out, const int dtype,
-    const Table4 tab, const uint16_t* __restrict__ L2, int r, int col0, const FinArg<FIN> fin) {
+    const Table4& tab, const uint16_t* __restrict__ L2, int r, int col0, const int row_id, const int col_id) {
   constexpr bool dq = DQ;
-  int row_id = blockIdx.y;                                   // workgroup row; the finalize workgroups fill the first ones
-  if constexpr (FIN) {
-    const int fin_rows = (fin.f.blocks() + (int)gridDim.x - 1) / (int)gridDim.x;
-    if (row_id < fin_rows) {
-      const int b = row_id * (int)gridDim.x + (int)blockIdx.x;
-      if (b < fin.f.blocks()) fin_block<4>(fin.f, b);
-      return;
-    }
-    row_id -= fin_rows;
-  }
   const uint32_t* __restrict__ packed = (const uint32_t*)packed_v;
   const int w_rows = (h + 63) >> 6;                          // workgroup rows of the weight
   if (row_id >= w_rows) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int kg = lane >> 3, ng = lane & 7;
-    const int n_blk = blockIdx.x * 4 + wave;
+    const int n_blk = col_id * 4 + wave;
     if (n_blk * 64 >= o) return;
     const int t_base = (row_id - w_rows) * 64 + kg * 8;
     const int n_first = n_blk * 64 + ng * 8;
@@ -149,35 +171,38 @@ __global__ __launch_bounds__(kDeqThreads) void dequant_nf4_t_kernel(
   }
   __shared__ float lut[16];
   __shared__ float unit[256];
-  init_lut16(lut, dtype, tab);
-  unit[threadIdx.x] = e4m3_unit(threadIdx.x);
-  __syncthreads();
-  const float mean = dq ? *mean_ptr : 0.0f;
-
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int kg = lane >> 3, ng = lane & 7;
-  const int n_blk = blockIdx.x * 4 + wave;                  // 64-column block index within a row
-  if (n_blk * 64 >= o) return;
+  const int n_blk = col_id * 4 + wave;                  // 64-column block index within a row
   const int k_base = row_id * 64 + kg * 8;
   const int blocks_per_row = o >> 6;
+  const bool inside = n_blk < blocks_per_row;               // per wave
 
-  uint32_t p[8], ph[8];
+  // all of a lane's loads are on their way while the tables are built
+  uint32_t p[8], ph[8], cd[8];
   float c2[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
-    const int k = k_base + j;
-    const bool ok = k < h;
-    const int64_t blk = (int64_t)(ok ? k : 0) * blocks_per_row + n_blk;
+    const int k = k_base + j, kc = k < h ? k : 0, bc = inside ? n_blk : 0;
+    const int64_t blk = (int64_t)kc * blocks_per_row + bc;
     if constexpr (I8) {                                       // 8 bytes = this lane's 8 columns of row k
       const uint2 pp = ((const uint2*)packed_v)[blk * 8 + ng];
-      p[j] = ok ? pp.x : 0u;
-      ph[j] = ok ? pp.y : 0u;
+      p[j] = pp.x; ph[j] = pp.y;
     } else {
-      p[j] = ok ? packed[blk * 8 + ng] : 0x77777777u;         // index 7 is the exact zero
+      p[j] = packed[blk * 8 + ng];
       ph[j] = 0u;
     }
-    if (dq) c2[j] = ok ? __fadd_rn(__fmul_rn(unit[code[code_pos(h, blocks_per_row, k, n_blk)]], c1[blk >> 8]), mean) : 0.0f;
-    else c2[j] = ok ? c1[blk] : 0.0f;
+    cd[j] = dq ? code[code_pos(h, blocks_per_row, kc, bc)] : 0u;
+    c2[j] = c1[dq ? blk >> 8 : blk];
+  }
+  const float mean = dq ? *mean_ptr : 0.0f;
+  init_lut16(lut, dtype, tab);
+  unit[threadIdx.x] = e4m3_unit(threadIdx.x);
+  __syncthreads();
+  if (!inside || k_base >= h) return;                         // h % 8 == 0: a lane's 8 rows are inside or outside together
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    if (dq) c2[j] = __fadd_rn(__fmul_rn(unit[cd[j]], c2[j]), mean);
     if constexpr (I8) c2[j] = __fdiv_rn(c2[j], 127.0f);       // Eq. 2: the step absmax / 127
   }
 #pragma unroll
@@ -194,8 +219,96 @@ __global__ __launch_bounds__(kDeqThreads) void dequant_nf4_t_kernel(
     q.z = pack_bf16x2(v[4], v[5]);
     q.w = pack_bf16x2(v[6], v[7]);
     const int n = n_blk * 64 + ng * 8 + e;
-    if (k_base < h) *(uint4*)(out + (int64_t)n * ld_out + k_base) = q;   // h % 8 == 0: all 8 or none
+    *(uint4*)(out + (int64_t)n * ld_out + k_base) = q;
   }
+}
+// The finalize workgroups fill the first workgroup rows.  True: this workgroup was one of them; else row_id is the weight's row.
+template <bool FIN>
+__device__ __forceinline__ bool deq_t_fin(const FinArg<FIN>& fin, int& row_id) {
+  row_id = blockIdx.y;
+  if constexpr (FIN) {
+    const int fin_rows = (fin.f.blocks() + (int)gridDim.x - 1) / (int)gridDim.x;
+    if (row_id < fin_rows) {
+      const int b = row_id * (int)gridDim.x + (int)blockIdx.x;
+      if (b < fin.f.blocks()) fin_block<4>(fin.f, b);
+      return true;
+    }
+    row_id -= fin_rows;
+  }
+  return false;
+}
+template <bool DQ, bool I8, bool FIN>
+__global__ __launch_bounds__(kDeqThreads) void dequant_nf4_t_kernel(
+    const void* __restrict__ packed_v, const uint8_t* __restrict__ code, const float* __restrict__ c1,
+    const float* __restrict__ mean_ptr, uint16_t* __restrict__ out, int h, int o, int64_t ld_out, const int dtype,
+    const Table4 tab, const uint16_t* __restrict__ L2, int r, int col0, const FinArg<FIN> fin) {
+  int row_id;
+  if (deq_t_fin(fin, row_id)) return;
+  dequant_t_body<DQ, I8>(packed_v, code, c1, mean_ptr, out, h, o, ld_out, dtype, tab, L2, r, col0, row_id, blockIdx.x);
+}
+template <bool FIN>
+__global__ __launch_bounds__(kDeqThreads) void dequant_nf4_t_list_kernel(const DeqLayers a, int h, const int dtype, const Table4 tab,
+                                                                         const int64_t ld_out, const FinArg<FIN> fin) {
+  int row_id;
+  if (deq_t_fin(fin, row_id)) return;
+  const int l = deq_layer(a, blockIdx.x);
+  const DeqLayer& y = a.l[l];
+  dequant_t_body<true, false>(y.packed, y.code, y.c1, y.mean, y.out, h, y.o, ld_out, dtype, tab, y.L2, y.r, y.col0, row_id,
+                              (int)blockIdx.x - a.first[l]);
+}
+
+// Can the layers share a launch?  One height, Double Quantization, one 4-bit data type.
+bool dequant_list_fits(const DeqDesc* d, int n) {
+  if (n < 2 || n > kDeqMax) return false;
+  for (int l = 0; l < n; ++l)
+    if (!d[l].w.dq || d[l].w.dtype == kTypeInt8 || d[l].w.dtype != d[0].w.dtype || d[l].w.rows != d[0].w.rows) return false;
+  return true;
+}
+namespace {
+DeqLayers deq_layers(const DeqDesc* d, int n) {
+  DeqLayers a{};
+  a.n = n;
+  for (int l = 0; l < n; ++l)
+    a.l[l] = DeqLayer{(const uint32_t*)d[l].w.packed, d[l].w.code, d[l].w.c1, d[l].w.mean, d[l].out, d[l].L2, (int)d[l].w.cols,
+                      d[l].L2 ? d[l].r : 0, d[l].L2 ? d[l].col0 : 0};
+  return a;
+}
+}  // namespace
+
+hipError_t launch_dequant_list(const DeqDesc* d, int n, int64_t ld_out, hipStream_t st) {
+  if (!dequant_list_fits(d, n) || ld_out % 8 != 0) return hipErrorInvalidValue;
+  DeqLayers a = deq_layers(d, n);
+  for (int l = 0; l < n; ++l) {
+    if (ld_out < d[l].w.cols) return hipErrorInvalidValue;
+    const int64_t blocks = (d[l].w.rows * d[l].w.cols / 8 + kDeqThreads - 1) / kDeqThreads, cap = 256 * 32;
+    a.first[l + 1] = a.first[l] + (int)std::min(blocks, cap);
+  }
+  hipLaunchKernelGGL(dequant_nf4_list_kernel, dim3((unsigned)a.first[n]), dim3(kDeqThreads), 0, st, a, (uint32_t)d[0].w.rows,
+                     d[0].w.dtype, table4_host(d[0].w.dtype), ld_out);
+  return hipGetLastError();
+}
+
+hipError_t launch_dequant_t_list(const DeqDesc* d, int n, int64_t ld_out, int rp, hipStream_t st, const FinList* fin) {
+  if (!dequant_list_fits(d, n) || rp % 64 != 0 || ld_out % 8 != 0 || ld_out < d[0].w.rows + rp) return hipErrorInvalidValue;
+  const int h = (int)d[0].w.rows;
+  DeqLayers a = deq_layers(d, n);
+  for (int l = 0; l < n; ++l) {
+    if (a.l[l].col0 < 0 || a.l[l].col0 + a.l[l].r > rp) return hipErrorInvalidValue;
+    a.first[l + 1] = a.first[l] + (int)((d[l].w.cols + 255) / 256);
+  }
+  const unsigned gx = (unsigned)a.first[n];
+  bool with_fin = fin && fin->n > 0;
+  unsigned fin_rows = with_fin ? ((unsigned)fin->blocks() + gx - 1) / gx : 0;
+  if (with_fin && (h + 63) / 64 + rp / 64 + (int)fin_rows > 65535) {   // more rows than a grid has: a launch of its own
+    if (hipError_t e = launch_fin(*fin, st)) return e;
+    with_fin = false;
+    fin_rows = 0;
+  }
+  const dim3 grid(gx, (unsigned)((h + 63) / 64 + rp / 64) + fin_rows);
+  const Table4 tab = table4_host(d[0].w.dtype);
+  if (with_fin) hipLaunchKernelGGL(dequant_nf4_t_list_kernel<true>, grid, dim3(kDeqThreads), 0, st, a, h, d[0].w.dtype, tab, ld_out, FinArg<true>{*fin});
+  else hipLaunchKernelGGL(dequant_nf4_t_list_kernel<false>, grid, dim3(kDeqThreads), 0, st, a, h, d[0].w.dtype, tab, ld_out, FinArg<false>{});
+  return hipGetLastError();
 }
 
 hipError_t launch_dequant_t(const NF4Dev& w, uint16_t* out, int64_t ld_out, hipStream_t st, const uint16_t* L2, int r,

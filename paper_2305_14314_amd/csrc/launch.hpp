@@ -41,6 +41,15 @@ hipError_t launch_dequant(const NF4Dev& w, uint16_t* out, hipStream_t st, int64_
 hipError_t launch_dequant_t(const NF4Dev& w, uint16_t* out, int64_t ld_out, hipStream_t st,
                             const uint16_t* L2 = nullptr, int r = 0, int rp = 0, int col0 = 0, const FinList* fin = nullptr);
 
+// The same for up to kDeqMax weights of one height in one launch, where dequant_list_fits().  launch_dequant_list: each into its
+// own `out` (columns of one wider buffer, row stride ld_out); launch_dequant_t_list: each into its own rows, with its adapter
+// segment as above (rp common).
+constexpr int kDeqMax = 4;
+struct DeqDesc { NF4Dev w; uint16_t* out; const uint16_t* L2; int r, col0; };
+bool dequant_list_fits(const DeqDesc* d, int n);
+hipError_t launch_dequant_list(const DeqDesc* d, int n, int64_t ld_out, hipStream_t st);
+hipError_t launch_dequant_t_list(const DeqDesc* d, int n, int64_t ld_out, int rp, hipStream_t st, const FinList* fin);
+
 // gemm.hip: C[M x N] = A0 B0^T + A1 B1^T, all operands K-contiguous bf16, K0 and K1 multiples of 64.
 hipError_t launch_gemm_nt(const uint16_t* A0, const uint16_t* B0, int64_t lda0, int64_t ldb0, int K0,
                           const uint16_t* A1, const uint16_t* B1, int64_t lda1, int64_t ldb1, int K1,

@@ -167,3 +167,32 @@ def test_stacked_backward_65b_qkv(oracle, synth):
         ref_c = ref_c + oracle.linear_bwd_dx(dYl, Whats[l], hL1[l], hL2[l], ss[l], cols=cols)
     _check(dXh[rows], ref_r, "qkv dX rows")
     _check(dXh[:, cols], ref_c, "qkv dX cols")
+
+
+@pytest.mark.parametrize("kinds", [("fp4", "fp4"), ("nf4", "fp4"), ("nf4", "plain"), ("int8", "nf4")])
+def test_stacked_storage_types(synth, kinds):
+    """Weights of one 4-bit data type are dequantised in one launch (another table in its arguments), others one after the
+    other: forward and input gradient against fp64 products with the dequantised weights."""
+    import paper_2305_14314_amd as ql
+    from gpu_util import bits_f64
+    M, h, outs, r = 130, 192, [320, 64], 16
+    s = [0.5, 2.0]
+    hX, hdY = synth.normal_bf16((M, h), 1.0, 7900), synth.normal_bf16((M, sum(outs)), 1.0, 7901)
+    Wqs, L1s, L2s, ref, dX, n0 = [], [], [], [], 0.0, 0
+    for l, (kind, o) in enumerate(zip(kinds, outs)):
+        W = synth.normal_f32_device((h, o), synth.SIGMA_W, 7910 + l)
+        Wq = (ql.qlora_quantize_int8(W) if kind == "int8" else
+              ql.qlora_quantize_4bit(W, ql.FP4_E2M1 if kind == "fp4" else ql.NF4, dq_blocksize=0 if kind == "plain" else 256))
+        Wqs.append(Wq)
+        l1, l2 = synth.normal_bf16((h, r), 0.05, 7920 + l), synth.normal_bf16((r, o), 0.05, 7930 + l)
+        L1s.append(dev_bf16(l1))
+        L2s.append(dev_bf16(l2))
+        What = bits_f64(host_bits(ql.qlora_nf4_dequant(Wq)))
+        X, g, l1, l2 = bits_f64(hX), bits_f64(hdY)[:, n0:n0 + o], bits_f64(l1), bits_f64(l2)
+        ref.append(X @ What + s[l] * (X @ l1) @ l2)
+        dX = dX + g @ What.T + s[l] * (g @ l2.T) @ l1.T
+        n0 += o
+    Y = ql.qlora_linear_fwd_stacked(dev_bf16(hX), Wqs, L1s, L2s, s)
+    _check(host_bits(Y), np.concatenate(ref, axis=1), f"Y {kinds}")
+    got = ql.qlora_linear_bwd_stacked(dev_bf16(hdY), dev_bf16(hX), Wqs, L1s, L2s, s)[0]
+    _check(host_bits(got), dX, f"dX {kinds}")
