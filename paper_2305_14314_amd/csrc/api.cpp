@@ -157,8 +157,12 @@ size_t mid_bytes(const qlora::MidPlan& p) {
 // or not the path is taken, because the adapter gradients' partials lie there too (dL1 and dL2 of 1024 x 1024 at rank 128 and
 // 512 tokens share a launch in it: 20.5 us, 24.6 without)
 size_t mid_region(size_t base, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r) {
-  const qlora::MidPlan p = qlora::mid_plan(bwd, M, h, o, r, std::max(base, kMidRoom));
-  return p.ok ? std::max(base, mid_bytes(p)) : base;
+  size_t bytes = base;
+  for (bool packed : {false, true}) {        // both are reported: a plan takes what it is given
+    const qlora::MidPlan p = qlora::mid_plan(bwd, M, h, o, r, std::max(base, kMidRoom), packed);
+    if (p.ok) bytes = std::max(bytes, mid_bytes(p));
+  }
+  return bytes;
 }
 MidWs plan_mid(void* buf, size_t room, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r, bool fix = false) {
   MidWs m{};

@@ -191,7 +191,8 @@ struct MidPlan {
   size_t part_floats, lpart_floats, pack_elems;
   double us;                                 // estimate of the main kernel's time
 };
-MidPlan mid_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room);
+//   packed: only plans that pack the token operand, where there are any (the size queries also report their room)
+MidPlan mid_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room, bool packed = false);
 // Is the plan worth taking, or is the weight dequantised and multiplied sooner?  fix: that path would need the dropout fix-up.
 bool mid_pays(const MidPlan& p, bool bwd, int64_t M, int64_t h, int64_t o, int r, bool fix);
 //   forward: out (M x o) = X dequant(W) + scale (mask o X L1) L2, hl (M x 2r or NULL) = [hi | lo] of mask o X L1;

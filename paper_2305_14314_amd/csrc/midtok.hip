@@ -8,13 +8,13 @@
 // 158 -> 87 us; forward + backward 1024 x 1024 at 256 tokens 96 -> 48 us, 4096 x 4096 at 512 tokens 220 -> 99 us.
 //
 // Two or three launches on the caller's stream:
-//   pre       (backward, and forward above 48 tokens) the token operand in MFMA-fragment order, so that the main kernel's operand loads
-//             are whole contiguous kilobytes; beside it the partial sums of the adapter's inner product T = X L1 (U = dY L2^T)
+//   pre       (where the plan finds it worth a launch) the token operand in MFMA-fragment order, so that the main kernel's operand
+//             loads are whole contiguous kilobytes; beside it the partial sums of the adapter's inner product T = X L1 (U = dY L2^T)
 //   main      the products of all tiles (16 MF tokens x 128 outputs) are one line of units (KW steps of the contraction),
 //             cut into equal ranges, one per workgroup: whatever the shape, every compute unit multiplies the same
 //             amount.  Within a tile a workgroup's waves take the steps in turn, each with the whole tile in
-//             accumulators, and are summed through LDS into one fp32 partial tile.  No barrier in the loop.  Forward at
-//             up to 48 tokens the adapter's partial sums are extra workgroups here and the operand is read as it lies.
+//             accumulators, and are summed through LDS into one fp32 partial tile.  No barrier in the loop.  Without a pre
+//             launch the adapter's partial sums are extra workgroups here and the operand is read as it lies.
 //   finalize  out = bf16( sum of a tile's partials + s * (sum of T's partials) * L2 ), in a fixed order, one rounding; T
 //             as a [hi | lo] pair of bf16 operands (16 significant bits) on MFMA; writes T_save
 //
@@ -39,9 +39,6 @@ using few::init_pair_lut;
 using few::pair_lookup_b;
 using few::work_index;
 
-// Up to this many tokens the forward main kernel reads the token operand as it lies and computes the adapter's partials
-// itself: the pre launch costs 5 - 8 us; the operand's scattered loads cost 1 us at 40 tokens and 12 us at 64.
-constexpr int kMidUnpacked = 48;
 constexpr int kSlab = 128;                   // outputs per workgroup
 // LDS map: the decode table stays for all segments of a workgroup; beside it the cross-wave sums
 constexpr int kRedMid = 64 * 1024, kMRed = kLutBytes;
@@ -240,8 +237,8 @@ __global__ __launch_bounds__(KW * 64) void mid_main_kernel(const MidArgs p) {
   const int work = work_index();
   if constexpr (!PACK) {
     if (work < p.n_items) {
-      if (p.mask) adapter_partial<KW, false, true>(p, work, (float*)smem);
-      else adapter_partial<KW, false, false>(p, work, (float*)smem);
+      if (!BWD && p.mask) adapter_partial<KW, BWD, !BWD>(p, work, (float*)smem);
+      else adapter_partial<KW, BWD, false>(p, work, (float*)smem);
       return;
     }
   }
@@ -760,12 +757,19 @@ void launch_main(const MidArgs& a, hipStream_t st) {
 }  // namespace
 
 namespace {
+// Forward, the token operand as it lies or packed by a launch of its own: kPackLaunch us for that launch, kScattered us per step
+// of a wave for the loads of 64-byte row pieces (backward operands are always packed).  Whole calls, us, as it lies / packed: 64 tokens
+// 1024 x 1024 12.1 / 18.6, 4096 x 4096 17.8 / 22.5, 8192 x 2048 19.2 / 27.5; 128 tokens 4096 x 4096 21.4 / 24.2; 256 tokens 1024 x 1024
+// 14.8 / 19.8; but 64 tokens 4096 x 11008 28.3 / 26.6, 80 tokens 8192 x 8192 40 / 34, 256 tokens 4096 x 4096 34 / 29.  Up to
+// kPackFrom tokens, one group of three tiles, packing never won (40 tokens 8192 x 8192 25.5 / 28.1).
+constexpr double kScattered = 0.24, kPackLaunch = 4.8;
+constexpr int kPackFrom = 48;
 // One of the launch shapes: kw = 4, one wave per SIMD with tiles of up to `group` = 128 or 64 tokens, or kw = 8, two waves
 // per SIMD with tiles of up to 64.  Per unit of work tiles of 128 tokens are fastest (a decoded fragment meets twice the
 // tokens); tiles of 64 have the cheaper fixed part and give a small layer twice the workgroups (dX of
 // 1024 x 1024 at 256 tokens: main kernel 16.5 -> 12.7 us with 128 workgroups instead of 64; 4096 x 4096 at 128 tokens, the
 // three kernels together: 37.1 -> 33.8; 4096 x 4096 at 512 tokens, where both fill the chip: 48.3, and 51.5 with 64).
-MidPlan plan_shape(bool bwd, int kw, int group, int64_t M, int64_t K, int64_t N, int r, size_t room, double* us) {
+MidPlan plan_shape(bool bwd, int kw, int group, bool pack, int64_t M, int64_t K, int64_t N, int r, size_t room, double* us) {
   MidPlan p{};
   const int n_tg = (int)((M + group - 1) / group);
   p.KW = kw;
@@ -774,7 +778,7 @@ MidPlan plan_shape(bool bwd, int kw, int group, int64_t M, int64_t K, int64_t N,
   p.n_tg = (int)((M + 16 * p.MF - 1) / (16 * p.MF));
   p.n_slabs = (int)((N + kSlab - 1) / kSlab);
   p.steps = (int)(bwd ? K / 64 : K / 32);
-  p.pack = bwd || M > kMidUnpacked;
+  p.pack = pack;
   // about ten partials of the adapter's inner product, of at least 512 contraction elements each
   p.chunk = (int)std::max<int64_t>(512, ((K + 9) / 10 + 63) / 64 * 64);
   p.n_lparts = r > 0 ? (int)((K + p.chunk - 1) / p.chunk) : 0;
@@ -792,7 +796,7 @@ MidPlan plan_shape(bool bwd, int kw, int group, int64_t M, int64_t K, int64_t N,
   // (4 token tiles 31.8 at 32); kw = 8 with 4 tiles 29.5 at 16, 66.8 at 43; a workgroup whose range crosses into a second tile pays a second end
   // (4096 x 11008 at 40 tokens: 21.3 with ranges that cross, 17.4 with every tile in two equal parts).  All in closed form:
   // a call plans on the host every time.
-  const double step = (bwd ? 2.0 : 1.0) * (kw == 4 ? 0.38 + 0.0775 * p.MF : 0.55 + 0.20 * p.MF);
+  const double step = (bwd ? 2.0 : 1.0) * ((kw == 4 ? 0.38 + 0.0775 * p.MF : 0.55 + 0.20 * p.MF) + (pack ? 0.0 : kScattered));
   const double seg_end = 2.0 + 0.75 * p.MF, tile_us = p.MF * 16 * kSlab * 4 / 4.0e6;
   const int64_t units = tiles * ups, most = std::min<int64_t>(256 - std::min(items, 128), units);
   const size_t one = (size_t)M * N * 4;
@@ -809,22 +813,24 @@ MidPlan plan_shape(bool bwd, int kw, int group, int64_t M, int64_t K, int64_t N,
 }
 }  // namespace
 
-MidPlan mid_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room) {
+MidPlan mid_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room, bool packed) {
   const int64_t K = bwd ? o : h, N = bwd ? h : o;
   if (M < 1 || M > kMidTokens || o > (1 << 24) || h > (1 << 24) || (M + 127) * K * 2 >= (1ll << 31) || h * o / 2 >= (1ll << 31))
     return MidPlan{};                                        // 32-bit buffer offsets
-  // the least estimated time; of equal ones the first
+  // the least estimated time, with the launch that packs the operand; of equal ones the first
   MidPlan best{};
   double best_us = 0;
-  auto consider = [&](int kw, int group) {
+  auto consider = [&](int kw, int group, bool pack) {
     double us = 0;
-    const MidPlan p = plan_shape(bwd, kw, group, M, K, N, r, room, &us);
-    if (p.ok && (!best.ok || us < best_us)) { best = p; best.us = best_us = us; }
+    const MidPlan p = plan_shape(bwd, kw, group, pack, M, K, N, r, room, &us);
+    const double all = us + (pack ? kPackLaunch : 0.0);
+    if (p.ok && (!best.ok || all < best_us)) { best = p; best.us = us; best_us = all; }
   };
-  if (!bwd) consider(8, 64);
-  if (bwd || M > kMidUnpacked) {
-    consider(4, 128);
-    if (M > 64) consider(4, 64);                             // below, tiles of 128 hold all tokens anyway
+  if (!bwd && !(packed && M > kPackFrom)) consider(8, 48, false);
+  if (bwd || M > kPackFrom) {
+    if (!bwd) consider(8, 64, true);
+    consider(4, 128, true);
+    if (M > 64) consider(4, 64, true);                       // below, tiles of 128 hold all tokens anyway
   }
   return best;
 }

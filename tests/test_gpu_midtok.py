@@ -165,3 +165,26 @@ def test_smallest_accepted_workspace(oracle, synth, M, h, o, r):
                 _check(host_bits(dL1), r1, "dL1", few_terms=M < 64)
                 _check(host_bits(dL2), r2, "dL2", few_terms=M < 64)
         assert int((ws[n:] != 0x7F).sum()) == 0
+
+
+@pytest.mark.parametrize("M", [52, 90, 113, 160, 333, 500])
+@pytest.mark.parametrize("h,o", [(4096, 11008), (1088, 1344)])
+def test_midtok_forward_packed_or_not(synth, M, h, o):
+    """The forward's token operand packed by a launch of its own (the large weight) and read as it lies, in several groups of
+    tokens (the small one), against fp64 products with the dequantised weight; the same with T saved, bit for bit."""
+    import paper_2305_14314_amd as ql
+    r, s = 48, 0.5
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4000 + M)
+    bf = lambda *shape, sd=1.0: torch.empty(shape, device="cuda").normal_(0, sd, generator=g).bfloat16()
+    Wq = ql.qlora_nf4_quantize(synth.normal_f32_device((h, o), synth.SIGMA_W, 4100 + M))
+    X, L1, L2 = bf(M, h), bf(h, r, sd=0.05), bf(r, o, sd=0.05)
+    Y = ql.qlora_linear_fwd(X, Wq, L1, L2, s)
+    T = torch.empty((M, 2 * r), dtype=torch.bfloat16, device="cuda")
+    Y2 = ql.qlora_linear_fwd(X, Wq, L1, L2, s, T_save=T)
+    t = X.double() @ L1.double()
+    ref = X.double() @ ql.qlora_nf4_dequant(Wq).double() + s * t @ L2.double()
+    _check(host_bits(Y), ref.cpu().numpy(), f"Y M={M}")
+    assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))
+    got = T[:, :r].double() + T[:, r:].double()               # 16 significant bits
+    assert (got - t).abs().max() <= 2.0 ** -14 * t.abs().max() + 1e-6
