@@ -614,8 +614,14 @@ qlora_status linear_fwd_impl(const uint16_t* X, const qlora_nf4_view* Wq, const 
   if (qlora_status st = check_linear(M, h, o, r)) return st;
   if (!X || !Y || !workspace) return QLORA_ERR_NULL;
   if (r > 0 && (!L1 || !L2)) return QLORA_ERR_NULL;
-  const FwdPlan p = plan_fwd(workspace, M, h, o, r, keep_mask == nullptr && streams_few(Wq));
+  FwdPlan p = plan_fwd(workspace, M, h, o, r, keep_mask == nullptr && streams_few(Wq));
   if (workspace_bytes < p.min_bytes) return QLORA_ERR_WORKSPACE;
+  if (p.few && streams_mid(Wq) && qlora::mid_beats_few(M, h, o, r)) {  // with the room that the size query reports; less streams as ever
+    const FwdPlan q = plan_fwd(workspace, M, h, o, r, false);
+    if (workspace_bytes >= q.bytes &&
+        plan_mid((char*)workspace + qlora::kWorkspaceHeaderBytes, q.bytes - qlora::kWorkspaceHeaderBytes, false, M, h, o, r).plan.ok)
+      p = q;
+  }
   if (!aligned16(X) || !aligned16(Y) || !aligned16(workspace) || !aligned16(L1) || !aligned16(L2) ||
       !aligned16(T_save))
     return QLORA_ERR_ALIGN;

@@ -195,6 +195,8 @@ struct MidPlan {
 MidPlan mid_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room, bool packed = false);
 // Is the plan worth taking, or is the weight dequantised and multiplied sooner?  fix: that path would need the dropout fix-up.
 bool mid_pays(const MidPlan& p, bool bwd, int64_t M, int64_t h, int64_t o, int r, bool fix);
+// Forward at up to kFewTokens tokens: is this path sooner done than the streaming kernel (fewtok.hip)?
+bool mid_beats_few(int64_t M, int64_t h, int64_t o, int r);
 //   forward: out (M x o) = X dequant(W) + scale (mask o X L1) L2, hl (M x 2r or NULL) = [hi | lo] of mask o X L1;
 //   backward: X is dY (M x o), out (M x h) = dY dequant(W)^T + scale mask o ((dY L2^T) L1^T), hl = [hi | lo] of dY L2^T.
 //   mask: keep-bits over M x h elements, or NULL.

@@ -580,10 +580,12 @@ struct MidFinArgs {
   const uint8_t* mask;                       // backward under LoRA dropout: keep-bits of the output elements, or NULL
 };
 
-template <int TF, bool BWD, bool LEAN>
+// TERMS: bf16 terms of T.  Two carry 16 significant bits; at few tokens, where the streaming kernels multiply the fp32 value, three
+// hold it whole (3 x 8 bits).
+template <int TF, bool BWD, bool LEAN, int TERMS>
 __global__ __launch_bounds__(256) void mid_finalize_kernel(const MidFinArgs p) {
   constexpr int kPitch = 256 + 8;
-  __shared__ __attribute__((aligned(16))) uint16_t Th[16 * TF * kPitch], Tl[16 * TF * kPitch];
+  __shared__ __attribute__((aligned(16))) uint16_t Tp[TERMS][16 * TF * kPitch];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int i = lane & 15, g = lane >> 4;
   const int m0 = blockIdx.y * 16 * TF;
@@ -678,15 +680,18 @@ __global__ __launch_bounds__(256) void mid_finalize_kernel(const MidFinArgs p) {
         t_load(idx, q0);
       }
       if (!ok) t = f32x4{0.f, 0.f, 0.f, 0.f};
-      uint2 hi, lo;
-      hi.x = pack_bf16x2(t[0], t[1]); hi.y = pack_bf16x2(t[2], t[3]);
-      lo.x = pack_bf16x2(t[0] - bf16_lo_to_f32(hi.x), t[1] - bf16_hi_to_f32(hi.x));
-      lo.y = pack_bf16x2(t[2] - bf16_lo_to_f32(hi.y), t[3] - bf16_hi_to_f32(hi.y));
-      *(uint2*)(Th + ml * kPitch + 4 * c) = hi;
-      *(uint2*)(Tl + ml * kPitch + 4 * c) = lo;
+      uint2 term[TERMS];
+#pragma unroll
+      for (int k = 0; k < TERMS; ++k) {
+        term[k].x = pack_bf16x2(t[0], t[1]);
+        term[k].y = pack_bf16x2(t[2], t[3]);
+        t[0] -= bf16_lo_to_f32(term[k].x); t[1] -= bf16_hi_to_f32(term[k].x);
+        t[2] -= bf16_lo_to_f32(term[k].y); t[3] -= bf16_hi_to_f32(term[k].y);
+        *(uint2*)(Tp[k] + ml * kPitch + 4 * c) = term[k];
+      }
       if (ok && p.hl && blockIdx.x == 0) {
-        *(uint2*)(p.hl + (int64_t)m * 2 * p.r + 4 * c) = hi;
-        *(uint2*)(p.hl + (int64_t)m * 2 * p.r + p.r + 4 * c) = lo;
+        *(uint2*)(p.hl + (int64_t)m * 2 * p.r + 4 * c) = term[0];
+        *(uint2*)(p.hl + (int64_t)m * 2 * p.r + p.r + 4 * c) = term[1];
       }
     }
     __syncthreads();
@@ -706,13 +711,14 @@ __global__ __launch_bounds__(256) void mid_finalize_kernel(const MidFinArgs p) {
         if (t0 + 32 * RB < p.r) b_load(bf[k], t0 + 32 * RB);
 #pragma unroll
         for (int f = 0; f < TF; ++f) {
-          const bf16x8 th = *(const bf16x8*)(Th + (16 * f + i) * kPitch + t0 + 8 * g);
-          const bf16x8 tl = *(const bf16x8*)(Tl + (16 * f + i) * kPitch + t0 + 8 * g);
+          bf16x8 tt[TERMS];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            lora[f][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(th, __builtin_bit_cast(bf16x8, w[e]), lora[f][e], 0, 0, 0);
-            lora[f][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tl, __builtin_bit_cast(bf16x8, w[e]), lora[f][e], 0, 0, 0);
-          }
+          for (int k2 = 0; k2 < TERMS; ++k2) tt[k2] = *(const bf16x8*)(Tp[k2] + (16 * f + i) * kPitch + t0 + 8 * g);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int k2 = 0; k2 < TERMS; ++k2)
+              lora[f][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tt[k2], __builtin_bit_cast(bf16x8, w[e]), lora[f][e], 0, 0, 0);
         }
       }
     }
@@ -851,6 +857,18 @@ bool mid_pays(const MidPlan& p, bool bwd, int64_t M, int64_t h, int64_t o, int r
   return mid <= 1.2 * gemm;
 }
 
+// Up to 16 tokens the streaming kernel reads the weight once and ends in an output stage of its own; two launches here, but a
+// decode that all tokens share and an output stage on many workgroups.  Forward calls, us, streamed / here (rank 64 but where
+// stated): 1024 x 1024 rank 16 at 3, 8, 16 tokens 10.7 / 10.0, 12.1 / 10.1, 14.5 / 10.3; 2048 x 2048 rank 16 at 6, 11, 16
+// 11.6 / 10.9, 12.8 / 11.0, 14.5 / 11.1; 4096 x 4096 at 8, 11, 16 14.0 / 14.4, 14.5 / 14.4, 16.2 / 14.8; 4096 x 11008 at 14, 16
+// 18.4 / 16.3, 19.2 / 16.5; 1024 x 16384 at 8, 11, 16 13.6 / 13.3, 14.5 / 13.5, 16.0 / 13.7; 8192 x 8192 at 12 19.9 / 20.0.  A
+// contraction longer than the outputs are wide has too few strips (3072 x 1536 at 4, 11 11.6 / 12.7, 13.2 / 13.4), and a large rank
+// makes the adapter's launch the longer part (2048 x 2048 rank 256 at 4, 11 22.7 / 23.9, 24.8 / 24.9).  So: above
+// sqrt(4 weights / 2^20) tokens, contraction no longer than the outputs, rank up to 128.
+bool mid_beats_few(int64_t M, int64_t h, int64_t o, int r) {
+  return h <= o && r <= 128 && (double)(M * M) > 4. * (double)h * (double)o / (1 << 20) && M >= 3;
+}
+
 hipError_t launch_mid(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const MidPlan& p, const uint16_t* L1,
                       const uint16_t* L2, int r, float scale, const uint8_t* mask, float* part, float* lpart, uint16_t* xpack,
                       uint16_t* out, uint16_t* hl, hipStream_t st) {
@@ -911,7 +929,12 @@ hipError_t launch_mid(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const
   const bool two = (int64_t)gx * ((M + 31) / 32) >= 1024;
   const dim3 grid(gx, (unsigned)(two ? (M + 31) / 32 : (M + 15) / 16));
   const bool lean = grid.x * grid.y > kLeanBlocks;
-  auto launch = [&](auto T, auto D, auto L) { hipLaunchKernelGGL((mid_finalize_kernel<T.value, D.value, L.value>), grid, dim3(256), 0, st, f); };
+  if (!bwd && M <= 16) {
+    if (lean) hipLaunchKernelGGL((mid_finalize_kernel<1, false, true, 3>), grid, dim3(256), 0, st, f);
+    else hipLaunchKernelGGL((mid_finalize_kernel<1, false, false, 3>), grid, dim3(256), 0, st, f);
+    return hipGetLastError();
+  }
+  auto launch = [&](auto T, auto D, auto L) { hipLaunchKernelGGL((mid_finalize_kernel<T.value, D.value, L.value, 2>), grid, dim3(256), 0, st, f); };
   auto pick = [&](auto T, auto D) { if (lean) launch(T, D, std::true_type{}); else launch(T, D, std::false_type{}); };
   if (two) { if (bwd) pick(Int<2>{}, std::true_type{}); else pick(Int<2>{}, std::false_type{}); }
   else     { if (bwd) pick(Int<1>{}, std::true_type{}); else pick(Int<1>{}, std::false_type{}); }

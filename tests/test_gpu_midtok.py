@@ -188,3 +188,31 @@ def test_midtok_forward_packed_or_not(synth, M, h, o):
     assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))
     got = T[:, :r].double() + T[:, r:].double()               # 16 significant bits
     assert (got - t).abs().max() <= 2.0 ** -14 * t.abs().max() + 1e-6
+
+
+@pytest.mark.parametrize("M", [3, 9, 16])
+@pytest.mark.parametrize("h,o,r", [(1024, 1024, 0), (1088, 1344, 48), (1024, 1024, 128), (2048, 4096, 64)])
+def test_few_tokens_forward_decoded_once(synth, M, h, o, r):
+    """Up to 16 tokens on a small weight, forward: with the reported workspace (several tokens: decoded once for all of them)
+    and with the smallest that the streaming kernel takes, both against fp64 products with the dequantised weight.  T is a
+    sum of h terms of which neither path drops bits, so the two agree to one rounding of the result and the order of the sums."""
+    import paper_2305_14314_amd as ql
+    s = 2.0
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5000 + M + r)
+    bf = lambda *shape, sd=1.0: torch.empty(shape, device="cuda").normal_(0, sd, generator=g).bfloat16()
+    Wq = ql.qlora_nf4_quantize(synth.normal_f32_device((h, o), synth.SIGMA_W, 5100 + M))
+    X, L1, L2 = bf(M, h), (bf(h, r, sd=0.05) if r else None), (bf(r, o, sd=0.05) if r else None)
+    small = accepted_workspace(ql.binding.lib(), False, M, h, o, r)
+    T = torch.empty((M, 2 * r), dtype=torch.bfloat16, device="cuda") if r else None
+    Y = ql.qlora_linear_fwd(X, Wq, L1, L2, s, T_save=T)
+    ws = torch.zeros(small, dtype=torch.uint8, device="cuda")
+    Ys = ql.qlora_linear_fwd(X, Wq, L1, L2, s, workspace=ws)
+    ref = X.double() @ ql.qlora_nf4_dequant(Wq).double()
+    if r:
+        t = X.double() @ L1.double()
+        ref = ref + s * t @ L2.double()
+        got = T[:, :r].double() + T[:, r:].double()
+        assert (got - t).abs().max() <= 2.0 ** -14 * t.abs().max() + 1e-6
+    _check(host_bits(Y), ref.cpu().numpy(), f"Y M={M}")
+    _check(host_bits(Ys), ref.cpu().numpy(), f"Y, smallest workspace, M={M}")
