@@ -174,7 +174,8 @@ hipError_t launch_workspace_init(void* workspace, hipStream_t st);
 // Up to kMidTokens mid_pays() weighs a plan against dequantise + GEMM; above, that path is taken unweighed.  There neither is
 // better everywhere (us at rank 64, dequantised / decoded inside; K x N at tokens): 4096 x 4096 at 576 forward 58.6 / 55.4, dX
 // 57.0 / 62.1; 5120 x 13824 at 576 119 / 147, at 1024 143 / 267; 8192 x 8192 at 768 121 / 137; but 22016 x 8192 at 768
-// 439 / 306.  The estimate is fitted to calls of up to 512 tokens.
+// 439 / 306.  Those are of one weight called again and again; with three in turn and today's tiles the dequantised
+// ones take 44.5, 42.0 (128 x 128 tiles; 56.9, 55.0 without), 137, 154, 169 and 426.  The estimate is fitted to calls of up to 512 tokens.
 constexpr int kMidTokens = 512;
 // `units` units in tiles of `ups`, cut into `wgs` ranges whose sizes differ by at most one.
 struct MidLine {

@@ -5,7 +5,7 @@
 // Why its own path: with 256 x 256 tiles a product of a few hundred tokens has 4 .. 100 tiles for 256 compute units, and
 // the pass that dequantises the weight moves five times the bytes of the packed weight (2.5 against 0.5 per weight).
 // Whole forward call, dequantise + GEMM against this: 4096 x 11008 at 40 tokens 108 -> 20 us, 5120 x 13824 at 333 tokens
-// 158 -> 87 us; forward + backward 1024 x 1024 at 256 tokens 96 -> 48 us, 4096 x 4096 at 512 tokens 220 -> 99 us.
+// 158 -> 85 us; forward + backward 1024 x 1024 at 256 tokens 96 -> 42 us, 4096 x 4096 at 512 tokens 220 -> 99 us.
 //
 // Two or three launches on the caller's stream:
 //   pre       (where the plan finds it worth a launch) the token operand in MFMA-fragment order, so that the main kernel's operand
@@ -845,8 +845,10 @@ MidPlan mid_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room, 
 // 22016, 64 .. 65536 outputs, ranks 0 .. 256; each estimate within 20 % on nine calls of ten).  Decoding inside the product
 // loses where the contraction is short (its partials are then as large as the product: dX with K = 64, N = 16384 at 384 tokens
 // 43 us against 12) or the rank large (K = 1024, N = 8192, rank 256 at 512 tokens 66 against 32); it wins where the weight is
-// what counts (K = 22016, N = 8192, rank 64 at 256 tokens 117 against 421).  Both paths have become faster
-// since by about the same (2 - 4 us here, tiles of 128 x 128 there); the line stays where the fit put it.  Near the line either will do: a call goes to the
+// what counts (K = 22016, N = 8192, rank 64 at 256 tokens 117 against 421).  The fit is older than the tiles of 128 x 128
+// and today's line is not the fastest one: with K up to about 3000 at 100 - 512 tokens the other path is now as fast or faster
+// (dX 2752 x 3136, rank 144, 511 tokens 53.8 here, 35.1 dequantised).  Those calls stay here because the tests of this path hold them
+// to it (mid_choice_check.cpp, test_midtok_is_reached).  Near the line either will do: a call goes to the
 // other path where that is faster by a fifth, so that seven of the fitted calls lose more than 3 % by it, the worst 20 %.
 bool mid_pays(const MidPlan& p, bool bwd, int64_t M, int64_t h, int64_t o, int r, bool fix) {
   const double K = (double)(bwd ? o : h), N = (double)(bwd ? h : o), MN = 1e-6 * (double)M * N;
