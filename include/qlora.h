@@ -239,7 +239,7 @@ qlora_status qlora_linear_bwd_sizes(int64_t M, int64_t h, int64_t o, int32_t r, 
  * r must be a multiple of 16 and at most 256.  T_save (M x 2r bf16, may be NULL)
  * receives T = X * L1 for the backward pass as a pair of bf16 matrices side by
  * side: columns [0, r) hold bf16(T), columns [r, 2r) hold bf16(T - bf16(T)).  Any M >= 1 is accepted: a few
- * tokens (M <= 16) take a bandwidth-bound streaming path -- several of them on a small weight, with the reported workspace,
+ * tokens (M <= 16) take a bandwidth-bound streaming path -- 12 or more of them on a small weight, with the reported workspace,
  * already the next --, up to 512 a product that decodes the weight itself unless an estimate says that the next is faster
  * (short contractions, large ranks), larger M the MFMA GEMM on a dequantised copy. */
 qlora_status qlora_linear_fwd(const uint16_t* X, const qlora_nf4_view* Wq,

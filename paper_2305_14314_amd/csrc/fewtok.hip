@@ -2,7 +2,7 @@
 // Eq. 5 / Eq. 6 at generation-time batch sizes): bandwidth-bound streaming kernels that read the
 // packed NF4 weight and its double-quantised constants exactly once (0.516 B per weight),
 // dequantise in registers to the same bf16 values as the standalone doubleDequant, and feed
-// MFMA 16x16x32 with the tokens as the 16-wide dimension.  (A forward of several tokens on a small weight takes midtok.hip where
+// MFMA 16x16x32 with the tokens as the 16-wide dimension.  (A forward of 12 tokens or more on a small weight takes midtok.hip where
 // mid_beats_few() says so.)  One launch per call:
 //
 //   main workgroups    : part[split][m][n] = partial sums of X * What (forward) or dY * What^T (backward)

@@ -865,10 +865,12 @@ bool mid_pays(const MidPlan& p, bool bwd, int64_t M, int64_t h, int64_t o, int r
 // 11.6 / 10.9, 12.8 / 11.0, 14.5 / 11.1; 4096 x 4096 at 8, 11, 16 14.0 / 14.4, 14.5 / 14.4, 16.2 / 14.8; 4096 x 11008 at 14, 16
 // 18.4 / 16.3, 19.2 / 16.5; 1024 x 16384 at 8, 11, 16 13.6 / 13.3, 14.5 / 13.5, 16.0 / 13.7; 8192 x 8192 at 12 19.9 / 20.0.  A
 // contraction longer than the outputs are wide has too few strips (3072 x 1536 at 4, 11 11.6 / 12.7, 13.2 / 13.4), and a large rank
-// makes the adapter's launch the longer part (2048 x 2048 rank 256 at 4, 11 22.7 / 23.9, 24.8 / 24.9).  So: above
-// sqrt(4 weights / 2^20) tokens, contraction no longer than the outputs, rank up to 128.
+// makes the adapter's launch the longer part (2048 x 2048 rank 256 at 4, 11 22.7 / 23.9, 24.8 / 24.9).  And two launches cost the host
+// 12.5 us a call against 9.2: called one by one, 1024 x 2624 rank 32 at 5 tokens takes 11.5 streamed and 12.6 here, 2048 x 2048 at
+// 8, 11, 14 12.6 / 12.6, 13.4 / 12.8, 14.5 / 12.7, 1024 x 1024 at 16 15.0 / 12.8.  So: from 12 tokens, where any layer streams for
+// longer than that, and above sqrt(4 weights / 2^20), contraction no longer than the outputs, rank up to 128.
 bool mid_beats_few(int64_t M, int64_t h, int64_t o, int r) {
-  return h <= o && r <= 128 && (double)(M * M) > 4. * (double)h * (double)o / (1 << 20) && M >= 3;
+  return h <= o && r <= 128 && (double)(M * M) > 4. * (double)h * (double)o / (1 << 20) && M >= 12;
 }
 
 hipError_t launch_mid(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const MidPlan& p, const uint16_t* L1,

@@ -190,7 +190,7 @@ def test_midtok_forward_packed_or_not(synth, M, h, o):
     assert (got - t).abs().max() <= 2.0 ** -14 * t.abs().max() + 1e-6
 
 
-@pytest.mark.parametrize("M", [3, 9, 16])
+@pytest.mark.parametrize("M", [3, 9, 11, 12, 16])
 @pytest.mark.parametrize("h,o,r", [(1024, 1024, 0), (1088, 1344, 48), (1024, 1024, 128), (2048, 4096, 64)])
 def test_few_tokens_forward_decoded_once(synth, M, h, o, r):
     """Up to 16 tokens on a small weight, forward: with the reported workspace (several tokens: decoded once for all of them)
