@@ -262,6 +262,33 @@ __device__ void lora_bwd_partial(const FewArgs& p, int wg, float* red /* [NT / 6
   }
 }
 
+// Four fp32 values as three bf16 terms each whose sum they are (3 x 8 bits hold fp32's 24), cut off rather than rounded: every
+// term has its value's sign, and none overflows where the value does not.  What has nothing left to hold takes 2^-40 of the
+// value instead of zero, far below fp32's last bit: an infinite value, or an infinite factor, then gives the infinity that
+// the product with the fp32 value gives, where Inf - Inf and 0 * Inf gave NaN.
+__device__ __forceinline__ void split3(f32x4 t, uint2 (&term)[3]) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const u32x4 b = __builtin_bit_cast(u32x4, t);
+    term[k].x = __builtin_amdgcn_perm(b[1], b[0], 0x07060302u);
+    term[k].y = __builtin_amdgcn_perm(b[3], b[2], 0x07060302u);
+    if (k < 2) {
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        const float rest = t[d] - __builtin_bit_cast(float, b[d] & 0xffff0000u);
+        t[d] = __builtin_fabsf(rest) > 0.0f ? rest : t[d] * 0x1p-40f;   // no rest: zero, or Inf - Inf
+      }
+    }
+  }
+}
+// Four fp32 values as [hi | lo] bf16 pairs, both rounded (16 significant bits): what is saved of T.
+__device__ __forceinline__ void split_hl(f32x4 t, uint2& hi, uint2& lo) {
+  hi.x = pack_bf16x2(t[0], t[1]);
+  hi.y = pack_bf16x2(t[2], t[3]);
+  lo.x = pack_bf16x2(t[0] - bf16_lo_to_f32(hi.x), t[1] - bf16_hi_to_f32(hi.x));
+  lo.y = pack_bf16x2(t[2] - bf16_lo_to_f32(hi.y), t[3] - bf16_hi_to_f32(hi.y));
+}
+
 // ---- output stage ---------------------------------------------------------------------------------
 // An arrival's outcome: others are still to come (0); the last one; ... and the adapter's partials are all there.
 constexpr int kLast = 1, kReady = 2;
@@ -276,7 +303,7 @@ constexpr int kLast = 1, kReady = 2;
 // for its share of the outputs in MFMA layout (4 of 64 lanes with a value at one token) the requests alone took 1.7 us.
 // `meet`: the adapter's workgroups are not known to be done; `met` waits for them, and what was read of T before is read
 // again (false: they come later and finish the slab).  The adapter's product runs on MFMA 16x16x32, a wave 16 (NT = 512: 32)
-// outputs: T is split exactly into three bf16 terms (3 x 8 bits hold fp32's 24), so its products with the bf16 matrix are
+// outputs: T travels as three bf16 terms that hold all of it (split3), so its products with the bf16 matrix are
 // those of the fp32 value, summed in fp32.  Weight side first: lane (i, g) ends with the four neighbouring outputs 4g .. 4g+3
 // of token i.
 constexpr int kTileRanks = 64;               // ranks staged at a time
@@ -367,17 +394,16 @@ __device__ __forceinline__ void output_stage(const FewArgs& p, int slab, const f
       }
       if (!t_lane) t = f32x4{0.f, 0.f, 0.f, 0.f};
       uint2 term[3];
+      split3(t, term);
+      if (4 * lane < rp) {
 #pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        term[k].x = pack_bf16x2(t[0], t[1]);
-        term[k].y = pack_bf16x2(t[2], t[3]);
-        t[0] -= bf16_lo_to_f32(term[k].x); t[1] -= bf16_hi_to_f32(term[k].x);
-        t[2] -= bf16_lo_to_f32(term[k].y); t[3] -= bf16_hi_to_f32(term[k].y);
-        if (4 * lane < rp) *(uint2*)(Tp + k * kTPlane + m * kTPitch + 4 * lane) = term[k];
+        for (int k = 0; k < 3; ++k) *(uint2*)(Tp + k * kTPlane + m * kTPitch + 4 * lane) = term[k];
       }
       if (p.hl && slab == 0 && t_lane) {
-        *(uint2*)(p.hl + (int64_t)m * 2 * p.r + 4 * lane) = term[0];
-        *(uint2*)(p.hl + (int64_t)m * 2 * p.r + p.r + 4 * lane) = term[1];
+        uint2 hi, lo;
+        split_hl(t, hi, lo);
+        *(uint2*)(p.hl + (int64_t)m * 2 * p.r + 4 * lane) = hi;
+        *(uint2*)(p.hl + (int64_t)m * 2 * p.r + p.r + 4 * lane) = lo;
       }
     }
   }

@@ -580,6 +580,12 @@ struct MidFinArgs {
   const uint8_t* mask;                       // backward under LoRA dropout: keep-bits of the output elements, or NULL
 };
 
+// An infinite hi is the whole value: what is left of it is NaN (or, of a value that rounded up to infinity, -Inf).  Two bf16 per dword.
+__device__ __forceinline__ uint32_t lo_of_finite(uint32_t hi, uint32_t lo) {
+  const uint32_t m = ((hi & 0x7f807f80u) + 0x00800080u) & 0x80008000u;      // the exponent is all ones
+  return lo & ~((m - (m >> 15)) | m);
+}
+
 // TERMS: bf16 terms of T.  Two carry 16 significant bits; at few tokens, where the streaming kernels multiply the fp32 value, three
 // hold it whole (3 x 8 bits).
 template <int TF, bool BWD, bool LEAN, int TERMS>
@@ -680,18 +686,19 @@ __global__ __launch_bounds__(256) void mid_finalize_kernel(const MidFinArgs p) {
         t_load(idx, q0);
       }
       if (!ok) t = f32x4{0.f, 0.f, 0.f, 0.f};
+      uint2 hi, lo;
+      few::split_hl(t, hi, lo);
       uint2 term[TERMS];
-#pragma unroll
-      for (int k = 0; k < TERMS; ++k) {
-        term[k].x = pack_bf16x2(t[0], t[1]);
-        term[k].y = pack_bf16x2(t[2], t[3]);
-        t[0] -= bf16_lo_to_f32(term[k].x); t[1] -= bf16_hi_to_f32(term[k].x);
-        t[2] -= bf16_lo_to_f32(term[k].y); t[3] -= bf16_hi_to_f32(term[k].y);
-        *(uint2*)(Tp[k] + ml * kPitch + 4 * c) = term[k];
+      if constexpr (TERMS == 3) few::split3(t, term);
+      else {
+        term[0] = hi;
+        term[1] = uint2{lo_of_finite(hi.x, lo.x), lo_of_finite(hi.y, lo.y)};
       }
+#pragma unroll
+      for (int k = 0; k < TERMS; ++k) *(uint2*)(Tp[k] + ml * kPitch + 4 * c) = term[k];
       if (ok && p.hl && blockIdx.x == 0) {
-        *(uint2*)(p.hl + (int64_t)m * 2 * p.r + 4 * c) = term[0];
-        *(uint2*)(p.hl + (int64_t)m * 2 * p.r + p.r + 4 * c) = term[1];
+        *(uint2*)(p.hl + (int64_t)m * 2 * p.r + 4 * c) = hi;
+        *(uint2*)(p.hl + (int64_t)m * 2 * p.r + p.r + 4 * c) = lo;
       }
     }
     __syncthreads();
