@@ -26,7 +26,6 @@
 // kernel raises the header's sticky status word, which qlora_workspace_check reports.  Every wait is a bounded
 // poll, so all waves exit whatever the header held.
 #include <algorithm>
-#include <vector>
 
 #include "fewtok_common.hpp"
 
@@ -697,7 +696,7 @@ ListPlan fewlist_plan(bool bwd, int M, int n, const int* h, const int* o, const 
   ListPlan P{};
   if (n < 1 || n > kListMax || M < 1 || M > kFewTokens) return P;
   int64_t units = 0;
-  int adapters = 0, slabs = 0, ups_max = 1;
+  int adapters = 0, slabs = 0;
   for (int l = 0; l < n; ++l) {
     const int outs = bwd ? h[l] : o[l], contr = bwd ? o[l] : h[l];
     P.n_slabs[l] = (outs + 255) / 256;
@@ -705,7 +704,6 @@ ListPlan fewlist_plan(bool bwd, int M, int n, const int* h, const int* o, const 
     P.unit0[l] = (int)units;
     units += (int64_t)P.n_slabs[l] * P.ups[l];
     if (units >= (1ll << 30)) return P;
-    ups_max = std::max(ups_max, P.ups[l]);
     // adapter items: at most 23 per layer (bits 0 .. 22 of a handshake word), at least kLoraK contraction elements each
     int chunk = kListLoraChunk;
     if (r[l] > 0 && (contr + chunk - 1) / chunk > 23) chunk = ((contr + 22) / 23 + 63) / 64 * 64;
@@ -726,57 +724,77 @@ ListPlan fewlist_plan(bool bwd, int M, int n, const int* h, const int* o, const 
   // smallest bound T for which a greedy walk (every workgroup takes what fits under T) covers the line with `grid`
   // workgroups.
   const ListCosts costs = (compact ? kListCostsCompact : kListCosts)[bwd];
-  const int kTail = costs.tail, kFin = costs.stage, kItem = costs.item;
-  std::vector<int> slab_end;                                 // ascending unit index where each slab ends
-  for (int l = 0; l < n; ++l)
-    for (int sidx = 0; sidx < P.n_slabs[l]; ++sidx) slab_end.push_back(P.unit0[l] + (sidx + 1) * P.ups[l]);
-  auto walk = [&](int grid, int64_t T, int* start) -> bool { // fills start[0 .. grid] when it returns true
-    int u = 0, next_end = 0;                                 // next_end: index of the first slab that ends after u
-    for (int rho = 0; rho < grid; ++rho) {
-      if (start) start[rho] = u;
-      const int items = rho < adapters ? (adapters - rho + grid - 1) / grid : 0;
-      int64_t budget = T - (int64_t)kItem * items;
+  const int kTail = costs.tail, kFin = costs.stage, kItem = costs.item, slab_cost = kTail + kFin;
+  auto walk = [&](ListPart& q, int T) -> bool {              // fills q.start; true: the ranges cover the line
+    const int item_rounds = adapters / q.grid, item_rest = adapters % q.grid;
+    int u = 0, l = 0, ups = P.ups[0], s_begin = 0, left = P.n_slabs[0];   // the slab that holds u; slabs of its layer from it on
+    auto next_slab = [&] {
+      s_begin += ups;
+      if (--left == 0 && ++l < n) { ups = P.ups[l]; left = P.n_slabs[l]; }
+    };
+    for (int rho = 0; rho < q.grid; ++rho) {
+      q.start[rho] = u;
+      int budget = T - kItem * (item_rounds + (rho < item_rest));
       bool took = false;
       while (u < (int)units && budget > 0) {
-        while (slab_end[next_end] <= u) ++next_end;
-        const int s_begin = next_end == 0 ? 0 : slab_end[next_end - 1];
-        const int64_t overhead = kTail + (u == s_begin ? kFin : 0);
+        const bool first = u == s_begin;
+        const int overhead = kTail + (first ? kFin : 0), whole = ups + slab_cost;
         if (budget <= overhead) {                            // not worth another segment; but nobody with a budget leaves empty-handed
-          if (!took) { ++u; took = true; }
+          if (!took && ++u == s_begin + ups) next_slab();
           break;
         }
-        const int64_t room = budget - overhead;
-        const int to_end = slab_end[next_end] - u;
-        const int take = room >= to_end ? to_end : (int)room;
-        u += take; budget -= overhead + take; took = true;
+        if (first && left > 1 && budget >= 2 * whole) {      // whole slabs of one layer at once
+          const int k = std::min(budget / whole, left - 1);
+          u += k * ups; s_begin += k * ups; left -= k; budget -= k * whole;
+        } else {
+          const int take = std::min(budget - overhead, s_begin + ups - u);
+          u += take; budget -= overhead + take;
+          if (u == s_begin + ups) next_slab();
+        }
+        took = true;
       }
     }
-    if (start) start[grid] = (int)units;
+    q.start[q.grid] = (int)units;
     return u >= (int)units;
   };
+  const int all = (int)(units + (int64_t)slab_cost * slabs + (int64_t)kItem * adapters + 1);   // one workgroup covers the line with it
   // fewer workgroups than compute units when there is less than one unit each, or when a slab would otherwise be
   // shared by more workgroups than an arrival word has bits for
+  ListPart best{}, probe{};
+  best.n_adapter = probe.n_adapter = adapters;
+  int lo = 0;
   for (int grid = (int)std::min<int64_t>(kListGridMax, units); grid >= 1; grid = grid > 32 ? grid - 32 : grid - 1) {
-    ListPart q{};
-    q.grid = grid;
-    q.n_adapter = adapters;
-    int64_t lo = 0, hi = units + (int64_t)(kTail + kFin) * slabs + (int64_t)kItem * adapters + 1;   // walk(hi) succeeds with one workgroup
-    while (hi - lo > 1) {
-      const int64_t mid = (lo + hi) / 2;
-      if (walk(grid, mid, nullptr)) hi = mid; else lo = mid;
+    // A larger T never covers less, and one above an even share by what a workgroup can lose -- a begun slab's second tail, a
+    // rest too short for a segment -- covers the line.  Halving between the share and that takes 8 walks a call, each as
+    // long as the line has segments (from 0 and `all` about 20: 36 and 29 us of host time for the seven linears of a 65B-shaped
+    // block, forward and backward, against 11 and 5; 22 and 17 against 8 and 5 for a 7B-shaped one, whose kernels take 40).
+    // Fewer workgroups do not cover more: a smaller grid goes on from the bound of the one before, in growing steps.
+    best.grid = probe.grid = grid;
+    int hi = std::min(all, (all + grid - 1) / grid + 2 * kTail + kFin);   // walk(lo) leaves something undone, walk(hi) nothing
+    bool filled = false;
+    int64_t step = lo > 0 ? 1 : all;
+    for (int T = std::max(all / grid, lo + 1); hi - lo > 1; step *= 2) {
+      if (T >= hi) T = lo + (hi - lo) / 2;
+      if (walk(probe, T)) { hi = T; std::swap(best, probe); filled = true; }
+      else lo = T;
+      T = lo + (int)std::min<int64_t>(step, (hi - lo) / 2);
     }
-    walk(grid, hi, q.start);
-    int worst = 1;
+    if (!filled) walk(best, hi);
+    int worst = 1, rho = 0;
     for (int l = 0; l < n; ++l) {
       int mc = 1;
-      for (int s = 0; s < P.n_slabs[l]; ++s) {
-        const int U0 = P.unit0[l] + s * P.ups[l];
-        mc = std::max(mc, list_rho_of(q, U0 + P.ups[l] - 1) - list_rho_of(q, U0) + 1);
+      for (int s = 0; s < P.n_slabs[l]; ++s) {               // list_rho_of() of the slab's first and last unit, both ascending
+        const int U0 = P.unit0[l] + s * P.ups[l], U1 = U0 + P.ups[l] - 1;
+        while (rho + 1 < grid && best.start[rho + 1] <= U0) ++rho;
+        const int first = rho;
+        while (rho + 1 < grid && best.start[rho + 1] <= U1) ++rho;
+        mc = std::max(mc, rho - first + 1);
       }
       P.max_contrib[l] = mc;
       worst = std::max(worst, mc);
     }
-    if (worst <= 23) { P.part = q; P.ok = true; break; }
+    if (worst <= 23) { P.part = best; P.ok = true; break; }
+    lo = hi - 1;
   }
   if (!P.ok) return P;
   for (int l = 0; l < n; ++l) {
