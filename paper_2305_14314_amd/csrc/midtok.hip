@@ -590,6 +590,7 @@ __device__ __forceinline__ uint32_t lo_of_finite(uint32_t hi, uint32_t lo) {
 // hold it whole (3 x 8 bits).
 template <int TF, bool BWD, bool LEAN, int TERMS>
 __global__ __launch_bounds__(256) void mid_finalize_kernel(const MidFinArgs p) {
+  static_assert(LEAN || TF == 1, "two token tiles only where there are many workgroups");
   constexpr int kPitch = 256 + 8;
   __shared__ __attribute__((aligned(16))) uint16_t Tp[TERMS][16 * TF * kPitch];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -937,6 +938,7 @@ hipError_t launch_mid(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const
   f.part = part; f.line = p.line; f.MF = p.MF; f.n_tg = p.n_tg; f.M = M; f.N = a.N; f.lpart = lpart; f.n_lparts = a.n_lparts; f.r = r;
   f.B = bwd ? L1 : L2; f.scale = scale; f.out = out; f.hl = r > 0 ? hl : nullptr; f.mask = bwd ? mask : nullptr;
   const unsigned gx = (unsigned)((a.N + 255) / 256);
+  static_assert(kLeanBlocks < 1024, "two token tiles: lean");
   const bool two = (int64_t)gx * ((M + 31) / 32) >= 1024;
   const dim3 grid(gx, (unsigned)(two ? (M + 31) / 32 : (M + 15) / 16));
   const bool lean = grid.x * grid.y > kLeanBlocks;
@@ -946,9 +948,12 @@ hipError_t launch_mid(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const
     return hipGetLastError();
   }
   auto launch = [&](auto T, auto D, auto L) { hipLaunchKernelGGL((mid_finalize_kernel<T.value, D.value, L.value, 2>), grid, dim3(256), 0, st, f); };
-  auto pick = [&](auto T, auto D) { if (lean) launch(T, D, std::true_type{}); else launch(T, D, std::false_type{}); };
-  if (two) { if (bwd) pick(Int<2>{}, std::true_type{}); else pick(Int<2>{}, std::false_type{}); }
-  else     { if (bwd) pick(Int<1>{}, std::true_type{}); else pick(Int<1>{}, std::false_type{}); }
+  auto pick = [&](auto D) {
+    if (two) launch(Int<2>{}, D, std::true_type{});          // 1024 workgroups and more
+    else if (lean) launch(Int<1>{}, D, std::true_type{});
+    else launch(Int<1>{}, D, std::false_type{});
+  };
+  if (bwd) pick(std::true_type{}); else pick(std::false_type{});
   return hipGetLastError();
 }
 
