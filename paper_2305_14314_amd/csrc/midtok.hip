@@ -580,6 +580,13 @@ struct MidFinArgs {
   const uint8_t* mask;                       // backward under LoRA dropout: keep-bits of the output elements, or NULL
 };
 
+// Quadruples of ranks of a token, as a shift, and how many of them a thread of a finalize workgroup sums together: one by one up
+// to rank 64 and at few tokens, else all of its up to four.  (A batch of requests for each, one after the other, found by
+// divisions, and the tokens past M summed too: forward calls of 2 tokens 256 x 1344 at rank 256 19.1 us, 47 tokens 256 x 7296 at
+// rank 256 22.4, 25 tokens 512 x 2048 at rank 128 13.3; now 17.2, 20.4, 12.3.)
+__host__ __device__ inline int mid_quad_shift(int r) { return r <= 32 ? 3 : r <= 64 ? 4 : r <= 128 ? 5 : 6; }
+inline int mid_quads(int M, int r) { return std::min(M, 16) << mid_quad_shift(r) <= 256 ? 1 : 4; }
+
 // An infinite hi is the whole value: what is left of it is NaN (or, of a value that rounded up to infinity, -Inf).  Two bf16 per dword.
 __device__ __forceinline__ uint32_t lo_of_finite(uint32_t hi, uint32_t lo) {
   const uint32_t m = ((hi & 0x7f807f80u) + 0x00800080u) & 0x80008000u;      // the exponent is all ones
@@ -588,7 +595,8 @@ __device__ __forceinline__ uint32_t lo_of_finite(uint32_t hi, uint32_t lo) {
 
 // TERMS: bf16 terms of T.  Two carry 16 significant bits; at few tokens, where the streaming kernels multiply the fp32 value, three
 // hold it whole (3 x 8 bits).
-template <int TF, bool BWD, bool LEAN, int TERMS>
+// TI: quadruples of T per thread that are summed together (mid_quads).
+template <int TF, bool BWD, bool LEAN, int TERMS, int TI>
 __global__ __launch_bounds__(256) void mid_finalize_kernel(const MidFinArgs p) {
   static_assert(LEAN || TF == 1, "two token tiles only where there are many workgroups");
   constexpr int kPitch = 256 + 8;
@@ -602,14 +610,23 @@ __global__ __launch_bounds__(256) void mid_finalize_kernel(const MidFinArgs p) {
 
   // What a workgroup waits for is memory round trips: the partials of T, the first fragments of the outer matrix and the
   // first two partials of the tile are requested together, without branches between them (clamped addresses).
-  const int r4 = p.r >> 2, rp = (p.r + 31) & ~31;
-  constexpr int LB = LEAN ? 4 : 8;                           // partials of T in flight
+  // T in quadruples of ranks: number idx is quadruple idx % 2^qs of token idx / 2^qs (past the rank zeros; rows of tokens >= M stay
+  // as they are and only reach outputs that are not stored).  LB / TI partials of TI quadruples per round trip.
+  const int r4 = p.r >> 2, qs = mid_quad_shift(p.r), n_idx = (p.M - m0 < 16 * TF ? p.M - m0 : 16 * TF) << qs;
+  constexpr int LB = LEAN ? 4 : 8, TQ = LB / TI;             // partials of T in flight
   f32x4 lp[LB];
+  uint32_t off[TI];
   auto t_load = [&](int idx, int q0) {
-    const int ml = idx / (rp >> 2), c = idx - ml * (rp >> 2), m = m0 + ml < p.M ? m0 + ml : p.M - 1;
-    const float* src = p.lpart + (int64_t)m * p.r + (c < r4 ? 4 * c : 0);
 #pragma unroll
-    for (int q = 0; q < LB; ++q) lp[q] = *(const f32x4*)(src + (int64_t)(q0 + q < p.n_lparts ? q0 + q : p.n_lparts - 1) * p.M * p.r);
+    for (int k = 0; k < TI; ++k) {
+      const int at = TI == 1 || idx + 256 * k < n_idx ? idx + 256 * k : 0, c = at & ((1 << qs) - 1);
+      off[k] = (uint32_t)((m0 + (at >> qs)) * p.r + (c < r4 ? 4 * c : 0));
+    }
+#pragma unroll
+    for (int k = 0; k < LB; ++k) {
+      const int q = q0 + k % TQ;
+      lp[k] = *(const f32x4*)(p.lpart + (int64_t)(q < p.n_lparts ? q : p.n_lparts - 1) * (p.M * p.r) + off[k / TQ]);
+    }
   };
   constexpr int RB = LEAN ? 1 : 2;                           // steps of 32 ranks in flight
   struct OutFrag { u32x4 w[4]; };                            // forward: 8 rows x 4 columns as loaded; backward: [e], ranks of output 4i + e
@@ -632,9 +649,8 @@ __global__ __launch_bounds__(256) void mid_finalize_kernel(const MidFinArgs p) {
       }
     }
   };
-  const int n_idx = 16 * TF * (rp >> 2);
   if (p.r > 0) {                                             // uniform
-    t_load(threadIdx.x < n_idx ? threadIdx.x : 0, 0);
+    t_load((int)threadIdx.x < n_idx ? threadIdx.x : 0, 0);
 #pragma unroll
     for (int k = 0; k < RB; ++k) b_load(bf[k], 32 * k);
   }
@@ -673,19 +689,9 @@ __global__ __launch_bounds__(256) void mid_finalize_kernel(const MidFinArgs p) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) lora[f][e] = f32x4{0.f, 0.f, 0.f, 0.f};
   if (p.r > 0) {
-    for (int idx = threadIdx.x; idx < n_idx; idx += 256) {
-      if (idx >= 256) t_load(idx, 0);
-      const int ml = idx / (rp >> 2), c = idx - ml * (rp >> 2), m = m0 + ml;
-      const bool ok = m < p.M && c < r4;
-      f32x4 t = f32x4{0.f, 0.f, 0.f, 0.f};
-      for (int q0 = 0;;) {
-#pragma unroll
-        for (int q = 0; q < LB; ++q)
-          if (q0 + q < p.n_lparts) t += lp[q];
-        q0 += LB;
-        if (q0 >= p.n_lparts) break;
-        t_load(idx, q0);
-      }
+    auto store = [&](int idx, f32x4 t) {
+      const int ml = idx >> qs, c = idx & ((1 << qs) - 1), m = m0 + ml;
+      const bool ok = c < r4;
       if (!ok) t = f32x4{0.f, 0.f, 0.f, 0.f};
       uint2 hi, lo;
       few::split_hl(t, hi, lo);
@@ -701,6 +707,23 @@ __global__ __launch_bounds__(256) void mid_finalize_kernel(const MidFinArgs p) {
         *(uint2*)(p.hl + (int64_t)m * 2 * p.r + 4 * c) = hi;
         *(uint2*)(p.hl + (int64_t)m * 2 * p.r + p.r + 4 * c) = lo;
       }
+    };
+    for (int idx = threadIdx.x; idx < n_idx; idx += 256 * TI) {
+      if (idx >= 256 * TI) t_load(idx, 0);
+      f32x4 t[TI];
+#pragma unroll
+      for (int k = 0; k < TI; ++k) t[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int q0 = 0;;) {
+#pragma unroll
+        for (int k = 0; k < LB; ++k)
+          if (q0 + k % TQ < p.n_lparts) t[k / TQ] += lp[k];
+        q0 += TQ;
+        if (q0 >= p.n_lparts) break;
+        t_load(idx, q0);
+      }
+#pragma unroll
+      for (int k = 0; k < TI; ++k)
+        if (idx + 256 * k < n_idx) store(idx + 256 * k, t[k]);
     }
     __syncthreads();
     for (int tb = 0; tb < p.r; tb += 32 * RB) {
@@ -942,18 +965,19 @@ hipError_t launch_mid(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const
   const bool two = (int64_t)gx * ((M + 31) / 32) >= 1024;
   const dim3 grid(gx, (unsigned)(two ? (M + 31) / 32 : (M + 15) / 16));
   const bool lean = grid.x * grid.y > kLeanBlocks;
-  if (!bwd && M <= 16) {
-    if (lean) hipLaunchKernelGGL((mid_finalize_kernel<1, false, true, 3>), grid, dim3(256), 0, st, f);
-    else hipLaunchKernelGGL((mid_finalize_kernel<1, false, false, 3>), grid, dim3(256), 0, st, f);
-    return hipGetLastError();
-  }
-  auto launch = [&](auto T, auto D, auto L) { hipLaunchKernelGGL((mid_finalize_kernel<T.value, D.value, L.value, 2>), grid, dim3(256), 0, st, f); };
-  auto pick = [&](auto D) {
-    if (two) launch(Int<2>{}, D, std::true_type{});          // 1024 workgroups and more
-    else if (lean) launch(Int<1>{}, D, std::true_type{});
-    else launch(Int<1>{}, D, std::false_type{});
+  auto launch = [&](auto T, auto D, auto L, auto terms, auto quads) {
+    hipLaunchKernelGGL((mid_finalize_kernel<T.value, D.value, L.value, terms.value, quads.value>), grid, dim3(256), 0, st, f);
   };
-  if (bwd) pick(std::true_type{}); else pick(std::false_type{});
+  auto pick = [&](auto D, auto terms) {                      // one tile of tokens
+    if (lean) launch(Int<1>{}, D, std::true_type{}, terms, Int<1>{});
+    else if (mid_quads(M, r) == 1) launch(Int<1>{}, D, std::false_type{}, terms, Int<1>{});
+    else launch(Int<1>{}, D, std::false_type{}, terms, Int<4>{});
+  };
+  if (!bwd && M <= 16) pick(std::false_type{}, Int<3>{});
+  else if (two && bwd) launch(Int<2>{}, std::true_type{}, std::true_type{}, Int<2>{}, Int<1>{});      // 1024 workgroups and more
+  else if (two) launch(Int<2>{}, std::false_type{}, std::true_type{}, Int<2>{}, Int<1>{});
+  else if (bwd) pick(std::true_type{}, Int<2>{});
+  else pick(std::false_type{}, Int<2>{});
   return hipGetLastError();
 }
 

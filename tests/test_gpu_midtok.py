@@ -216,3 +216,28 @@ def test_few_tokens_forward_decoded_once(synth, M, h, o, r):
         assert (got - t).abs().max() <= 2.0 ** -14 * t.abs().max() + 1e-6
     _check(host_bits(Y), ref.cpu().numpy(), f"Y M={M}")
     _check(host_bits(Ys), ref.cpu().numpy(), f"Y, smallest workspace, M={M}")
+
+
+@pytest.mark.parametrize("M,h,o,r", [(2, 4096, 320, 256), (5, 1600, 1088, 112), (9, 320, 64, 80), (17, 1600, 1088, 256), (31, 1088, 2112, 128),
+                                      (40, 512, 704, 208), (33, 1600, 11008, 144)])
+def test_finalize_sums_every_quadruple(synth, M, h, o, r):
+    """T of several quadruples of ranks per thread, of one to eight partials, tokens that do not fill the last tile of 16, on few
+    workgroups and on many (the widest output): forward without Double Quantization and dX, against fp64 products.  T_save is
+    checked too: 16 significant bits of sums of h terms."""
+    import paper_2305_14314_amd as ql
+    s = 0.5
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6000 + M)
+    bf = lambda *shape, sd=1.0: torch.empty(shape, device="cuda").normal_(0, sd, generator=g).bfloat16()
+    Wq = ql.qlora_nf4_quantize(synth.normal_f32_device((h, o), synth.SIGMA_W, 6100 + M), dq_blocksize=0)
+    What = ql.qlora_nf4_dequant(Wq).double()
+    X, dY, L1, L2 = bf(M, h), bf(M, o), bf(h, r, sd=0.05), bf(r, o, sd=0.05)
+    print(f"case finalize M={M} h={h} o={o} r={r}", flush=True)
+    T = torch.full((M, 2 * r), float("nan"), dtype=torch.bfloat16, device="cuda")
+    Y = ql.qlora_linear_fwd(X, Wq, L1, L2, s, T_save=T)
+    dX, _, _ = ql.qlora_linear_bwd(dY, None, Wq, L1, L2, s, need_dL=False)
+    t = X.double() @ L1.double()
+    _check(host_bits(Y), (X.double() @ What + s * t @ L2.double()).cpu().numpy(), "Y")
+    _check(host_bits(dX), (dY.double() @ What.T + s * (dY.double() @ L2.double().T) @ L1.double().T).cpu().numpy(), "dX")
+    got = T[:, :r].double() + T[:, r:].double()
+    assert (got - t).abs().max() <= 2.0 ** -14 * t.abs().max() + 1e-6
