@@ -183,7 +183,7 @@ __device__ __forceinline__ bool meet_adapter_mask(const FewArgs& p, unsigned* sh
 template <bool BWD, int NT>
 __device__ __forceinline__ void list_finalize(const FewArgs& p, int slab, const float* part, int contrib, char* scratch, bool ready,
                                               unsigned* shake, int* flag) {
-  output_stage<BWD, NT, BWD ? 2 : 4, BWD ? 4 : 8>(p, slab, part, contrib, p.M * 256, 256, scratch, !ready && shake,
+  output_stage<BWD, NT, BWD ? 2 : 4, BWD ? 4 : 8, !BWD>(p, slab, part, contrib, p.M * 256, 256, scratch, !ready && shake,
                         [&] { return meet_adapter_mask(p, shake, flag); });
 }
 

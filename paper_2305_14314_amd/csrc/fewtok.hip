@@ -98,17 +98,17 @@ __device__ __forceinline__ bool meet_adapter(unsigned* shake, unsigned n_adapter
 
 // The output stage of one slab; its splits lie [split][token][N].
 constexpr int kPendOff = 120 * 1024;         // LDS beyond what the output stage uses
-template <bool BWD, int NT>
+template <bool BWD, int NT, bool EXACT>
 __device__ __forceinline__ void finalize_slab(const FewArgs& p, int slab, char* smem, bool ready, unsigned* shake, int* flag) {
   static_assert(kOutStageBytes <= kPendOff, "LDS map");
   const int N = BWD ? p.h : p.o;
-  output_stage<BWD, NT, 8, 8>(p, slab, p.part + slab * 256, p.splits, p.M * N, N, smem, !ready && shake,
+  output_stage<BWD, NT, 8, 8, EXACT>(p, slab, p.part + slab * 256, p.splits, p.M * N, N, smem, !ready && shake,
                         [&] { return meet_adapter(shake, (unsigned)p.n_lparts, flag); });
 }
 
 // Called by every adapter workgroup after its partial is stored: it counts itself in at every slab's handshake.
 // A slab whose count it completes (the slab's splits gave up waiting: rare) is finished right here.
-template <bool BWD, int NT>
+template <bool BWD, int NT, bool EXACT>
 __device__ void adapter_arrive(const FewArgs& p, char* smem, int* flag) {
   int* npend = (int*)(smem + kPendOff);
   int* pend = npend + 1;
@@ -125,7 +125,7 @@ __device__ void adapter_arrive(const FewArgs& p, char* smem, int* flag) {
   __syncthreads();
   const int n = *npend;
   for (int q = 0; q < n; ++q) {
-    finalize_slab<BWD, NT>(p, pend[q], smem, true, nullptr, flag);
+    finalize_slab<BWD, NT, EXACT>(p, pend[q], smem, true, nullptr, flag);
     __syncthreads();
   }
 }
@@ -164,7 +164,7 @@ __device__ __forceinline__ void fewtok_fwd_body(const FewArgs& p, const int work
   __shared__ int flag;
   if (work < p.n_lparts) {
     lora_fwd_partial<NT>(p, work, red);
-    adapter_arrive<false, NT>(p, smem, &flag);
+    adapter_arrive<false, NT, true>(p, smem, &flag);
     return;
   }
 
@@ -330,7 +330,7 @@ __device__ __forceinline__ void fewtok_fwd_body(const FewArgs& p, const int work
   }
   unsigned* shake = p.ctr + kCtrShake + slab;
   if (const int f = arrive(p.ctr + slab, (unsigned)p.splits, shake, (unsigned)p.n_lparts, &flag))
-    finalize_slab<false, NT>(p, slab, smem, (f & kReady) != 0, shake, &flag);
+    finalize_slab<false, NT, true>(p, slab, smem, (f & kReady) != 0, shake, &flag);
 }
 
 template <int MT, int NT>
@@ -368,8 +368,11 @@ __global__ __launch_bounds__(NT) void fewtok_fwd_multi_kernel(const FewMulti m) 
 // (0..3) uses dword t of each load, so one token fragment serves four weight rows.
 struct BwdStep { u32x4 w[4]; u32x4 y[4]; uint32_t code[4]; float c1[4]; };   // raw loads only
 
-__global__ __launch_bounds__(kFewThreads) void fewtok_bwd_kernel(const FewArgs p) {
+template <bool ADAPTER>
+__global__ __launch_bounds__(kFewThreads) void fewtok_bwd_kernel(const FewArgs args) {
   constexpr int NT = kFewThreads;
+  FewArgs p = args;
+  if (!ADAPTER) { p.r = 0; p.n_lparts = 0; }
   __shared__ __attribute__((aligned(256))) char smem[kSmemBytes];
   f32x2* lut2 = (f32x2*)smem;
   float* red = (float*)smem;
@@ -378,7 +381,7 @@ __global__ __launch_bounds__(kFewThreads) void fewtok_bwd_kernel(const FewArgs p
   const int work = work_index();
   if (work < p.n_lparts) {
     lora_bwd_partial<NT>(p, work, red);
-    adapter_arrive<true, NT>(p, smem, &flag);
+    adapter_arrive<true, NT, !ADAPTER>(p, smem, &flag);
     return;
   }
 
@@ -497,7 +500,7 @@ __global__ __launch_bounds__(kFewThreads) void fewtok_bwd_kernel(const FewArgs p
   }
   unsigned* shake = p.ctr + kCtrShake + slab;
   if (const int f = arrive(p.ctr + slab, (unsigned)p.splits, shake, (unsigned)p.n_lparts, &flag))
-    finalize_slab<true, NT>(p, slab, smem, (f & kReady) != 0, shake, &flag);
+    finalize_slab<true, NT, !ADAPTER>(p, slab, smem, (f & kReady) != 0, shake, &flag);
 }
 
 // One 16-wave workgroup occupies a CU (its LDS map is 133 KB), so the launch is sized to fit the 256 CUs
@@ -601,7 +604,9 @@ hipError_t launch_fewtok_bwd(const uint16_t* dY, int M, const NF4Dev& w, float* 
   a.ctr = ctr; a.Bmat = L1; a.scale = scale; a.out = dX; a.hl = r > 0 ? U_hl : nullptr;
   a.lora_chunk = kLoraN; a.hdr = ctr; a.nonce = 0u; a.spin_limit = kSpinLimit;
   if (a.n_slabs > kFewMaxSlabs) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(fewtok_bwd_kernel, dim3((unsigned)(a.n_slabs * splits + a.n_lparts)), dim3(kFewThreads), 0, st, a);
+  const dim3 grid((unsigned)(a.n_slabs * splits + a.n_lparts));
+  if (r > 0) hipLaunchKernelGGL(fewtok_bwd_kernel<true>, grid, dim3(kFewThreads), 0, st, a);
+  else hipLaunchKernelGGL(fewtok_bwd_kernel<false>, grid, dim3(kFewThreads), 0, st, a);
   return hipGetLastError();
 }
 

@@ -335,12 +335,17 @@ __device__ __forceinline__ void tile_load(OutTile<BWD, NT>& t, const FewArgs& p,
   }
 }
 //   PB, LB: split partials and partials of T in flight per token and wave
-template <bool BWD, int NT, int PB, int LB, class Met>
+//   EXACT: nothing is requested for an adapter that is not there, and two partials instead of a batch where there are no more: at
+//   16 tokens a batch that nobody needs is 0.85 us of the address unit.  (8 tokens, three layers of 384 x 512 without an adapter
+//   10.4 -> 9.4 us, 14 tokens, three of 576 x 1344 12.7 -> 11.0.)  The backward kernels with an adapter have no registers for
+//   the branches: 8192 x 8192 at one token 22.4 -> 23.7 with both, at 16 30.2 -> 30.6 with the first.
+template <bool BWD, int NT, int PB, int LB, bool EXACT, class Met>
 __device__ __forceinline__ void output_stage(const FewArgs& p, int slab, const float* part0, int n_part, int ld_part, int ld_tok,
                                              char* smem /* kOutStageBytes */, bool meet, Met&& met) {
   constexpr int RC = kTileRanks;
   constexpr int W = NT / 64, PW = 16 / W;                    // waves; tokens, and groups of 16 outputs, of a wave
   constexpr int IT = 2048 / NT;
+  static_assert(PB >= 2, "the first two partials are always requested");
   uint16_t* Tp = (uint16_t*)smem;                            // [3][16][kTPitch]: the terms of T[m][j]
   uint16_t* Bs = Tp + 3 * kTPlane;                           // forward: [RC][kTPitch]
   float* sum = (float*)smem;                                 // [16][kSumPitch]: the adapter's product, once the terms are done with
@@ -358,8 +363,13 @@ __device__ __forceinline__ void output_stage(const FewArgs& p, int slab, const f
   f32x4 acc[PW], v[PW][PB], lp[PW][LB];
   auto part_load = [&](int u, int s0) {
     const uint32_t at = (uint32_t)((wave + W * u) * ld_tok + (n_ok ? 4 * lane : 0));
+    auto one = [&](int q) { v[u][q] = agent_load(part, at + (uint32_t)((s0 + q < n_part ? s0 + q : n_part - 1) * ld_part)); };
+    one(0);
+    one(1);
+    if (!EXACT || n_part - s0 > 2) {
 #pragma unroll
-    for (int q = 0; q < PB; ++q) v[u][q] = agent_load(part, at + (uint32_t)((s0 + q < n_part ? s0 + q : n_part - 1) * ld_part));
+      for (int q = 2; q < PB; ++q) one(q);
+    }
   };
   auto t_load = [&](int u, int q0) {
 #pragma unroll
@@ -372,10 +382,10 @@ __device__ __forceinline__ void output_stage(const FewArgs& p, int slab, const f
 #pragma unroll
   for (int u = 0; u < PW; ++u)
     if (wave + W * u < p.M) {                                // uniform
-      t_load(u, 0);
+      if (!EXACT || p.r > 0) t_load(u, 0);
       part_load(u, 0);
     }
-  tile_load(tile, p, slab, 0);
+  if (!EXACT || p.r > 0) tile_load(tile, p, slab, 0);
   if (p.r > 0) {
     if (meet && !met()) return;                              // the adapter came after the bounded wait: the slab is its
 #pragma unroll

@@ -29,6 +29,16 @@ def test_fewtok_output_stage_edges(oracle, synth, M, h, o, r):
     _run_case(oracle, ql, L, f"few M={M} h={h} o={o} r={r}", with_lora=True)
 
 
+@pytest.mark.parametrize("r", [0, 16])
+@pytest.mark.parametrize("M,h,o", [(7, 512, 1024), (16, 512, 1024), (5, 1024, 2048), (12, 1024, 2048), (3, 1600, 3136), (16, 5120, 8256)])
+def test_fewtok_partial_counts(oracle, synth, M, h, o, r):
+    """One, two, three and many split partials of a slab (forward by h, dX by o), with and without an adapter: the output stage asks
+    for no more than two where there are no more, and for nothing of an adapter that is not there."""
+    import paper_2305_14314_amd as ql
+    L = synth.make_layer(0, 0, M=M, h=h, o=o, r=max(r, 16))
+    _run_case(oracle, ql, L, f"few partials M={M} h={h} o={o} r={r}", with_lora=r > 0)
+
+
 @pytest.mark.parametrize("layer", [0, 4, 6])
 def test_fewtok_65b_shapes(oracle, synth, layer):
     """Workload 4: 65B-shaped linears at 1, 4 and 16 tokens, forward and dX, all outputs checked."""
