@@ -696,12 +696,13 @@ ListPlan fewlist_plan(bool bwd, int M, int n, const int* h, const int* o, const 
   ListPlan P{};
   if (n < 1 || n > kListMax || M < 1 || M > kFewTokens) return P;
   int64_t units = 0;
-  int adapters = 0, slabs = 0;
+  int adapters = 0, slabs = 0, ups_max = 1;
   for (int l = 0; l < n; ++l) {
     const int outs = bwd ? h[l] : o[l], contr = bwd ? o[l] : h[l];
     P.n_slabs[l] = (outs + 255) / 256;
     P.ups[l] = bwd ? (contr + 127) / 128 : (contr + 15) / 16;
     P.unit0[l] = (int)units;
+    ups_max = std::max(ups_max, P.ups[l]);
     units += (int64_t)P.n_slabs[l] * P.ups[l];
     if (units >= (1ll << 30)) return P;
     // adapter items: at most 23 per layer (bits 0 .. 22 of a handshake word), at least kLoraK contraction elements each
@@ -762,7 +763,11 @@ ListPlan fewlist_plan(bool bwd, int M, int n, const int* h, const int* o, const 
   // shared by more workgroups than an arrival word has bits for
   ListPart best{}, probe{};
   best.n_adapter = probe.n_adapter = adapters;
+  // Below this bound 23 workgroups do not cover the longest slab, the first taking T - kTail - kFin (at least one unit), the others
+  // T - kTail at most: a grid that covers the line with less is passed over at once.
+  const int need = ups_max > 23 ? kTail + std::min((ups_max + 20) / 22, (ups_max + kFin + 22) / 23) : 0;
   int lo = 0;
+  bool follows = false;
   for (int grid = (int)std::min<int64_t>(kListGridMax, units); grid >= 1; grid = grid > 32 ? grid - 32 : grid - 1) {
     // A larger T never covers less, and one above an even share by what a workgroup can lose -- a begun slab's second tail, a
     // rest too short for a segment -- covers the line.  Halving between the share and that takes 8 walks a call, each as
@@ -771,8 +776,12 @@ ListPlan fewlist_plan(bool bwd, int M, int n, const int* h, const int* o, const 
     // Fewer workgroups do not cover more: a smaller grid goes on from the bound of the one before, in growing steps.
     best.grid = probe.grid = grid;
     int hi = std::min(all, (all + grid - 1) / grid + 2 * kTail + kFin);   // walk(lo) leaves something undone, walk(hi) nothing
+    if (need - 1 > lo && all / grid < need) {
+      if (hi < need || walk(probe, need - 1)) continue;
+      lo = need - 1;
+    }
     bool filled = false;
-    int64_t step = lo > 0 ? 1 : all;
+    int64_t step = follows ? 1 : all;
     for (int T = std::max(all / grid, lo + 1); hi - lo > 1; step *= 2) {
       if (T >= hi) T = lo + (hi - lo) / 2;
       if (walk(probe, T)) { hi = T; std::swap(best, probe); filled = true; }
@@ -795,6 +804,7 @@ ListPlan fewlist_plan(bool bwd, int M, int n, const int* h, const int* o, const 
     }
     if (worst <= 23) { P.part = best; P.ok = true; break; }
     lo = hi - 1;
+    follows = true;
   }
   if (!P.ok) return P;
   for (int l = 0; l < n; ++l) {
