@@ -159,14 +159,18 @@ size_t mid_bytes(const qlora::MidPlan& p) {
 size_t mid_region(size_t base, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r) {
   size_t bytes = base;
   for (bool packed : {false, true}) {        // both are reported: a plan takes what it is given
+    if (packed && (bwd || M <= qlora::kMidPackFrom)) break;            // the same plan
     const qlora::MidPlan p = qlora::mid_plan(bwd, M, h, o, r, std::max(base, kMidRoom), packed);
     if (p.ok) bytes = std::max(bytes, mid_bytes(p));
   }
   return bytes;
 }
-MidWs plan_mid(void* buf, size_t room, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r, bool fix = false) {
+//   The plan of a call with `room` bytes: the one behind the size query where it fits (it is the best of any that do), else the
+//   best that fits.  One search a call, as a rule: each is 0.5 us of host time, 3 us for a long contraction with few outputs.
+MidWs plan_mid(void* buf, size_t room, size_t base, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r, bool fix = false) {
   MidWs m{};
-  m.plan = qlora::mid_plan(bwd, M, h, o, r, room);
+  m.plan = qlora::mid_plan(bwd, M, h, o, r, std::max(base, kMidRoom));
+  if (m.plan.ok && mid_bytes(m.plan) > room) m.plan = qlora::mid_plan(bwd, M, h, o, r, room);
   m.plan.ok = m.plan.ok && qlora::mid_pays(m.plan, bwd, M, h, o, r, fix);
   if (!m.plan.ok) return m;
   char* p = (char*)buf;
@@ -293,10 +297,10 @@ struct FwdPlan {
   float* lpart;      // few-token path: partials of X L1
   int rp, fsplits, n_lparts;
   bool few;
-  size_t bytes;      // what the size queries report
+  size_t bytes;      // what the size queries report (only with `sizes`: a call has no use for it)
   size_t min_bytes;  // what a call accepts
 };
-FwdPlan plan_fwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allow_few = true) {
+FwdPlan plan_fwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allow_few = true, bool sizes = true) {
   FwdPlan p{};
   Carver c(ws);
   p.rp = (r + 63) / 64 * 64;
@@ -317,7 +321,7 @@ FwdPlan plan_fwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allo
     p.part = c.take<float>(pe);
   }
   p.min_bytes = c.off;
-  p.bytes = qlora::kWorkspaceHeaderBytes + mid_region(c.off - qlora::kWorkspaceHeaderBytes, false, M, h, o, r);
+  if (sizes) p.bytes = qlora::kWorkspaceHeaderBytes + mid_region(c.off - qlora::kWorkspaceHeaderBytes, false, M, h, o, r);
   return p;
 }
 
@@ -373,7 +377,7 @@ struct MultiPlan {
   float* lpart[qlora::kFewMaxLayers];
   int splits;
   bool few;
-  size_t bytes, min_bytes;                   // reported / accepted, see FwdPlan
+  size_t bytes, min_bytes;                   // reported (without a workspace) / accepted, see FwdPlan
 };
 MultiPlan plan_fwd_multi(void* ws, int64_t M, int32_t n, int64_t h, const int64_t* o, const int32_t* r) {
   MultiPlan p{};
@@ -394,7 +398,7 @@ MultiPlan plan_fwd_multi(void* ws, int64_t M, int32_t n, int64_t h, const int64_
     p.bytes = p.min_bytes = c.off;
   } else {
     for (int l = 0; l < n; ++l) {
-      const FwdPlan f = plan_fwd(nullptr, M, h, o[l], r[l]);
+      const FwdPlan f = plan_fwd(nullptr, M, h, o[l], r[l], true, !ws);
       p.bytes = std::max(p.bytes, f.bytes);
       p.min_bytes = std::max(p.min_bytes, f.min_bytes);
     }
@@ -411,7 +415,7 @@ struct ListWs {
   float* part[qlora::kListMax];
   float* lpart[qlora::kListMax];
   bool few;
-  size_t bytes, min_bytes;                   // reported / accepted, see FwdPlan
+  size_t bytes, min_bytes;                   // reported (without a workspace) / accepted, see FwdPlan
 };
 ListWs plan_list(void* ws, bool bwd, int64_t M, int32_t n, const int64_t* h, const int64_t* o, const int32_t* r,
                  bool compact = false) {
@@ -429,8 +433,8 @@ ListWs plan_list(void* ws, bool bwd, int64_t M, int32_t n, const int64_t* h, con
     p.bytes = p.min_bytes = c.off;
   } else {
     for (int l = 0; l < n; ++l) {
-      const FwdPlan f = plan_fwd(nullptr, M, h[l], o[l], r[l]);
-      p.bytes = std::max(p.bytes, bwd ? plan_bwd(nullptr, M, h[l], o[l], r[l]).bytes : f.bytes);
+      const FwdPlan f = plan_fwd(nullptr, M, h[l], o[l], r[l], true, !ws && !bwd);
+      if (!ws) p.bytes = std::max(p.bytes, bwd ? plan_bwd(nullptr, M, h[l], o[l], r[l]).bytes : f.bytes);
       p.min_bytes = std::max(p.min_bytes, bwd ? plan_bwd(nullptr, M, h[l], o[l], r[l], true, false).bytes : f.min_bytes);
     }
   }
@@ -614,34 +618,34 @@ qlora_status linear_fwd_impl(const uint16_t* X, const qlora_nf4_view* Wq, const 
   if (qlora_status st = check_linear(M, h, o, r)) return st;
   if (!X || !Y || !workspace) return QLORA_ERR_NULL;
   if (r > 0 && (!L1 || !L2)) return QLORA_ERR_NULL;
-  FwdPlan p = plan_fwd(workspace, M, h, o, r, keep_mask == nullptr && streams_few(Wq));
+  FwdPlan p = plan_fwd(workspace, M, h, o, r, keep_mask == nullptr && streams_few(Wq), false);
   if (workspace_bytes < p.min_bytes) return QLORA_ERR_WORKSPACE;
-  if (p.few && streams_mid(Wq) && qlora::mid_beats_few(M, h, o, r)) {  // with the room that the size query reports; less streams as ever
-    const FwdPlan q = plan_fwd(workspace, M, h, o, r, false);
-    if (workspace_bytes >= q.bytes &&
-        plan_mid((char*)workspace + qlora::kWorkspaceHeaderBytes, q.bytes - qlora::kWorkspaceHeaderBytes, false, M, h, o, r).plan.ok)
-      p = q;
-  }
   if (!aligned16(X) || !aligned16(Y) || !aligned16(workspace) || !aligned16(L1) || !aligned16(L2) ||
       !aligned16(T_save))
     return QLORA_ERR_ALIGN;
   hipStream_t st = (hipStream_t)hip_stream;
   const qlora::NF4Dev W = to_dev(Wq);
 
+  auto mid_ws = [&](size_t min_bytes) {
+    return plan_mid((char*)workspace + qlora::kWorkspaceHeaderBytes, workspace_bytes - qlora::kWorkspaceHeaderBytes,
+                    min_bytes - qlora::kWorkspaceHeaderBytes, false, M, h, o, r);
+  };
+  MidWs mid{};
+  if (!p.few && streams_mid(Wq)) mid = mid_ws(p.min_bytes);
+  else if (p.few && qlora::mid_beats_few(M, h, o, r)) {        // with the room that the size query reports; less streams as ever
+    const FwdPlan q = plan_fwd(workspace, M, h, o, r, false);
+    if (workspace_bytes >= q.bytes) mid = mid_ws(q.min_bytes);
+  }
+  if (mid.plan.ok) {
+    QL_TRY(qlora::launch_mid(false, X, (int)M, W, mid.plan, L1, L2, r, s, keep_mask, mid.part, mid.lpart, mid.xpack, Y, T_save, st));
+    return QLORA_OK;
+  }
   if (p.few) {
     // few tokens: one launch streams the packed weight once and dequantises in registers; the adapter's
     // T = X L1 comes from a few extra workgroups and is applied (and saved) by each slab's last arriver
     QL_TRY(qlora::launch_fewtok_fwd(X, (int)M, W, p.fpart, p.fsplits, L1, L2, r, s, p.lpart, (unsigned*)workspace, Y,
                                     T_save, st));
     return QLORA_OK;
-  }
-  if (streams_mid(Wq)) {
-    const MidWs mid = plan_mid((char*)workspace + qlora::kWorkspaceHeaderBytes,
-                               std::min(workspace_bytes, p.bytes) - qlora::kWorkspaceHeaderBytes, false, M, h, o, r);
-    if (mid.plan.ok) {
-      QL_TRY(qlora::launch_mid(false, X, (int)M, W, mid.plan, L1, L2, r, s, keep_mask, mid.part, mid.lpart, mid.xpack, Y, T_save, st));
-      return QLORA_OK;
-    }
   }
   SmallBatch batch(p.part, p.part_bytes, st);
   if (r > 0) {
@@ -867,7 +871,7 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
                      qlora::gemm_nt_fused_fits((int)o, K1, (int)h);
   // a few hundred tokens: decode inside the product; the finalize step applies the dropout mask to the adapter's term
   const MidWs mid = !p.few && dX && !fused && streams_mid(Wq)
-                        ? plan_mid(p.Wd, p.wd_bytes, true, M, h, o, r, keep_mask != nullptr) : MidWs{};
+                        ? plan_mid(p.Wd, p.wd_bytes, (size_t)h * o * sizeof(uint16_t), true, M, h, o, r, keep_mask != nullptr) : MidWs{};
   qlora::FinList fin{};
   if (mid.plan.ok) {
     QL_TRY(qlora::launch_mid(true, dY, (int)M, W, mid.plan, L1, L2, r, s, keep_mask, mid.part, mid.lpart, mid.xpack, dX,

@@ -177,6 +177,7 @@ hipError_t launch_workspace_init(void* workspace, hipStream_t st);
 // 439 / 306.  Those are of one weight called again and again; with three in turn and today's tiles the dequantised
 // ones take 44.5, 42.0 (128 x 128 tiles; 56.9, 55.0 without), 137, 154, 169 and 426.  The estimate is fitted to calls of up to 512 tokens.
 constexpr int kMidTokens = 512;
+constexpr int kMidPackFrom = 48;             // forward: up to here no plan packs the token operand
 // `units` units in tiles of `ups`, cut into `wgs` ranges whose sizes differ by at most one.
 struct MidLine {
   int units, ups, wgs;

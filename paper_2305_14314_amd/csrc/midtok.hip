@@ -798,9 +798,8 @@ namespace {
 // of a wave for the loads of 64-byte row pieces (backward operands are always packed).  Whole calls, us, as it lies / packed: 64 tokens
 // 1024 x 1024 12.1 / 18.6, 4096 x 4096 17.8 / 22.5, 8192 x 2048 19.2 / 27.5; 128 tokens 4096 x 4096 21.4 / 24.2; 256 tokens 1024 x 1024
 // 14.8 / 19.8; but 64 tokens 4096 x 11008 28.3 / 26.6, 80 tokens 8192 x 8192 40 / 34, 256 tokens 4096 x 4096 34 / 29.  Up to
-// kPackFrom tokens, one group of three tiles, packing never won (40 tokens 8192 x 8192 25.5 / 28.1).
+// kMidPackFrom tokens, one group of three tiles, packing never won (40 tokens 8192 x 8192 25.5 / 28.1).
 constexpr double kScattered = 0.24, kPackLaunch = 4.8;
-constexpr int kPackFrom = 48;
 // One of the launch shapes: kw = 4, one wave per SIMD with tiles of up to `group` = 128 or 64 tokens, or kw = 8, two waves
 // per SIMD with tiles of up to 64.  Per unit of work tiles of 128 tokens are fastest (a decoded fragment meets twice the
 // tokens); tiles of 64 have the cheaper fixed part and give a small layer twice the workgroups (dX of
@@ -863,8 +862,8 @@ MidPlan mid_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room, 
     const double all = us + (pack ? kPackLaunch : 0.0);
     if (p.ok && (!best.ok || all < best_us)) { best = p; best.us = us; best_us = all; }
   };
-  if (!bwd && !(packed && M > kPackFrom)) consider(8, 48, false);
-  if (bwd || M > kPackFrom) {
+  if (!bwd && !(packed && M > kMidPackFrom)) consider(8, 48, false);
+  if (bwd || M > kMidPackFrom) {
     if (!bwd) consider(8, 64, true);
     consider(4, 128, true);
     if (M > 64) consider(4, 64, true);                       // below, tiles of 128 hold all tokens anyway

@@ -485,3 +485,23 @@ def test_kbit_arguments_are_rejected_on_the_host(L):
         assert f(fake, 64, 64, 1, fake, None) == -3 and f(fake, 0, 64, 3, fake, None) == -2
         assert f(ctypes.c_void_p(0x1008), 64, 64, 3, fake, None) == -5
         assert f(fake, 64, 64, 2, ctypes.c_void_p(0x1004), None) == -5
+
+
+def test_forward_plans_once():
+    """The plan of a call for up to 512 tokens is a search of microseconds on the host (22016 x 128: some 3).  A call makes it once, and
+    not before its arguments are checked: a refused call costs the host no more at 512 tokens than at 600, where there is no such
+    plan.  (With the plans of the size query made inside each call it was 3 - 4 x as much.)"""
+    import time
+    from paper_2305_14314_amd import binding
+    L = binding.lib()
+    h, o, r = 22016, 128, 64
+    v = binding.qlora_nf4_view(0x1000, 0x1000, 0x1000, 0x1000, h, o, 64, 256)
+    fake, odd = ctypes.c_void_p(0x1000), ctypes.c_void_p(0x1008)
+    best = {512: 1e9, 600: 1e9}
+    for _ in range(300):
+        for M in best:
+            t = time.perf_counter()
+            for _ in range(20):
+                assert L.qlora_linear_fwd(odd, ctypes.byref(v), fake, fake, 1.0, M, r, fake, None, fake, 1 << 40, None) == -5
+            best[M] = min(best[M], time.perf_counter() - t)
+    assert best[512] < 1.5 * best[600], best
