@@ -1,9 +1,9 @@
 // Standalone doubleDequant (arXiv 2305.14314, Eq. 6 and Eq. 2): packed NF4 indices and
 // double-quantised constants -> bf16 weights.  HBM-bound: 0.516 B read + 2 B written per element.
-// One lane decodes one packed dword (8 weights of one 64-block) and stores 16 bytes.  8192 x 8192 38.4 -> 37.1 us and 4096 x 11008
-// 27.3 -> 25.9 without a memory round trip for the value table; the transposing kernel also asks for its data before it builds
-// the tables (a forward call of 1000 tokens through 4096 x 11008 101.4 -> 98.5).  The same in the flat kernel, whose workgroups
-// take several turns, made large weights slower (8192 x 22016 95 -> 115; why was not examined) and stayed out.
+// One lane decodes one packed dword (8 weights of one 64-block) and stores 16 bytes.  The transposing kernel asks for its data
+// before it builds the tables (a forward call of 1000 tokens through 4096 x 11008 101.4 -> 98.5 us).  The same in the flat
+// kernel, whose workgroups take several turns, made large weights slower (8192 x 22016 95 -> 115; why was not examined) and
+// stayed out.
 #include <algorithm>
 
 #include "common.hpp"
@@ -19,19 +19,13 @@ static_assert(kDeqThreads == kFinThreads, "finalize workgroups share the launch"
 template <bool FIN> struct FinArg { FinList f; };
 template <> struct FinArg<false> {};
 
-// The 16 values of the data type into LDS, NF4's or (Section 4) those of the argument: picked from scalars by the first wave's
-// lanes (a lane-indexed read of a constant array is a memory round trip, of a by-value argument goes through scratch).
-__device__ __forceinline__ void init_lut16(float* lut, int dtype, const Table4& tab) {
-  if (threadIdx.x < 64) {
-    constexpr float t[16] = {QLORA_NF4_VALUES};
-    float v = 0.0f;
+// The 16 values of the data type from the arguments into LDS: one thread, four stores of scalars (a lane-indexed read of a constant
+// array is a memory round trip, of a by-value argument goes through scratch; picking them by lane from literals or arguments is 48
+// vector operations ahead of the barrier: 4096 x 4096 9.9 and 10.2 us, 9.6 so; 7040 x 1664 7.5, 8.0, 7.5; 8192 x 22016 95.7, 94.7, 94.4).
+__device__ __forceinline__ void init_lut16(float* lut, const Table4& tab) {
+  if (threadIdx.x == 0) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      float x = t[i];
-      if (dtype != 0) x = tab.v[i];                          // uniform
-      v = (int)threadIdx.x == i ? x : v;
-    }
-    if (threadIdx.x < 16) lut[threadIdx.x] = v;
+    for (int i = 0; i < 16; ++i) lut[i] = tab.v[i];
   }
 }
 
@@ -44,13 +38,13 @@ template <bool DQ, bool I8, bool GAP>
 __device__ __forceinline__ void dequant_body(
     const void* __restrict__ packed_v, const uint8_t* __restrict__ code, const float* __restrict__ c1,
     const float* __restrict__ mean_ptr, uint4* __restrict__ out, int64_t n_dwords, uint32_t rows, uint32_t bpr,
-    const int dtype, const Table4& tab, const int64_t row_gap, const int bid, const int n_bid) {
+    const Table4& tab, const int64_t row_gap, const int bid, const int n_bid) {
   // GAP: the output rows are row_gap 16-byte groups apart (a wider buffer: several weights side by side); else back to back
   constexpr bool dq = DQ;                                    // Double Quantization, or the fp32 constants as they are
   const uint32_t* __restrict__ packed = (const uint32_t*)packed_v;
   __shared__ float lut[16];
   __shared__ float unit[256];
-  init_lut16(lut, dtype, tab);
+  init_lut16(lut, tab);
   unit[threadIdx.x] = e4m3_unit(threadIdx.x);               // 256 threads, 256 codes
   __syncthreads();
   const float mean = dq ? *mean_ptr : 0.0f;
@@ -96,13 +90,13 @@ template <bool DQ, bool I8, bool GAP, bool FIN>
 __global__ __launch_bounds__(kDeqThreads) void dequant_nf4_kernel(
     const void* __restrict__ packed_v, const uint8_t* __restrict__ code, const float* __restrict__ c1,
     const float* __restrict__ mean_ptr, uint4* __restrict__ out, int64_t n_dwords, uint32_t rows, uint32_t bpr,
-    const int dtype, const Table4 tab, const int64_t row_gap, const FinArg<FIN> fin) {
+    const Table4 tab, const int64_t row_gap, const FinArg<FIN> fin) {
   int bid = blockIdx.x, n_bid = gridDim.x;
   if constexpr (FIN) {
     if (bid < fin.f.blocks()) { fin_block<4>(fin.f, bid); return; }
     bid -= fin.f.blocks(); n_bid -= fin.f.blocks();
   }
-  dequant_body<DQ, I8, GAP>(packed_v, code, c1, mean_ptr, out, n_dwords, rows, bpr, dtype, tab, row_gap, bid, n_bid);
+  dequant_body<DQ, I8, GAP>(packed_v, code, c1, mean_ptr, out, n_dwords, rows, bpr, tab, row_gap, bid, n_bid);
 }
 
 // Several weights of one height side by side (stacked layers), double-quantised 4-bit ones of one data type: a launch apiece ramps
@@ -114,12 +108,12 @@ __device__ __forceinline__ int deq_layer(const DeqLayers& a, int at) {
   while (l + 1 < a.n && at >= a.first[l + 1]) ++l;
   return l;
 }
-__global__ __launch_bounds__(kDeqThreads) void dequant_nf4_list_kernel(const DeqLayers a, uint32_t rows, const int dtype,
-                                                                       const Table4 tab, const int64_t ld_out) {
+__global__ __launch_bounds__(kDeqThreads) void dequant_nf4_list_kernel(const DeqLayers a, uint32_t rows, const Table4 tab,
+                                                                       const int64_t ld_out) {
   const int l = deq_layer(a, blockIdx.x);
   const DeqLayer& y = a.l[l];
   dequant_body<true, false, true>(y.packed, y.code, y.c1, y.mean, (uint4*)y.out, (int64_t)rows * y.o / 8, rows, (uint32_t)(y.o >> 6),
-                                  dtype, tab, (ld_out - y.o) / 8, (int)blockIdx.x - a.first[l], a.first[l + 1] - a.first[l]);
+                                  tab, (ld_out - y.o) / 8, (int)blockIdx.x - a.first[l], a.first[l + 1] - a.first[l]);
 }
 
 // Transposed variant for the forward GEMM: out[n][k] = dequant(W)[k][n], row stride ld_out >= h.
@@ -136,7 +130,7 @@ __global__ __launch_bounds__(kDeqThreads) void dequant_nf4_list_kernel(const Deq
 template <bool DQ, bool I8>
 __device__ __forceinline__ void dequant_t_body(
     const void* __restrict__ packed_v, const uint8_t* __restrict__ code, const float* __restrict__ c1,
-    const float* __restrict__ mean_ptr, uint16_t* __restrict__ out, int h, int o, int64_t ld_out, const int dtype,
+    const float* __restrict__ mean_ptr, uint16_t* __restrict__ out, int h, int o, int64_t ld_out,
     const Table4& tab, const uint16_t* __restrict__ L2, int r, int col0, const int row_id, const int col_id) {
   constexpr bool dq = DQ;
   const uint32_t* __restrict__ packed = (const uint32_t*)packed_v;
@@ -196,7 +190,7 @@ __device__ __forceinline__ void dequant_t_body(
     c2[j] = c1[dq ? blk >> 8 : blk];
   }
   const float mean = dq ? *mean_ptr : 0.0f;
-  init_lut16(lut, dtype, tab);
+  init_lut16(lut, tab);
   unit[threadIdx.x] = e4m3_unit(threadIdx.x);
   __syncthreads();
   if (!inside || k_base >= h) return;                         // h % 8 == 0: a lane's 8 rows are inside or outside together
@@ -240,20 +234,20 @@ __device__ __forceinline__ bool deq_t_fin(const FinArg<FIN>& fin, int& row_id) {
 template <bool DQ, bool I8, bool FIN>
 __global__ __launch_bounds__(kDeqThreads) void dequant_nf4_t_kernel(
     const void* __restrict__ packed_v, const uint8_t* __restrict__ code, const float* __restrict__ c1,
-    const float* __restrict__ mean_ptr, uint16_t* __restrict__ out, int h, int o, int64_t ld_out, const int dtype,
+    const float* __restrict__ mean_ptr, uint16_t* __restrict__ out, int h, int o, int64_t ld_out,
     const Table4 tab, const uint16_t* __restrict__ L2, int r, int col0, const FinArg<FIN> fin) {
   int row_id;
   if (deq_t_fin(fin, row_id)) return;
-  dequant_t_body<DQ, I8>(packed_v, code, c1, mean_ptr, out, h, o, ld_out, dtype, tab, L2, r, col0, row_id, blockIdx.x);
+  dequant_t_body<DQ, I8>(packed_v, code, c1, mean_ptr, out, h, o, ld_out, tab, L2, r, col0, row_id, blockIdx.x);
 }
 template <bool FIN>
-__global__ __launch_bounds__(kDeqThreads) void dequant_nf4_t_list_kernel(const DeqLayers a, int h, const int dtype, const Table4 tab,
+__global__ __launch_bounds__(kDeqThreads) void dequant_nf4_t_list_kernel(const DeqLayers a, int h, const Table4 tab,
                                                                          const int64_t ld_out, const FinArg<FIN> fin) {
   int row_id;
   if (deq_t_fin(fin, row_id)) return;
   const int l = deq_layer(a, blockIdx.x);
   const DeqLayer& y = a.l[l];
-  dequant_t_body<true, false>(y.packed, y.code, y.c1, y.mean, y.out, h, y.o, ld_out, dtype, tab, y.L2, y.r, y.col0, row_id,
+  dequant_t_body<true, false>(y.packed, y.code, y.c1, y.mean, y.out, h, y.o, ld_out, tab, y.L2, y.r, y.col0, row_id,
                               (int)blockIdx.x - a.first[l]);
 }
 
@@ -284,7 +278,7 @@ hipError_t launch_dequant_list(const DeqDesc* d, int n, int64_t ld_out, hipStrea
     a.first[l + 1] = a.first[l] + (int)std::min(blocks, cap);
   }
   hipLaunchKernelGGL(dequant_nf4_list_kernel, dim3((unsigned)a.first[n]), dim3(kDeqThreads), 0, st, a, (uint32_t)d[0].w.rows,
-                     d[0].w.dtype, table4_host(d[0].w.dtype), ld_out);
+                     table4_host(d[0].w.dtype), ld_out);
   return hipGetLastError();
 }
 
@@ -306,8 +300,8 @@ hipError_t launch_dequant_t_list(const DeqDesc* d, int n, int64_t ld_out, int rp
   }
   const dim3 grid(gx, (unsigned)((h + 63) / 64 + rp / 64) + fin_rows);
   const Table4 tab = table4_host(d[0].w.dtype);
-  if (with_fin) hipLaunchKernelGGL(dequant_nf4_t_list_kernel<true>, grid, dim3(kDeqThreads), 0, st, a, h, d[0].w.dtype, tab, ld_out, FinArg<true>{*fin});
-  else hipLaunchKernelGGL(dequant_nf4_t_list_kernel<false>, grid, dim3(kDeqThreads), 0, st, a, h, d[0].w.dtype, tab, ld_out, FinArg<false>{});
+  if (with_fin) hipLaunchKernelGGL(dequant_nf4_t_list_kernel<true>, grid, dim3(kDeqThreads), 0, st, a, h, tab, ld_out, FinArg<true>{*fin});
+  else hipLaunchKernelGGL(dequant_nf4_t_list_kernel<false>, grid, dim3(kDeqThreads), 0, st, a, h, tab, ld_out, FinArg<false>{});
   return hipGetLastError();
 }
 
@@ -328,7 +322,7 @@ hipError_t launch_dequant_t(const NF4Dev& w, uint16_t* out, int64_t ld_out, hipS
   const bool i8 = w.dtype == kTypeInt8;
 #define QL_DEQ_T2(DQ, I8, FIN, FARG)                                                                            \
   hipLaunchKernelGGL((dequant_nf4_t_kernel<DQ, I8, FIN>), grid, dim3(kDeqThreads), 0, st, (const void*)w.packed, w.code, \
-                     w.c1, w.mean, out, h, o, ld_out, w.dtype, table4_host(w.dtype), L2, r, col0, FARG)
+                     w.c1, w.mean, out, h, o, ld_out, table4_host(w.dtype), L2, r, col0, FARG)
 #define QL_DEQ_T(DQ, I8)                                                                                        \
   do { if (with_fin) QL_DEQ_T2(DQ, I8, true, FinArg<true>{*fin}); else QL_DEQ_T2(DQ, I8, false, FinArg<false>{}); } while (0)
   if (w.dq) { if (i8) QL_DEQ_T(true, true); else QL_DEQ_T(true, false); }
@@ -345,12 +339,12 @@ __global__ __launch_bounds__(kDeqThreads) void block_consts_kernel(const uint8_t
                                                                    const float* __restrict__ c1,
                                                                    const float* __restrict__ mean_ptr,
                                                                    float* __restrict__ out, int64_t n_blocks,
-                                                                   uint32_t rows, uint32_t bpr, const int dtype,
-                                                                   const Table4 tab, float* __restrict__ tab_out,
+                                                                   uint32_t rows, uint32_t bpr, const Table4 tab,
+                                                                   float* __restrict__ tab_out,
                                                                    const bool dq) {
   __shared__ float lut[16];
   __shared__ float unit[256];
-  init_lut16(lut, dtype, tab);
+  init_lut16(lut, tab);
   unit[threadIdx.x] = e4m3_unit(threadIdx.x);
   __syncthreads();
   if (blockIdx.x == 0 && threadIdx.x < 16) tab_out[threadIdx.x] = lut[threadIdx.x];
@@ -370,7 +364,7 @@ hipError_t launch_block_consts(const NF4Dev& w, float* consts, float* tab16, hip
   int64_t blocks = w.dq ? (n_blocks + kDeqThreads - 1) / kDeqThreads : 1;
   if (blocks > 256 * 8) blocks = 256 * 8;
   hipLaunchKernelGGL(block_consts_kernel, dim3((unsigned)blocks), dim3(kDeqThreads), 0, st, w.code, w.c1, w.mean, consts,
-                     n_blocks, (uint32_t)w.rows, (uint32_t)(w.cols / 64), w.dtype, table4_host(w.dtype), tab16, w.dq);
+                     n_blocks, (uint32_t)w.rows, (uint32_t)(w.cols / 64), table4_host(w.dtype), tab16, w.dq);
   return hipGetLastError();
 }
 
@@ -388,7 +382,7 @@ hipError_t launch_dequant(const NF4Dev& w, uint16_t* out, hipStream_t st, int64_
 #define QL_DEQ2(DQ, I8, GAP, FIN, FARG)                                                                     \
   hipLaunchKernelGGL((dequant_nf4_kernel<DQ, I8, GAP, FIN>), dim3((unsigned)blocks), dim3(kDeqThreads), 0, st,   \
                      (const void*)w.packed, w.code, w.c1, w.mean, (uint4*)out, n_dwords, (uint32_t)w.rows,  \
-                     (uint32_t)(w.cols / 64), w.dtype, table4_host(w.dtype), (ld_out - w.cols) / 8, FARG)
+                     (uint32_t)(w.cols / 64), table4_host(w.dtype), (ld_out - w.cols) / 8, FARG)
 #define QL_DEQ(DQ, I8)                                                                                      \
   do {                                                                                                      \
     if (gap) QL_DEQ2(DQ, I8, true, false, FinArg<false>{});                                                 \
