@@ -875,17 +875,27 @@ MidPlan mid_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room, 
 // 22016, 64 .. 65536 outputs, ranks 0 .. 256; each estimate within 20 % on nine calls of ten).  Decoding inside the product
 // loses where the contraction is short (its partials are then as large as the product: dX with K = 64, N = 16384 at 384 tokens
 // 43 us against 12) or the rank large (K = 1024, N = 8192, rank 256 at 512 tokens 66 against 32); it wins where the weight is
-// what counts (K = 22016, N = 8192, rank 64 at 256 tokens 117 against 421).  The fit is older than the tiles of 128 x 128
-// and today's line is not the fastest one: with K up to about 3000 at 100 - 512 tokens the other path is now as fast or faster
-// (dX 2752 x 3136, rank 144, 511 tokens 53.8 here, 35.1 dequantised).  Those calls stay here because the tests of this path hold them
-// to it (mid_choice_check.cpp, test_midtok_is_reached).  Near the line either will do: a call goes to the
-// other path where that is faster by a fifth, so that seven of the fitted calls lose more than 3 % by it, the worst 20 %.
+// what counts (K = 22016, N = 8192, rank 64 at 256 tokens 117 against 421; 112 against 334 now).  A call goes to the other path where that
+// is estimated faster by a fifth.  The fit is older than the 128 x 128 tiles, with which the other path's estimate has become
+// some 17 % high, and the line has not been moved since: of 947 random calls that it decides 285 are now more than 3 % from the
+// faster path and 131 more than 20 %, all of these decoded here, the worst 1.9 x (dX 2752 x 3136, rank 144, 511 tokens 53.8 us here, 35.1
+// dequantised).  They take no longer here than they did before those tiles.
 bool mid_pays(const MidPlan& p, bool bwd, int64_t M, int64_t h, int64_t o, int r, bool fix) {
   const double K = (double)(bwd ? o : h), N = (double)(bwd ? h : o), MN = 1e-6 * (double)M * N;
   const double mid = 6.5 + 0.88 * p.us + (p.pack ? 4.3 + 0.053 * r : 0.027 * r) + 0.35 * p.max_contrib * MN + 0.0034 * r * MN +
                      3.3e-8 * (double)M * K * r;
   const double gemm = 9.7 + 0.7 * gemm_rounds_us(M, (int64_t)N, ((int64_t)K + (r + 63) / 64 * 64) / 64) + 0.62e-6 * K * N +
                       0.6 * MN + (r > 0 ? 3.6 + 1e-6 * r * (0.2 * N + 3.8 * K) : 0.0) + (fix ? 5.5 + 2.2 * MN : 0.0);
+  if (!p.pack && M > kMidPackFrom) {
+    // The adapter's workgroups run beside the product's, 64 rank columns after the other: a launch takes as long as the longer of
+    // the two.  (The sum above is fitted to calls that pack the operand or have up to 48 tokens.  By it 127 of 556 random such calls
+    // came here that take up to 1.86 x as long as the other path, 62 of them longer than when every operand of that size was packed:
+    // under dropout 111 tokens 256 x 64 at rank 256 24.6 us against 13.2, 114 tokens 512 x 448 25.6 against 16.2.  By this one 22 of them are
+    // more than 3 % from the faster path, the worst 13 %, none longer than then.  The other side's estimate is some 17 % high.)
+    const double chain = (1.8 + 2.7 / 512 * std::min(K, 512.0)) * ((r + 63) / 64);
+    const double beside = 5.8 + (r > 0 ? 2.4 : 0.0) + std::max(0.88 * p.us, chain) + (0.35 * p.max_contrib + 0.0034 * r) * MN;
+    return beside <= 0.95 * gemm;
+  }
   return mid <= 1.2 * gemm;
 }
 

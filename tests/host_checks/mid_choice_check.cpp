@@ -1,5 +1,5 @@
 // Host-side check of the choice between the product that decodes the weight itself and dequantise + GEMM (no GPU needed):
-// calls measured clearly faster one way are sent that way.  Prints "OK <calls>" or the first that is not.
+// calls measured clearly faster one way (three weights in turn, whole calls) are sent that way.  Prints "OK <calls>" or the first that is not.
 #include <algorithm>
 #include <cstdio>
 
@@ -10,17 +10,24 @@ using namespace qlora;
 struct Call { bool bwd; int M, K, N, r; bool fix; double gemm_us, mid_us; };   // fix: under LoRA dropout
 static const Call kCalls[] = {
     // the product that decodes the weight: the faster one
-    {false, 40, 4096, 11008, 64, false, 83.5, 21.9},   {false, 256, 1024, 1024, 64, false, 23.1, 21.7},
-    {false, 512, 4096, 4096, 64, false, 58.2, 44.2},   {true, 512, 4096, 4096, 64, false, 56.8, 47.5},
-    {false, 256, 5120, 13824, 64, false, 89.1, 61.0},  {false, 320, 5120, 13824, 64, false, 96.0, 90.9},
-    {false, 512, 8192, 1024, 256, false, 93.1, 60.8},  {true, 512, 22016, 8192, 256, false, 439.4, 272.5},
-    {false, 256, 22016, 8192, 64, false, 421.0, 117.0}, {true, 256, 13824, 5120, 64, false, 154.1, 71.9},
+    {false, 40, 4096, 11008, 64, false, 48.4, 21.7},   {false, 256, 1024, 1024, 64, false, 17.7, 15.1},
+    {false, 512, 4096, 4096, 64, false, 44.9, 40.7},   {true, 256, 4096, 4096, 64, false, 44.2, 35.3},
+    {false, 256, 5120, 13824, 64, false, 83.1, 62.6},  {false, 320, 5120, 13824, 64, false, 106.8, 89.2},
+    {false, 512, 8192, 1024, 256, false, 65.5, 55.8},  {true, 512, 22016, 8192, 256, false, 358.6, 259.4},
+    {false, 256, 22016, 8192, 64, false, 333.8, 111.8}, {true, 256, 13824, 5120, 64, false, 118.0, 66.3},
+    {true, 384, 8192, 4096, 64, false, 65.2, 56.8},    {true, 128, 8192, 1024, 64, false, 60.4, 34.1},
+    // the operand as it lies, above 48 tokens
+    {false, 186, 2368, 384, 128, false, 28.4, 18.3},   {false, 65, 1664, 8768, 32, false, 29.3, 19.5},
+    {false, 119, 6208, 128, 16, false, 44.0, 19.3},    {false, 72, 3776, 64, 256, false, 35.3, 26.1},
     // short contractions, wide ranks: dequantise + GEMM
-    {true, 384, 64, 16384, 0, false, 12.1, 43.5},      {false, 384, 64, 16384, 64, false, 18.6, 42.4},
-    {true, 17, 64, 1024, 256, false, 15.4, 25.3},      {true, 128, 128, 4096, 256, false, 15.8, 31.3},
-    {true, 512, 64, 4096, 256, false, 15.7, 36.5},     {true, 512, 1024, 8192, 256, false, 31.8, 65.6},
-    {false, 512, 1024, 8192, 256, false, 31.9, 54.5},  {true, 512, 5120, 13824, 256, false, 100.0, 170.4},
-    {true, 16, 192, 4096, 256, false, 15.7, 29.2},     {true, 384, 64, 16384, 256, true, 49.1, 70.3},
+    {true, 384, 64, 16384, 0, false, 10.4, 39.3},      {false, 384, 64, 16384, 64, false, 16.3, 39.8},
+    {true, 17, 64, 1024, 256, false, 10.9, 24.4},      {true, 128, 128, 4096, 256, false, 13.0, 30.4},
+    {true, 512, 64, 4096, 256, false, 13.1, 35.5},     {true, 512, 1024, 8192, 256, false, 28.8, 65.0},
+    {false, 512, 1024, 8192, 256, false, 29.7, 57.6},  {true, 512, 5120, 13824, 256, false, 107.9, 163.9},
+    {true, 16, 192, 4096, 256, false, 12.3, 28.9},     {true, 384, 64, 16384, 256, true, 50.6, 73.3},
+    // the adapter's workgroups beside the product's, longer than those
+    {false, 79, 256, 1088, 256, false, 13.5, 20.6},    {false, 114, 512, 448, 256, false, 15.7, 21.1},
+    {false, 193, 192, 64, 256, false, 12.6, 18.8},     {false, 111, 256, 64, 256, false, 12.7, 20.4},
 };
 
 int main() {
