@@ -589,7 +589,6 @@ __global__ __launch_bounds__(256, NSLOT == 5 ? 2 : 1) void gemm_nt_half_kernel(c
 // With 128 x 128 tiles, whole calls: 600 tokens 4096 x 4096 forward 56.7 -> 44.1 us (with the five-slot ring 51.0), 1024
 // tokens dX 4096 x 11008 177 -> 142 (146), 900 tokens dX 1536 x 3072 44.8 -> 35.0 (38.9), 1024 tokens 1024 x 1024 24.5 -> 19.4
 // (20.6); where the larger tiles fill their rounds they lose: 4096 tokens 4096 x 4096 117 against 135.
-struct GemmCut { int wide, rest, rest_width, half; };        // half: the whole output in that many columns of 128 x 128 tiles
 struct RoundCost { int width, empty, full; };                // of a round, in 0.01 us per K-step
 constexpr RoundCost kWide = {256, 105, 136}, kNarrow[2] = {{192, 86, 105}, {128, 66, 79}};
 constexpr RoundCost kHalf1 = {0, 45, 57}, kHalf2 = {0, 58, 84};   // 128 x 128: up to one, up to two workgroups per CU
@@ -602,29 +601,29 @@ int64_t half_cost(int64_t M, int64_t N, int64_t steps) {
   const int64_t tiles = (M + kHalfRows - 1) / kHalfRows * ((N + 127) / 128);
   return tiles <= kCUs ? rounds_cost(kHalf1, tiles, steps) : rounds_cost(kHalf2, tiles, steps, 2 * kCUs);
 }
+}  // namespace
+
 GemmCut gemm_cut(int M, int N, int steps) {
   constexpr int kLaunch = 300;
   const int tiles_m = (M + kMainRows - 1) / kMainRows;
   auto cost = [&](const RoundCost& c, int cols) { return rounds_cost(c, (int64_t)cols * tiles_m, steps); };
   const int tiles_n = (N + 255) / 256;
-  GemmCut best = {tiles_n, 0, 256, 0};
+  GemmCut best = {tiles_n, 0, 256, 0, 0};
   int64_t best_cost = cost(kWide, tiles_n);
   auto consider = [&](int wide) {
     for (const RoundCost& c : kNarrow) {
       const int rest = (N - wide * 256 + c.width - 1) / c.width;
       const int64_t t = cost(kWide, wide) + cost(c, rest) + (wide > 0 ? kLaunch : 0);
-      if (t * 101 < best_cost * 100) { best_cost = t; best = {wide, rest, c.width, 0}; }
+      if (t * 101 < best_cost * 100) { best_cost = t; best = {wide, rest, c.width, 0, 0}; }
     }
   };
   for (int wide = tiles_n - 1; wide > 0 && wide >= tiles_n - kCUs; --wide) consider(wide);   // a round has at most 256 columns
   consider(0);
-  const int half_n = (N + 127) / 128;
+  const int half_n = (N + 127) / 128, half_m = (M + kHalfRows - 1) / kHalfRows;
   const int64_t t = half_cost(M, N, steps);
-  if (t * 101 < best_cost * 100) best = {0, 0, 0, half_n};
+  if (t * 101 < best_cost * 100) best = {0, 0, 0, half_n, (int64_t)half_m * half_n > kCUs ? 5 : 9};
   return best;
 }
-
-}  // namespace
 
 double gemm_rounds_us(int64_t M, int64_t N, int64_t steps) {
   const int64_t tiles_m = (M + kMainRows - 1) / kMainRows;
@@ -656,7 +655,7 @@ hipError_t launch_gemm_nt(const uint16_t* A0, const uint16_t* B0, int64_t lda0, 
     if (width == 256) hipLaunchKernelGGL((gemm_nt_kernel<256, kMainWaves, false>), grid, block, 0, st, a);
     else if (width == 192) hipLaunchKernelGGL((gemm_nt_kernel<192, 4, false>), grid, block, 0, st, a);
     else if (width == 128) hipLaunchKernelGGL((gemm_nt_kernel<128, 4, false>), grid, block, 0, st, a);
-    else if (grid.x > kCUs) hipLaunchKernelGGL(gemm_nt_half_kernel<5>, grid, block, 0, st, a);
+    else if (cut.slots == 5) hipLaunchKernelGGL(gemm_nt_half_kernel<5>, grid, block, 0, st, a);
     else hipLaunchKernelGGL(gemm_nt_half_kernel<9>, grid, block, 0, st, a);
   };
   if (cut.half > 0) launch(kHalf1.width, 0, cut.half);

@@ -54,6 +54,10 @@ hipError_t launch_dequant_t_list(const DeqDesc* d, int n, int64_t ld_out, int rp
 hipError_t launch_gemm_nt(const uint16_t* A0, const uint16_t* B0, int64_t lda0, int64_t ldb0, int K0,
                           const uint16_t* A1, const uint16_t* B1, int64_t lda1, int64_t ldb1, int K1,
                           uint16_t* C, int64_t ldc, int M, int N, hipStream_t st);
+// How the output is cut: 256-wide tile columns from the left, then `rest` of rest_width; or all of it in `half` columns of 128 x 128
+// tiles by the kernel with a ring of `slots` (5 or 9).
+struct GemmCut { int wide, rest, rest_width, half, slots; };
+GemmCut gemm_cut(int M, int N, int steps);
 // Estimated time of the product from the measured costs of a tile round (whole outputs of one tile width, 256 rows), `steps`
 // K-steps: what mid_pays' estimate is fitted to.
 double gemm_rounds_us(int64_t M, int64_t N, int64_t steps);

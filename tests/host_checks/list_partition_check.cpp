@@ -1,7 +1,8 @@
 // Host-side check of the work partition of the few-token list kernels (no GPU needed): for many shape lists the
 // plan's ranges must tile the line of units exactly, be ascending with empty ranges only at the two ends, list_rho_of
 // must invert list_start, and the number of workgroups that share a slab (brute force over the ranges) must equal what the
-// kernels derive from the formula, stay within an arrival word's 23 bits and within the plan's buffer sizes.
+// kernels derive from the formula, stay within an arrival word's 23 bits and within the plan's buffer sizes -- for the plan that
+// the size queries report and for the compact one of a call with less.
 // Prints "OK <plans>" or the first violation.
 #include <cstdio>
 #include <cstdlib>
@@ -16,8 +17,8 @@ static int fail(const char* what, int a, int b, int c) {
   return 1;
 }
 
-static int check(bool bwd, int M, int n, const int* h, const int* o, const int* r) {
-  const ListPlan P = fewlist_plan(bwd, M, n, h, o, r);
+static int check(bool bwd, bool compact, int M, int n, const int* h, const int* o, const int* r) {
+  const ListPlan P = fewlist_plan(bwd, M, n, h, o, r, compact);
   if (!P.ok) return -1;
   const ListPart& q = P.part;
   if (q.grid < 1 || q.grid > 256) return fail("grid", q.grid, 0, 0);
@@ -78,11 +79,12 @@ int main() {
     const int h[7] = {8192, 8192, 8192, 8192, 8192, 8192, 22016}, o[7] = {8192, 8192, 8192, 8192, 22016, 22016, 8192};
     const int r[7] = {64, 64, 64, 64, 64, 64, 64};
     for (int bwd = 0; bwd < 2; ++bwd)
-      for (int M : {1, 4, 16}) {
-        const int rc = check(bwd, M, 7, h, o, r);
-        if (rc) return rc < 0 ? fail("the 65B block is not plannable", bwd, M, 0) : rc;
-        ++plans;
-      }
+      for (int M : {1, 4, 16})
+        for (bool compact : {false, true}) {
+          const int rc = check(bwd, compact, M, 7, h, o, r);
+          if (rc) return rc < 0 ? fail("the 65B block is not plannable", bwd, M, compact) : rc;
+          ++plans;
+        }
   }
   for (int it = 0; it < 4000; ++it) {
     int h[kListMax], o[kListMax], r[kListMax];
@@ -93,9 +95,12 @@ int main() {
       o[l] = 64 * (1 + rnd(big == 0 ? 4 : big == 1 ? 40 : 400));
       r[l] = 16 * rnd(5);
     }
-    const int rc = check(rnd(2), M, n, h, o, r);
-    if (rc > 0) return rc;
-    if (rc == 0) ++plans;
+    const bool bwd = rnd(2);
+    for (bool compact : {false, true}) {
+      const int rc = check(bwd, compact, M, n, h, o, r);
+      if (rc > 0) return rc;
+      if (rc == 0) ++plans;
+    }
   }
   std::printf("OK %d\n", plans);
   return 0;

@@ -2,6 +2,8 @@
 along its contraction: against the fp64 oracle at the edges of its tiles (16 tokens, groups of at most 128, slabs of 128
 outputs, steps of 32 / 128), with and without an adapter, under dropout, for the other 4-bit types and for weights
 without Double Quantization."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -13,6 +15,20 @@ from test_gpu_fused_bwd import _dx, _gemm_launches, fused  # noqa: F401
 from test_gpu_linear import _check
 
 pytestmark = pytest.mark.gpu
+
+
+class _Plan(ctypes.Structure):
+    _fields_ = ([("ok", ctypes.c_bool), ("pack", ctypes.c_bool)] + [(n, ctypes.c_int) for n in ("MF", "KW", "n_tg", "n_slabs", "steps", "n_lparts",
+                "chunk", "max_contrib", "units", "ups", "wgs")] + [(n, ctypes.c_size_t) for n in ("part_floats", "lpart_floats", "pack_elems")] +
+                [("us", ctypes.c_double)])
+
+
+def _plan(M, h, o, r):
+    """The plan of a forward call that brings the reported workspace (the library's internal struct)."""
+    from paper_2305_14314_amd import binding
+    f = ctypes.CDLL(binding.LIB_PATH)._ZN5qlora8mid_planEblllimb
+    f.restype, f.argtypes = _Plan, [ctypes.c_bool, ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_size_t, ctypes.c_bool]
+    return f(False, M, h, o, r, max((h + (r + 63) // 64 * 64) * o * 2, 32 << 20), False)
 
 
 # token tiles 2 .. 8 per group, one to five groups, a remainder of one token; h and o with a 64-wide remainder (half a slab
@@ -170,10 +186,12 @@ def test_smallest_accepted_workspace(oracle, synth, M, h, o, r):
 @pytest.mark.parametrize("M", [52, 90, 113, 160, 333, 500])
 @pytest.mark.parametrize("h,o", [(4096, 11008), (1088, 1344)])
 def test_midtok_forward_packed_or_not(synth, M, h, o):
-    """The forward's token operand packed by a launch of its own (the large weight) and read as it lies, in several groups of
-    tokens (the small one), against fp64 products with the dequantised weight; the same with T saved, bit for bit."""
+    """The forward's token operand packed by a launch of its own (the large weight, but for 90 tokens) and read as it lies, in
+    several groups of tokens (the small one), against fp64 products with the dequantised weight; the same with T saved, bit for bit."""
     import paper_2305_14314_amd as ql
     r, s = 48, 0.5
+    plan = _plan(M, h, o, r)
+    assert plan.ok and plan.pack == (o == 11008 and M != 90) and (plan.pack or plan.n_tg > 1)
     g = torch.Generator(device="cuda")
     g.manual_seed(4000 + M)
     bf = lambda *shape, sd=1.0: torch.empty(shape, device="cuda").normal_(0, sd, generator=g).bfloat16()
@@ -191,11 +209,13 @@ def test_midtok_forward_packed_or_not(synth, M, h, o):
 
 
 @pytest.mark.parametrize("M", [3, 9, 11, 12, 16])
-@pytest.mark.parametrize("h,o,r", [(1024, 1024, 0), (1088, 1344, 48), (1024, 1024, 128), (2048, 4096, 64)])
+@pytest.mark.parametrize("h,o,r", [(1024, 1024, 0), (1088, 1344, 48), (1024, 1024, 128), (2048, 4096, 64), (1344, 1088, 48), (1024, 1024, 144)])
 def test_few_tokens_forward_decoded_once(synth, M, h, o, r):
-    """Up to 16 tokens on a small weight, forward: with the reported workspace (several tokens: decoded once for all of them)
-    and with the smallest that the streaming kernel takes, both against fp64 products with the dequantised weight.  T is a
-    sum of h terms of which neither path drops bits, so the two agree to one rounding of the result and the order of the sums."""
+    """Up to 16 tokens on a small weight, forward: with the reported workspace (from 12 tokens on decoded once for all of them, if the
+    contraction is no longer than the outputs and the rank up to 128) and with the smallest that the streaming kernel takes, both
+    against fp64 products with the dequantised weight.  Which of the two ran shows in how much of the workspace was written.
+    T is a sum of h terms of which neither path drops bits, so the two agree to one rounding of the result and the order of the
+    sums: a unit in the last place, 2^-7 of the value at most, and h 2^-24 of the largest."""
     import paper_2305_14314_amd as ql
     s = 2.0
     g = torch.Generator(device="cuda")
@@ -203,11 +223,23 @@ def test_few_tokens_forward_decoded_once(synth, M, h, o, r):
     bf = lambda *shape, sd=1.0: torch.empty(shape, device="cuda").normal_(0, sd, generator=g).bfloat16()
     Wq = ql.qlora_nf4_quantize(synth.normal_f32_device((h, o), synth.SIGMA_W, 5100 + M))
     X, L1, L2 = bf(M, h), (bf(h, r, sd=0.05) if r else None), (bf(r, o, sd=0.05) if r else None)
-    small = accepted_workspace(ql.binding.lib(), False, M, h, o, r)
+    small, head = accepted_workspace(ql.binding.lib(), False, M, h, o, r), ql.binding.WORKSPACE_HEADER_BYTES
     T = torch.empty((M, 2 * r), dtype=torch.bfloat16, device="cuda") if r else None
-    Y = ql.qlora_linear_fwd(X, Wq, L1, L2, s, T_save=T)
-    ws = torch.zeros(small, dtype=torch.uint8, device="cuda")
-    Ys = ql.qlora_linear_fwd(X, Wq, L1, L2, s, workspace=ws)
+
+    def run(n, **kw):                                          # the output, and the bytes behind the header up to the last one written
+        ws = ql.workspace_alloc(ql.qlora_linear_fwd_sizes(M, h, o, r))
+        ws[head:].fill_(0x7F)
+        Y = ql.qlora_linear_fwd(X, Wq, L1, L2, s, workspace=ws[:n], **kw)
+        assert int(ws[:head].max()) == 0
+        return Y, int((ws[head:] != 0x7F).nonzero().max()) + 1
+
+    Y, used = run(None, T_save=T)
+    Ys, streamed = run(small)
+    plan = _plan(M, h, o, r)
+    align = lambda b: (b + 255) // 256 * 256
+    decoded = align(plan.part_floats * 4) + plan.lpart_floats * 4 if r else plan.part_floats * 4
+    assert abs(decoded - streamed) > 256                       # the two can be told apart
+    assert abs(used - (decoded if M >= 12 and h <= o and r <= 128 else streamed)) < 16
     ref = X.double() @ ql.qlora_nf4_dequant(Wq).double()
     if r:
         t = X.double() @ L1.double()
@@ -216,6 +248,7 @@ def test_few_tokens_forward_decoded_once(synth, M, h, o, r):
         assert (got - t).abs().max() <= 2.0 ** -14 * t.abs().max() + 1e-6
     _check(host_bits(Y), ref.cpu().numpy(), f"Y M={M}")
     _check(host_bits(Ys), ref.cpu().numpy(), f"Y, smallest workspace, M={M}")
+    assert ((Y.double() - Ys.double()).abs() <= 2.0 ** -7 * Ys.double().abs() + h * 2.0 ** -24 * ref.abs().max()).all()
 
 
 @pytest.mark.parametrize("M,h,o,r", [(2, 4096, 320, 256), (5, 1600, 1088, 112), (9, 320, 64, 80), (17, 1600, 1088, 256), (31, 1088, 2112, 128),

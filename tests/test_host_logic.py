@@ -25,7 +25,8 @@ def test_nf4_index_schemes_agree(tmp_path):
 
 def test_list_partition_tiles_the_work(tmp_path):
     """The range formula of the few-token list kernels (evaluated alike by the size queries, the launcher and the
-    kernels): exact tiling, inverse map, contributor counts against brute force, for thousands of shape lists."""
+    kernels): exact tiling, inverse map, contributor counts against brute force, for thousands of shape lists and both plans
+    of each."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     if not (os.path.exists(hipcc) or shutil.which(hipcc)):
         pytest.skip("hipcc not available")
@@ -39,7 +40,7 @@ def test_list_partition_tiles_the_work(tmp_path):
                     "-L", pkg, "-lqlora_hip", "-Wl,-rpath," + pkg], check=True, capture_output=True)
     out = subprocess.run([exe], check=True, capture_output=True, text=True, timeout=300).stdout
     assert out.startswith("OK "), out
-    assert int(out.split()[1]) > 2000
+    assert int(out.split()[1]) > 4000
 
 
 def test_list_plan_is_the_plain_search(tmp_path):

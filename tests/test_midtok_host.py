@@ -51,3 +51,18 @@ def test_mid_mfma_operands_are_written_in_time(tmp_path):
                          text=True).stdout
     assert out.startswith("OK "), out
     assert int(out.split()[1]) > 3000
+
+
+def test_several_tokens_decoded_once_thresholds():
+    """From which call on a forward of up to 16 tokens leaves the streaming kernel: tokens, the longer side, rank, weights."""
+    import ctypes
+    from paper_2305_14314_amd import binding, build
+    if not os.path.exists(binding.LIB_PATH):
+        build.build(verbose=False)
+    f = ctypes.CDLL(binding.LIB_PATH)._ZN5qlora13mid_beats_fewEllli
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_int64] * 3 + [ctypes.c_int]
+    assert not f(11, 1024, 1024, 16) and f(12, 1024, 1024, 16)
+    assert f(16, 2048, 2048, 64) and f(16, 2048, 2112, 64) and not f(16, 2112, 2048, 64)
+    assert f(16, 2048, 2048, 128) and not f(16, 2048, 2048, 144)
+    assert f(16, 4096, 16320, 64) and not f(16, 4096, 16384, 64)     # 4 weights / 2^20 against the square of the tokens
+    assert f(13, 4096, 8192, 64) and not f(12, 4096, 9216, 64)
