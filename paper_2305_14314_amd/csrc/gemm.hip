@@ -580,8 +580,11 @@ __global__ __launch_bounds__(256, NSLOT == 5 ? 2 : 1) void gemm_nt_half_kernel(c
 // One workgroup per CU: tiles run in rounds of 256, and a narrower tile costs less than its share is worth only where it
 // fills a round better.  Measured per K-step of 64 (a launch's time / rounds / steps): a round of 256-wide tiles takes
 // 1.05 us nearly empty and 1.36 us full (the board's power limit), 192-wide 0.86 / 1.05, 128-wide 0.66 / 0.79; a second
-// launch about 3 us.  Tiles of 128 x 128 take 0.45 / 0.57 in a round of 256 (nine slots), 0.58 / 0.84 in a round of 512, two to
-// a CU (five slots).  The cut of the least cost by these figures is taken (of
+// launch about 3 us.  Tiles of 128 x 128 take 0.45 / 0.57 in a round of 256 (nine slots), 0.78 / 0.82 in a round of 512, two to
+// a CU (five slots), less 1 us: with short contractions they win, with long ones the operands they read twice as often cost more.
+// (At 0.58 / 0.84 and nothing less calls of 257 - 300 tiles with K from 2300 on took 4 - 15 % longer than with larger tiles: 1591 x 2880, K 5504
+// 78 us against 68, 2340 x 1984 at rank 128, K 4096 68 against 62; of 243 random products of more than 256 tiles 13 lost more than 3 %, now none.)
+// The cut of the least cost by these figures is taken (of
 // about equal ones, the one of more 256-wide tiles).  dX of a stacked q / k / v at 2000 tokens
 // (5120 columns, K 15552: 160 tiles of 256) 310 -> 263 us inside the training call with 216 tiles of 192; each alone and
 // repeated: 1024 x 4096 (K 4160) 69 -> 43 us and 600 x 8192 (K 8256) 132 -> 86 us with 128-wide tiles; 4096 x 5120 (K 5184) 193 -> 162 and 1500 x 11008 (K 4160)
@@ -591,7 +594,8 @@ __global__ __launch_bounds__(256, NSLOT == 5 ? 2 : 1) void gemm_nt_half_kernel(c
 // (20.6); where the larger tiles fill their rounds they lose: 4096 tokens 4096 x 4096 117 against 135.
 struct RoundCost { int width, empty, full; };                // of a round, in 0.01 us per K-step
 constexpr RoundCost kWide = {256, 105, 136}, kNarrow[2] = {{192, 86, 105}, {128, 66, 79}};
-constexpr RoundCost kHalf1 = {0, 45, 57}, kHalf2 = {0, 58, 84};   // 128 x 128: up to one, up to two workgroups per CU
+constexpr RoundCost kHalf1 = {0, 45, 57}, kHalf2 = {0, 78, 82};   // 128 x 128: up to one, up to two workgroups per CU
+constexpr int kHalf2Less = 100;                              // the latter's shorter start and end, 0.01 us
 constexpr int kCUs = 256;
 int64_t rounds_cost(const RoundCost& c, int64_t tiles, int64_t steps, int64_t per_round = kCUs) {
   const int64_t last = tiles % per_round;
@@ -599,7 +603,7 @@ int64_t rounds_cost(const RoundCost& c, int64_t tiles, int64_t steps, int64_t pe
 }
 int64_t half_cost(int64_t M, int64_t N, int64_t steps) {
   const int64_t tiles = (M + kHalfRows - 1) / kHalfRows * ((N + 127) / 128);
-  return tiles <= kCUs ? rounds_cost(kHalf1, tiles, steps) : rounds_cost(kHalf2, tiles, steps, 2 * kCUs);
+  return tiles <= kCUs ? rounds_cost(kHalf1, tiles, steps) : rounds_cost(kHalf2, tiles, steps, 2 * kCUs) - kHalf2Less;
 }
 }  // namespace
 

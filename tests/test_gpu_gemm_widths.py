@@ -35,8 +35,8 @@ def _cut(M, K, N, r):
 # one K-step, up to ten (one turn of the nine-slot ring and the segment switch), ragged rows and columns, up to one workgroup per
 # compute unit and just above
 @pytest.mark.parametrize("M,h,o,r,slots", [(513, 64, 128, 16, 9), (640, 128, 192, 0, 9), (641, 512, 320, 16, 9), (769, 576, 64, 32, 9),
-                                           (1025, 640, 3520, 16, 9), (700, 704, 5504, 0, 5), (2049, 1216, 1984, 48, 5),
-                                           (1100, 320, 4224, 16, 5), (1300, 768, 3520, 48, 5)])
+                                           (1025, 640, 3520, 16, 9), (700, 704, 5504, 0, 5), (1100, 320, 4224, 16, 5),
+                                           (1300, 768, 3520, 48, 5), (2300, 832, 2368, 64, 5)])
 def test_half_tiles(oracle, synth, M, h, o, r, slots):
     """Tiles of 128 x 128 by the kernel that the shape is meant for."""
     assert _cut(M, h, o, r) == (False, 0, slots)
@@ -51,8 +51,8 @@ def test_nine_slot_ring(oracle, synth, kt, r):
     _widths(oracle, synth, 520, 64 * kt, 320, r)
 
 
-@pytest.mark.parametrize("M,h,o,r,cut", [(1000, 128, 15296, 16, (True, 0, 0)), (513, 64, 9024, 16, (False, 128, 0)), (1500, 320, 3200, 16, (False, 128, 0)),
-                                         (1000, 64, 8256, 16, (False, 192, 0)), (4096, 640, 13376, 16, (True, 192, 0)),
+@pytest.mark.parametrize("M,h,o,r,cut", [(1000, 640, 15296, 16, (True, 0, 0)), (2049, 1216, 1984, 48, (False, 128, 0)),
+                                         (1500, 1280, 3200, 16, (False, 128, 0)), (1000, 64, 8256, 16, (False, 192, 0)), (4096, 640, 13376, 16, (True, 192, 0)),
                                          (4100, 640, 12544, 16, (True, 128, 0))])
 def test_each_cut(oracle, synth, M, h, o, r, cut):
     """256-wide columns alone, narrower ones alone, and both beside each other."""
