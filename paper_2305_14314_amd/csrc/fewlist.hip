@@ -763,9 +763,18 @@ ListPlan fewlist_plan(bool bwd, int M, int n, const int* h, const int* o, const 
   // shared by more workgroups than an arrival word has bits for
   ListPart best{}, probe{};
   best.n_adapter = probe.n_adapter = adapters;
-  // Below this bound 23 workgroups do not cover the longest slab, the first taking T - kTail - kFin (at least one unit), the others
-  // T - kTail at most: a grid that covers the line with less is passed over at once.
+  // A bound too low for a grid that fits: below `need` 23 workgroups do not cover the longest slab, the first taking
+  // T - kTail - kFin (at least one unit), the others T - kTail at most; and the first workgroups, whose adapter items leave them
+  // little, must not be more than 23 on the first slab.  A grid that covers the line with less is passed over at once.
   const int need = ups_max > 23 ? kTail + std::min((ups_max + 20) / 22, (ups_max + kFin + 22) / 23) : 0;
+  auto first_slab_fits = [&](int grid, int T) {
+    int u = 0;
+    for (int rho = 0, used = 0; rho < grid && used < 23 && u < P.ups[0]; ++rho) {
+      const int budget = T - kItem * (adapters / grid + (rho < adapters % grid));
+      if (budget > 0) { u += std::max(budget - kTail - (u == 0 ? kFin : 0), 1); ++used; }
+    }
+    return u >= P.ups[0];
+  };
   int lo = 0;
   bool follows = false;
   for (int grid = (int)std::min<int64_t>(kListGridMax, units); grid >= 1; grid = grid > 32 ? grid - 32 : grid - 1) {
@@ -776,9 +785,18 @@ ListPlan fewlist_plan(bool bwd, int M, int n, const int* h, const int* o, const 
     // Fewer workgroups do not cover more: a smaller grid goes on from the bound of the one before, in growing steps.
     best.grid = probe.grid = grid;
     int hi = std::min(all, (all + grid - 1) / grid + 2 * kTail + kFin);   // walk(lo) leaves something undone, walk(hi) nothing
-    if (need - 1 > lo && all / grid < need) {
-      if (hi < need || walk(probe, need - 1)) continue;
-      lo = need - 1;
+    int low = all / grid < need ? std::max(lo, need - 1) : lo;
+    if (!first_slab_fits(grid, std::max(low + 1, all / grid))) {
+      const int items = kItem * (adapters / grid + 1);       // above it every workgroup takes something, the more the higher the bound
+      if (low < items && items < hi && !walk(probe, items)) lo = low = items;
+      for (int fits = hi + 1; low >= items && fits - low > 1;) {
+        const int T = low + (fits - low) / 2;
+        (first_slab_fits(grid, T) ? fits : low) = T;
+      }
+    }
+    if (low > lo) {
+      if (low >= hi || walk(probe, low)) continue;
+      lo = low;
     }
     bool filled = false;
     int64_t step = follows ? 1 : all;
