@@ -581,11 +581,15 @@ struct MidFinArgs {
 };
 
 // Quadruples of ranks of a token, as a shift, and how many of them a thread of a finalize workgroup sums together: one by one up
-// to rank 64 and at few tokens, else all of its up to four.  (A batch of requests for each, one after the other, found by
+// to rank 64 and at few tokens, else all of its two or up to four.  (A batch of requests for each, one after the other, found by
 // divisions, and the tokens past M summed too: forward calls of 2 tokens 256 x 1344 at rank 256 19.1 us, 47 tokens 256 x 7296 at
-// rank 256 22.4, 25 tokens 512 x 2048 at rank 128 13.3; now 17.2, 20.4, 12.3.)
+// rank 256 22.4, 25 tokens 512 x 2048 at rank 128 13.3, 39 tokens 2944 x 1280 at rank 128 17.6; now 17.2, 20.4, 12.2, 17.1 -- the last 17.8
+// with four quadruples per thread where there are two.)
 __host__ __device__ inline int mid_quad_shift(int r) { return r <= 32 ? 3 : r <= 64 ? 4 : r <= 128 ? 5 : 6; }
-inline int mid_quads(int M, int r) { return std::min(M, 16) << mid_quad_shift(r) <= 256 ? 1 : 4; }
+inline int mid_quads(int M, int r) {
+  const int n = std::min(M, 16) << mid_quad_shift(r);
+  return n <= 256 ? 1 : n <= 512 ? 2 : 4;
+}
 
 // An infinite hi is the whole value: what is left of it is NaN (or, of a value that rounded up to infinity, -Inf).  Two bf16 per dword.
 __device__ __forceinline__ uint32_t lo_of_finite(uint32_t hi, uint32_t lo) {
@@ -980,6 +984,7 @@ hipError_t launch_mid(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const
   auto pick = [&](auto D, auto terms) {                      // one tile of tokens
     if (lean) launch(Int<1>{}, D, std::true_type{}, terms, Int<1>{});
     else if (mid_quads(M, r) == 1) launch(Int<1>{}, D, std::false_type{}, terms, Int<1>{});
+    else if (mid_quads(M, r) == 2) launch(Int<1>{}, D, std::false_type{}, terms, Int<2>{});
     else launch(Int<1>{}, D, std::false_type{}, terms, Int<4>{});
   };
   if (!bwd && M <= 16) pick(std::false_type{}, Int<3>{});
