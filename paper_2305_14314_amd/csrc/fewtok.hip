@@ -20,11 +20,12 @@
 //
 // Where the time of a call goes (8192 x 8192, one token, rank 64, clock readings in the kernel, us from its start): table
 // built 1.7, first wave out of the loop 7.4, last 10.0 (the decode's vector and LDS work, ~5.5 each, not the stream of
-// 34.6 MB), partial stored 10.8, slab complete 12.4, partials read 14.3, output 15.5.  The whole call takes 15.7, 20.3 when the
+// 34.6 MB), partial stored 10.8, slab complete 12.4, partials read 14.3, output 15.5.  The whole call takes 15.7 (three weights in turn, 104 MB, part of
+// which the last-level cache still holds), 20.3 when the
 // way from the loop to the output was fences, partials read in groups of four with the adapter's behind them, and a
 // scalar product over the ranks on a quarter of the threads (10.8 -> 21.6).  4096 x 4096 15.4 -> 11.5; 4096 x 11008
 // 18.6 -> 13.8; 2048 x 8192 at rank 128 24.4 -> 13.1; 12 tokens 8192 x 8192 26.4 -> 19.9; q / k / v 3 x 5120 x 5120 at 4
-// tokens in one launch 21.4 -> 18.3; input gradient 8192 x 8192 26.6 -> 23.1 at one token, 34.7 -> 30.3 at 16.
+// tokens in one launch 21.4 -> 18.2; input gradient 8192 x 8192 26.6 -> 23.1 at one token, 34.7 -> 30.3 at 16.
 //
 // A step of a wave costs address-unit, LDS-lookup, VALU and MFMA time one after the other (a wave issues
 // in order), so workgroups are 16 waves (4 per SIMD, 128 VGPRs each) and every wave keeps 2-3 steps of

@@ -882,8 +882,8 @@ MidPlan mid_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room, 
 // what counts (K = 22016, N = 8192, rank 64 at 256 tokens 117 against 421; 112 against 334 now).  A call goes to the other path where that
 // is estimated faster by a fifth.  The fit is older than the 128 x 128 tiles, with which the other path's estimate has become
 // some 17 % high, and the line has not been moved since: of 947 random calls that it decides 285 are now more than 3 % from the
-// faster path and 131 more than 20 %, all of these decoded here, the worst 1.9 x (dX 2752 x 3136, rank 144, 511 tokens 53.8 us here, 35.1
-// dequantised).  They take no longer here than they did before those tiles.
+// faster path and 131 more than 20 %, all of these decoded here, the worst 1.9 x (under dropout 30 tokens 256 x 64 at rank 256 23.6 us
+// here, 12.6 dequantised; dX 2752 x 3136, rank 144, 511 tokens 53.8 and 35.1).  They take no longer here than they did before those tiles.
 bool mid_pays(const MidPlan& p, bool bwd, int64_t M, int64_t h, int64_t o, int r, bool fix) {
   const double K = (double)(bwd ? o : h), N = (double)(bwd ? h : o), MN = 1e-6 * (double)M * N;
   const double mid = 6.5 + 0.88 * p.us + (p.pack ? 4.3 + 0.053 * r : 0.027 * r) + 0.35 * p.max_contrib * MN + 0.0034 * r * MN +
