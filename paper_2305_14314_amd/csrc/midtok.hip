@@ -911,10 +911,16 @@ bool mid_pays(const MidPlan& p, bool bwd, int64_t M, int64_t h, int64_t o, int r
 // contraction longer than the outputs are wide has too few strips (3072 x 1536 at 4, 11 11.6 / 12.7, 13.2 / 13.4), and a large rank
 // makes the adapter's launch the longer part (2048 x 2048 rank 256 at 4, 11 22.7 / 23.9, 24.8 / 24.9).  And two launches cost the host
 // 12.5 us a call against 9.2: called one by one, 1024 x 2624 rank 32 at 5 tokens takes 11.5 streamed and 12.6 here, 2048 x 2048 at
-// 8, 11, 14 12.6 / 12.6, 13.4 / 12.8, 14.5 / 12.7, 1024 x 1024 at 16 15.0 / 12.8.  So: from 12 tokens, where any layer streams for
-// longer than that, and above sqrt(4 weights / 2^20), contraction no longer than the outputs, rank up to 128.
+// 8, 11, 14 12.6 / 12.6, 13.4 / 12.8, 14.5 / 12.7, 1024 x 1024 at 16 15.0 / 12.8.  So: from 12 tokens, above sqrt(4 weights / 2^20),
+// contraction no longer than the outputs, rank up to 128, and a contraction that streams for as long as the host takes over two
+// launches.  One by one at 12, 16 tokens on 4096 outputs: rank 64, K = 64 9.9 / 11.4, 10.8 / 11.4, 256 11.2 / 11.9, 12.3 / 11.9,
+// 512 12.9 / 12.1, 13.8 / 12.2, 1024 13.1 / 12.1, 14.0 / 12.0; rank 128, K = 64 11.2 / 11.2, 12.0 / 11.3, 256 12.4 / 12.3, 13.3 / 12.5;
+// no adapter, K = 256 8.8 / 11.6, 8.9 / 11.8, 1024 10.2 / 11.8, 10.6 / 11.9, 2048 11.0 / 11.9, 11.8 / 11.8, 2752 11.4 / 11.0,
+// 12.3 / 10.9, 4096 12.1 / 11.7, 12.9 / 11.8 (2048 x 2048 at 16 11.5 / 11.9).  Replayed from a graph most of what that last condition leaves
+// to the streaming kernel would be faster here (rank 64, 256 x 4096 at 16 12.8 / 10.6; no adapter, 1024 x 4096 11.2 / 9.4).
 bool mid_beats_few(int64_t M, int64_t h, int64_t o, int r) {
-  return h <= o && r <= 128 && (double)(M * M) > 4. * (double)h * (double)o / (1 << 20) && M >= 12;
+  const bool long_enough = r > 64 ? h >= 256 : r > 0 ? h >= 512 : M * h > 32768;
+  return M >= 12 && long_enough && h <= o && r <= 128 && (double)(M * M) > 4. * (double)h * (double)o / (1 << 20);
 }
 
 hipError_t launch_mid(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const MidPlan& p, const uint16_t* L1,

@@ -54,7 +54,8 @@ def test_mid_mfma_operands_are_written_in_time(tmp_path):
 
 
 def test_several_tokens_decoded_once_thresholds():
-    """From which call on a forward of up to 16 tokens leaves the streaming kernel: tokens, the longer side, rank, weights."""
+    """From which call on a forward of up to 16 tokens leaves the streaming kernel: tokens, the longer side, rank, weights, and a
+    contraction long enough that the host has the second launch out in time (called one by one)."""
     import ctypes
     from paper_2305_14314_amd import binding, build
     if not os.path.exists(binding.LIB_PATH):
@@ -66,3 +67,6 @@ def test_several_tokens_decoded_once_thresholds():
     assert f(16, 2048, 2048, 128) and not f(16, 2048, 2048, 144)
     assert f(16, 4096, 16320, 64) and not f(16, 4096, 16384, 64)     # 4 weights / 2^20 against the square of the tokens
     assert f(13, 4096, 8192, 64) and not f(12, 4096, 9216, 64)
+    assert f(12, 512, 4096, 16) and not f(16, 448, 4096, 64)         # short contractions stream in less than two launches take the host
+    assert f(12, 256, 4096, 80) and not f(16, 192, 4096, 128)
+    assert f(12, 2752, 4096, 0) and not f(12, 2688, 4096, 0) and not f(16, 2048, 4096, 0)
