@@ -221,13 +221,13 @@ qlora_status qlora_workspace_init(void* workspace, size_t workspace_bytes, void*
 
 /* Workspace (bytes) qlora_linear_fwd / qlora_linear_bwd need for this shape
  * (header included), whatever the weight's data type and the path it takes:
- * the streaming kernels (4-bit double-quantised, M <= 16), the product that
- * decodes the weight itself (4-bit, M <= 512) or dequantise + GEMM.  The
+ * the streaming kernels (4-bit double-quantised, M <= 16), a product that
+ * decodes the weight itself (4-bit, M <= 2048) or dequantise + GEMM.  The
  * largest is reported; a call also accepts the smaller size of the dequantise
  * + GEMM plan and then splits the second kind of product less or takes the
  * third.  Every call with at least the reported size gives the same bits for
  * the same arguments; with less the fp32 sums may be formed in another order.
- * Up to 512 tokens that order depends on M too, so a token's row can differ in
+ * Up to 2048 tokens that order depends on M too, so a token's row can differ in
  * its last bits between calls of different M. */
 qlora_status qlora_linear_fwd_sizes(int64_t M, int64_t h, int64_t o, int32_t r, size_t* workspace_bytes);
 qlora_status qlora_linear_bwd_sizes(int64_t M, int64_t h, int64_t o, int32_t r, size_t* workspace_bytes);
@@ -240,8 +240,9 @@ qlora_status qlora_linear_bwd_sizes(int64_t M, int64_t h, int64_t o, int32_t r, 
  * receives T = X * L1 for the backward pass as a pair of bf16 matrices side by
  * side: columns [0, r) hold bf16(T), columns [r, 2r) hold bf16(T - bf16(T)).  Any M >= 1 is accepted: a few
  * tokens (M <= 16) take a bandwidth-bound streaming path -- 12 or more of them on a small weight, with the reported workspace,
- * already the next --, up to 512 a product that decodes the weight itself unless an estimate says that the next is faster
- * (short contractions, large ranks), larger M the MFMA GEMM on a dequantised copy. */
+ * already the next --, up to 512 one of two products that decode the weight themselves unless an estimate says that the next is
+ * faster (short contractions, large ranks), up to 2048 the second of them where it is estimated faster than the next, and larger M the MFMA
+ * GEMM on a dequantised copy. */
 qlora_status qlora_linear_fwd(const uint16_t* X, const qlora_nf4_view* Wq,
                               const uint16_t* L1, const uint16_t* L2, float s,
                               int64_t M, int32_t r,
@@ -257,7 +258,7 @@ qlora_status qlora_linear_fwd(const uint16_t* X, const qlora_nf4_view* Wq,
  * Each of dX, dL1, dL2 may be NULL and is then not computed.  X is needed only
  * for dL1 / dL2 (may be NULL when both are NULL).  T_saved is the T_save of the
  * forward call or NULL, in which case X * L1 is recomputed (gradient
- * checkpointing; up to 512 tokens the sum may be formed in another order than
+ * checkpointing; up to 2048 tokens the sum may be formed in another order than
  * in the forward call).  With r = 0 only dX is produced. */
 qlora_status qlora_linear_bwd(const uint16_t* dY, const uint16_t* X, const qlora_nf4_view* Wq,
                               const uint16_t* L1, const uint16_t* L2, float s,
@@ -418,7 +419,7 @@ qlora_status qlora_hbm_probe(int32_t mode, const void* src, void* dst, int64_t b
  * never in HBM).  The decoded tiles are the same bits either way; the adapter term is added first instead of last in
  * mode 1, so outputs may differ in the last bf16 bit.  Mode 1 applies to 4-bit types with cols % 64 == 0 and r <= 64 and
  * falls back to mode 0 otherwise.  Neither form runs where the few-token streaming kernels do, and in mode 0 a 4-bit
- * weight at up to 512 tokens takes the product described at qlora_linear_fwd instead.  mode < 0 only queries.
+ * weight at up to 2048 tokens takes the products described at qlora_linear_fwd instead where those are estimated faster.  mode < 0 only queries.
  * Returns the previous mode.  Process-wide. */
 int32_t qlora_bwd_fused_dequant(int32_t mode);
 

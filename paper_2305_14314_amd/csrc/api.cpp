@@ -180,6 +180,20 @@ MidWs plan_mid(void* buf, size_t room, size_t base, bool bwd, int64_t M, int64_t
   return m;
 }
 
+// The form of that path whose waves share a decode, in the same region, where a call of more than kFewTokens tokens is sooner done so than by
+// `mid` (whose plan is made either way) or by dequantise + GEMM.  The sizes do not ask for it: a shape without the room goes the other way.
+struct WideWs { qlora::WidePlan plan; float* lpart; uint16_t* xpack; };
+WideWs plan_wide(void* buf, size_t room, const qlora::MidPlan& mid, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r,
+                 bool fix = false) {
+  WideWs w{};
+  if (M <= qlora::kFewTokens) return w;
+  w.plan = qlora::wide_plan(bwd, M, h, o, r, room);
+  w.plan.ok = w.plan.ok && qlora::wide_pays(w.plan, mid.ok ? &mid : nullptr, bwd, M, h, o, r, fix);
+  w.lpart = (float*)buf;
+  w.xpack = (uint16_t*)((char*)buf + align_up(w.plan.lpart_floats * sizeof(float), 256));
+  return w;
+}
+
 // Floats of the split-K partials of the largest of a layer's skinny products, each in a launch of its own.
 size_t small_part_floats(int64_t M, int64_t h, int64_t o, int32_t r) {
   const size_t u = (size_t)qlora::small_job_splits((int)M, r, (int)o, 0) * M * r;
@@ -636,6 +650,14 @@ qlora_status linear_fwd_impl(const uint16_t* X, const qlora_nf4_view* Wq, const 
     const FwdPlan q = plan_fwd(workspace, M, h, o, r, false);
     if (workspace_bytes >= q.bytes) mid = mid_ws(q.min_bytes);
   }
+  if (!p.few && streams_mid(Wq)) {
+    const WideWs wide = plan_wide((char*)workspace + qlora::kWorkspaceHeaderBytes, workspace_bytes - qlora::kWorkspaceHeaderBytes, mid.plan,
+                                  false, M, h, o, r);
+    if (wide.plan.ok) {
+      QL_TRY(qlora::launch_wide(false, X, (int)M, W, wide.plan, L1, L2, r, s, keep_mask, wide.lpart, wide.xpack, Y, T_save, st));
+      return QLORA_OK;
+    }
+  }
   if (mid.plan.ok) {
     QL_TRY(qlora::launch_mid(false, X, (int)M, W, mid.plan, L1, L2, r, s, keep_mask, mid.part, mid.lpart, mid.xpack, Y, T_save, st));
     return QLORA_OK;
@@ -870,10 +892,16 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
   const bool fused = !p.few && dX && g_bwd_fused.load(std::memory_order_relaxed) && W.dtype != qlora::kTypeInt8 && o % 64 == 0 &&
                      qlora::gemm_nt_fused_fits((int)o, K1, (int)h);
   // a few hundred tokens: decode inside the product; the finalize step applies the dropout mask to the adapter's term
-  const MidWs mid = !p.few && dX && !fused && streams_mid(Wq)
-                        ? plan_mid(p.Wd, p.wd_bytes, (size_t)h * o * sizeof(uint16_t), true, M, h, o, r, keep_mask != nullptr) : MidWs{};
+  const bool decoded = !p.few && dX && !fused && streams_mid(Wq);
+  const MidWs mid = decoded ? plan_mid(p.Wd, p.wd_bytes, (size_t)h * o * sizeof(uint16_t), true, M, h, o, r, keep_mask != nullptr) : MidWs{};
+  // (that kernel reads the mask eight bytes at a time)
+  const WideWs wide = decoded && ((uintptr_t)keep_mask & 7) == 0 ? plan_wide(p.Wd, p.wd_bytes, mid.plan, true, M, h, o, r, keep_mask != nullptr)
+                                                                     : WideWs{};
   qlora::FinList fin{};
-  if (mid.plan.ok) {
+  if (wide.plan.ok) {
+    QL_TRY(qlora::launch_wide(true, dY, (int)M, W, wide.plan, L1, L2, r, s, keep_mask, wide.lpart, wide.xpack, dX,
+                              (r > 0 && want1) ? p.Uhl : nullptr, st));
+  } else if (mid.plan.ok) {
     QL_TRY(qlora::launch_mid(true, dY, (int)M, W, mid.plan, L1, L2, r, s, keep_mask, mid.part, mid.lpart, mid.xpack, dX,
                              (r > 0 && want1) ? p.Uhl : nullptr, st));
   } else if (p.few && dX) {
@@ -890,7 +918,7 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
     QL_TRY(batch.launch());
     fin = batch.fin;
   }
-  if (!p.few && dX && !mid.plan.ok) {
+  if (!p.few && dX && !mid.plan.ok && !wide.plan.ok) {
     const uint16_t* B1 = L1;
     if (r > 0 && p.L1p) { fin.add(fin_pad(L1, h, r, p.L1p, p.rp, p.rp)); B1 = p.L1p; }
     if (fused) {

@@ -635,6 +635,7 @@ double gemm_rounds_us(int64_t M, int64_t N, int64_t steps) {
   for (const RoundCost& c : kNarrow) best = std::min(best, rounds_cost(c, (N + c.width - 1) / c.width * tiles_m, steps));
   return 0.01 * (double)best;
 }
+double gemm_us(int64_t M, int64_t N, int64_t steps) { return std::min(gemm_rounds_us(M, N, steps), 0.01 * (double)half_cost(M, N, steps)); }
 
 hipError_t launch_gemm_nt(const uint16_t* A0, const uint16_t* B0, int64_t lda0, int64_t ldb0, int K0,
                           const uint16_t* A1, const uint16_t* B1, int64_t lda1, int64_t ldb1, int K1,

@@ -61,6 +61,8 @@ GemmCut gemm_cut(int M, int N, int steps);
 // Estimated time of the product from the measured costs of a tile round (whole outputs of one tile width, 256 rows), `steps`
 // K-steps: what mid_pays' estimate is fitted to.
 double gemm_rounds_us(int64_t M, int64_t N, int64_t steps);
+// The same with the 128 x 128 tiles among them: what wide_pays weighs against.
+double gemm_us(int64_t M, int64_t N, int64_t steps);
 
 // The same product with the weight-side operand of segment 0 decoded inside the kernel: Bq = N rows of K0 / 2 bytes of
 // 4-bit codes, Bc = N x K0 / 64 fp32 block constants, tab16 = the data type's 16 values (all device memory).  The
@@ -210,6 +212,25 @@ bool mid_beats_few(int64_t M, int64_t h, int64_t o, int r);
 hipError_t launch_mid(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const MidPlan& p, const uint16_t* L1,
                       const uint16_t* L2, int r, float scale, const uint8_t* mask, float* part, float* lpart, uint16_t* xpack,
                       uint16_t* out, uint16_t* hl, hipStream_t st);
+
+// widetok.hip: the same products, the decode shared by the waves of a workgroup, which finishes its outputs itself: no partial sums of
+// the product.  Above kMidTokens too; from kWideTokens on dequantise + GEMM is the faster one nearly always (1200 - 2048 tokens: 36 of 112
+// random calls are faster here, by 3 % on average).
+constexpr int kWideTokens = 2048;
+struct WidePlan {
+  bool ok;
+  int MF, BN;                                // tiles of 64 MF tokens x BN outputs
+  int n_tg, n_slabs, steps, k_pad, n_lparts, chunk;
+  size_t lpart_floats, pack_elems;
+  double us;                                 // estimate of the whole call's time
+};
+WidePlan wide_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room);
+// Is it sooner done than `mid`, or, without one, than dequantise + GEMM?  fix: as of mid_pays.
+bool wide_pays(const WidePlan& p, const MidPlan* mid, bool bwd, int64_t M, int64_t h, int64_t o, int r, bool fix);
+//   arguments as of launch_mid
+hipError_t launch_wide(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const WidePlan& p, const uint16_t* L1, const uint16_t* L2,
+                       int r, float scale, const uint8_t* mask, float* lpart, uint16_t* xpack, uint16_t* out, uint16_t* hl,
+                       hipStream_t st);
 
 // fewlist.hip: the same two products for a LIST of independent layers (each with its own token rows) in one
 // persistent launch.  The work of all layers is one line of units (forward: 16 weight rows x 256 columns; backward:

@@ -1,0 +1,112 @@
+"""Forward and input gradient by the kernels whose waves share one decode of the weight: every tile shape in both directions, with tokens,
+outputs and contractions that do not fill a tile, a slab or a step, against fp64 products with the dequantised weight."""
+import ctypes
+
+import pytest
+import torch
+
+from gpu_util import host_bits
+from test_gpu_fused_bwd import _gemm_launches
+from test_gpu_linear import _check
+
+pytestmark = pytest.mark.gpu
+
+
+class _Plan(ctypes.Structure):
+    _fields_ = ([("ok", ctypes.c_bool)] + [(n, ctypes.c_int) for n in ("MF", "BN", "n_tg", "n_slabs", "steps", "k_pad", "n_lparts", "chunk")] +
+                [(n, ctypes.c_size_t) for n in ("lpart_floats", "pack_elems")] + [("us", ctypes.c_double)])
+
+
+def _plan(bwd, M, h, o, r):
+    """The plan of a call with room for it (the library's internal struct)."""
+    from paper_2305_14314_amd import binding
+    f = ctypes.CDLL(binding.LIB_PATH)._ZN5qlora9wide_planEblllim
+    f.restype, f.argtypes = _Plan, [ctypes.c_bool, ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_size_t]
+    return f(bwd, M, h, o, r, h * o * 2)
+
+
+# A step is 128 elements of the contraction with slabs of 128 outputs, else 256: contractions that end in a quarter, half or three
+# quarters of one; a single step, odd and even numbers of them; the last slab of 128 half empty; ranks none, below 32, above 64 (several
+# passes), the largest; a few tokens in the last tile, and a full one
+@pytest.mark.parametrize("tile,bwd,M,h,o,r,dtype,dq,drop", [
+    ((1, 64), False, 390, 5248, 1728, 64, "NF4", 256, 0.0), ((1, 64), True, 244, 2112, 1664, 48, "NF4", 256, 0.0),
+    ((2, 64), False, 481, 2880, 2496, 80, "NF4", 256, 0.0), ((2, 64), True, 159, 7488, 2176, 32, "NF4", 0, 0.3),
+    ((3, 64), False, 377, 1920, 6976, 16, "FP4_E2M1", 256, 0.0), ((3, 64), True, 472, 4928, 7616, 96, "NF4", 256, 0.2),
+    ((4, 64), False, 411, 5696, 6464, 64, "NF4", 256, 0.1), ((4, 64), True, 419, 7360, 1728, 48, "INT4", 256, 0.0),
+    ((1, 128), False, 198, 1408, 6208, 160, "NF4", 256, 0.0), ((1, 128), True, 138, 9536, 384, 48, "NF4", 256, 0.5),
+    ((2, 128), False, 457, 1664, 6592, 80, "NF4", 0, 0.0), ((2, 128), True, 199, 13248, 1728, 128, "NF4", 256, 0.0),
+    ((3, 128), False, 278, 2176, 11328, 0, "NF4", 256, 0.0), ((3, 128), True, 361, 11584, 1984, 0, "NF4", 256, 0.0),
+    ((1, 128), False, 63, 128, 1472, 0, "NF4", 256, 0.0), ((1, 128), True, 34, 1728, 128, 32, "NF4", 256, 0.0),
+    ((3, 128), False, 333, 5120, 13824, 128, "NF4", 256, 0.2), ((4, 64), False, 512, 8192, 8192, 256, "NF4", 256, 0.0),
+    ((3, 128), False, 768, 8192, 8192, 64, "NF4", 256, 0.0),
+    ((2, 64), True, 512, 4096, 4096, 64, "NF4", 256, 0.1)])
+def test_widetok(synth, tile, bwd, M, h, o, r, dtype, dq, drop):
+    import paper_2305_14314_amd as ql
+    s = 0.5
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7000 + M)
+    bf = lambda *shape, sd=1.0: torch.empty(shape, device="cuda").normal_(0, sd, generator=g).bfloat16()
+    Wq = ql.qlora_quantize_4bit(synth.normal_f32_device((h, o), synth.SIGMA_W, 7100 + M), getattr(ql, dtype), dq_blocksize=dq)
+    What = ql.qlora_nf4_dequant(Wq).double()
+    X, dY = bf(M, h), bf(M, o)
+    L1, L2 = (bf(h, r, sd=0.05), bf(r, o, sd=0.05)) if r else (None, None)
+    keep = torch.rand((M, h), device="cuda", generator=g) >= drop
+    mask, D = ql.pack_keep_mask(keep), keep.double() / (1.0 - drop)
+    plan, head = _plan(bwd, M, h, o, r), ql.binding.WORKSPACE_HEADER_BYTES
+    assert plan.ok and (plan.MF, plan.BN) == tile
+    need = (max(ql.qlora_linear_dropout_sizes(M, h, o, r)) if drop else
+            (ql.qlora_linear_bwd_sizes if bwd else ql.qlora_linear_fwd_sizes)(M, h, o, r))
+    ws = ql.workspace_alloc(need + 4096)
+    ws[head:].fill_(0x7F)                                      # stale contents: NaN-ish everywhere
+    T = torch.full((M, 2 * r), float("nan"), dtype=torch.bfloat16, device="cuda") if r else None
+    print(f"case wide {tile} bwd={bwd} M={M} h={h} o={o} r={r} {dtype} dq={dq} drop={drop}", flush=True)
+
+    def call():
+        if bwd and drop:
+            return ql.qlora_linear_bwd_dropout(dY, X, Wq, L1, L2, s, mask, drop, need_dL=False, workspace=ws[:need])[0]
+        if bwd:
+            return ql.qlora_linear_bwd(dY, X, Wq, L1, L2, s, need_dL=False, workspace=ws[:need])[0]
+        if drop:
+            return ql.qlora_linear_fwd_dropout(X, Wq, L1, L2, s, mask, drop, T_save=T, workspace=ws[:need])
+        return ql.qlora_linear_fwd(X, Wq, L1, L2, s, T_save=T, workspace=ws[:need])
+
+    out, n = _gemm_launches(ql, call)
+    torch.cuda.synchronize()
+    assert n == 0 and int((ws[need:] != 0x7F).sum()) == 0
+    # which path ran shows in how much of the workspace was written: the partials of T, and behind them the packed operand
+    used = int((ws[head:need] != 0x7F).nonzero().max()) + 1
+    assert abs(used - ((plan.lpart_floats * 4 + 255) // 256 * 256 + plan.pack_elems * 2)) < 16
+    x, y = X.double(), dY.double()
+    if bwd:
+        ref = y @ What.T
+        if r:
+            ref = ref + s * (D if drop else 1.0) * ((y @ L2.double().T) @ L1.double().T)
+    else:
+        ref = x @ What
+        if r:
+            t = (x * (keep if drop else 1.0)) @ L1.double()
+            ref = ref + s / (1.0 - drop) * (t @ L2.double())
+            got = T[:, :r].double() + T[:, r:].double()        # 16 significant bits
+            assert (got - t).abs().max() <= 2.0 ** -14 * t.abs().max() + 1e-6
+    _check(host_bits(out), ref.cpu().numpy(), "dX" if bwd else "Y")
+    # half a bf16 step (2^-8 of the value at most), the fp32 sums and the 16 bits that T keeps: one rounding, under dropout too
+    err, rms = (out.double() - ref).abs(), ref.square().mean().sqrt()
+    assert (err <= 2.0 ** -8 * ref.abs() + 2e-4 * rms).all()
+    assert torch.equal(call().view(torch.int16), out.view(torch.int16))      # the same bits again, on a used workspace
+
+
+def test_widetok_infinite_t(synth):
+    """A U that overflows makes its token's outputs infinite, with the outer matrix' sign, as an fp32 product would."""
+    import paper_2305_14314_amd as ql
+    M, h, o, r = 250, 2112, 1664, 64
+    assert _plan(True, M, h, o, r).ok
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    bf = lambda *shape, sd=1.0: torch.empty(shape, device="cuda").normal_(0, sd, generator=g).bfloat16()
+    Wq = ql.qlora_nf4_quantize(synth.normal_f32_device((h, o), synth.SIGMA_W, 8))
+    dY, L1 = bf(M, o), torch.zeros((h, r), dtype=torch.bfloat16, device="cuda")
+    L2 = torch.full((r, o), 3e38, dtype=torch.bfloat16, device="cuda")
+    dY[5] = 1.0
+    L1[:] = torch.where(torch.arange(h, device="cuda") % 2 == 0, 1.0, -1.0).bfloat16()[:, None]
+    dX = ql.qlora_linear_bwd(dY, None, Wq, L1, L2, 1.0, need_dL=False)[0]
+    assert torch.equal(dX[5].float(), L1[:, 0].float() * float("inf"))
