@@ -218,10 +218,14 @@ struct SmallBatch {
 
   // `tiles`: output tiles of the products that share the launch (0: this one alone), counted from the layers' shapes: the
   // order of a sum, and with it every bit of what is summed here, does not depend on which outputs a call wants or on the
-  // room it has.
-  hipError_t add(qlora::SmallJob j, int tiles, int floor = 0) {
-    j.direct = (j.kind == qlora::kSmallDL1 || j.kind == qlora::kSmallDL2) && (j.K + 63) / 64 <= 4;
-    j.fin.splits = j.direct ? 1 : qlora::small_job_splits(j.I, j.J, j.K, std::max(tiles - qlora::small_tiles(j.I, j.J), 0), floor);
+  // room it has.  `groups` (small_groups): more than 0 finishes the job in its product's launch.
+  hipError_t add(qlora::SmallJob j, int tiles, int floor = 0, int groups = 0) {
+    const int own = qlora::small_tiles(j.I, j.J);
+    if (jobs.n > 0 && jobs.groups != std::max(groups, 1))    // groups of waves are a launch's, not a job's
+      if (hipError_t e = finish()) return e;
+    jobs.groups = std::max(groups, 1);
+    j.direct = groups > 0;
+    j.fin.splits = j.direct ? 1 : qlora::small_job_splits(j.I, j.J, j.K, std::max(tiles - own, 0), floor);
     for (int turn = 0; turn < 2; ++turn) {
       const size_t need = j.direct ? 0 : (size_t)j.fin.splits * j.I * j.J * sizeof(float);
       if (jobs.n < qlora::kSmallMax && (j.direct || fin.n < qlora::kFinMax) && used + need <= room) {
@@ -252,22 +256,24 @@ struct SmallBatch {
     return e;
   }
 };
-// How dL1 and dL2 of a layer are split (the last two arguments of SmallBatch::add).  They share a launch where `room`, which
+// How dL1 and dL2 of a layer are split (the last three arguments of SmallBatch::add).  Without partials they share a launch
+// (small_groups), and with them where `room`, which
 // depends on the shape alone, holds their partials -- with a floor under the smaller one's workgroups if it holds those too.
 // Where it does not, each gets a launch of its own, and its own splits if a shared launch's would leave chains of eight
 // K-steps and more: 4096 x 1024 at rank 256 and 4096 tokens (32 K-steps) 74 us with a shared launch's splits, 65 with its
 // own; 320 x 1088 at rank 64 (3 K-steps) 50 and 53.  The gradients of stacked layers are not held to the floor: over
 // 240 calls none is slower than with separate launches, and its partials would send some off in a second launch.
-struct DlSplit { int tiles, floor; };
+struct DlSplit { int tiles, floor, groups; };
 DlSplit dl_split(int64_t M, int64_t h, int64_t o, int r, size_t room) {
   const int t1 = qlora::small_tiles((int)h, r), t2 = qlora::small_tiles(r, (int)o);
+  if (const int groups = qlora::small_groups((int)M, t1 + t2, std::min(t1, t2))) return {t1 + t2, 0, groups};
   auto fits = [&](int floor) {
     return align_up((size_t)qlora::small_job_splits((int)h, r, (int)M, t2, floor) * h * r * sizeof(float), 256) +
                align_up((size_t)qlora::small_job_splits(r, (int)o, (int)M, t1, floor) * r * o * sizeof(float), 256) <= room;
   };
-  if (fits(qlora::kSmallFloor)) return {t1 + t2, qlora::kSmallFloor};
+  if (fits(qlora::kSmallFloor)) return {t1 + t2, qlora::kSmallFloor, 0};
   const int64_t chain = (M + 63) / 64 / qlora::small_job_splits((int)h, r, (int)M, t2);
-  return {fits(0) || chain < 8 ? t1 + t2 : 0, 0};
+  return {fits(0) || chain < 8 ? t1 + t2 : 0, 0, 0};
 }
 qlora::SmallJob job_t(const uint16_t* X, int64_t h, const uint16_t* L1, int64_t M, int r, const uint8_t* mask) {
   qlora::SmallJob j{};
@@ -954,10 +960,10 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
       T = p.Thl;
     }
     // dL1 = s X^T U: contraction over the tokens, both operands stored token-major; U enters as hi + lo
-    if (want1) QL_TRY(batch.add(job_dl1(X, h, p.Uhl, M, r, s, keep_mask, dL1, aL1), split.tiles, split.floor));
-    if (need_t) QL_TRY(batch.finish());
+    if (want1) QL_TRY(batch.add(job_dl1(X, h, p.Uhl, M, r, s, keep_mask, dL1, aL1), split.tiles, split.floor, split.groups));
+    if (need_t && batch.jobs.groups == 1) QL_TRY(batch.finish());
     // dL2 = s T^T dY with T as hi + lo rows
-    if (want2) QL_TRY(batch.add(job_dl2(T, dY, o, o, M, r, s, dL2, aL2), split.tiles, split.floor));
+    if (want2) QL_TRY(batch.add(job_dl2(T, dY, o, o, M, r, s, dL2, aL2), split.tiles, split.floor, split.groups));
     QL_TRY(batch.finish());
   }
   return QLORA_OK;
@@ -1096,6 +1102,7 @@ qlora_status qlora_linear_bwd_stacked(const uint16_t* dY, const uint16_t* X, int
         tiles_tu += qlora::small_tiles((int)M, r[l]);
         tiles_dl += qlora::small_tiles((int)h, r[l]) + qlora::small_tiles(r[l], (int)o[l]);
       }
+    const int groups = qlora::small_groups((int)M, tiles_dl, tiles_dl);
     for (int l = l0; l < l1; ++l) {
       if (r[l] == 0) continue;
       // U_l = dY_l L2_l^T: bf16(s_l U_l) into the layer's rank columns of Us, the [hi | lo] pair for dL1
@@ -1116,10 +1123,10 @@ qlora_status qlora_linear_bwd_stacked(const uint16_t* dY, const uint16_t* X, int
       }
     QL_TRY(batch.finish());
     for (int l = l0; l < l1; ++l) {
-      if (want1(l)) QL_TRY(batch.add(job_dl1(X, h, uhl(l), M, r[l], s[l], nullptr, dL1[l], nullptr), tiles_dl));     // s_l X^T U_l
+      if (want1(l)) QL_TRY(batch.add(job_dl1(X, h, uhl(l), M, r[l], s[l], nullptr, dL1[l], nullptr), tiles_dl, 0, groups));     // s_l X^T U_l
       if (want2(l))                                                                                        // s_l T_l^T dY_l
         QL_TRY(batch.add(job_dl2(need_t(l) ? thl(l) : T_saved[l], dY + col[l], N, o[l], M, r[l], s[l], dL2[l], nullptr),
-                         tiles_dl));
+                         tiles_dl, 0, groups));
     }
     QL_TRY(batch.finish());
   }

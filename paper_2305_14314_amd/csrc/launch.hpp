@@ -120,16 +120,22 @@ struct SmallJob {
   int64_t hl_off;
   const uint8_t* amask;                      // LoRA dropout (T, dL1; lda % 8 == 0): elements of A whose keep-bit -- bit e % 8 of byte e / 8, e the offset from A -- is clear enter as zero
   int kind, I, J, K, k_per_split;            // k_per_split: filled by the launcher
-  int direct;                                // dL1, dL2 in one split: the finalize step (out0 with w0 = J, acc) in the product's epilogue
+  int direct;                                // dL1, dL2: the finalize step (out0 with w0 = J, acc) in the product's epilogue
   FinJob fin;                                // part, splits and the outputs; I, J: filled by the launcher
 };
 constexpr int kSmallMax = 8;
-struct SmallJobs { int n; int first[kSmallMax]; SmallJob j[kSmallMax]; };
+struct SmallJobs {
+  int n, groups = 1;                         // 2 or 4, where every job is direct: that many groups of four waves share a tile's K range
+  int first[kSmallMax]; SmallJob j[kSmallMax];
+};
 static_assert(sizeof(SmallJobs) <= 2048 && sizeof(FinList) <= 1024, "kernel arguments");
 int small_tiles(int I, int J);
 //   splits of a job that shares its launch with `other_tiles` output tiles of other jobs; never more than without any
 constexpr int kSmallFloor = 256;             // workgroups a job of a shared launch should have of its own
 int small_job_splits(int I, int J, int K, int other_tiles, int floor = 0);
+//   dL1 and dL2 over K tokens, `tiles` output tiles in all, `least` the fewest that one of them has: the groups of waves to
+//   a tile if they are finished in the products' launch, 0 if not
+int small_groups(int K, int tiles, int least);
 hipError_t launch_small_jobs(SmallJobs& jobs, hipStream_t st);
 hipError_t launch_fin(const FinList& f, hipStream_t st);
 //   LoRA dropout: dX[m][k] -= sum_t Us[m][t] L1[k][t] (bf16 operands, fp32 sum, one more rounding to bf16) wherever the

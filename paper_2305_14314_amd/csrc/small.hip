@@ -4,7 +4,10 @@
 //
 //   part[split][I x J] (fp32) = sum over this split's K range of A(i,k) * B(k,j)
 //   finalize (fin.hpp): out = bf16(scale * sum over splits) and/or the sum as a [hi | lo] pair of bf16 matrices; dL1 and
-//   dL2 of at most four K-steps do it in the product's own epilogue
+//   dL2 do it in the product's own epilogue where small_groups says so: their splits are then groups of four waves in one
+//   workgroup, whose sums meet in LDS.  What that saves is the finalize launch (4 - 6 us) and the partials' way through
+//   memory; the loop is the same.  dL1 and dL2 of 4096 x 4096, rank 64, 512 tokens under dropout, kernels' times: 9.0 + 4.6 ->
+//   10.1 us; of stacked q, k, v of 5120 x 5120 at 2000 tokens 40.4 + 6.3 -> 43.5
 //
 // Up to eight such products (of one or more layers) share a launch, and so do their finalize steps, which may also ride in
 // a dequantise launch.  A stacked q / k / v forward + backward at 2000 tokens (5120 x 5120, rank 64) spent 204 of 770 us in
@@ -130,18 +133,23 @@ __device__ __forceinline__ SmallOperands pin_operands(const SmallJob& j) {
 }
 
 constexpr int kSmallTile = ST * kTPitch * 2;  // bytes of one operand tile in LDS
-template <bool TA, bool TB, int HL, bool MASK>
-__device__ __forceinline__ void small_gemm_body(const SmallJob& job, int local, char* smem) {
+// G > 1: a tile's K ranges are summed by G groups of four waves in one workgroup, each with operand tiles of its own
+// (27 KB: one workgroup of four groups to a CU, two of two).
+template <bool TA, bool TB, int HL, bool MASK, int G>
+__device__ __forceinline__ void small_gemm_body(const SmallJob& job, int local, char* smem0) {
   const SmallOperands p = pin_operands(job);
   static_assert(HL == 0 || (HL == 1 && TA) || (HL == 2 && TB), "a [hi | lo] operand is stored token-major");
   static_assert(!MASK || HL != 1, "the masked operand is X itself");
+  const int group = G > 1 ? (int)threadIdx.x / kSmallThreads : 0;
+  constexpr int kGroupLds = (HL != 0 ? 3 : 2) * kSmallTile;
+  char* smem = smem0 + group * kGroupLds;
   lds_char* sA = (lds_char*)smem;
   lds_char* sB = (lds_char*)(smem + kSmallTile);
   lds_char* sC = (lds_char*)(smem + 2 * kSmallTile);
   const int gi = (p.I + ST - 1) / ST, gj = (p.J + ST - 1) / ST;
-  const int bi = local % gi, bj = local / gi % gj, split = local / (gi * gj);
+  const int bi = local % gi, bj = local / gi % gj, split = G > 1 ? group : local / (gi * gj);
 
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = G > 1 ? (int)threadIdx.x % kSmallThreads : threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int i0 = bi * ST, j0 = bj * ST;
   const int k_begin = split * p.k_per_split;
   const int k_end = (k_begin + p.k_per_split < p.K) ? k_begin + p.k_per_split : p.K;
@@ -195,12 +203,33 @@ __device__ __forceinline__ void small_gemm_body(const SmallJob& job, int local, 
   Regs R0, R1;
   fetch(R0, k_begin);
   fetch(R1, k_begin + ST);
-  for (int k0 = k_begin; k0 < k_end; k0 += 2 * ST) {
+  const int k_last = G > 1 ? k_begin + p.k_per_split : k_end;   // every group takes part in every barrier: past k_end it adds zeros
+  for (int k0 = k_begin; k0 < k_last; k0 += 2 * ST) {
     step(R0, k0 + 2 * ST);
-    if (k0 + ST < k_end) step(R1, k0 + 3 * ST);
+    if (k0 + ST < k_last) step(R1, k0 + 3 * ST);
   }
 
   const int j = j0 + wj * 32 + (lane & 31);
+  if constexpr (G > 1) {                                     // the finalize step's sum, in its order; a group takes 1/G of the tile
+    static_assert(HL != 0 && kGroupLds >= 16 * kSmallThreads * 4, "a group's tiles make room for its sums");
+    __syncthreads();
+    float* mine = (float*)smem + tid;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) mine[v * kSmallThreads] = acc[v];
+    __syncthreads();
+    if (j >= p.J) return;
+#pragma unroll
+    for (int q = 0; q < 16 / G; ++q) {
+      const int v = group * (16 / G) + q, i = i0 + wi * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
+      if (i >= p.I) continue;
+      float sum = 0.0f;
+#pragma unroll
+      for (int g = 0; g < G; ++g) sum += ((const float*)(smem0 + g * kGroupLds))[v * kSmallThreads + tid];
+      if (job.fin.out0) job.fin.out0[(int64_t)i * job.fin.ld0 + j] = bf16_bits(sum * job.fin.scale0);
+      if (job.fin.acc) job.fin.acc[(int64_t)i * p.J + j] += sum * job.fin.scale0;
+    }
+    return;
+  }
   if (j >= p.J) return;
   if (HL != 0 && job.direct) {                               // one split: what the finalize step would do, right here
 #pragma unroll
@@ -220,12 +249,12 @@ __device__ __forceinline__ void small_gemm_body(const SmallJob& job, int local, 
   }
 }
 
-template <int KIND, bool MASK>
+template <int KIND, bool MASK, int G = 1>
 __device__ __forceinline__ void small_gemm_kind(const SmallJob& p, int local, char* smem) {
-  if constexpr (KIND == kSmallT) small_gemm_body<false, true, 0, MASK>(p, local, smem);
-  if constexpr (KIND == kSmallU) small_gemm_body<false, false, 0, false>(p, local, smem);
-  if constexpr (KIND == kSmallDL1) small_gemm_body<true, true, 2, MASK>(p, local, smem);
-  if constexpr (KIND == kSmallDL2) small_gemm_body<true, true, 1, false>(p, local, smem);
+  if constexpr (KIND == kSmallT) small_gemm_body<false, true, 0, MASK, 1>(p, local, smem);
+  if constexpr (KIND == kSmallU) small_gemm_body<false, false, 0, false, 1>(p, local, smem);
+  if constexpr (KIND == kSmallDL1) small_gemm_body<true, true, 2, MASK, G>(p, local, smem);
+  if constexpr (KIND == kSmallDL2) small_gemm_body<true, true, 1, false, G>(p, local, smem);
 }
 constexpr int small_lds(int kinds) { return ((kinds & 12) ? 3 : 2) * kSmallTile; }
 
@@ -239,17 +268,18 @@ __global__ __launch_bounds__(kSmallThreads) void small_job_kernel(const SmallJob
 
 // Several products in one launch: workgroup b belongs to the last job whose first workgroup is <= b.  KINDS: the kinds that
 // occur (1 << kind), so that a launch carries no code it cannot reach.
-template <int KINDS, bool MASK>
-__global__ __launch_bounds__(kSmallThreads) void small_jobs_kernel(const SmallJobs jobs) {
-  __shared__ __attribute__((aligned(16))) char smem[small_lds(KINDS)];
+template <int KINDS, bool MASK, int G = 1>
+__global__ __launch_bounds__(kSmallThreads * G) void small_jobs_kernel(const SmallJobs jobs) {
+  static_assert(G == 1 || !(KINDS & 3), "groups finish dL1 and dL2 only");
+  __shared__ __attribute__((aligned(16))) char smem[G * small_lds(KINDS)];
   int q = 0;
   while (q + 1 < jobs.n && (int)blockIdx.x >= jobs.first[q + 1]) ++q;
   const SmallJob& p = jobs.j[q];
   const int local = blockIdx.x - jobs.first[q];
   if ((KINDS & 1) && p.kind == kSmallT) small_gemm_kind<kSmallT, MASK>(p, local, smem);
   if ((KINDS & 2) && p.kind == kSmallU) small_gemm_kind<kSmallU, MASK>(p, local, smem);
-  if ((KINDS & 4) && p.kind == kSmallDL1) small_gemm_kind<kSmallDL1, MASK>(p, local, smem);
-  if ((KINDS & 8) && p.kind == kSmallDL2) small_gemm_kind<kSmallDL2, MASK>(p, local, smem);
+  if ((KINDS & 4) && p.kind == kSmallDL1) small_gemm_kind<kSmallDL1, MASK, G>(p, local, smem);
+  if ((KINDS & 8) && p.kind == kSmallDL2) small_gemm_kind<kSmallDL2, MASK, G>(p, local, smem);
 }
 
 __global__ __launch_bounds__(kFinThreads) void fin_job_kernel(const FinJob job) { fin_job(job, blockIdx.x, gridDim.x); }
@@ -266,16 +296,43 @@ int small_job_splits(int I, int J, int K, int other_tiles, int floor) {
 }
 int small_tiles(int I, int J) { return ((I + ST - 1) / ST) * ((J + ST - 1) / ST); }
 
+// Whole backward calls, us, with partials and a finalize launch -> finished in the products' launch.
+// - Up to four K-steps (256 tokens) one group reads them in a chain that is no longer than a finalize launch; while there is
+//   a CU to every tile, as many groups as K-steps shorten it: 4096 x 4096, rank 64, 256 tokens, one -> four groups 64.4 -> 63.1.
+//   With more tiles the wide workgroups queue up: 5120 x 13824, rank 64 (296 tiles) 130.8 -> 132.9.
+// - Five to eight K-steps: four groups, 4096 x 4096, rank 64, 512 tokens 85.1 -> 80.3; 296 tiles, 320 tokens 166 -> 163;
+//   512 tiles even; 688 tiles and more lose (4096 x 11008, rank 256, 330 tokens 200 -> 205), see below.
+// - Longer chains: four groups to a tile leave the CUs without a tile idle, so up to one tile per CU it takes enough of them
+//   for the length: 1024 tokens (16 K-steps), 64 tiles +0.5, 80 tiles 74.9 -> 71.7, 256 tiles 320 -> 316; 1400 tokens, 112 and
+//   144 tiles +0.7, 2048 tokens, 160 tiles 226.8 -> 225.2; 3000 tokens, 256 tiles 239 -> 236.
+// - More tiles than CUs have two splits, i.e. two groups, which do not spread as well as split workgroups if the tiles are
+//   few: 600 tokens, 288 tiles 327 -> 322, but 4096 tokens, 288 tiles +5 and 320 tiles 188 -> 194; 472 tiles at 1024 tokens
+//   867 -> 860, at 4096 2225 -> 2220; stacked q, k, v of 2000 tokens (480 tiles) 616 -> 611.  Where `floor` gives a product of few tiles
+//   more splits than that, it keeps them.
+// - From 512 tiles on a tile has one split, which needs no sum: 4096 x 11008, rank 256 (944 tiles), 512 tokens 236 -> 225;
+//   11008 x 4096 at 4096 tokens 757 -> 751.
+int small_groups(int K, int tiles, int least) {
+  const int ksteps = (K + ST - 1) / ST;
+  if (ksteps <= 4) return tiles > 256 || ksteps == 1 ? 1 : ksteps == 2 ? 2 : 4;
+  if (ksteps <= 8 && tiles <= 512) return 4;
+  if (tiles <= 256) return tiles >= 5 * ksteps && (ksteps <= 16 || tiles >= 150) ? 4 : 0;
+  if (tiles < 512) return least >= 128 && (ksteps <= 16 || tiles >= 400) ? 2 : 0;
+  return least >= 256 ? 1 : 0;
+}
+
 hipError_t launch_small_jobs(SmallJobs& jobs, hipStream_t st) {
   if (jobs.n == 0) return hipSuccess;
+  if (jobs.groups != 1 && jobs.groups != 2 && jobs.groups != 4) return hipErrorInvalidValue;
   int kinds = 0, wgs = 0;
   bool mask = false;
   for (int q = 0; q < jobs.n; ++q) {
     SmallJob& p = jobs.j[q];
     const int ksteps = (p.K + ST - 1) / ST;
-    p.k_per_split = (ksteps + p.fin.splits - 1) / p.fin.splits * ST;
+    const int splits = p.direct ? jobs.groups : p.fin.splits;
+    p.k_per_split = (ksteps + splits - 1) / splits * ST;
     p.fin.I = p.I; p.fin.J = p.J;
-    if (p.direct && ((p.kind != kSmallDL1 && p.kind != kSmallDL2) || p.fin.splits != 1 || p.fin.hl || (p.fin.out0 && p.fin.w0 != p.J)))
+    if (p.direct ? (p.kind != kSmallDL1 && p.kind != kSmallDL2) || p.fin.splits != 1 || p.fin.hl || (p.fin.out0 && p.fin.w0 != p.J)
+                 : jobs.groups != 1)
       return hipErrorInvalidValue;
     if (p.amask && (p.lda % 8 != 0 || (p.kind != kSmallT && p.kind != kSmallDL1))) return hipErrorInvalidValue;
     kinds |= 1 << p.kind;
@@ -286,7 +343,18 @@ hipError_t launch_small_jobs(SmallJobs& jobs, hipStream_t st) {
   if (mask)                                                  // one mask for a launch: every T and dL1 job brings it
     for (int q = 0; q < jobs.n; ++q)
       if ((jobs.j[q].kind == kSmallT || jobs.j[q].kind == kSmallDL1) && !jobs.j[q].amask) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)wgs), block(kSmallThreads);
+  const dim3 grid((unsigned)wgs), block(kSmallThreads * jobs.groups);
+#define QL_SMALL_G(KINDS, MASK, G)                                                                                   \
+  case (2 * KINDS + MASK) * 8 + G: hipLaunchKernelGGL((small_jobs_kernel<KINDS, MASK, G>), grid, block, 0, st, jobs); break;
+  if (jobs.groups > 1) {
+    switch ((2 * kinds + mask) * 8 + jobs.groups) {
+      QL_SMALL_G(4, 0, 2) QL_SMALL_G(4, 1, 2) QL_SMALL_G(8, 0, 2) QL_SMALL_G(12, 0, 2) QL_SMALL_G(12, 1, 2)
+      QL_SMALL_G(4, 0, 4) QL_SMALL_G(4, 1, 4) QL_SMALL_G(8, 0, 4) QL_SMALL_G(12, 0, 4) QL_SMALL_G(12, 1, 4)
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
+#undef QL_SMALL_G
 #define QL_SMALL_ONE(KIND, MASK)                                                                                     \
   case 2 * (1 << KIND) + MASK: hipLaunchKernelGGL((small_job_kernel<KIND, MASK>), grid, block, 0, st, jobs.j[0]); break;
 #define QL_SMALL(KINDS, MASK)                                                                                        \
