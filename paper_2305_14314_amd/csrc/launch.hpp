@@ -183,12 +183,9 @@ hipError_t launch_workspace_init(void* workspace, hipStream_t st);
 // midtok.hip: tens to hundreds of tokens, 4-bit weights (with or without Double Quantization): the weight is decoded inside
 // the product, whose work is one line of equal ranges over the compute units, and a last kernel sums a tile's partials and
 // adds the adapter's term.  The plan uses at most `room` bytes of workspace; ok = false: not for this path.
-// Up to kMidTokens mid_pays() weighs a plan against dequantise + GEMM; above, that path is taken unweighed.  There it is the faster
-// one where outputs are many or square, the slower one where the contraction is long.  us at rank 64, three weights in turn,
-// dequantised / decoded inside; K x N at tokens: 4096 x 4096 at 576 forward 45 / 50, dX 44 / 57; 5120 x 13824 at 576 127 / 143, at 1024
-// 148 / 269; 8192 x 8192 at 768 forward 131 / 128, dX 125 / 133, at 1024 149 / 170; but 8192 x 1024 at 513 63 / 39, 11008 x 4096 at 640
-// 94 / 87, 22016 x 8192 at 768 forward 424 / 292, dX 450 / 304, at 1024 437 / 377.  Weighing these too is open: the estimate is fitted to
-// calls of up to 512 tokens.
+// Up to kMidTokens mid_pays() weighs a plan against dequantise + GEMM; above, there is none: at those sizes the form of widetok.hip, which
+// has no partials of the product, takes the calls that gain from decoding inside (8192 x 8192 at 768 tokens, rank 64, forward: 169 us
+// dequantised, 113 there).
 constexpr int kMidTokens = 512;
 constexpr int kMidPackFrom = 48;             // forward: up to here no plan packs the token operand
 // `units` units in tiles of `ups`, cut into `wgs` ranges whose sizes differ by at most one.

@@ -4,8 +4,8 @@
 //
 // Why its own path: with 256 x 256 tiles a product of a few hundred tokens has 4 .. 100 tiles for 256 compute units, and
 // the pass that dequantises the weight moves five times the bytes of the packed weight (2.5 against 0.5 per weight).
-// Whole forward call, dequantise + GEMM against this: 4096 x 11008 at 40 tokens 108 -> 20 us, 5120 x 13824 at 333 tokens
-// 158 -> 85 us; forward + backward 1024 x 1024 at 256 tokens 96 -> 42 us, 4096 x 4096 at 512 tokens 220 -> 99 us.
+// Whole forward call, dequantise + GEMM against this: 4096 x 11008 at 40 tokens 108 -> 20 us.  With
+// many tokens to a weight the form of widetok.hip, whose waves share the decode, is the faster one of the two (figures there).
 //
 // Two or three launches on the caller's stream:
 //   pre       (where the plan finds it worth a launch) the token operand in MFMA-fragment order, so that the main kernel's operand

@@ -619,8 +619,8 @@ WidePlan wide_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room
 
 // The same of the path that a call takes otherwise: the plan of midtok.hip, or (mid NULL) dequantise + GEMM, whose bf16 weight above some 50 M
 // elements no longer stays in the last-level cache between the two, and which under dropout (fix) corrects dX afterwards.  A call comes here where
-// it is estimated 15 % faster than the former or 8 % faster than the latter: of the calls above 347 of 1091, which take 0.79 of the time
-// (mean); two of them take more than 3 % longer (at most 10 %).  At 10 and 6 % 408 (0.81), nine of them longer, one by 27 %.
+// it is estimated 15 % faster than the former or 8 % faster than the latter: of the calls above 315 of 1091, which take 0.78 of the time
+// (mean); one of them takes more than 3 % longer (10 %).  At 10 and 6 %, small weights included, 408 (0.81), nine of them longer, one by 27 %.
 bool wide_pays(const WidePlan& p, const MidPlan* mid, bool bwd, int64_t M, int64_t h, int64_t o, int r, bool fix) {
   const double K = (double)(bwd ? o : h), N = (double)(bwd ? h : o), MN = 1e-6 * (double)M * N, KN = 1e-6 * K * N, rMK = 1e-6 * r * (double)M * K;
   if (mid) {
