@@ -149,49 +149,63 @@ struct Carver {
 // than that for enough splits: the size queries then report more, and a caller that brings only the dequantise + GEMM
 // plan's bytes is still served, with fewer splits or by that plan (and other last bits).
 constexpr size_t kMidRoom = (size_t)32 << 20;
-struct MidWs { qlora::MidPlan plan; float* part; float* lpart; uint16_t* xpack; };
 size_t mid_bytes(const qlora::MidPlan& p) {
   return align_up(p.part_floats * sizeof(float), 256) + align_up(p.lpart_floats * sizeof(float), 256) + align_up(p.pack_elems * 2, 256);
 }
-// bytes of the region that holds either the dequantised weight (`base` bytes) or the buffers of this path; asked for whether
-// or not the path is taken, because the adapter gradients' partials lie there too (dL1 and dL2 of 1024 x 1024 at rank 128 and
-// 512 tokens share a launch in it: 20.5 us, 24.6 without)
+size_t wide_bytes(const qlora::WidePlan& p) {
+  return align_up(p.lpart_floats * sizeof(float), 256) + align_up(p.pack_elems * 2, 256);
+}
+// The plan of a shape by the path for tens to hundreds of tokens: what the region of the size queries is made for.
+qlora::MidPlan shape_mid(size_t base, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r, bool packed = false) {
+  return qlora::mid_plan(bwd, M, h, o, r, std::max(base, kMidRoom), packed);
+}
+// The plan of a call with `room` bytes: its shape's where that fits (it is the best of any that do), else the best that fits; ok where it is
+// also the faster way, against dequantise + GEMM.  One search a call, as a rule: each is 0.5 us of host time, 3 us for a long contraction with
+// few outputs.
+qlora::MidPlan choose_mid(size_t room, size_t base, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r, bool fix) {
+  qlora::MidPlan p = shape_mid(base, bwd, M, h, o, r);
+  if (p.ok && mid_bytes(p) > room) p = qlora::mid_plan(bwd, M, h, o, r, room);
+  p.ok = p.ok && qlora::mid_pays(p, bwd, M, h, o, r, fix);
+  return p;
+}
+// The form of that path whose waves share a decode, in the same region, where a call of more than kFewTokens tokens is sooner done so than by
+// `mid` (whose plan is made either way) or by dequantise + GEMM.  The same rule for its room: the shape's plan or, short of room, the best that fits.
+qlora::WidePlan choose_wide(size_t room, const qlora::MidPlan& mid, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r, bool fix) {
+  if (M <= qlora::kFewTokens) return qlora::WidePlan{};
+  qlora::WidePlan p = qlora::wide_plan(bwd, M, h, o, r, SIZE_MAX);
+  if (p.ok && wide_bytes(p) > room) p = qlora::wide_plan(bwd, M, h, o, r, room);
+  p.ok = p.ok && qlora::wide_pays(p, mid.ok ? &mid : nullptr, bwd, M, h, o, r, fix);
+  return p;
+}
+// bytes of the region that holds either the dequantised weight (`base` bytes) or the buffers of these paths; the first one's asked for
+// whether or not it is taken, because the adapter gradients' partials lie there too (dL1 and dL2 of 1024 x 1024 at rank 128 and
+// 512 tokens share a launch in it: 20.5 us, 24.6 without).  Forward, the second's too where it is taken: with that the choice among the
+// paths follows from the shape alone for every call that brings the reported size, however much more it brings (fwd_route).
+// Backward the region itself follows from the shape, and a shape without the room there goes another way.
 size_t mid_region(size_t base, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r) {
   size_t bytes = base;
   for (bool packed : {false, true}) {        // both are reported: a plan takes what it is given
     if (packed && (bwd || M <= qlora::kMidPackFrom)) break;            // the same plan
-    const qlora::MidPlan p = qlora::mid_plan(bwd, M, h, o, r, std::max(base, kMidRoom), packed);
+    const qlora::MidPlan p = shape_mid(base, bwd, M, h, o, r, packed);
     if (p.ok) bytes = std::max(bytes, mid_bytes(p));
+  }
+  if (!bwd && M > qlora::kFewTokens) {
+    const qlora::WidePlan w = choose_wide(SIZE_MAX, choose_mid(SIZE_MAX, base, bwd, M, h, o, r, false), bwd, M, h, o, r, false);
+    if (w.ok) bytes = std::max(bytes, wide_bytes(w));
   }
   return bytes;
 }
-//   The plan of a call with `room` bytes: the one behind the size query where it fits (it is the best of any that do), else the
-//   best that fits.  One search a call, as a rule: each is 0.5 us of host time, 3 us for a long contraction with few outputs.
-MidWs plan_mid(void* buf, size_t room, size_t base, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r, bool fix = false) {
-  MidWs m{};
-  m.plan = qlora::mid_plan(bwd, M, h, o, r, std::max(base, kMidRoom));
-  if (m.plan.ok && mid_bytes(m.plan) > room) m.plan = qlora::mid_plan(bwd, M, h, o, r, room);
-  m.plan.ok = m.plan.ok && qlora::mid_pays(m.plan, bwd, M, h, o, r, fix);
-  if (!m.plan.ok) return m;
+struct MidWs { qlora::MidPlan plan; float* part; float* lpart; uint16_t* xpack; };
+MidWs mid_ws(void* buf, const qlora::MidPlan& plan) {
   char* p = (char*)buf;
-  m.part = (float*)p; p += align_up(m.plan.part_floats * sizeof(float), 256);
-  m.lpart = (float*)p; p += align_up(m.plan.lpart_floats * sizeof(float), 256);
-  m.xpack = (uint16_t*)p;
+  MidWs m{plan, (float*)p, nullptr, nullptr};
+  m.lpart = (float*)(p += align_up(plan.part_floats * sizeof(float), 256));
+  m.xpack = (uint16_t*)(p + align_up(plan.lpart_floats * sizeof(float), 256));
   return m;
 }
-
-// The form of that path whose waves share a decode, in the same region, where a call of more than kFewTokens tokens is sooner done so than by
-// `mid` (whose plan is made either way) or by dequantise + GEMM.  The sizes do not ask for it: a shape without the room goes the other way.
 struct WideWs { qlora::WidePlan plan; float* lpart; uint16_t* xpack; };
-WideWs plan_wide(void* buf, size_t room, const qlora::MidPlan& mid, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r,
-                 bool fix = false) {
-  WideWs w{};
-  if (M <= qlora::kFewTokens) return w;
-  w.plan = qlora::wide_plan(bwd, M, h, o, r, room);
-  w.plan.ok = w.plan.ok && qlora::wide_pays(w.plan, mid.ok ? &mid : nullptr, bwd, M, h, o, r, fix);
-  w.lpart = (float*)buf;
-  w.xpack = (uint16_t*)((char*)buf + align_up(w.plan.lpart_floats * sizeof(float), 256));
-  return w;
+WideWs wide_ws(void* buf, const qlora::WidePlan& plan) {
+  return WideWs{plan, (float*)buf, (uint16_t*)((char*)buf + align_up(plan.lpart_floats * sizeof(float), 256))};
 }
 
 // Floats of the split-K partials of the largest of a layer's skinny products, each in a launch of its own.
@@ -344,6 +358,21 @@ FwdPlan plan_fwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allo
   if (sizes) p.bytes = qlora::kWorkspaceHeaderBytes + mid_region(c.off - qlora::kWorkspaceHeaderBytes, false, M, h, o, r);
   return p;
 }
+
+}  // namespace
+namespace qlora {
+FwdRoute fwd_route(int64_t M, int64_t h, int64_t o, int r, bool few, size_t workspace_bytes) {
+  FwdRoute f{};
+  if (few && !mid_beats_few(M, h, o, r)) return f;
+  const FwdPlan p = plan_fwd(nullptr, M, h, o, r, false, few);
+  if (few && workspace_bytes < p.bytes) return f;            // with the room that the size query reports; less streams as ever
+  const size_t room = workspace_bytes - kWorkspaceHeaderBytes;
+  f.mid = choose_mid(room, p.min_bytes - kWorkspaceHeaderBytes, false, M, h, o, r, false);
+  if (!few) f.wide = choose_wide(room, f.mid, false, M, h, o, r, false);
+  return f;
+}
+}  // namespace qlora
+namespace {
 
 struct BwdPlan {
   uint16_t* Wd;      // h x o     dequantised weight (K-contiguous for the backward)
@@ -646,26 +675,16 @@ qlora_status linear_fwd_impl(const uint16_t* X, const qlora_nf4_view* Wq, const 
   hipStream_t st = (hipStream_t)hip_stream;
   const qlora::NF4Dev W = to_dev(Wq);
 
-  auto mid_ws = [&](size_t min_bytes) {
-    return plan_mid((char*)workspace + qlora::kWorkspaceHeaderBytes, workspace_bytes - qlora::kWorkspaceHeaderBytes,
-                    min_bytes - qlora::kWorkspaceHeaderBytes, false, M, h, o, r);
-  };
-  MidWs mid{};
-  if (!p.few && streams_mid(Wq)) mid = mid_ws(p.min_bytes);
-  else if (p.few && qlora::mid_beats_few(M, h, o, r)) {        // with the room that the size query reports; less streams as ever
-    const FwdPlan q = plan_fwd(workspace, M, h, o, r, false);
-    if (workspace_bytes >= q.bytes) mid = mid_ws(q.min_bytes);
+  const qlora::FwdRoute route = streams_mid(Wq) ? qlora::fwd_route(M, h, o, r, p.few, workspace_bytes) : qlora::FwdRoute{};
+  void* region = (char*)workspace + qlora::kWorkspaceHeaderBytes;
+  if (route.wide.ok) {
+    const WideWs w = wide_ws(region, route.wide);
+    QL_TRY(qlora::launch_wide(false, X, (int)M, W, w.plan, L1, L2, r, s, keep_mask, w.lpart, w.xpack, Y, T_save, st));
+    return QLORA_OK;
   }
-  if (!p.few && streams_mid(Wq)) {
-    const WideWs wide = plan_wide((char*)workspace + qlora::kWorkspaceHeaderBytes, workspace_bytes - qlora::kWorkspaceHeaderBytes, mid.plan,
-                                  false, M, h, o, r);
-    if (wide.plan.ok) {
-      QL_TRY(qlora::launch_wide(false, X, (int)M, W, wide.plan, L1, L2, r, s, keep_mask, wide.lpart, wide.xpack, Y, T_save, st));
-      return QLORA_OK;
-    }
-  }
-  if (mid.plan.ok) {
-    QL_TRY(qlora::launch_mid(false, X, (int)M, W, mid.plan, L1, L2, r, s, keep_mask, mid.part, mid.lpart, mid.xpack, Y, T_save, st));
+  if (route.mid.ok) {
+    const MidWs m = mid_ws(region, route.mid);
+    QL_TRY(qlora::launch_mid(false, X, (int)M, W, m.plan, L1, L2, r, s, keep_mask, m.part, m.lpart, m.xpack, Y, T_save, st));
     return QLORA_OK;
   }
   if (p.few) {
@@ -899,10 +918,12 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
                      qlora::gemm_nt_fused_fits((int)o, K1, (int)h);
   // a few hundred tokens: decode inside the product; the finalize step applies the dropout mask to the adapter's term
   const bool decoded = !p.few && dX && !fused && streams_mid(Wq);
-  const MidWs mid = decoded ? plan_mid(p.Wd, p.wd_bytes, (size_t)h * o * sizeof(uint16_t), true, M, h, o, r, keep_mask != nullptr) : MidWs{};
+  MidWs mid{};
+  if (decoded) mid = mid_ws(p.Wd, choose_mid(p.wd_bytes, (size_t)h * o * sizeof(uint16_t), true, M, h, o, r, keep_mask != nullptr));
   // (that kernel reads the mask eight bytes at a time)
-  const WideWs wide = decoded && ((uintptr_t)keep_mask & 7) == 0 ? plan_wide(p.Wd, p.wd_bytes, mid.plan, true, M, h, o, r, keep_mask != nullptr)
-                                                                     : WideWs{};
+  WideWs wide{};
+  if (decoded && ((uintptr_t)keep_mask & 7) == 0)
+    wide = wide_ws(p.Wd, choose_wide(p.wd_bytes, mid.plan, true, M, h, o, r, keep_mask != nullptr));
   qlora::FinList fin{};
   if (wide.plan.ok) {
     QL_TRY(qlora::launch_wide(true, dY, (int)M, W, wide.plan, L1, L2, r, s, keep_mask, wide.lpart, wide.xpack, dX,

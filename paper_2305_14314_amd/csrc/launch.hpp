@@ -235,6 +235,12 @@ hipError_t launch_wide(bool bwd, const uint16_t* X, int M, const NF4Dev& w, cons
                        int r, float scale, const uint8_t* mask, float* lpart, uint16_t* xpack, uint16_t* out, uint16_t* hl,
                        hipStream_t st);
 
+// api.cpp: which of these two a forward call on a 4-bit weight takes with a workspace of that many bytes (at least the size that it
+// accepts): `wide`, else `mid`, where ok; neither ok: the streaming kernels (few: they can take it) or dequantise + GEMM.  From the reported
+// size on it does not depend on the bytes.
+struct FwdRoute { MidPlan mid; WidePlan wide; };
+FwdRoute fwd_route(int64_t M, int64_t h, int64_t o, int r, bool few, size_t workspace_bytes);
+
 // fewlist.hip: the same two products for a LIST of independent layers (each with its own token rows) in one
 // persistent launch.  The work of all layers is one line of units (forward: 16 weight rows x 256 columns; backward:
 // 256 rows x 128 columns) and workgroup rho of `grid` takes units [start[rho], start[rho + 1]); the first n_adapter

@@ -110,3 +110,27 @@ def test_widetok_infinite_t(synth):
     L1[:] = torch.where(torch.arange(h, device="cuda") % 2 == 0, 1.0, -1.0).bfloat16()[:, None]
     dX = ql.qlora_linear_bwd(dY, None, Wq, L1, L2, 1.0, need_dL=False)[0]
     assert torch.equal(dX[5].float(), L1[:, 0].float() * float("inf"))
+
+
+@pytest.mark.parametrize("M,h,o,r", [(1536, 8192, 1024, 64), (2000, 4096, 1024, 64), (1412, 5952, 1280, 32), (700, 8192, 512, 0)])
+def test_forward_bits_do_not_follow_the_workspace(synth, M, h, o, r):
+    """A contraction longer than the outputs are many, whose packed operand is larger than the dequantised weight: the same bits with
+    the reported workspace, with a larger one, and behind a wider layer whose workspace both share."""
+    import paper_2305_14314_amd as ql
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    bf = lambda *shape, sd=1.0: torch.empty(shape, device="cuda").normal_(0, sd, generator=g).bfloat16()
+    W = [ql.qlora_nf4_quantize(synth.normal_f32_device((h, n), synth.SIGMA_W, 11 + n)) for n in (o, 4 * o)]
+    X = bf(M, h)
+    L = [(bf(h, r, sd=0.05), bf(r, n, sd=0.05)) if r else (None, None) for n in (o, 4 * o)]
+    print(f"case M={M} h={h} o={o} r={r}", flush=True)
+    need = ql.qlora_linear_fwd_sizes(M, h, o, r)
+    want, n = _gemm_launches(ql, lambda: ql.qlora_linear_fwd(X, W[0], *L[0], 0.5, workspace=ql.workspace_alloc(need)))
+    assert n == 0                                              # the path this is about, with no more than the reported size
+    for more in (256, 16 << 20, 64 << 20):
+        got = ql.qlora_linear_fwd(X, W[0], *L[0], 0.5, workspace=ql.workspace_alloc(need + more))
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16)), more
+    got = ql.qlora_linear_fwd_multi(X, W, [l[0] for l in L], [l[1] for l in L], [0.5, 0.5])[0]
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    _check(host_bits(want), (X.double() @ ql.qlora_nf4_dequant(W[0]).double() +
+                             (0.5 * (X.double() @ L[0][0].double()) @ L[0][1].double() if r else 0.0)).cpu().numpy(), "Y")
