@@ -413,14 +413,16 @@ qlora_status qlora_mfma_probe(int32_t lds_traffic, int32_t iters, float* out, si
 qlora_status qlora_hbm_probe(int32_t mode, const void* src, void* dst, int64_t bytes, uint32_t* sink, int32_t wgs_per_cu,
                              void* hip_stream);
 
-/* Which of two forms of the large-token backward product runs (arXiv 2305.14314, Eq. 5-6 and the backward through the
+/* Which form of the large-token backward product runs (arXiv 2305.14314, Eq. 5-6 and the backward through the
  * dequantised weight): mode 0 dequantises the weight into the workspace and multiplies; mode 1 decodes the weight's
  * tiles inside the product (codes and block constants go from HBM to the matrix cores' LDS tiles, the bf16 weight is
- * never in HBM).  The decoded tiles are the same bits either way; the adapter term is added first instead of last in
- * mode 1, so outputs may differ in the last bf16 bit.  Mode 1 applies to 4-bit types with cols % 64 == 0 and r <= 64 and
- * falls back to mode 0 otherwise.  Neither form runs where the few-token streaming kernels do, and in mode 0 a 4-bit
- * weight at up to 2048 tokens takes the products described at qlora_linear_fwd instead where those are estimated faster.  mode < 0 only queries.
- * Returns the previous mode.  Process-wide. */
+ * never in HBM); mode 2, the default, is mode 0 except that a 4-bit weight at 513 to 2048 tokens takes the second product
+ * described at qlora_linear_fwd where that is estimated faster.  The decoded tiles are the same bits in all of them.  Above 512 tokens
+ * modes 0 and 1 sum in the same order but for the adapter term, which mode 1 adds first instead of last: without an adapter
+ * dX is the same bits; with one, the last bf16 bit may differ.  In mode 2 the fp32 sums may be formed in another order.  Mode 1 applies to 4-bit types with cols % 64 == 0 and r <= 64 and
+ * falls back to mode 0 otherwise.  No form runs where the few-token streaming kernels do, and in modes 0 and 2 a 4-bit
+ * weight at up to 512 tokens takes the products described at qlora_linear_fwd instead where those are estimated faster.  mode < 0 only
+ * queries; any other value is taken as 1.  Returns the previous mode.  Process-wide. */
 int32_t qlora_bwd_fused_dequant(int32_t mode);
 
 /* Testing aid: how many times a slab's last contributor polls for the adapter's partial sums before it hands the

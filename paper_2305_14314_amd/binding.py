@@ -494,7 +494,8 @@ def qlora_mfma_probe(lds_traffic: int, iters: int, out=None, stream=None) -> flo
 
 
 def qlora_bwd_fused_dequant(mode: int) -> int:
-    """0: dequantise, then multiply; 1: decode the weight's tiles inside the backward product; < 0: query.  Returns the previous mode."""
+    """0: dequantise, then multiply; 1: decode the weight's tiles inside the backward product; 2 (the default): as 0, but 513 to 2048
+    tokens decode inside the product where that is estimated faster; < 0: query.  Returns the previous mode."""
     return int(lib().qlora_bwd_fused_dequant(int(mode)))
 
 

@@ -65,8 +65,9 @@ hipError_t gemm_nt_timed(const uint16_t* A0, const uint16_t* B0, int64_t lda0, i
 
 thread_local int g_last_hip_error = 0;
 
-// Whether the large-token backward decodes the weight inside the product (qlora_bwd_fused_dequant).
-std::atomic<int> g_bwd_fused{0};
+// The form of the large-token backward product (qlora_bwd_fused_dequant).
+enum BwdForm { kBwdDequantised = 0, kBwdFused = 1, kBwdFastest = 2 };
+std::atomic<int> g_bwd_form{kBwdFastest};
 
 // The fused form of gemm_nt_timed's product (weight-side operand of segment 0 as codes + constants), timed alike.
 hipError_t gemm_nt_fused_timed(const uint16_t* A0, const uint8_t* Bq, const float* Bc, const float* tab16, int64_t lda0,
@@ -914,7 +915,8 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
   const qlora::NF4Dev W = to_dev(Wq);
 
   const int K1 = r > 0 ? p.rp : 0;
-  const bool fused = !p.few && dX && g_bwd_fused.load(std::memory_order_relaxed) && W.dtype != qlora::kTypeInt8 && o % 64 == 0 &&
+  const int form = g_bwd_form.load(std::memory_order_relaxed);
+  const bool fused = !p.few && dX && form == kBwdFused && W.dtype != qlora::kTypeInt8 && o % 64 == 0 &&
                      qlora::gemm_nt_fused_fits((int)o, K1, (int)h);
   // a few hundred tokens: decode inside the product; the finalize step applies the dropout mask to the adapter's term
   const bool decoded = !p.few && dX && !fused && streams_mid(Wq);
@@ -922,7 +924,7 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
   if (decoded) mid = mid_ws(p.Wd, choose_mid(p.wd_bytes, (size_t)h * o * sizeof(uint16_t), true, M, h, o, r, keep_mask != nullptr));
   // (that kernel reads the mask eight bytes at a time)
   WideWs wide{};
-  if (decoded && ((uintptr_t)keep_mask & 7) == 0)
+  if (decoded && (form == kBwdFastest || M <= qlora::kMidTokens) && ((uintptr_t)keep_mask & 7) == 0)
     wide = wide_ws(p.Wd, choose_wide(p.wd_bytes, mid.plan, true, M, h, o, r, keep_mask != nullptr));
   qlora::FinList fin{};
   if (wide.plan.ok) {
@@ -1329,8 +1331,8 @@ qlora_status qlora_mfma_probe(int32_t lds_traffic, int32_t iters, float* out, si
 }
 
 int32_t qlora_bwd_fused_dequant(int32_t mode) {
-  if (mode < 0) return g_bwd_fused.load(std::memory_order_relaxed);
-  return g_bwd_fused.exchange(mode != 0 ? 1 : 0, std::memory_order_relaxed);
+  if (mode < 0) return g_bwd_form.load(std::memory_order_relaxed);
+  return g_bwd_form.exchange(mode == kBwdDequantised || mode == kBwdFastest ? mode : kBwdFused, std::memory_order_relaxed);
 }
 
 void qlora_fewtok_poll_limit(int32_t polls) { g_poll_limit.store(polls < 0 ? 0 : polls, std::memory_order_relaxed); }

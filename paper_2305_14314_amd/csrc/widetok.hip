@@ -587,9 +587,6 @@ WidePlan wide_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room
   const int64_t K = bwd ? o : h, N = bwd ? h : o;
   WidePlan best{};
   if (M < 1 || M > kWideTokens || o > (1 << 24) || h > (1 << 24) || h * o / 2 >= (1ll << 31)) return best;    // 32-bit buffer offsets
-  // Above kMidTokens small weights stay with dequantise + GEMM, whose two forms (qlora_bwd_fused_dequant) promise the same bits without an
-  // adapter and are compared there.  Given up by it, us: 986 tokens 768 x 1920 rank 64 dX under dropout 29.1 / 20.6, 796 tokens 1088 x 1024 18.6 / 19.3.
-  if (M > kMidTokens && h * o <= (1 << 21)) return best;
   auto consider = [&](int MF, int BN) {
     WidePlan p{};
     p.MF = MF; p.BN = BN;

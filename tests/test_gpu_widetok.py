@@ -134,3 +134,30 @@ def test_forward_bits_do_not_follow_the_workspace(synth, M, h, o, r):
     assert torch.equal(got.view(torch.int16), want.view(torch.int16))
     _check(host_bits(want), (X.double() @ ql.qlora_nf4_dequant(W[0]).double() +
                              (0.5 * (X.double() @ L[0][0].double()) @ L[0][1].double() if r else 0.0)).cpu().numpy(), "Y")
+
+
+@pytest.mark.parametrize("M,h,o,here", [(768, 1024, 8192, (0, 16)), (1024, 4096, 4096, (0,)), (768, 8192, 8192, (0, 16)), (640, 960, 2048, (0, 16))])
+def test_backward_modes_above_512_tokens(synth, M, h, o, here):
+    """Modes 0 and 1 dequantise and decode inside the GEMM, one launch of it each, and give the same bits without an adapter whatever the
+    weight's size; the default, mode 2, takes this path where it is estimated faster (`here`: with these ranks)."""
+    import paper_2305_14314_amd as ql
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    bf = lambda *shape, sd=1.0: torch.empty(shape, device="cuda").normal_(0, sd, generator=g).bfloat16()
+    Wq, dY, L1, L2 = ql.qlora_nf4_quantize(synth.normal_f32_device((h, o), synth.SIGMA_W, 12)), bf(M, o), bf(h, 16, sd=0.05), bf(16, o, sd=0.05)
+    What = ql.qlora_nf4_dequant(Wq).double()
+    out = {}
+    for mode in (2, 0, 1):
+        prev = ql.qlora_bwd_fused_dequant(mode)
+        try:
+            for r in (0, 16):
+                print(f"case M={M} h={h} o={o} r={r} mode={mode}", flush=True)
+                a = (L1, L2, 0.5) if r else (None, None, 0.0)
+                out[mode, r], n = _gemm_launches(ql, lambda: ql.qlora_linear_bwd(dY, None, Wq, *a, need_dL=False)[0])
+                assert n == (0 if mode == 2 and r in here else 1)
+                ref = dY.double() @ What.T + (0.5 * (dY.double() @ L2.double().T) @ L1.double().T if r else 0.0)
+                _check(host_bits(out[mode, r]), ref.cpu().numpy(), f"dX mode {mode}")
+        finally:
+            ql.qlora_bwd_fused_dequant(prev)
+        assert prev == 2
+    assert torch.equal(out[0, 0].view(torch.int16), out[1, 0].view(torch.int16))
