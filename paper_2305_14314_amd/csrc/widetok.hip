@@ -580,9 +580,10 @@ void launch_wide_main(const WideArgs& a, unsigned grid, hipStream_t st) {
 }  // namespace
 
 // Microseconds of a call by this path: its two launches, the steps of its rounds of tiles (one workgroup per compute unit), per 64
-// ranks and round the adapter's start, the outputs, and the adapter's inner product.  Fitted, like the other paths' estimates below, to 1091
-// random calls by each path (17 - 2048 tokens, sides 64 - 16384, ranks 0 - 256; forward, dX, dX under dropout; replayed, three weights in
-// turn): within 11 % on eight calls of ten, the others within 16 %.
+// ranks and round the adapter's start, the outputs, the adapter's inner product, and above kMidTokens the packed copy of the operand, which up to there
+// the margins below allow for.  Fitted, like the other paths' estimates, to random calls by each path (sides 64 - 16384, ranks 0 - 256;
+// forward, dX, dX under dropout; replayed, three weights in turn; every path seen to be the one that ran): up to 512 tokens within 11 % on eight
+// calls of ten; above, 2155 calls, within 9 %, dequantise + GEMM there within 8 %.
 WidePlan wide_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room) {
   const int64_t K = bwd ? o : h, N = bwd ? h : o;
   WidePlan best{};
@@ -603,9 +604,13 @@ WidePlan wide_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room
     p.pack_elems = (size_t)p.n_tg * bm * p.k_pad;
     if (p.pack_elems * 2 >= (1ull << 31) || (p.lpart_floats * 4 + 255) / 256 * 256 + p.pack_elems * 2 > room) return;
     const int64_t tiles = (int64_t)p.n_tg * p.n_slabs, rounds = (tiles + 255) / 256;
-    const double MN = 1e-6 * (double)M * (double)N;
-    p.us = 7.5 + (double)(rounds * p.steps) * (BN == 128 ? 0.69 + 0.21 * MF : 0.70 + 0.27 * MF) +
-           (double)((r + 63) / 64 * rounds) * (2.76 + 1.06 * MF) + 1.17 * MN + 9.6e-9 * r * (double)M * (double)K;
+    const double MN = 1e-6 * (double)M * (double)N, MK = 1e-6 * (double)M * (double)K, ranks = (double)((r + 63) / 64 * rounds);
+    if (M <= kMidTokens)
+      p.us = 7.5 + (double)(rounds * p.steps) * (BN == 128 ? 0.69 + 0.21 * MF : 0.70 + 0.27 * MF) + ranks * (2.76 + 1.06 * MF) + 1.17 * MN +
+             0.0096 * r * MK;
+    else
+      p.us = 8.8 + (double)(rounds * p.steps) * ((bwd ? 0.0 : 0.084) + (BN == 128 ? 0.60 + 0.205 * MF : 0.517 + 0.2825 * MF)) +
+             ranks * (2.4 + 1.14 * MF) + 1.146 * MN + (0.61 + 0.0111 * r) * MK;
     p.ok = true;
     if (!best.ok || p.us < best.us) best = p;
   };
@@ -615,18 +620,26 @@ WidePlan wide_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room
 }
 
 // The same of the path that a call takes otherwise: the plan of midtok.hip, or (mid NULL) dequantise + GEMM, whose bf16 weight above some 50 M
-// elements no longer stays in the last-level cache between the two, and which under dropout (fix) corrects dX afterwards.  A call comes here where
-// it is estimated 15 % faster than the former or 8 % faster than the latter: of the calls above 315 of 1091, which take 0.78 of the time
-// (mean); one of them takes more than 3 % longer (10 %).  At 10 and 6 %, small weights included, 408 (0.81), nine of them longer, one by 27 %.
+// elements no longer stays in the last-level cache between the two, and which under dropout (fix) corrects dX afterwards.  Up to 512 tokens a call
+// comes here where it is estimated 15 % faster than the former or 8 % faster than the latter: 142 of 595 calls, which take 0.75 of the time (mean);
+// three of them take more than 3 % longer (12 % at most).  Above, 3 % faster than the latter, or 8 % with up to 512 outputs, where the estimates
+// scatter more, and 0.8 us, which they scatter by on the shortest calls: 460 of 2155 calls, 0.85 of the time, four more than 3 % longer (6 %).  With no margin there 692 calls, 44 of them longer (15 % at most).
+// Without the packed copy's term, 8 % of margin and weights above 2 M elements only, 279 calls, 17 of them longer (19 %).
 bool wide_pays(const WidePlan& p, const MidPlan* mid, bool bwd, int64_t M, int64_t h, int64_t o, int r, bool fix) {
   const double K = (double)(bwd ? o : h), N = (double)(bwd ? h : o), MN = 1e-6 * (double)M * N, KN = 1e-6 * K * N, rMK = 1e-6 * r * (double)M * K;
   if (mid) {
     const double us = 6.65 + 0.71 * mid->us + (mid->pack ? 5.4 + 0.054 * r : 0.0) + 1.12 * mid->max_contrib * MN + (r > 0 ? 2.3 : 0.0) + 0.037 * rMK;
     return p.us <= 0.85 * us;
   }
-  const double us = 7.2 + 0.77 * gemm_us(M, (int64_t)N, ((int64_t)K + (r + 63) / 64 * 64) / 64) + 0.33 * KN + 0.37 * std::max(0.0, KN - 50.0) +
-                    1.07 * MN + (r > 0 ? 4.2 + 1e-6 * r * (1.65 * N + 0.1 * K) : 0.0) + 0.0056 * rMK + (fix ? 6.4 + 1.9 * MN : 0.0);
-  return p.us <= 0.92 * us;
+  const double product = gemm_us(M, (int64_t)N, ((int64_t)K + (r + 63) / 64 * 64) / 64);
+  if (M <= kMidTokens) {
+    const double us = 7.2 + 0.77 * product + 0.33 * KN + 0.37 * std::max(0.0, KN - 50.0) +
+                      1.07 * MN + (r > 0 ? 4.2 + 1e-6 * r * (1.65 * N + 0.1 * K) : 0.0) + 0.0056 * rMK + (fix ? 6.4 + 1.9 * MN : 0.0);
+    return p.us <= 0.92 * us;
+  }
+  const double us = 7.0 + 0.745 * product + 0.464 * KN + 0.616 * std::max(0.0, KN - 50.0) + 0.843 * MN +
+                    (r > 0 ? 5.1 + 1e-6 * r * (2.92 * K + 7.1 * (double)M) : 0.0) + 0.0016 * rMK + (fix ? 7.5 + 1.56 * MN : 0.0);
+  return p.us <= std::min((N <= 512 ? 0.92 : 0.97) * us, us - 0.8);
 }
 
 hipError_t launch_wide(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const WidePlan& p, const uint16_t* L1, const uint16_t* L2,

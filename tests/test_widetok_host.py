@@ -17,3 +17,9 @@ def test_backward_modes_are_kept_and_restored():
         assert f(0) == 2 and f(-1) == 0 and f(1) == 0 and f(7) == 1 and f(2) == 1 and f(-5) == 2
     finally:
         f(2)
+
+
+def test_shared_decode_plans_and_choice(tmp_path):
+    out = _run_check(tmp_path, "wide_choice_check")
+    assert out.startswith("OK 29 "), out
+    assert int(out.split()[2]) > 15000
