@@ -922,9 +922,8 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
   const bool decoded = !p.few && dX && !fused && streams_mid(Wq);
   MidWs mid{};
   if (decoded) mid = mid_ws(p.Wd, choose_mid(p.wd_bytes, (size_t)h * o * sizeof(uint16_t), true, M, h, o, r, keep_mask != nullptr));
-  // (that kernel reads the mask eight bytes at a time)
   WideWs wide{};
-  if (decoded && (form == kBwdFastest || M <= qlora::kMidTokens) && ((uintptr_t)keep_mask & 7) == 0)
+  if (decoded && (form == kBwdFastest || M <= qlora::kMidTokens))
     wide = wide_ws(p.Wd, choose_wide(p.wd_bytes, mid.plan, true, M, h, o, r, keep_mask != nullptr));
   qlora::FinList fin{};
   if (wide.plan.ok) {

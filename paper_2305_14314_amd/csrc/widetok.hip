@@ -361,7 +361,8 @@ __global__ __launch_bounds__(512) void wide_main_kernel(const WideArgs p) {
 #pragma unroll
           for (int x = 0; x < NE / 4; ++x) {                 // N % 64 == 0: 64 outputs are inside or outside together
             const int n = n0 + 64 * x;
-            const uint2 b = *(const uint2*)(p.keep + (((int64_t)(m < p.M ? m : 0) * p.N + (n < p.N ? n : 0)) >> 3));
+            uint2 b;                                         // the caller's bytes, at any address: one load all the same
+            __builtin_memcpy(&b, p.keep + (((int64_t)(m < p.M ? m : 0) * p.N + (n < p.N ? n : 0)) >> 3), 8);
             bits[2 * x] = b.x; bits[2 * x + 1] = b.y;
           }
         }

@@ -162,3 +162,26 @@ def test_backward_modes_above_512_tokens(synth, M, h, o, here):
             ql.qlora_bwd_fused_dequant(prev)
         assert prev == 2
     assert torch.equal(out[0, 0].view(torch.int16), out[1, 0].view(torch.int16))
+
+
+@pytest.mark.parametrize("M,h,o,r", [(512, 4096, 4096, 64), (1555, 5504, 128, 64)])
+def test_mask_at_any_address(synth, M, h, o, r):
+    """The keep-bits are bytes: dX, and U with it (dL1), have the same bits wherever the mask lies."""
+    import paper_2305_14314_amd as ql
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    bf = lambda *shape, sd=1.0: torch.empty(shape, device="cuda").normal_(0, sd, generator=g).bfloat16()
+    Wq = ql.qlora_nf4_quantize(synth.normal_f32_device((h, o), synth.SIGMA_W, 13))
+    X, dY, L1, L2 = bf(M, h), bf(M, o), bf(h, r, sd=0.05), bf(r, o, sd=0.05)
+    mask = ql.pack_keep_mask(torch.rand((M, h), device="cuda", generator=g) >= 0.1).flatten()
+    room = torch.zeros(mask.numel() + 16, dtype=torch.uint8, device="cuda")
+    want = None
+    for at in (0, 1, 3, 4, 6):
+        print(f"case M={M} h={h} o={o} mask at {at}", flush=True)
+        m = room[at:at + mask.numel()]
+        m.copy_(mask)
+        got, n = _gemm_launches(ql, lambda: ql.qlora_linear_bwd_dropout(dY, X, Wq, L1, L2, 0.5, m, 0.1))
+        assert m.data_ptr() % 8 == at and n == 0
+        got = [t.view(torch.int16) for t in got]
+        want = want or got
+        assert all(torch.equal(a, b) for a, b in zip(got, want)), at
