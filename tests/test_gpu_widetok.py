@@ -22,7 +22,7 @@ def _plan(bwd, M, h, o, r):
     from paper_2305_14314_amd import binding
     f = ctypes.CDLL(binding.LIB_PATH)._ZN5qlora9wide_planEblllim
     f.restype, f.argtypes = _Plan, [ctypes.c_bool, ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_size_t]
-    return f(bwd, M, h, o, r, h * o * 2)
+    return f(bwd, M, h, o, r, h * o * 2 if bwd else 1 << 40)   # the dequantised weight's place; forward the reported size brings what it needs
 
 
 # A step is 128 elements of the contraction with slabs of 128 outputs, else 256: contractions that end in a quarter, half or three
@@ -39,7 +39,13 @@ def _plan(bwd, M, h, o, r):
     ((1, 128), False, 63, 128, 1472, 0, "NF4", 256, 0.0), ((1, 128), True, 34, 1728, 128, 32, "NF4", 256, 0.0),
     ((3, 128), False, 333, 5120, 13824, 128, "NF4", 256, 0.2), ((4, 64), False, 512, 8192, 8192, 256, "NF4", 256, 0.0),
     ((3, 128), False, 768, 8192, 8192, 64, "NF4", 256, 0.0),
-    ((2, 64), True, 512, 4096, 4096, 64, "NF4", 256, 0.1)])
+    ((2, 64), True, 512, 4096, 4096, 64, "NF4", 256, 0.1),
+    # up to the most tokens; from the third on more tiles than compute units
+    ((2, 64), False, 1412, 5952, 1280, 32, "NF4", 256, 0.0), ((1, 64), False, 1252, 9984, 256, 64, "NF4", 256, 0.0),
+    ((2, 64), False, 808, 4864, 4672, 0, "NF4", 256, 0.0), ((2, 64), True, 795, 4672, 6400, 64, "NF4", 256, 0.0),
+    ((3, 128), True, 1618, 6848, 512, 64, "NF4", 256, 0.2), ((2, 128), True, 1376, 5632, 896, 64, "NF4", 0, 0.1),
+    ((4, 64), True, 1760, 4672, 1280, 64, "NF4", 256, 0.1), ((3, 128), True, 1126, 5120, 6656, 0, "NF4", 256, 0.0),
+    ((3, 128), True, 2048, 8192, 640, 64, "NF4", 256, 0.1)])
 def test_widetok(synth, tile, bwd, M, h, o, r, dtype, dq, drop):
     import paper_2305_14314_amd as ql
     s = 0.5
@@ -110,6 +116,58 @@ def test_widetok_infinite_t(synth):
     L1[:] = torch.where(torch.arange(h, device="cuda") % 2 == 0, 1.0, -1.0).bfloat16()[:, None]
     dX = ql.qlora_linear_bwd(dY, None, Wq, L1, L2, 1.0, need_dL=False)[0]
     assert torch.equal(dX[5].float(), L1[:, 0].float() * float("inf"))
+
+
+def test_widetok_infinite_t_forward_and_under_dropout(synth):
+    """The same in the forward pass, and under dropout where an input element is kept; a dropped one gets the frozen product alone."""
+    import paper_2305_14314_amd as ql
+    g = torch.Generator(device="cuda")
+    g.manual_seed(9)
+    bf = lambda *shape, sd=1.0: torch.empty(shape, device="cuda").normal_(0, sd, generator=g).bfloat16()
+    signs = lambda n: torch.where(torch.arange(n, device="cuda") % 2 == 0, 1.0, -1.0).bfloat16()
+    big = lambda *shape: torch.full(shape, 3e38, dtype=torch.bfloat16, device="cuda")
+    M, h, o, r = 1412, 5952, 1280, 32
+    Wq, X, L2 = ql.qlora_nf4_quantize(synth.normal_f32_device((h, o), synth.SIGMA_W, 14)), bf(M, h), signs(o).repeat(r, 1)
+    X[5] = 1.0
+    Y, n = _gemm_launches(ql, lambda: ql.qlora_linear_fwd(X, Wq, big(h, r), L2, 1.0))
+    assert n == 0 and torch.equal(Y[5].float(), signs(o).float() * float("inf"))
+    M, h, o, r = 1618, 6848, 512, 64
+    Wq, dY, L1 = ql.qlora_nf4_quantize(synth.normal_f32_device((h, o), synth.SIGMA_W, 15)), bf(M, o), signs(h)[:, None].repeat(1, r)
+    dY[5] = 1.0
+    keep = torch.rand((M, h), device="cuda", generator=g) >= 0.3
+    dX, n = _gemm_launches(ql, lambda: ql.qlora_linear_bwd_dropout(dY, None, Wq, L1, big(r, o), 1.0, ql.pack_keep_mask(keep), 0.3, need_dL=False)[0])
+    assert n == 0 and torch.equal(dX[5][keep[5]].float(), signs(h)[keep[5]].float() * float("inf"))
+    frozen = (dY[5].double() @ ql.qlora_nf4_dequant(Wq).double().T)[~keep[5]]
+    assert ((dX[5][~keep[5]].double() - frozen).abs() <= 2.0 ** -8 * frozen.abs() + 2e-4 * frozen.square().mean().sqrt()).all()
+
+
+@pytest.mark.parametrize("M,h,o,r,drop", [(795, 4672, 6400, 64, 0.0), (1376, 5632, 896, 64, 0.1), (1212, 1472, 1792, 16, 0.0), (1131, 1600, 9600, 32, 0.0)])
+def test_adapter_gradient_from_the_u_it_leaves(synth, M, h, o, r, drop):
+    """dL1 of a call whose dX takes this path: the [hi | lo] pair of U that the first slab's workgroups write."""
+    import paper_2305_14314_amd as ql
+    s = 0.5
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    bf = lambda *shape, sd=1.0: torch.empty(shape, device="cuda").normal_(0, sd, generator=g).bfloat16()
+    Wq = ql.qlora_nf4_quantize(synth.normal_f32_device((h, o), synth.SIGMA_W, 16))
+    X, dY, L1, L2 = bf(M, h), bf(M, o), bf(h, r, sd=0.05), bf(r, o, sd=0.05)
+    keep = torch.rand((M, h), device="cuda", generator=g) >= drop
+    if drop:
+        call = lambda: ql.qlora_linear_bwd_dropout(dY, X, Wq, L1, L2, s, ql.pack_keep_mask(keep), drop)
+    else:
+        call = lambda: ql.qlora_linear_bwd(dY, X, Wq, L1, L2, s)
+    print(f"case M={M} h={h} o={o} r={r} drop={drop}", flush=True)
+    (dX, dL1, dL2), n = _gemm_launches(ql, call)
+    assert n == 0
+    x, y, a, b = X.double() * keep / (1.0 - drop), dY.double(), L1.double(), L2.double()
+    U = y @ b.T
+    da = s * (U @ a.T)
+    _check(host_bits(dX), (y @ ql.qlora_nf4_dequant(Wq).double().T + (da * keep / (1.0 - drop))).cpu().numpy(), "dX")
+    ref = s * (x.T @ U)
+    _check(host_bits(dL1), ref.cpu().numpy(), "dL1")
+    # half a bf16 step, fp32 sums, and the 16 significant bits of U's pair
+    assert ((dL1.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2e-4 * ref.square().mean().sqrt()).all()
+    _check(host_bits(dL2), (s * ((x @ a).T @ y)).cpu().numpy(), "dL2")
 
 
 @pytest.mark.parametrize("M,h,o,r,here", [(1536, 8192, 1024, 64, False), (2000, 4096, 1024, 64, False), (1412, 5952, 1280, 32, True),

@@ -1,0 +1,43 @@
+"""Host-side check of how dL1 and dL2 are split among groups of waves: the measured calls get the split that was the faster one."""
+import ctypes
+import os
+
+import pytest
+
+
+@pytest.fixture(scope="module")
+def lib():
+    from paper_2305_14314_amd import binding, build
+    if not os.path.exists(binding.LIB_PATH):
+        build.build(verbose=False)
+    return ctypes.CDLL(binding.LIB_PATH)
+
+
+def _tiles(h, o, r):
+    """64 x 64 output tiles of dL1 (h x r) and dL2 (r x o)."""
+    up = lambda n: (n + 63) // 64
+    return up(h) * up(r), up(r) * up(o)
+
+
+# 0: partials and a finalize launch; else the groups of waves that share a tile's tokens and finish it
+@pytest.mark.parametrize("tokens,h,o,r,groups", [
+    (64, 1024, 1024, 16, 1), (65, 1024, 1024, 16, 2), (128, 4096, 4096, 64, 2), (256, 4096, 4096, 64, 4), (256, 5120, 13824, 64, 1),
+    (257, 5120, 13824, 64, 4), (512, 4096, 4096, 64, 4), (512, 4096, 11008, 256, 1), (1024, 2048, 2048, 64, 0), (1024, 2560, 2560, 64, 4),
+    (1024, 8192, 8192, 64, 4), (1400, 3584, 3584, 64, 0), (1400, 4608, 4608, 64, 0), (2048, 5120, 5120, 64, 4), (3000, 8192, 8192, 64, 4),
+    (600, 9216, 9216, 64, 2), (4096, 9216, 9216, 64, 0), (4096, 10240, 10240, 64, 0), (4096, 8192, 22016, 64, 2), (4096, 11008, 4096, 256, 1)])
+def test_measured_calls(lib, tokens, h, o, r, groups):
+    f = lib._ZN5qlora12small_groupsEiii
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int] * 3
+    t1, t2 = _tiles(h, o, r)
+    assert f(tokens, t1 + t2, min(t1, t2)) == groups
+
+
+def test_groups_have_kernels(lib):
+    """Whatever the tokens and tiles: 0, or a number of groups that the launch takes; several only where a tile's tokens are several K-steps."""
+    f = lib._ZN5qlora12small_groupsEiii
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int] * 3
+    for tokens in (1, 16, 63, 64, 65, 128, 129, 192, 193, 256, 257, 320, 500, 512, 513, 640, 1000, 1024, 1025, 2048, 4096, 1 << 20, 1 << 30):
+        for tiles in (1, 2, 16, 79, 80, 149, 150, 255, 256, 257, 399, 400, 511, 512, 513, 2000, 100000):
+            for least in {1, min(tiles, 128), min(tiles, 256), tiles}:
+                n = f(tokens, tiles, least)
+                assert n in (0, 1, 2, 4) and (n <= 1 or tokens > 64), (tokens, tiles, least)
