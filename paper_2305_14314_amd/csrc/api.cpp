@@ -1064,7 +1064,34 @@ StackBwdPlan plan_bwd_stacked(void* ws, int64_t M, int32_t n, int64_t h, const i
   p.bytes = c.off;
   return p;
 }
+// Have all layers' pairs U, T and the partials of a product room where the dequantised weights will lie?
+size_t stack_pair(const StackBwdPlan& p, int64_t M) { return align_up((size_t)M * 2 * std::max(p.r_max, 1) * sizeof(uint16_t), 256); }
+size_t stack_room(const StackBwdPlan& p, int64_t h) { return (size_t)h * p.N * sizeof(uint16_t) / 256 * 256; }
+bool stack_together(const StackBwdPlan& p, int64_t M, int32_t n, int64_t h) { return stack_room(p, h) > 2 * n * stack_pair(p, M) + p.part_bytes; }
 }  // namespace
+}  // extern "C"
+namespace qlora {
+// Layers that share a launch: small_groups over the tiles of all of them.  Layer by layer the launch has its own tiles only, and what goes
+// with partials is splits counted over all layers, a launch and a finalize launch each: us against that by groups, fitted to 500
+// calls of 65 - 4096 tokens (h 128 - 8192, 1 - 4 layers) with 0, 1, 2 and 4 of them.  Taken where a microsecond faster, these calls
+// take 0.90 of the time (mean; 1.3 % longer at most).  By small_groups over all layers' tiles they took 0.92, 13 of them more than 2 % longer,
+// up to 18 %: h 448, outputs 4288, 3712, 576, 4416, rank 64, 1938 tokens 189 -> 200 us (four groups to each layer's 74 tiles at most), 189 by this rule;
+// h 320, 6080 outputs, rank 256, 3787 tokens 148 -> 130 by both.
+int stack_groups(int64_t M, int n, int64_t h, const int64_t* o, const int32_t* r, int layer) {
+  int tiles = 0;
+  for (int l = 0; l < n; ++l) tiles += r[l] > 0 ? small_tiles((int)h, r[l]) + small_tiles(r[l], (int)o[l]) : 0;
+  if (stack_together(plan_bwd_stacked(nullptr, M, n, h, o, r), M, n, h)) return small_groups((int)M, tiles, tiles);
+  const int own = small_tiles((int)h, r[layer]) + small_tiles(r[layer], (int)o[layer]), ksteps = (int)((M + 63) / 64);
+  if (ksteps <= 4) return small_groups((int)M, own, own);
+  const int splits = std::max(1, std::min(std::min((512 + tiles - 1) / tiles, 64), ksteps));               // as of small_job_splits
+  auto chain = [&](int parts) { return (double)((ksteps + parts - 1) / parts); };
+  const double with_partials = chain(splits) * (0.474 + 3.28 * std::max(0.0, own * splits / 512.0 - 1.0));
+  const double us[3] = {-6.3 + 0.62 * chain(1), -6.4 + 0.93 * chain(2), -6.2 + chain(4) * (1.656 + 2.14 * std::max(0.0, own / 256.0 - 1.0))};
+  const int best = us[1] < us[0] ? (us[2] < us[1] ? 2 : 1) : (us[2] < us[0] ? 2 : 0);
+  return us[best] < with_partials - 1.0 ? 1 << best : 0;
+}
+}  // namespace qlora
+extern "C" {
 
 qlora_status qlora_linear_bwd_stacked_sizes(int64_t M, int32_t n, int64_t h, const int64_t* o, const int32_t* r,
                                             size_t* workspace_bytes) {
@@ -1105,9 +1132,8 @@ qlora_status qlora_linear_bwd_stacked(const uint16_t* dY, const uint16_t* X, int
   const int64_t N = p.N;
   // The skinny products come first, all layers together, while the place of the dequantised weights is free for their
   // pairs U, T and their partials; without the room there, layer by layer in the plan's own buffers.
-  const size_t pair = align_up((size_t)M * 2 * std::max(p.r_max, 1) * sizeof(uint16_t), 256);
-  const size_t wd_bytes = (size_t)h * N * sizeof(uint16_t) / 256 * 256;
-  const bool together = wd_bytes > 2 * n * pair + p.part_bytes;
+  const size_t pair = stack_pair(p, M), wd_bytes = stack_room(p, h);
+  const bool together = stack_together(p, M, n, h);
   int64_t col[QLORA_MULTI_MAX], n0 = 0;
   for (int l = 0; l < n; ++l) { col[l] = n0; n0 += o[l]; }
   for (int l0 = 0, l1; l0 < n; l0 = l1) {
@@ -1124,7 +1150,6 @@ qlora_status qlora_linear_bwd_stacked(const uint16_t* dY, const uint16_t* X, int
         tiles_tu += qlora::small_tiles((int)M, r[l]);
         tiles_dl += qlora::small_tiles((int)h, r[l]) + qlora::small_tiles(r[l], (int)o[l]);
       }
-    const int groups = qlora::small_groups((int)M, tiles_dl, tiles_dl);
     for (int l = l0; l < l1; ++l) {
       if (r[l] == 0) continue;
       // U_l = dY_l L2_l^T: bf16(s_l U_l) into the layer's rank columns of Us, the [hi | lo] pair for dL1
@@ -1145,6 +1170,7 @@ qlora_status qlora_linear_bwd_stacked(const uint16_t* dY, const uint16_t* X, int
       }
     QL_TRY(batch.finish());
     for (int l = l0; l < l1; ++l) {
+      const int groups = r[l] > 0 ? qlora::stack_groups(M, n, h, o, r, l) : 0;
       if (want1(l)) QL_TRY(batch.add(job_dl1(X, h, uhl(l), M, r[l], s[l], nullptr, dL1[l], nullptr), tiles_dl, 0, groups));     // s_l X^T U_l
       if (want2(l))                                                                                        // s_l T_l^T dY_l
         QL_TRY(batch.add(job_dl2(need_t(l) ? thl(l) : T_saved[l], dY + col[l], N, o[l], M, r[l], s[l], dL2[l], nullptr),

@@ -235,6 +235,9 @@ hipError_t launch_wide(bool bwd, const uint16_t* X, int M, const NF4Dev& w, cons
                        int r, float scale, const uint8_t* mask, float* lpart, uint16_t* xpack, uint16_t* out, uint16_t* hl,
                        hipStream_t st);
 
+// api.cpp: small_groups for dL1 and dL2 of a layer of a stacked call (M tokens; n layers h x o[l], ranks r[l]).
+int stack_groups(int64_t M, int n, int64_t h, const int64_t* o, const int32_t* r, int layer);
+
 // api.cpp: which of these two a forward call on a 4-bit weight takes with a workspace of that many bytes (at least the size that it
 // accepts): `wide`, else `mid`, where ok; neither ok: the streaming kernels (few: they can take it) or dequantise + GEMM.  From the reported
 // size on it does not depend on the bytes.

@@ -52,3 +52,35 @@ def test_gradients_in_groups(synth, M, h, o, r, dropout):
         for form in (0, 1):
             err = np.abs(bits_f64(host_bits(got[form][i])) - want[i])
             assert (err <= bound + 2.0 ** -8 * np.abs(want[i])).all(), (i, form, float((err / bound).max()))
+
+
+# two groups and four, four and none, none; a rank of 0 between
+@pytest.mark.parametrize("M,h,outs,ranks", [(757, 128, [4416, 768], [256, 256]), (450, 128, [2048, 64, 4416], [256, 0, 256]),
+                                            (780, 640, [256, 768, 1536], [64, 64, 64]), (300, 64, [64, 192], [64, 48])])
+def test_stacked_layers_one_by_one(synth, M, h, outs, ranks):
+    """The gradients of stacked layers with too little room for one launch, each layer's in the groups of its own launch; T saved and recomputed.
+    The bound is the one above."""
+    import paper_2305_14314_amd as ql
+    ss = [0.5 + l for l in range(len(outs))]
+    hX, hdY = synth.normal_bf16((M, h), 1.0, 9800), synth.normal_bf16((M, sum(outs)), 1.0, 9801)
+    hL = [(synth.normal_bf16((h, max(r, 1)), 0.05, 9810 + l), synth.normal_bf16((max(r, 1), o), 0.05, 9820 + l)) for l, (o, r) in enumerate(zip(outs, ranks))]
+    Wqs = [ql.qlora_nf4_quantize(torch.from_numpy(synth.normal_f32((h, o), synth.SIGMA_W, 9830 + l)).cuda()) for l, o in enumerate(outs)]
+    L1s, L2s = ([dev_bf16(p[i]) if r else None for p, r in zip(hL, ranks)] for i in (0, 1))
+    Ts = [torch.empty((M, 2 * r), dtype=torch.bfloat16, device="cuda") if r else None for r in ranks]
+    print(f"case stacked one by one M={M} h={h} o={outs} r={ranks}", flush=True)
+    X, dY = dev_bf16(hX), dev_bf16(hdY)
+    ql.qlora_linear_fwd_stacked(X, Wqs, L1s, L2s, ss, T_saves=Ts)
+    for saved in (Ts, None):
+        _, dL1s, dL2s = ql.qlora_linear_bwd_stacked(dY, X, Wqs, L1s, L2s, ss, T_saveds=saved)
+        torch.cuda.synchronize()
+        X64, n0 = bits_f64(hX), 0
+        for l, (o, r) in enumerate(zip(outs, ranks)):
+            g, n0 = bits_f64(hdY)[:, n0:n0 + o], n0 + o
+            if not r:
+                continue
+            a, b, s = bits_f64(hL[l][0]), bits_f64(hL[l][1]), ss[l]
+            want = (s * X64.T @ (g @ b.T), s * (X64 @ a).T @ g)
+            mags = (s * np.abs(X64).T @ (np.abs(g) @ np.abs(b).T), s * (np.abs(X64) @ np.abs(a)).T @ np.abs(g))
+            for i, (n, got) in enumerate(((o, dL1s[l]), (h, dL2s[l]))):
+                err = np.abs(bits_f64(host_bits(got)) - want[i])
+                assert (err <= (2.0 ** -16 + (n + M) * 2.0 ** -24) * mags[i] + 2.0 ** -8 * np.abs(want[i])).all(), (l, i)

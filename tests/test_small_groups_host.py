@@ -41,3 +41,17 @@ def test_groups_have_kernels(lib):
             for least in {1, min(tiles, 128), min(tiles, 256), tiles}:
                 n = f(tokens, tiles, least)
                 assert n in (0, 1, 2, 4) and (n <= 1 or tokens > 64), (tokens, tiles, least)
+
+
+# all layers' gradients in one launch, or, with little room where the weights will lie, a launch per layer: then its own tiles count
+@pytest.mark.parametrize("tokens,h,outs,r,groups", [
+    (2000, 5120, (5120, 5120, 5120), 64, (2, 2, 2)), (512, 1024, (1024, 1024), 64, (4, 4)),
+    (1938, 448, (4288, 3712, 576, 4416), 64, (0, 0, 0, 0)), (780, 640, (256, 768, 1536), 64, (0, 0, 0)),
+    (1647, 448, (2624, 3776, 320, 5504), 64, (0, 0, 0, 0)), (1132, 320, (1088, 4480, 1152, 4288), 64, (0, 0, 0, 0)),
+    (757, 128, (4416, 768), 256, (2, 4)), (755, 192, (576, 256), 256, (4, 4)), (3787, 320, (6080,), 256, (2,)), (194, 640, (128, 128), 64, (4, 4))])
+def test_stacked_layers(lib, tokens, h, outs, r, groups):
+    f = lib._ZN5qlora12stack_groupsElilPKlPKii
+    f.restype = ctypes.c_int
+    n = len(outs)
+    o, ranks = (ctypes.c_int64 * n)(*outs), (ctypes.c_int32 * n)(*[r] * n)
+    assert tuple(f(ctypes.c_int64(tokens), n, ctypes.c_int64(h), o, ranks, l) for l in range(n)) == groups
