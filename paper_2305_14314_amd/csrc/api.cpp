@@ -171,17 +171,18 @@ qlora::MidPlan choose_mid(size_t room, size_t base, bool bwd, int64_t M, int64_t
 }
 // The form of that path whose waves share a decode, in the same region, where a call of more than kFewTokens tokens is sooner done so than by
 // `mid` (whose plan is made either way) or by dequantise + GEMM.  The same rule for its room: the shape's plan or, short of room, the best that fits.
-qlora::WidePlan choose_wide(size_t room, const qlora::MidPlan& mid, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r, bool fix) {
+qlora::WidePlan choose_wide(size_t room, const qlora::MidPlan& mid, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r, bool fix, bool dq) {
   if (M <= qlora::kFewTokens) return qlora::WidePlan{};
   qlora::WidePlan p = qlora::wide_plan(bwd, M, h, o, r, SIZE_MAX);
   if (p.ok && wide_bytes(p) > room) p = qlora::wide_plan(bwd, M, h, o, r, room);
-  p.ok = p.ok && qlora::wide_pays(p, mid.ok ? &mid : nullptr, bwd, M, h, o, r, fix);
+  p.ok = p.ok && qlora::wide_pays(p, mid.ok ? &mid : nullptr, bwd, M, h, o, r, fix, dq);
   return p;
 }
 // bytes of the region that holds either the dequantised weight (`base` bytes) or the buffers of these paths; the first one's asked for
 // whether or not it is taken, because the adapter gradients' partials lie there too (dL1 and dL2 of 1024 x 1024 at rank 128 and
 // 512 tokens share a launch in it: 20.5 us, 24.6 without).  Forward, the second's too where it is taken: with that the choice among the
-// paths follows from the shape alone for every call that brings the reported size, however much more it brings (fwd_route).
+// paths follows from the shape alone (and dq: calls without Double Quantization take it by the same plan, but fewer) for every call that brings
+// the reported size, however much more it brings (fwd_route).
 // Backward the region itself follows from the shape, and a shape without the room there goes another way.
 size_t mid_region(size_t base, bool bwd, int64_t M, int64_t h, int64_t o, int32_t r) {
   size_t bytes = base;
@@ -191,7 +192,7 @@ size_t mid_region(size_t base, bool bwd, int64_t M, int64_t h, int64_t o, int32_
     if (p.ok) bytes = std::max(bytes, mid_bytes(p));
   }
   if (!bwd && M > qlora::kFewTokens) {
-    const qlora::WidePlan w = choose_wide(SIZE_MAX, choose_mid(SIZE_MAX, base, bwd, M, h, o, r, false), bwd, M, h, o, r, false);
+    const qlora::WidePlan w = choose_wide(SIZE_MAX, choose_mid(SIZE_MAX, base, bwd, M, h, o, r, false), bwd, M, h, o, r, false, true);
     if (w.ok) bytes = std::max(bytes, wide_bytes(w));
   }
   return bytes;
@@ -362,14 +363,14 @@ FwdPlan plan_fwd(void* ws, int64_t M, int64_t h, int64_t o, int32_t r, bool allo
 
 }  // namespace
 namespace qlora {
-FwdRoute fwd_route(int64_t M, int64_t h, int64_t o, int r, bool few, size_t workspace_bytes) {
+FwdRoute fwd_route(int64_t M, int64_t h, int64_t o, int r, bool few, bool dq, size_t workspace_bytes) {
   FwdRoute f{};
   if (few && !mid_beats_few(M, h, o, r)) return f;
   const FwdPlan p = plan_fwd(nullptr, M, h, o, r, false, few);
   if (few && workspace_bytes < p.bytes) return f;            // with the room that the size query reports; less streams as ever
   const size_t room = workspace_bytes - kWorkspaceHeaderBytes;
   f.mid = choose_mid(room, p.min_bytes - kWorkspaceHeaderBytes, false, M, h, o, r, false);
-  if (!few) f.wide = choose_wide(room, f.mid, false, M, h, o, r, false);
+  if (!few) f.wide = choose_wide(room, f.mid, false, M, h, o, r, false, dq);
   return f;
 }
 }  // namespace qlora
@@ -676,7 +677,7 @@ qlora_status linear_fwd_impl(const uint16_t* X, const qlora_nf4_view* Wq, const 
   hipStream_t st = (hipStream_t)hip_stream;
   const qlora::NF4Dev W = to_dev(Wq);
 
-  const qlora::FwdRoute route = streams_mid(Wq) ? qlora::fwd_route(M, h, o, r, p.few, workspace_bytes) : qlora::FwdRoute{};
+  const qlora::FwdRoute route = streams_mid(Wq) ? qlora::fwd_route(M, h, o, r, p.few, W.dq, workspace_bytes) : qlora::FwdRoute{};
   void* region = (char*)workspace + qlora::kWorkspaceHeaderBytes;
   if (route.wide.ok) {
     const WideWs w = wide_ws(region, route.wide);
@@ -924,7 +925,7 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
   if (decoded) mid = mid_ws(p.Wd, choose_mid(p.wd_bytes, (size_t)h * o * sizeof(uint16_t), true, M, h, o, r, keep_mask != nullptr));
   WideWs wide{};
   if (decoded && (form == kBwdFastest || M <= qlora::kMidTokens))
-    wide = wide_ws(p.Wd, choose_wide(p.wd_bytes, mid.plan, true, M, h, o, r, keep_mask != nullptr));
+    wide = wide_ws(p.Wd, choose_wide(p.wd_bytes, mid.plan, true, M, h, o, r, keep_mask != nullptr, W.dq));
   qlora::FinList fin{};
   if (wide.plan.ok) {
     QL_TRY(qlora::launch_wide(true, dY, (int)M, W, wide.plan, L1, L2, r, s, keep_mask, wide.lpart, wide.xpack, dX,

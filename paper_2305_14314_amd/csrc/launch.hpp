@@ -228,8 +228,9 @@ struct WidePlan {
   double us;                                 // estimate of the whole call's time
 };
 WidePlan wide_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room);
-// Is it sooner done than `mid`, or, without one, than dequantise + GEMM?  fix: as of mid_pays.
-bool wide_pays(const WidePlan& p, const MidPlan* mid, bool bwd, int64_t M, int64_t h, int64_t o, int r, bool fix);
+// Is it sooner done than `mid`, or, without one, than dequantise + GEMM?  fix: as of mid_pays.  dq: Double Quantization; without it fewer calls come here,
+// by the same plan.
+bool wide_pays(const WidePlan& p, const MidPlan* mid, bool bwd, int64_t M, int64_t h, int64_t o, int r, bool fix, bool dq);
 //   arguments as of launch_mid
 hipError_t launch_wide(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const WidePlan& p, const uint16_t* L1, const uint16_t* L2,
                        int r, float scale, const uint8_t* mask, float* lpart, uint16_t* xpack, uint16_t* out, uint16_t* hl,
@@ -242,7 +243,7 @@ int stack_groups(int64_t M, int n, int64_t h, const int64_t* o, const int32_t* r
 // accepts): `wide`, else `mid`, where ok; neither ok: the streaming kernels (few: they can take it) or dequantise + GEMM.  From the reported
 // size on it does not depend on the bytes.
 struct FwdRoute { MidPlan mid; WidePlan wide; };
-FwdRoute fwd_route(int64_t M, int64_t h, int64_t o, int r, bool few, size_t workspace_bytes);
+FwdRoute fwd_route(int64_t M, int64_t h, int64_t o, int r, bool few, bool dq, size_t workspace_bytes);
 
 // fewlist.hip: the same two products for a LIST of independent layers (each with its own token rows) in one
 // persistent launch.  The work of all layers is one line of units (forward: 16 weight rows x 256 columns; backward:

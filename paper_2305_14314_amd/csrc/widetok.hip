@@ -581,10 +581,10 @@ void launch_wide_main(const WideArgs& a, unsigned grid, hipStream_t st) {
 }  // namespace
 
 // Microseconds of a call by this path: its two launches, the steps of its rounds of tiles (one workgroup per compute unit), per 64
-// ranks and round the adapter's start, the outputs, the adapter's inner product, and above kMidTokens the packed copy of the operand, which up to there
-// the margins below allow for.  Fitted, like the other paths' estimates, to random calls by each path (sides 64 - 16384, ranks 0 - 256;
-// forward, dX, dX under dropout; replayed, three weights in turn; every path seen to be the one that ran): up to 512 tokens within 11 % on eight
-// calls of ten; above, 2155 calls, within 9 %, dequantise + GEMM there within 8 %.
+// ranks and round the adapter's start, the outputs, the adapter's inner product, and above kMidTokens the packed copy of the operand.  Fitted, like
+// the other paths' estimates, to random calls by each path (sides 64 - 16384, ranks 0 - 256; forward, dX, dX under dropout; replayed, three weights in
+// turn; every path seen to be the one that ran): up to 512 tokens within 11 % on eight calls of ten, which is enough to choose a tile; above, 2155 calls,
+// within 9 %.
 WidePlan wide_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room) {
   const int64_t K = bwd ? o : h, N = bwd ? h : o;
   WidePlan best{};
@@ -621,26 +621,44 @@ WidePlan wide_plan(bool bwd, int64_t M, int64_t h, int64_t o, int r, size_t room
 }
 
 // The same of the path that a call takes otherwise: the plan of midtok.hip, or (mid NULL) dequantise + GEMM, whose bf16 weight above some 50 M
-// elements no longer stays in the last-level cache between the two, and which under dropout (fix) corrects dX afterwards.  Up to 512 tokens a call
-// comes here where it is estimated 15 % faster than the former or 8 % faster than the latter: 142 of 595 calls, which take 0.75 of the time (mean);
-// three of them take more than 3 % longer (12 % at most).  Above, 3 % faster than the latter, or 8 % with up to 512 outputs, where the estimates
-// scatter more, and 0.8 us, which they scatter by on the shortest calls: 460 of 2155 calls, 0.85 of the time, four more than 3 % longer (6 %).  With no margin there 692 calls, 44 of them longer (15 % at most).
-// Without the packed copy's term, 8 % of margin and weights above 2 M elements only, 279 calls, 17 of them longer (19 %).
-bool wide_pays(const WidePlan& p, const MidPlan* mid, bool bwd, int64_t M, int64_t h, int64_t o, int r, bool fix) {
+// elements no longer stays in the last-level cache between the two, and which under dropout (fix) corrects dX afterwards.  A call comes here where the
+// plan's estimate is, up to 512 tokens, 15 % below the former's or 8 % below the latter's; above, 3 % below the latter's, or 8 % with up to 512
+// outputs or without Double Quantization (dq), where they scatter more, and 0.8 us, which they scatter by on the shortest calls.
+// A second estimate may refuse it: one that knows that a tile sums T's partials first, that midtok.hip's adapter items take 64 rank columns after the
+// other, and that without Double Quantization a step loads four bytes a block, forward from rows far apart (within 7 % on eight of ten calls near the
+// line).  Against midtok.hip it refuses a call from 2 % above on where the tiles leave compute units idle, which a split of the contraction would use, and
+// from 5 % below on, however many tiles, without Double Quantization; against dequantise + GEMM from 5 % below on, above 512 tokens 2 %.
+// Of 20160 random calls 4743 came here by the plan's estimate alone, at 0.742 of the time (mean), 120 of them more than 3 % longer, 47 more
+// than 10 %: forward 493 tokens 9216 x 384, rank 256 51.1 -> 72.8 us, 299 tokens 3712 x 2176, rank 64, without Double Quantization 28.7 -> 32.1.  Of the
+// 4506 that are left, at 0.727, 19 are more than 3 % longer, none more than 10 %.
+bool wide_pays(const WidePlan& p, const MidPlan* mid, bool bwd, int64_t M, int64_t h, int64_t o, int r, bool fix, bool dq) {
   const double K = (double)(bwd ? o : h), N = (double)(bwd ? h : o), MN = 1e-6 * (double)M * N, KN = 1e-6 * K * N, rMK = 1e-6 * r * (double)M * K;
+  const int64_t tiles = (int64_t)p.n_tg * p.n_slabs, rounds = (tiles + 255) / 256;
+  const double steps = (double)(rounds * p.steps), ranks = (r + 63) / 64;
+  const double second = 6.61 + steps * (p.BN == 128 ? 0.569 + 0.256 * p.MF : 0.662 + 0.279 * p.MF) + (dq || bwd ? 0.0 : 0.18) * steps +
+                        ranks * (double)rounds * (2.64 + 1.18 * p.MF + 0.237 * p.n_lparts) + 1.18 * MN + 0.0188 * rMK;
   if (mid) {
     const double us = 6.65 + 0.71 * mid->us + (mid->pack ? 5.4 + 0.054 * r : 0.0) + 1.12 * mid->max_contrib * MN + (r > 0 ? 2.3 : 0.0) + 0.037 * rMK;
-    return p.us <= 0.85 * us;
+    if (p.us > 0.85 * us) return false;
+    if (dq && tiles >= 256) return true;
+    const double chunk = std::min(K, (double)mid->chunk);
+    const double us2 = mid->pack ? 7.85 + (bwd ? 0.948 : 0.728) * mid->us + ranks * (2.6 + 0.00576 * chunk) +
+                                       mid->max_contrib * (0.312 + 1.68 * MN) + 0.0039 * r * MN
+                                 : 4.05 + (r > 0 ? 1.69 : 0.0) + std::max(0.89 * mid->us, ranks * (2.64 + 0.00254 * chunk)) +
+                                       mid->max_contrib * (0.357 + 1.3 * MN) + 0.0159 * r * MN;
+    return second <= (dq ? 1.02 : 0.95) * us2;
   }
   const double product = gemm_us(M, (int64_t)N, ((int64_t)K + (r + 63) / 64 * 64) / 64);
   if (M <= kMidTokens) {
     const double us = 7.2 + 0.77 * product + 0.33 * KN + 0.37 * std::max(0.0, KN - 50.0) +
                       1.07 * MN + (r > 0 ? 4.2 + 1e-6 * r * (1.65 * N + 0.1 * K) : 0.0) + 0.0056 * rMK + (fix ? 6.4 + 1.9 * MN : 0.0);
-    return p.us <= 0.92 * us;
+    const double us2 = 6.37 + 0.812 * product + 0.71 * KN + 0.82 * MN + (r > 0 ? 3.31 + 1e-6 * r * (0.19 * N + 1.71 * K) : 0.0) + 0.0366 * rMK +
+                       (fix ? 12.6 + 1.28 * MN : 0.0);
+    return p.us <= 0.92 * us && second <= 0.95 * us2;
   }
   const double us = 7.0 + 0.745 * product + 0.464 * KN + 0.616 * std::max(0.0, KN - 50.0) + 0.843 * MN +
                     (r > 0 ? 5.1 + 1e-6 * r * (2.92 * K + 7.1 * (double)M) : 0.0) + 0.0016 * rMK + (fix ? 7.5 + 1.56 * MN : 0.0);
-  return p.us <= std::min((N <= 512 ? 0.92 : 0.97) * us, us - 0.8);
+  return p.us <= std::min((N <= 512 || !dq ? 0.92 : 0.97) * us, us - 0.8) && second <= 0.98 * us;
 }
 
 hipError_t launch_wide(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const WidePlan& p, const uint16_t* L1, const uint16_t* L2,

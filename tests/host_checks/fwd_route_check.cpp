@@ -34,9 +34,10 @@ int main() {
     const int r = 16 * pick(0, 16);
     size_t need = 0;
     if (qlora_linear_fwd_sizes(M, h, o, r, &need) != QLORA_OK) return 1;
-    const FwdRoute a = fwd_route(M, h, o, r, few, need);
+    const bool dq = few || it % 16 < 12;                     // one size for weights with and without Double Quantization
+    const FwdRoute a = fwd_route(M, h, o, r, few, dq, need);
     for (size_t more : {(size_t)256, (size_t)pick(1, 1 << 20) * 256, (size_t)1 << 40})
-      if (!same(a, fwd_route(M, h, o, r, few, need + more))) {
+      if (!same(a, fwd_route(M, h, o, r, few, dq, need + more))) {
         std::printf("FAIL M %ld h %ld o %ld r %d: another route with %zu bytes more than reported\n", M, h, o, r, more);
         return 1;
       }
@@ -44,7 +45,7 @@ int main() {
       const size_t least = QLORA_WORKSPACE_HEADER_BYTES + up((size_t)(h + (r > 0 ? (r + 63) / 64 * 64 : 0)) * o * 2);
       for (int t = 0; t < 3; ++t) {
         const size_t ws = t == 0 || need <= least ? least : least + rng() % (need - least);
-        if (used(fwd_route(M, h, o, r, few, ws)) > ws - QLORA_WORKSPACE_HEADER_BYTES) {
+        if (used(fwd_route(M, h, o, r, few, dq, ws)) > ws - QLORA_WORKSPACE_HEADER_BYTES) {
           std::printf("FAIL M %ld h %ld o %ld r %d: buffers beyond %zu bytes\n", M, h, o, r, ws);
           return 1;
         }

@@ -10,7 +10,7 @@
 
 using namespace qlora;
 
-struct Call { bool bwd; int M, K, N, r; bool fix; double other_us, wide_us; };   // fix: under LoRA dropout; other: the path it takes otherwise
+struct Call { bool bwd; int M, K, N, r; bool fix; double other_us, wide_us; bool dq = true; };   // fix: under LoRA dropout; other: the path it takes otherwise
 static const Call kCalls[] = {
     // the shared decode: the faster one; weights of less and of more than 2 M elements, operands larger than the dequantised weight
     {false, 1097, 1280, 832, 16, false, 22.8, 20.2},   {true, 572, 1344, 768, 16, true, 27.6, 18.2},
@@ -30,6 +30,12 @@ static const Call kCalls[] = {
     // the form that splits the contraction
     {false, 179, 2304, 2624, 128, false, 21.2, 27.4},  {false, 31, 1024, 704, 32, false, 12.1, 15.0},
     {false, 488, 6208, 2688, 64, false, 41.5, 44.4},   {true, 37, 6592, 576, 256, false, 50.9, 61.1},
+    // and with large ranks over a long contraction, where a tile's start sums eight partials for every 64 of them
+    {false, 493, 9216, 384, 256, false, 51.1, 72.8},   {false, 444, 12864, 1088, 256, false, 67.7, 94.6},
+    {true, 503, 14208, 768, 256, false, 81.0, 109.4},  {true, 425, 13568, 1152, 256, true, 83.0, 104.9},
+    // without Double Quantization
+    {false, 299, 3712, 2176, 64, false, 28.7, 32.1, false}, {false, 485, 5696, 1280, 128, false, 38.2, 45.6, false},
+    {true, 1227, 9024, 3136, 0, false, 73.9, 86.9, false},  {true, 178, 2368, 1152, 64, false, 20.8, 16.6},
 };
 
 int main() {
@@ -65,7 +71,7 @@ int main() {
     const MidPlan m = mid_plan(c.bwd, c.M, h, o, c.r, std::max(base, (size_t)32 << 20));
     const bool mid = m.ok && mid_pays(m, c.bwd, c.M, h, o, c.r, c.fix);
     const WidePlan w = wide_plan(c.bwd, c.M, h, o, c.r, SIZE_MAX);
-    const bool wide = w.ok && wide_pays(w, mid ? &m : nullptr, c.bwd, c.M, h, o, c.r, c.fix);
+    const bool wide = w.ok && wide_pays(w, mid ? &m : nullptr, c.bwd, c.M, h, o, c.r, c.fix, c.dq);
     if (wide != (c.wide_us < c.other_us)) {
       std::printf("FAIL %s M %d K %d N %d r %d: %.1f us otherwise, %.1f with the shared decode, takes the %s\n", c.bwd ? "bwd" : "fwd", c.M, c.K, c.N,
                   c.r, c.other_us, c.wide_us, wide ? "latter" : "former");

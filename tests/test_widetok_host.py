@@ -21,5 +21,5 @@ def test_backward_modes_are_kept_and_restored():
 
 def test_shared_decode_plans_and_choice(tmp_path):
     out = _run_check(tmp_path, "wide_choice_check")
-    assert out.startswith("OK 29 "), out
+    assert out.startswith("OK 37 "), out
     assert int(out.split()[2]) > 15000
