@@ -220,11 +220,9 @@ size_t small_part_floats(int64_t M, int64_t h, int64_t o, int32_t r) {
 }
 
 // The skinny products of a call, several to a launch.  Their partials are carved from a pool; a job that finds no room
-// (or no place in the list) first sends off what is collected.  An adapter gradient of at most four K-steps takes no splits
-// and is finished in the product's epilogue: dL1 and dL2 of 256 tokens at
-// 1024 x 1024 take 6.7 us so (32 workgroups), and a finalize launch alone takes 4.9.  At eight K-steps (512 tokens,
-// 4096 x 4096) it is 19.5 us against 8.2 + 4.9 in four splits: the chain of K-steps is what such a workgroup waits for.
-// T and U never do, although a T that nobody saves could: Y would differ in bits from that of a call that saves it.
+// (or no place in the list) first sends off what is collected.  An adapter gradient for which the caller asks for groups (layer_groups,
+// stack_groups) takes no partials and is finished in its product's launch.  T and U never do, although a T that nobody saves could: Y would differ in
+// bits from that of a call that saves it.
 struct SmallBatch {
   qlora::SmallJobs jobs{};
   qlora::FinList fin{};
@@ -273,23 +271,53 @@ struct SmallBatch {
   }
 };
 // How dL1 and dL2 of a layer are split (the last three arguments of SmallBatch::add).  Without partials they share a launch
-// (small_groups), and with them where `room`, which
+// (layer_groups), and with them where `room`, which
 // depends on the shape alone, holds their partials -- with a floor under the smaller one's workgroups if it holds those too.
 // Where it does not, each gets a launch of its own, and its own splits if a shared launch's would leave chains of eight
 // K-steps and more: 4096 x 1024 at rank 256 and 4096 tokens (32 K-steps) 74 us with a shared launch's splits, 65 with its
 // own; 320 x 1088 at rank 64 (3 K-steps) 50 and 53.  The gradients of stacked layers are not held to the floor: over
 // 240 calls none is slower than with separate launches, and its partials would send some off in a second launch.
 struct DlSplit { int tiles, floor, groups; };
-DlSplit dl_split(int64_t M, int64_t h, int64_t o, int r, size_t room) {
+// with partials; shared: in one launch
+DlSplit partial_split(int64_t M, int64_t h, int64_t o, int r, size_t room, bool* shared) {
   const int t1 = qlora::small_tiles((int)h, r), t2 = qlora::small_tiles(r, (int)o);
-  if (const int groups = qlora::small_groups((int)M, t1 + t2, std::min(t1, t2))) return {t1 + t2, 0, groups};
   auto fits = [&](int floor) {
     return align_up((size_t)qlora::small_job_splits((int)h, r, (int)M, t2, floor) * h * r * sizeof(float), 256) +
                align_up((size_t)qlora::small_job_splits(r, (int)o, (int)M, t1, floor) * r * o * sizeof(float), 256) <= room;
   };
+  *shared = true;
   if (fits(qlora::kSmallFloor)) return {t1 + t2, qlora::kSmallFloor, 0};
+  *shared = fits(0);
   const int64_t chain = (M + 63) / 64 / qlora::small_job_splits((int)h, r, (int)M, t2);
-  return {fits(0) || chain < 8 ? t1 + t2 : 0, 0, 0};
+  return {*shared || chain < 8 ? t1 + t2 : 0, 0, 0};
+}
+}  // namespace
+namespace qlora {
+// small_groups, but partials where those can share a launch and four groups a tile are estimated no faster than they: few partials cost little, least
+// where the finalize step requests all of an output at once (eight splits), and under dropout a longer chain costs more.  Fitted to calls of 257 - 4096
+// tokens that want the gradients alone (sides 64 - 16384, ranks 16 - 256; each by partials and by 1, 2 and 4 groups).  Of 12039 such calls 4816 went by
+// groups and 139 of these took more than 3 % longer than with partials, up to 14 % (481 tokens 256 x 64, rank 16, dropout 12.2 -> 13.7 us; 1537 tokens
+// 192 x 9728 28.9 -> 32.5); with this, and two groups above 256 tiles, 13 of 4685, up to 9 %.
+int layer_groups(int64_t M, int64_t h, int64_t o, int r, size_t room, bool masked) {
+  const int t1 = small_tiles((int)h, r), t2 = small_tiles(r, (int)o), ksteps = (int)((M + 63) / 64);
+  const int groups = small_groups((int)M, t1 + t2, std::min(t1, t2));
+  if (groups != 4 || ksteps <= 4) return groups;
+  bool shared;
+  const DlSplit d = partial_split(M, h, o, r, room, &shared);
+  if (!shared) return groups;
+  const int s1 = small_job_splits((int)h, r, (int)M, t2, d.floor), s2 = small_job_splits(r, (int)o, (int)M, t1, d.floor);
+  auto batches = [](int splits) { return splits / 8 + splits % 8; };         // of loads in the finalize step
+  const double chain = std::max((ksteps + s1 - 1) / s1, (ksteps + s2 - 1) / s2);
+  const double partials = 1e-6 * ((double)s1 * (double)h * r + (double)s2 * (double)o * r);
+  const double us = -1.31 + (ksteps + 3) / 4 * (masked ? 1.51 : 1.28) - 0.74 * chain - 1.23 * partials - 0.21 * std::max(batches(s1), batches(s2));
+  return us < 0.0 ? groups : 0;
+}
+}  // namespace qlora
+namespace {
+DlSplit dl_split(int64_t M, int64_t h, int64_t o, int r, size_t room, bool masked) {
+  if (const int groups = qlora::layer_groups(M, h, o, r, room, masked)) return {qlora::small_tiles((int)h, r) + qlora::small_tiles(r, (int)o), 0, groups};
+  bool shared;
+  return partial_split(M, h, o, r, room, &shared);
 }
 qlora::SmallJob job_t(const uint16_t* X, int64_t h, const uint16_t* L1, int64_t M, int r, const uint8_t* mask) {
   qlora::SmallJob j{};
@@ -975,7 +1003,7 @@ qlora_status linear_bwd_impl(const uint16_t* dY, const uint16_t* X, const qlora_
     SmallBatch batch(big ? (void*)p.Wd : (void*)p.part, big ? p.wd_bytes : p.part_bytes, st);
     const uint16_t* T = T_saved;
     const bool need_t = want2 && !T;                        // gradient checkpointing: recompute T = X L1
-    const DlSplit split = dl_split(M, h, o, r, std::max(full_wd, p.part_bytes));
+    const DlSplit split = dl_split(M, h, o, r, std::max(full_wd, p.part_bytes), keep_mask != nullptr);
     if (need_t) {
       qlora::SmallJob t = job_t(X, h, L1, M, r, keep_mask);
       t.fin.hl = p.Thl;

@@ -236,6 +236,8 @@ hipError_t launch_wide(bool bwd, const uint16_t* X, int M, const NF4Dev& w, cons
                        int r, float scale, const uint8_t* mask, float* lpart, uint16_t* xpack, uint16_t* out, uint16_t* hl,
                        hipStream_t st);
 
+// api.cpp: small_groups for dL1 and dL2 of a layer, partials where they are the faster form (room: for those; masked: LoRA dropout)
+int layer_groups(int64_t M, int64_t h, int64_t o, int r, size_t room, bool masked);
 // api.cpp: small_groups for dL1 and dL2 of a layer of a stacked call (M tokens; n layers h x o[l], ranks r[l]).
 int stack_groups(int64_t M, int n, int64_t h, const int64_t* o, const int32_t* r, int layer);
 

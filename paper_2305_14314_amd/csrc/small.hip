@@ -300,21 +300,22 @@ int small_tiles(int I, int J) { return ((I + ST - 1) / ST) * ((J + ST - 1) / ST)
 // - Up to four K-steps (256 tokens) one group reads them in a chain that is no longer than a finalize launch; while there is
 //   a CU to every tile, as many groups as K-steps shorten it: 4096 x 4096, rank 64, 256 tokens, one -> four groups 64.4 -> 63.1.
 //   With more tiles the wide workgroups queue up: 5120 x 13824, rank 64 (296 tiles) 130.8 -> 132.9.
-// - Five to eight K-steps: four groups, 4096 x 4096, rank 64, 512 tokens 85.1 -> 80.3; 296 tiles, 320 tokens 166 -> 163;
-//   512 tiles even; 688 tiles and more lose (4096 x 11008, rank 256, 330 tokens 200 -> 205), see below.
+// - Five to eight K-steps: four groups while there is a CU to every tile, 4096 x 4096, rank 64, 512 tokens 85.1 -> 80.3; two up to 512
+//   tiles, where four take a second round (257 - 352 tiles, 119 calls: by four as long as with partials on average, by two 3.6 us shorter: 262 tokens 3072 x 14080,
+//   rank 16, dropout 22.0, by four 24.9, by two 21.2); 688 tiles and more lose (4096 x 11008, rank 256, 330 tokens 200 -> 205), see below.
 // - Longer chains: four groups to a tile leave the CUs without a tile idle, so up to one tile per CU it takes enough of them
 //   for the length: 1024 tokens (16 K-steps), 64 tiles +0.5, 80 tiles 74.9 -> 71.7, 256 tiles 320 -> 316; 1400 tokens, 112 and
 //   144 tiles +0.7, 2048 tokens, 160 tiles 226.8 -> 225.2; 3000 tokens, 256 tiles 239 -> 236.
 // - More tiles than CUs have two splits, i.e. two groups, which do not spread as well as split workgroups if the tiles are
 //   few: 600 tokens, 288 tiles 327 -> 322, but 4096 tokens, 288 tiles +5 and 320 tiles 188 -> 194; 472 tiles at 1024 tokens
-//   867 -> 860, at 4096 2225 -> 2220; stacked q, k, v of 2000 tokens (480 tiles) 616 -> 611.  Where `floor` gives a product of few tiles
-//   more splits than that, it keeps them.
+//   867 -> 860, at 4096 and stacked q, k, v of 2000 tokens (480 tiles) even.  Where `floor` gives a product of few tiles more splits than
+//   that, it keeps them.
 // - From 512 tiles on a tile has one split, which needs no sum: 4096 x 11008, rank 256 (944 tiles), 512 tokens 236 -> 225;
 //   11008 x 4096 at 4096 tokens 757 -> 751.
 int small_groups(int K, int tiles, int least) {
   const int ksteps = (K + ST - 1) / ST;
   if (ksteps <= 4) return tiles > 256 || ksteps == 1 ? 1 : ksteps == 2 ? 2 : 4;
-  if (ksteps <= 8 && tiles <= 512) return 4;
+  if (ksteps <= 8 && tiles <= 512) return tiles <= 256 ? 4 : 2;
   if (tiles <= 256) return tiles >= 5 * ksteps && (ksteps <= 16 || tiles >= 150) ? 4 : 0;
   if (tiles < 512) return least >= 128 && (ksteps <= 16 || tiles >= 400) ? 2 : 0;
   return least >= 256 ? 1 : 0;

@@ -9,11 +9,12 @@ from gpu_util import bits_f64, dev_bf16, host_bits, upload_quant
 pytestmark = pytest.mark.gpu
 
 
-# 65 tokens two groups; 129 and 200 four, one of them idle; 257 and 300 four of two K-steps, the last idle; 449 and 512; 577 with 51 tiles,
-# and with 48 by partials; 577 and 1500 with more tiles than CUs (two groups; one from 512 on); 200 with 544 (one group)
+# 65 tokens two groups; 129 and 200 four, one of them idle; 257 and 300 four of two K-steps, the last idle; 449 and 512; 577 with 51 and 48
+# tiles by partials; 640 and 1500 with 194 in four groups; 330, 577 and 1500 with more tiles than CUs (two groups; one from 512 on); 200 with 544 (one)
 @pytest.mark.parametrize("M,h,o,r", [(65, 64, 192, 16), (129, 320, 64, 48), (200, 1088, 320, 80), (257, 64, 64, 16), (300, 1088, 448, 112),
                                       (449, 192, 4160, 64), (512, 256, 256, 256), (577, 1664, 1600, 16), (577, 1536, 1536, 16),
-                                      (577, 2112, 2240, 256), (1500, 4160, 4096, 256), (200, 4352, 4352, 256), (1025, 3584, 2048, 144)])
+                                      (577, 2112, 2240, 256), (1500, 4160, 4096, 256), (200, 4352, 4352, 256), (1025, 3584, 2048, 144),
+                                      (640, 3072, 3136, 96), (330, 4160, 2048, 256), (1500, 3072, 3136, 128)])
 @pytest.mark.parametrize("dropout", [False, True])
 def test_gradients_in_groups(synth, M, h, o, r, dropout):
     """Both gradients in bf16 and added to fp32 sums, with T saved and recomputed, against float64 on the same bf16 operands.  Their
