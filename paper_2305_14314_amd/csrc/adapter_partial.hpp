@@ -14,12 +14,12 @@ __device__ __forceinline__ u32x4 apply_mask(u32x4 v, uint32_t b) {
 }
 
 // ---- adapter partials: lpart[chunk][m][j] = sum over the chunk of X[m][k] L1[k][j]  (dY[m][n] L2[j][n]) -----------------
-// Args: X (M x K), L, r, mask, chunk and lpart as in MidArgs.  One workgroup per 32 tokens and chunk; its KW waves take the chunk's
-// 32-wide steps in turn, D steps of loads in flight each, and are summed through LDS.
+// Args: MidArgs or WideArgs (X, M x K; L, r, mask, chunk, lpart).  One workgroup per 32 tokens and chunk; its KW waves take the chunk's
+// 32-wide steps in turn, two steps of loads in flight each, and are summed through LDS.
 constexpr int kAdTok = 32;
-template <int KW, int D, bool BWD, bool MASKED, typename Args>
+template <int KW, bool BWD, bool MASKED, typename Args>
 __device__ __forceinline__ void adapter_partial(const Args& p, int item, float* red /* [KW][32][64] */) {
-  constexpr int NT = KW * 64;
+  constexpr int NT = KW * 64, D = 2;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int i = lane & 15, g = lane >> 4;
   const int n_tt = (p.M + kAdTok - 1) / kAdTok;

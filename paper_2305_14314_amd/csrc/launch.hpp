@@ -217,8 +217,8 @@ hipError_t launch_mid(bool bwd, const uint16_t* X, int M, const NF4Dev& w, const
                       uint16_t* out, uint16_t* hl, hipStream_t st);
 
 // widetok.hip: the same products, the decode shared by the waves of a workgroup, which finishes its outputs itself: no partial sums of
-// the product.  Above kMidTokens too; from kWideTokens on dequantise + GEMM is the faster one nearly always (1200 - 2048 tokens: 36 of 112
-// random calls are faster here, by 3 % on average).
+// the product.  Above kMidTokens too, where a call is estimated faster than dequantise + GEMM: of random calls of 513 -
+// 800, 801 - 1200, 1201 - 1600 and 1601 - 2048 tokens 38, 19, 9 and 5 % take it, at 0.82 - 0.87 of the time; beyond, too few for a plan on every call.
 constexpr int kWideTokens = 2048;
 struct WidePlan {
   bool ok;

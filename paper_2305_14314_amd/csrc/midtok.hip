@@ -78,8 +78,8 @@ template <bool BWD>
 __global__ __launch_bounds__(512) void mid_pre_kernel(const MidArgs p, uint16_t* __restrict__ Xp, int tiles, int items) {
   __shared__ __attribute__((aligned(16))) char smem[8 * kAdTok * 64 * 4];
   if ((int)blockIdx.x < items) {
-    if (!BWD && p.mask) adapter_partial<8, 2, BWD, !BWD>(p, blockIdx.x, (float*)smem);
-    else adapter_partial<8, 2, BWD, false>(p, blockIdx.x, (float*)smem);
+    if (!BWD && p.mask) adapter_partial<8, BWD, !BWD>(p, blockIdx.x, (float*)smem);
+    else adapter_partial<8, BWD, false>(p, blockIdx.x, (float*)smem);
     return;
   }
   const int n_kb = (p.K + kPreK - 1) / kPreK, at = (int)blockIdx.x - items;
@@ -126,8 +126,8 @@ __global__ __launch_bounds__(KW * 64) void mid_main_kernel(const MidArgs p) {
   const int work = work_index();
   if constexpr (!PACK) {
     if (work < p.n_items) {
-      if (!BWD && p.mask) adapter_partial<KW, 2, BWD, !BWD>(p, work, (float*)smem);
-      else adapter_partial<KW, 2, BWD, false>(p, work, (float*)smem);
+      if (!BWD && p.mask) adapter_partial<KW, BWD, !BWD>(p, work, (float*)smem);
+      else adapter_partial<KW, BWD, false>(p, work, (float*)smem);
       return;
     }
   }

@@ -78,8 +78,8 @@ template <bool BWD>
 __global__ __launch_bounds__(512) void wide_pre_kernel(const WideArgs p, uint16_t* __restrict__ Xp, int items, int k_pad) {
   __shared__ __attribute__((aligned(16))) char smem[8 * kAdTok * 64 * 4];
   if ((int)blockIdx.x < items) {
-    if (!BWD && p.mask) adapter_partial<8, 2, BWD, !BWD>(p, blockIdx.x, (float*)smem);
-    else adapter_partial<8, 2, BWD, false>(p, blockIdx.x, (float*)smem);
+    if (!BWD && p.mask) adapter_partial<8, BWD, !BWD>(p, blockIdx.x, (float*)smem);
+    else adapter_partial<8, BWD, false>(p, blockIdx.x, (float*)smem);
     return;
   }
   const int n_kb = (k_pad + kPreK - 1) / kPreK, at = (int)blockIdx.x - items;
@@ -104,8 +104,8 @@ __global__ __launch_bounds__(512) void wide_pre_kernel(const WideArgs p, uint16_
 //
 // What bounds it: the waves' issue and the waits around it.  A step of <3, 128> (192 tokens) takes 1.2 us on some compute units and
 // 1.35 on all; its products alone 0.73, with the fragment reads, the barrier and the loads 0.9; lookups, factors and stores of the decode add about
-// 0.1 each (timing builds with one of them taken out), the barrier 0.1.  Matrix pipes 58 % busy, LDS 51 %, a wave waits for data or the
-// barrier 27 % and for its turn 36 % of its time.  Slabs of 64 (half the outputs, twice the contraction a step) read the
+// 0.1 each (timing builds with one of them taken out), the barrier 0.1.  Over the whole kernel of 333 tokens 5120 x 13824 the matrix pipes are
+// 45 % busy, LDS 43 %, a wave waits for data or a barrier 33 % and for its turn 32 % of its time.  Slabs of 64 (half the outputs, twice the contraction a step) read the
 // token operand twice as often, 64 bytes a clock per compute unit, and are for outputs that 128-wide slabs leave compute units idle
 // with.  Tried and slower: four waves of twice the tokens with everything interleaved in one wave (1.64 at the same 192 tokens,
 // 6.3 M multiply-adds a step in 2.4 us where this takes 2.4), the decode by the two halves in turn (spills), eight 2-byte loads per lane and step
